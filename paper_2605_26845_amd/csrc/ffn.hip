@@ -7,7 +7,7 @@
 // blocks both run in one launch, phase-2 tiles waiting for the rows of H they read):
 //   phase 1:  H = silu(X Wg^T) * (X Wu^T)     tile = BM rows x (128 gate + 128 up) columns
 //   phase 2:  Y = H Wd^T                      tile = BM rows x 256 columns
-// A tile never spans two (slice, expert) groups.  Both operands are K-contiguous, are copied
+// A tile holds rows of one expert (of any slices, see FfnArgs).  Both operands are K-contiguous, are copied
 // global -> LDS in K slabs (2 to 4 in flight, XOR-swizzled 16-byte chunks; fp8 weights pass through
 // registers to be dequantised) and read back as 16-byte MFMA fragments.  The weights feed the MFMA
 // "A" port so that each lane ends up with 4 consecutive output columns of one row and can store
@@ -30,18 +30,25 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 constexpr int BN = 256;                // tile columns (phase 1: 128 gate + 128 up)
 constexpr int PLAN_THREADS = 1024;
 constexpr int MAX_GROUPS = 65536;
+constexpr int PLAN_EXPERTS_LDS = 2048; // row bases of the experts kept in LDS by the plan kernel (more: in the workspace)
+constexpr int LIST_PAD = 256;          // valid entries behind the last row of the row list (a row block may read past its end)
 constexpr int PLAN_HDR = 5;            // plan[0] = (row blocks, 0, 0, 0); plan[1..2] / plan[3..4] = tile queue counters of phase 1 / 2
 
 struct FfnArgs {
     const __bf16* x;                   // [M][d]
-    __bf16* h;                         // [M][f]   workspace
+    __bf16* h;                         // [M][f]   workspace, in the row order of the plan (see below)
     __bf16* y;                         // [M][d]
     const void *wg, *wu, *wd;          // bf16 or fp8 codes
     const float *sg, *su, *sd;         // block scales (fp8) or null
     int4* plan;                        // plan[0].x = number of row blocks; plan[PLAN_HDR + i] = (row0, row_end, expert, class)
     int d, f;
-    const int32_t* row_map;            // [M] or null: row m of the schedule is row row_map[m] of x and of y
-    const float* row_gate;             // [M] or null: y row is scaled by row_gate[m]
+    // Rows are worked on expert by expert, an expert's rows of all slices side by side ("positions" 0 .. M-1): what a
+    // row becomes depends on its expert and not on its slice, so a schedule of many small slices costs no more tiles, and
+    // reads the weights no more often, than one big slice.  36 833 rows of 4 experts, d = 2048, f = 1408: 228 slices
+    // (912 groups of 40 rows on average) 2099 -> 558 us, 10 slices (920 rows) with row map and weights 592 -> 554 us; 61 111
+    // rows of 4 experts, d = 7168, f = 2048, 18 slices: 4741 -> 4343 us (before: one tile never spanned two groups).
+    const int32_t* list;               // [M + LIST_PAD] or null (identity): position p is row list[p] of x and of y
+    const float* gate;                 // [M] or null: the y row of position p is scaled by gate[p]
     int panel1, panel2;                // column groups per panel of the tile walk, phase 1 / phase 2 (see TileGeom)
     int* ready;                        // [row blocks] column units of h complete per row block (fused launch), zeroed by the plan kernel
     // The plain grouped GEMM of the adaptive-shape kernels' "phase 2": out[m][n] = sum_k A[m][k] * B_e[n][k] for the
@@ -53,6 +60,7 @@ struct FfnArgs {
         long long strideB;
         __bf16* O; int ldo;
         int K, NU;
+        unsigned int o_bytes;              // bytes of O when rows are scattered with 32-bit offsets
         const int4* etab;                  // or null.  Per expert (k0, K, r0, 0): the tile contracts over columns k0 .. k0 + K - 1 of
                                            // A and B, and row m of the schedule is row m - r0 of A
         int* queues;                       // 8 tile queue counters, zero at launch
@@ -62,15 +70,16 @@ struct FfnArgs {
     __bf16* dgu;                           // [M][2 f]: dg in columns 0 .. f-1, du in f .. 2f-1
     int* queues1;                          // 8 tile queue counters of phase 1, zero at launch
 };
-// row of x that schedule row m reads (phase 1) / row of y it writes (phase 2)
-__device__ __forceinline__ int mapped_row(const FfnArgs& a, int m) { return a.row_map ? a.row_map[m] : m; }
+// row of x that position p reads (phase 1) / row of y it writes (phase 2)
+__device__ __forceinline__ int mapped_row(const FfnArgs& a, int p) { return a.list ? a.list[p] : p; }
 
 // ---------------------------------------------------------------------------------- plan kernel
-// Splits every group into row blocks of BM rows.  One workgroup.  Malformed offsets cannot make
-// it write outside the table: boundaries are clamped to [0, M] and to non-decreasing order, and
-// entries beyond `cap` are dropped.
-// Plan entry = (first row, end of the group, local expert, shape class of the block: 0 for more than 128 rows, else 1).
-// The partial last blocks of the groups come first in the table and the full blocks after them: a partial block's
+// Orders the rows by expert (see FfnArgs), writes the row list where the order differs from the schedule's, and splits
+// every expert's rows into row blocks of bm rows.  Malformed offsets cannot make it write outside its tables: boundaries
+// are clamped to [0, M] and to non-decreasing order, positions to M, and entries beyond `cap` are dropped.
+// Plan entry = (first position, end of the expert's positions, local expert, shape class of the block: 0 for more than
+// 128 rows, else 1).
+// The partial last blocks of the experts come first in the table and the full blocks after them: a partial block's
 // tiles take longer than a full block's (they read twice the weights per MFMA), and a long tile handed out late is
 // what the whole launch then waits for.  (A third class of 64 rows x 1024 columns for blocks of <= 64 rows was
 // measured: its tiles take twice as long as any other and made phase 1 of the bench schedule 7 % slower by finishing
@@ -117,54 +126,108 @@ __device__ __forceinline__ void plan_scan2(int a, int b, int tid, int* wave_a, i
     excl_a = base_a + ia - a;
     excl_b = base_b + ib - b;
 }
+// The workgroups of the launch share the row list: each scans all groups by itself (a few microseconds, and no hand-over
+// between workgroups) and fills its share of the entries; workgroup 0 also writes the table.  Without a list one
+// workgroup is launched.
+struct PlanArgs {
+    const int32_t* offsets;
+    int S, e_loc, M, bm, cap;
+    int4* plan;
+    int* ready;
+    const int32_t* row_map;            // [M] or null
+    const float* row_gate;             // [M] or null
+    int32_t* list;                     // [M + LIST_PAD] or null: not wanted
+    float* gate;                       // [M] or null: row_gate in list order
+    int* ebase;                        // [e_loc + 1], used when e_loc > PLAN_EXPERTS_LDS
+};
 __global__ __launch_bounds__(PLAN_THREADS)
-void ffn_plan_kernel(const int32_t* __restrict__ offsets, int G, int e_loc, int M, int bm, int cap, int4* __restrict__ plan,
-                     int* __restrict__ ready) {
+void ffn_plan_kernel(PlanArgs a) {
     __shared__ int wave_tot[PLAN_THREADS / 64], wave_tot2[PLAN_THREADS / 64];
+    __shared__ int g_pos[PLAN_THREADS + 1], g_row[PLAN_THREADS], g_end[PLAN_THREADS];
+    __shared__ int eb_lds[PLAN_EXPERTS_LDS + 1];
     const int tid = threadIdx.x;
-    auto bounds = [&](int g, int& lo, int& hi) {
-        lo = hi = 0;
-        if (g < G) {
-            lo = min(max(offsets[g], 0), M);
-            hi = min(max(offsets[g + 1], lo), M);
+    const int G = a.S * a.e_loc, M = a.M, bm = a.bm;
+    int* const eb = a.e_loc <= PLAN_EXPERTS_LDS ? eb_lds : a.ebase;      // first position of every expert (workgroup 0)
+    const bool table = blockIdx.x == 0;
+    // ---- the groups in expert-major order: entry i = group (slice i % S, expert i / S)
+    int base = 0;
+    for (int i0 = 0; i0 < G; i0 += PLAN_THREADS) {
+        const int i = i0 + tid, e = i / a.S, s = i - e * a.S;
+        int lo = 0, rows = 0;
+        if (i < G) {
+            const int g = s * a.e_loc + e;
+            lo = min(max(a.offsets[g], 0), M);
+            rows = min(max(a.offsets[g + 1], lo), M) - lo;
         }
-    };
-    // ---- number of partial blocks (groups whose size is not a multiple of bm); with at most one group per thread
+        int total;
+        const int excl = plan_scan(rows, tid, wave_tot, total);
+        const int pos = min(base + excl, M);
+        if (table && i < G && s == 0) eb[e] = pos;
+        if (a.list) {
+            g_pos[tid] = pos; g_row[tid] = lo;
+            if (tid == 0) g_pos[PLAN_THREADS] = min(base + total, M);
+            __syncthreads();
+            const int last = g_pos[PLAN_THREADS];
+            for (int p = g_pos[0] + (int)blockIdx.x * PLAN_THREADS + tid; p < last; p += (int)gridDim.x * PLAN_THREADS) {
+                int t = 0;                                                // the last entry that starts at or before p
+#pragma unroll
+                for (int step = PLAN_THREADS / 2; step > 0; step >>= 1)
+                    if (g_pos[t + step] <= p) t += step;
+                const int m = g_row[t] + (p - g_pos[t]);
+                int row = m;
+                if (a.row_map) { row = a.row_map[m]; row = (unsigned)row < (unsigned)M ? row : 0; }
+                a.list[p] = row;
+                if (a.gate) a.gate[p] = a.row_gate[m];
+            }
+            __syncthreads();                                              // the next pass overwrites the entries
+        }
+        base += total;
+    }
+    if (!table) return;
+    const int used = min(base, M);
+    if (tid == 0) eb[a.e_loc] = used;
+    if (a.list && tid < LIST_PAD) a.list[used + tid] = 0;                 // (used <= M: inside the list)
+    __threadfence_block();
+    __syncthreads();
+    // ---- number of partial blocks (experts whose row count is not a multiple of bm); with at most one expert per thread
     //      the scan of the table pass below yields it
     int n_partial = 0;
-    if (G > PLAN_THREADS) {
+    if (a.e_loc > PLAN_THREADS) {
         int partial = 0;
-        for (int g = tid; g < G; g += PLAN_THREADS) {
-            int lo, hi;
-            bounds(g, lo, hi);
-            partial += (hi - lo) % bm != 0;
-        }
+        for (int e = tid; e < a.e_loc; e += PLAN_THREADS) partial += (eb[e + 1] - eb[e]) % bm != 0;
         plan_scan(partial, tid, wave_tot, n_partial);
     }
-    // ---- table: partial blocks in group order, then the full blocks in group order
+    // ---- table: partial blocks in expert order, then the full blocks in expert order
     int run_partial = 0, run_full = n_partial;                        // (uniform: every thread adds the same totals)
-    for (int g0 = 0; g0 < G; g0 += PLAN_THREADS) {
-        const int g = g0 + tid;
-        int lo, hi;
-        bounds(g, lo, hi);
+    for (int e0 = 0; e0 < a.e_loc; e0 += PLAN_THREADS) {
+        const int e = e0 + tid;
+        const int lo = e < a.e_loc ? eb[e] : 0, hi = e < a.e_loc ? eb[e + 1] : 0;
         const int rows = hi - lo, nfull = rows / bm, has_partial = rows % bm != 0;
         int ex_partial, ex_full, tot_partial, tot_full;
         plan_scan2(has_partial, nfull, tid, wave_tot, wave_tot2, ex_partial, ex_full, tot_partial, tot_full);
-        if (G <= PLAN_THREADS) run_full = tot_partial;               // the only pass: all partial blocks are known now
+        if (a.e_loc <= PLAN_THREADS) run_full = tot_partial;          // the only pass: all partial blocks are known now
         const int at_partial = run_partial + ex_partial;
         run_partial += tot_partial;
-        int at_full = run_full + ex_full;
+        const int at_full0 = run_full, at_full = run_full + ex_full;
         run_full += tot_full;
-        for (int k = 0; k < nfull; ++k, ++at_full)
-            if (at_full < cap) plan[PLAN_HDR + at_full] = make_int4(lo + k * bm, hi, g % e_loc, bm > 128 ? 0 : 1);
-        if (has_partial && at_partial < cap) {
+        g_pos[tid] = at_full; g_row[tid] = lo; g_end[tid] = hi;
+        __syncthreads();
+        for (int at = at_full0 + tid; at < run_full; at += PLAN_THREADS) {
+            int t = 0;                                                    // the last expert whose full blocks start at or before `at`
+#pragma unroll
+            for (int step = PLAN_THREADS / 2; step > 0; step >>= 1)
+                if (g_pos[t + step] <= at) t += step;
+            if (at < a.cap) a.plan[PLAN_HDR + at] = make_int4(g_row[t] + (at - g_pos[t]) * bm, g_end[t], e0 + t, bm > 128 ? 0 : 1);
+        }
+        __syncthreads();
+        if (has_partial && at_partial < a.cap) {
             const int row = lo + nfull * bm;
-            plan[PLAN_HDR + at_partial] = make_int4(row, hi, g % e_loc, hi - row > 128 ? 0 : 1);
+            a.plan[PLAN_HDR + at_partial] = make_int4(row, hi, e, hi - row > 128 ? 0 : 1);
         }
     }
-    for (int i = tid; i < min(run_full, cap); i += PLAN_THREADS) ready[i] = 0;      // per row block: column units of h complete
-    if (tid == 0) plan[0] = make_int4(min(run_full, cap), 0, 0, 0);
-    if (tid >= 1 && tid < PLAN_HDR) plan[tid] = make_int4(0, 0, 0, 0);      // tile queue counters
+    for (int i = tid; i < min(run_full, a.cap); i += PLAN_THREADS) a.ready[i] = 0;      // per row block: column units of h complete
+    if (tid == 0) a.plan[0] = make_int4(min(run_full, a.cap), 0, 0, 0);
+    if (tid >= 1 && tid < PLAN_HDR) a.plan[tid] = make_int4(0, 0, 0, 0);    // tile queue counters
 }
 
 // ---------------------------------------------------------------------------------- helpers
@@ -537,7 +600,7 @@ void ffn_gemm_kernel(FfnArgs a) {
                         }
                 } else {
                     __bf16* out = a.y + (long long)mapped_row(a, m) * a.d + ent * BN + wn * 128 + 4 * lhi;
-                    const float gate = a.row_gate ? a.row_gate[m] : 1.0f;
+                    const float gate = a.gate ? a.gate[m] : 1.0f;
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -589,9 +652,14 @@ constexpr int STAGE_OFF = 131072;                             // slab buffers be
 constexpr int STAGE_WAVE = 4096;                              // staging per wavefront: 32 rows x 128 bytes
 constexpr int ADAPTIVE_LDS = STAGE_OFF + NW * STAGE_WAVE;      // 160 KiB: all of a compute unit's LDS
 
-// GATHER (phase 1 with a row map): the rows of a tile lie anywhere in x, so every thread carries the 64-bit address of
-// its rows; otherwise the rows of a tile are consecutive and one buffer descriptor per tile (64-bit base at the
-// tile's first row) plus 32-bit offsets inside the tile address them, whatever the size of the operand.
+// AROWS / OROWS say how the rows of the A operand / of the output behind a tile's positions are addressed (the forward
+// pass lists x in phase 1 and y in phase 2; h lies in position order).
+//   ROWS_PLAIN   they are consecutive: one buffer descriptor per tile (64-bit base at the tile's first row) plus 32-bit
+//                offsets inside the tile, whatever the size of the operand
+//   ROWS_LIST32  they are listed and the matrix is smaller than 4 GiB: one descriptor for the whole operand and 32-bit offsets.
+//                A wavefront's copy or store instruction covers 8 (16) consecutive list entries, which it fetches with
+//                scalar loads: nothing is added to the vector memory operations in flight, whose number the waits count
+//   ROWS_LIST64  they are listed and lie anywhere: every thread carries the 64-bit addresses of its rows
 // FUSED (both phases in one launch, see ffn_fused_kernel): a phase-1 tile, once its rows of h are stored, adds the
 // column units it covered to the ready counter of its row block; a phase-2 ticket is handed to the workgroup only when
 // the counter of its row block has reached the number of column units of h.  The hidden activations cross from one
@@ -603,9 +671,11 @@ constexpr int ADAPTIVE_LDS = STAGE_OFF + NW * STAGE_WAVE;      // 160 KiB: all o
 constexpr int DEVICE_SCOPE = 16;       // cache-policy bit sc1 of a buffer instruction
 // EPI (phase 1): 0 = h = silu(g) * u is stored; 1 = the backward pass: with dh read from memory, dg = dh * u * silu'(g) and
 // du = dh * silu(g) are stored side by side and h beside them.
-template <int PHASE, bool GATHER, bool FUSED, int EPI = 0>
+enum { ROWS_PLAIN = 0, ROWS_LIST32 = 1, ROWS_LIST64 = 2 };
+template <int PHASE, int AROWS, int OROWS, bool FUSED, int EPI = 0>
 __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned char* smem) {
-    static_assert(PHASE == 1 || !GATHER, "only phase 1 gathers its rows");
+    constexpr bool GATHER = AROWS == ROWS_LIST64;
+    static_assert(PHASE == 2 || OROWS == ROWS_PLAIN, "phase 1 stores in position order");
     static_assert(EPI == 0 || (PHASE == 1 && !FUSED), "the gradient read-out belongs to phase 1 of a launch of its own");
     // next tile: (block, tile index, class, first row, end row, expert); block -1 = none.  It shares its bytes with
     // wavefront 0's output staging: written by that wavefront after its read-out, read by the others before the
@@ -711,6 +781,15 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
     unsigned int a_voff[32 / NW];
     unsigned int b_soff[8];
 
+    // the rows behind WR consecutive positions: lane l gets the one of position at + l / (64 / WR)
+    auto list_row = [&](auto wr_tag, int at) __attribute__((always_inline)) -> int {
+        constexpr int WR = decltype(wr_tag)::value;
+        const __attribute__((address_space(4))) int* l = (const __attribute__((address_space(4))) int*)a.list + __builtin_amdgcn_readfirstlane(at);
+        int v = l[0];
+#pragma unroll
+        for (int k = 1; k < WR; ++k) v = lane / (64 / WR) == k ? l[k] : v;
+        return v;
+    };
     auto setup = [&](auto tag, int nt_) __attribute__((always_inline)) {
         typedef Cls<decltype(tag)::value> C;
         nt = __builtin_amdgcn_readfirstlane(nt_);
@@ -728,8 +807,14 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
 #pragma unroll
             for (int i = 0; i < C::CA; ++i) {
                 const int m = m0 + min(row0 + C::RPC * i, rows - 1);
-                a_ptr[i] = (const unsigned char*)Abase + ((unsigned long long)(unsigned int)a.row_map[m] * (unsigned int)lda + kcg * 8) * 2ull;
+                a_ptr[i] = (const unsigned char*)Abase + ((unsigned long long)(unsigned int)a.list[m] * (unsigned int)lda + kcg * 8) * 2ull;
             }
+        } else if constexpr (AROWS == ROWS_LIST32) {
+            aB = (unsigned long long)Abase;
+            constexpr int WR = C::RPC / NW;                               // rows of a wavefront's copy instruction
+#pragma unroll
+            for (int i = 0; i < C::CA; ++i)                               // (entries past the block's end are rows too: LIST_PAD)
+                a_voff[i] = (unsigned int)list_row(std::integral_constant<int, WR>{}, m0 + C::RPC * i + WR * wave) * (unsigned int)(lda * 2) + (unsigned int)(kcg * 16);
         } else {
             aB = (unsigned long long)Abase + ((unsigned long long)(unsigned int)(m0 - r0) * (unsigned int)lda + (unsigned int)k0) * 2ull;
 #pragma unroll
@@ -845,9 +930,24 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
         // copies just issued have landed: memory operations of a wavefront return in order).
         int next_k = 0;
         if (tid == 0) next_k = atomicAdd(&queues[my_xcd], 1);
+        // router weights of this wavefront's rows: fetched here, where they are older than every copy still to be issued
+        float gate[MB];
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) gate[mb] = 1.0f;
+        if (PHASE == 2 && OROWS != ROWS_PLAIN && a.gate) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) gate[mb] = a.gate[min(em0 + (wm * MB + mb) * 32 + l31, em_end - 1)];
+        }
         bf16x8 wf[2][NQ], xf[2][MB];
 #pragma unroll
         for (int i = 0; i < NR; ++i) load_frag_one(wf[0], xf[0], 0, 0, i);
+
+        auto hold_gate = [&]() __attribute__((always_inline)) {             // (waited for here, not at the read-out behind the next tile's copies)
+            if (PHASE == 2 && OROWS != ROWS_PLAIN) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(gate[mb]));
+            }
+        };
 
         // Slab s in buffer buf.  NEW: slab s + NSS exists (its slot 0 follows this slab's barrier); OLD: slab s - 1 + NSS
         // exists (its later slots go out during this slab's K steps); FINAL: the tile's last slab.
@@ -910,6 +1010,7 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
             if constexpr (decltype(tag)::value == 0) {
                 // 256-row class: K is a multiple of 128 and at least 256, so NS is even and >= 4; slab s sits in buffer s & 1
                 slab(0, 0, T, F, F, C0);
+                hold_gate();
                 if (tid == 0) fetch(next_k);
                 int s = 1;
                 for (; s + 2 < NS; ++s) slab(s, s & 1, T, T, F, C0);
@@ -926,6 +1027,7 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
                 auto next = [&]() __attribute__((always_inline)) { buf = buf + 1 == NSS ? 0 : buf + 1; };
                 if (NSS < NS) slab(0, 0, T, F, F, C0); else slab(0, 0, F, F, F, C0);        // (every K here has at least 2 slabs)
                 next();
+                hold_gate();
                 if (tid == 0) fetch(next_k);
                 int s = 1;
                 for (; s + NSS < NS; ++s) { slab(s, buf, T, T, F, C0); next(); }
@@ -962,7 +1064,7 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
         unsigned char* stage = smem + STAGE_OFF + wave * STAGE_WAVE;
         unsigned char* wr = stage + el31 * SROW + elhi * 8;
         const int wrow = em0 + wm * 32 * MB;                                // first row of this wavefront
-        const bool scatter = PHASE == 2 && (a.row_map || a.row_gate);
+        constexpr bool scatter = PHASE == 2 && OROWS == ROWS_LIST64;
         // plain case: rows and columns past the end fall outside the buffer descriptor and are dropped, so every
         // wavefront issues exactly NSTORE stores per tile
         constexpr int NPASS = EPI == 1 ? 3 : 1;                             // outputs per tile: h, or dg, du and h
@@ -972,29 +1074,39 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
 #pragma unroll
         for (int pass = 0; pass < NPASS; ++pass) {
             __bf16* obase;
-            if (PHASE == 2)                  { obase = a.g2.O + (long long)wrow * a.g2.ldo + ug * 256 + (wn & 1) * 128; rowb[pass] = a.g2.ldo * 2; }
+            if (PHASE == 2 && OROWS == ROWS_LIST32) { obase = a.g2.O + ug * 256 + (wn & 1) * 128; rowb[pass] = a.g2.ldo * 2; }
+            else if (PHASE == 2)             { obase = a.g2.O + (long long)wrow * a.g2.ldo + ug * 256 + (wn & 1) * 128; rowb[pass] = a.g2.ldo * 2; }
             else if (EPI == 0 || pass == 2)  { obase = a.h + (long long)wrow * a.f + ug * 128 + (wn & 1) * 64; rowb[pass] = a.f * 2; }
             else                             { obase = a.dgu + (long long)wrow * (2 * a.f) + pass * a.f + ug * 128 + (wn & 1) * 64; rowb[pass] = a.f * 4; }
             const unsigned long long ob = (unsigned long long)obase;      // (made uniform explicitly: the descriptor must sit in scalar registers)
             const unsigned int ob_lo = (unsigned int)__builtin_amdgcn_readfirstlane((unsigned int)ob);       // (the builtin returns int:
             const unsigned int ob_hi = (unsigned int)__builtin_amdgcn_readfirstlane((unsigned int)(ob >> 32)); //  widen as unsigned)
             const unsigned long long ob_u = ((unsigned long long)ob_hi << 32) | ob_lo;
-            rsO[pass] = __builtin_amdgcn_make_buffer_rsrc((void*)ob_u, 0, __builtin_amdgcn_readfirstlane(live * rowb[pass]), 0x00020000);
+            unsigned int bytes = live * rowb[pass];
+            if (PHASE == 2 && OROWS == ROWS_LIST32) bytes = ug < NU ? a.g2.o_bytes - (unsigned int)(ug * 512 + (wn & 1) * 256) : 0u;
+            rsO[pass] = __builtin_amdgcn_make_buffer_rsrc((void*)ob_u, 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00020000);
         }
         counted_stores = !scatter;
         if (!scatter || ug < NU) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
-                if (PHASE == 2 && scatter && a.row_gate) {                // router weight of the row
-                    float gate = 1.0f;
-                    if (wrow + mb * 32 + el31 < em_end) gate = a.row_gate[wrow + mb * 32 + el31];
+                if (PHASE == 2 && OROWS != ROWS_PLAIN && a.gate) {         // router weight of the row
 #pragma unroll
                     for (int q = 0; q < NQ; ++q)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) acc[mb][q][v] *= gate;
+                        for (int v = 0; v < 16; ++v) acc[mb][q][v] *= gate[mb];
                 }
-                // backward pass: the gradient of the hidden activations at this lane's 2 x 4 groups of 4 columns (rows
-                // and units past the end read the last valid ones; what is computed from them is not stored)
+                // byte offsets of the listed rows this lane stores; a row past the end gets one past the end of y
+                unsigned int srow[PHASE == 2 && OROWS == ROWS_LIST32 ? 32 / RPI : 1];
+                if constexpr (PHASE == 2 && OROWS == ROWS_LIST32) {
+#pragma unroll
+                    for (int i = 0; i < 32 / RPI; ++i) {
+                        const int at = wrow + mb * 32 + i * RPI;
+                        // (positions that no row of the tile has are not looked up: the list ends LIST_PAD after its last row)
+                        const int row = list_row(std::integral_constant<int, RPI>{}, min(at, em_end - 1));
+                        srow[i] = at + sr < em_end ? (unsigned int)row * (unsigned int)rowb[0] : 0xFFFFFF00u;
+                    }
+                }
                 // backward pass: the gradient of the hidden activations at this lane's 2 x 4 groups of 4 columns (rows
                 // and units past the end read the last valid ones; what is computed from them is not stored)
                 u32x2 dhv[EPI == 1 ? 8 : 1];
@@ -1045,7 +1157,11 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
                         const int r = i * RPI + sr;
                         v[i] = *reinterpret_cast<const u32x4*>(stage + r * SROW + ((sc ^ swz(r)) << 4));
                     }
-                    if (!scatter) {
+                    if constexpr (PHASE == 2 && OROWS == ROWS_LIST32) {
+#pragma unroll
+                        for (int i = 0; i < 32 / RPI; ++i)
+                            __builtin_amdgcn_raw_buffer_store_b128(v[i], rsO[pass], srow[i] + hq * SROW + sc * 16, 0, 0);
+                    } else if (!scatter) {
 #pragma unroll
                         for (int i = 0; i < 32 / RPI; ++i)
                             __builtin_amdgcn_raw_buffer_store_b128(v[i], rsO[pass], (mb * 32 + i * RPI + sr) * rowb[pass] + hq * SROW + sc * 16, 0,
@@ -1080,24 +1196,24 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
     }
 }
 
-template <int PHASE, bool GATHER, int EPI = 0>
+template <int PHASE, int AROWS, int OROWS, int EPI>
 __global__ __launch_bounds__(NW * 64, 1)
 void ffn_adaptive_kernel(FfnArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    ffn_adaptive_body<PHASE, GATHER, false, EPI>(a, smem);
+    ffn_adaptive_body<PHASE, AROWS, OROWS, false, EPI>(a, smem);
 }
 
 // Both phases in one launch: a workgroup works through the phase-1 tiles until none is left to hand out, then
 // through the phase-2 tiles, each of which starts when the rows of h it reads are complete (release by the writers,
 // acquire by the reader, at device scope).  The tail of phase 1 is filled with phase-2 tiles, and a call costs one
 // launch of the matrix kernels whatever the number of slices.
-template <bool GATHER>
+template <int ROWS>
 __global__ __launch_bounds__(NW * 64, 1)
 void ffn_fused_kernel(FfnArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    ffn_adaptive_body<1, GATHER, true>(a, smem);
+    ffn_adaptive_body<1, ROWS, ROWS_PLAIN, true>(a, smem);
     __syncthreads();                     // the ticket area and the staging buffers change hands
-    ffn_adaptive_body<2, false, true>(a, smem);
+    ffn_adaptive_body<2, ROWS_PLAIN, ROWS, true>(a, smem);
 }
 
 // Expands block-scaled E4M3 codes [rows][cols] to bf16, eight values per thread and step (HBM bound: 3 bytes per weight).
@@ -1117,6 +1233,9 @@ void ffn_expand_fp8_kernel(const unsigned char* __restrict__ codes, const float*
 
 int plan_capacity(int M) { return M / 64 + MAX_GROUPS + 1; }
 size_t h_bytes(int M, int f) { return (((size_t)M * f * 2) + 255) & ~(size_t)255; }
+size_t plan_bytes(int M) { return (((size_t)(plan_capacity(M) + PLAN_HDR) * sizeof(int4)) + 255) & ~(size_t)255; }
+size_t list_bytes(int M) { return ((((size_t)M + LIST_PAD) * sizeof(int32_t)) + 255) & ~(size_t)255; }
+constexpr size_t EBASE_BYTES = (((size_t)MAX_GROUPS + 1) * sizeof(int) + 255) & ~(size_t)255;
 size_t ready_bytes(int M) { return (((size_t)plan_capacity(M) * sizeof(int)) + 255) & ~(size_t)255; }
 
 std::atomic<int> g_force_rows{0};          // moe_ffn_tile_override: 0 = rows per tile chosen per call, else 64 / 128 / 256
@@ -1175,10 +1294,10 @@ moe_status launch_gemm(const FfnArgs& a, long long max_tiles, hipStream_t s) {
     return k.done();
 }
 
-template <int PHASE, bool GATHER, int EPI = 0>
+template <int PHASE, int AROWS, int OROWS, int EPI = 0>
 moe_status launch_adaptive(const FfnArgs& a, long long max_tiles, hipStream_t s, const char* name = nullptr) {
     static moe::DeviceOnce attr;
-    auto kern = ffn_adaptive_kernel<PHASE, GATHER, EPI>;
+    auto kern = ffn_adaptive_kernel<PHASE, AROWS, OROWS, EPI>;
     int dev;
     if (attr.needed(dev)) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ADAPTIVE_LDS);
@@ -1192,10 +1311,10 @@ moe_status launch_adaptive(const FfnArgs& a, long long max_tiles, hipStream_t s,
     return k.done();
 }
 
-template <bool GATHER>
+template <int ROWS>
 moe_status launch_fused(const FfnArgs& a, long long max_tiles, hipStream_t s) {
     static moe::DeviceOnce attr;
-    auto kern = ffn_fused_kernel<GATHER>;
+    auto kern = ffn_fused_kernel<ROWS>;
     int dev;
     if (attr.needed(dev)) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ADAPTIVE_LDS);
@@ -1209,15 +1328,13 @@ moe_status launch_fused(const FfnArgs& a, long long max_tiles, hipStream_t s) {
     return k.done();
 }
 
+template <int ROWS>
 moe_status launch_both_adaptive(const FfnArgs& a, long long max_blocks, hipStream_t s) {
-    if (g_force_kernels.load(std::memory_order_relaxed) != 2) {
-        const long long tiles = max_blocks * std::max(a.f / 128, a.d / 256);
-        return a.row_map ? launch_fused<true>(a, tiles, s) : launch_fused<false>(a, tiles, s);
-    }
-    moe_status st = a.row_map ? launch_adaptive<1, true>(a, max_blocks * (a.f / 128), s)
-                              : launch_adaptive<1, false>(a, max_blocks * (a.f / 128), s);
+    if (g_force_kernels.load(std::memory_order_relaxed) != 2)
+        return launch_fused<ROWS>(a, max_blocks * std::max(a.f / 128, a.d / 256), s);
+    moe_status st = launch_adaptive<1, ROWS, ROWS_PLAIN>(a, max_blocks * (a.f / 128), s);
     if (st != MOE_OK) return st;
-    return launch_adaptive<2, false>(a, max_blocks * (a.d / 256), s);
+    return launch_adaptive<2, ROWS_PLAIN, ROWS>(a, max_blocks * (a.d / 256), s);
 }
 
 template <int ROWS, bool FP8>
@@ -1225,6 +1342,14 @@ moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
     moe_status st = launch_gemm<1, ROWS, FP8>(a, max_blocks * (a.f / 128), s);
     if (st != MOE_OK) return st;
     return launch_gemm<2, ROWS, FP8>(a, max_blocks * (a.d / BN), s);
+}
+
+moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
+    // one workgroup per 8192 list entries, at most 64: each scans the groups anew
+    const int blocks = p.list ? std::min(64, p.M / (8 * PLAN_THREADS) + 1) : 1;
+    moe::LaunchScope k("ffn_plan_kernel", s);
+    hipLaunchKernelGGL(ffn_plan_kernel, dim3(blocks), dim3(PLAN_THREADS), 0, s, p);
+    return k.done();
 }
 
 // ---------------------------------------------------------------------------------- backward pass: helper kernels
@@ -1251,27 +1376,32 @@ int bwd_split(int M, int E_loc, int d, int f) {
 
 // One workgroup.  Expert-major numbering of the schedule's rows (the weight gradients contract over all rows of an
 // expert, which lie in one group per slice): expert e owns columns k0_e .. k0_e + K_e - 1 of the transposed operands,
-// K_e = its row count padded as above; src_row[c] = schedule row behind column c, or -1 for padding.
+// K_e = its row count padded as above; src_row[c] = schedule row behind column c, src_pos[c] = its position in the row
+// order of the plan (h, dg and du lie in that order), both -1 for padding.
 // The contraction of expert e is split into P parts ("virtual experts" v = e * P + p with partial results of their own):
 // etab[v] = (k0_e + p * K_e / P, K_e / P, v * f, 0).  Also clears the tile queue counters of the launches that follow.
 __global__ __launch_bounds__(PLAN_THREADS)
 void bwd_prep_kernel(const int32_t* __restrict__ offsets, int S, int e_loc, int M, int f, int cols_cap, int P, int4* __restrict__ etab,
-                     int* __restrict__ src_row, int* __restrict__ counters, int32_t* __restrict__ w_offsets) {
-    __shared__ int k0_of[MAX_GROUPS / 16];      // (e_loc <= 4096)
+                     int* __restrict__ src_row, int* __restrict__ src_pos, int* __restrict__ counters, int32_t* __restrict__ w_offsets) {
+    __shared__ int k0_of[MAX_GROUPS / 16], p0_of[MAX_GROUPS / 16];      // (e_loc <= 4096)
     const int tid = threadIdx.x;
     auto bound = [&](int g) { return min(max(offsets[g], 0), M); };
-    for (int i = tid; i < cols_cap; i += PLAN_THREADS) src_row[i] = -1;
+    for (int i = tid; i < cols_cap; i += PLAN_THREADS) src_row[i] = src_pos[i] = -1;
     for (int i = tid; i < BWD_GEMMS * 8; i += PLAN_THREADS) counters[i] = 0;
     for (int v = tid; v <= e_loc * P; v += PLAN_THREADS) w_offsets[v] = v * f;  // row groups of the weight gradients: f rows per part
     for (int e = tid; e < e_loc; e += PLAN_THREADS) {
         int rows = 0;
         for (int sl = 0; sl < S; ++sl) { const int g = sl * e_loc + e; rows += max(bound(g + 1) - bound(g), 0); }
+        p0_of[e] = rows;
         k0_of[e] = bwd_kpad(rows, P);
     }
     __syncthreads();
     if (tid == 0) {
-        int run = 0;
+        int run = 0, run_pos = 0;
         for (int e = 0; e < e_loc; ++e) {
+            const int rows = p0_of[e];
+            p0_of[e] = run_pos;
+            run_pos += rows;
             const int k = k0_of[e], kp = k / P;
             for (int p = 0; p < P; ++p) etab[e * P + p] = make_int4(run + p * kp, kp, (e * P + p) * f, 0);
             k0_of[e] = run;
@@ -1282,12 +1412,13 @@ void bwd_prep_kernel(const int32_t* __restrict__ offsets, int S, int e_loc, int 
     // one wavefront per expert at a time walks its groups in slice order
     const int wave = tid >> 6, lane = tid & 63;
     for (int e = wave; e < e_loc; e += PLAN_THREADS / 64) {
-        int base = k0_of[e];
+        const int k0 = k0_of[e], p0 = p0_of[e];
+        int base = k0;
         for (int sl = 0; sl < S; ++sl) {
             const int g = sl * e_loc + e;
             const int lo = bound(g), n = max(bound(g + 1) - lo, 0);
             for (int r = lane; r < n; r += 64)
-                if (base + r < cols_cap) src_row[base + r] = lo + r;
+                if (base + r < cols_cap) { src_row[base + r] = lo + r; src_pos[base + r] = p0 + (base - k0) + r; }
             base += n;
         }
     }
@@ -1369,7 +1500,7 @@ void bwd_transpose_kernel(const __bf16* __restrict__ src, int R, int C, int Cpad
 inline size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct BwdLayout {                              // byte offsets into the workspace of a backward call
-    size_t plan_rows, ready_rows, plan_w, ready_w, counters, etab, w_offsets, src_row, wdt, wgut, dh, dgu, h, tx, tdy, th, tdg, tdu, dwdt, part, total;
+    size_t plan_rows, ready_rows, plan_w, ready_w, list, ebase, counters, etab, w_offsets, src_row, src_pos, wdt, wgut, dh, dgu, h, tx, tdy, th, tdg, tdu, dwdt, part, total;
     int f_pad, cols_cap, P;
 };
 BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
@@ -1384,10 +1515,13 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
     L.ready_rows = take((size_t)plan_capacity(M) * sizeof(int));
     L.plan_w = take((size_t)(plan_capacity(wrows) + PLAN_HDR) * sizeof(int4));
     L.ready_w = take((size_t)plan_capacity(wrows) * sizeof(int));
+    L.list = take(list_bytes(M));
+    L.ebase = take(EBASE_BYTES);
     L.counters = take((size_t)BWD_GEMMS * 8 * sizeof(int));
     L.etab = take((size_t)E_loc * L.P * sizeof(int4));
     L.w_offsets = take((size_t)(E_loc * L.P + 1) * sizeof(int32_t));
     L.src_row = take((size_t)L.cols_cap * sizeof(int));
+    L.src_pos = take((size_t)L.cols_cap * sizeof(int));
     L.wdt = take((size_t)E_loc * L.f_pad * d * 2);
     L.wgut = take((size_t)E_loc * d * 2 * f * 2);
     L.dh = take((size_t)M * L.f_pad * 2);
@@ -1408,7 +1542,8 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
 
 extern "C" size_t moe_ffn_workspace_bytes(int M, int d, int f) {
     if (M < 0 || d < 1 || f < 1) return 0;
-    return h_bytes(M, f) + (size_t)(plan_capacity(M) + PLAN_HDR) * sizeof(int4) + ready_bytes(M);
+    // hidden activations, plan, ready counters, row list, router weights in list order, row bases of the experts
+    return h_bytes(M, f) + plan_bytes(M) + ready_bytes(M) + 2 * list_bytes(M) + EBASE_BYTES;
 }
 
 extern "C" moe_status moe_ffn_tile_override(int tile_rows, int kernels, int panel_groups) {
@@ -1471,8 +1606,8 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
                                             row_map, row_gate, y, workspace, base_bytes, hip_stream);
     }
 
-    // rows per tile: large groups take 256-row tiles, fragmented schedules smaller ones
-    const long long avg = M / G;
+    // rows per tile by the rows an expert has on average (its slices are merged)
+    const long long avg = M / E_loc;
     int bm = avg >= 768 ? 256 : (avg >= 96 ? 128 : 64);
     if (const int forced = g_force_rows.load(std::memory_order_relaxed)) bm = forced;
 
@@ -1482,32 +1617,42 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     a.y = (__bf16*)y;
     a.wg = w_gate; a.wu = w_up; a.wd = w_down;
     a.sg = s_gate; a.su = s_up; a.sd = s_down;
-    int4* plan = (int4*)((char*)workspace + h_bytes(M, f));
+    char* at = (char*)workspace + h_bytes(M, f);
+    auto take = [&](size_t bytes) { char* p = at; at += bytes; return p; };
+    int4* plan = (int4*)take(plan_bytes(M));
     a.plan = plan;
-    a.ready = (int*)(plan + PLAN_HDR + plan_capacity(M));
+    a.ready = (int*)take(ready_bytes(M));
+    int32_t* list = (int32_t*)take(list_bytes(M));
+    float* gate = (float*)take(list_bytes(M));
+    int* ebase = (int*)take(EBASE_BYTES);
     a.d = d; a.f = f;
-    a.row_map = row_map; a.row_gate = row_gate;
+    // with one slice or one expert the rows already lie expert by expert.  (Otherwise they are always listed: what the
+    // list costs, 1 % where every group is many tiles long, is less than the one ragged tile per group it saves.)
+    const bool listed = row_map || row_gate || (S > 1 && E_loc > 1);
+    a.list = listed ? list : nullptr;
+    a.gate = row_gate ? gate : nullptr;
     a.queues1 = (int*)(plan + 1);
     a.g2.A = a.h; a.g2.lda = f;
     a.g2.B = (const __bf16*)w_down; a.g2.ldb = f; a.g2.strideB = (long long)d * f;
     a.g2.O = a.y; a.g2.ldo = d;
     a.g2.K = f; a.g2.NU = d / 256;
+    const bool off32 = (unsigned long long)M * d * 2 < 0xFFFFFF00ull;       // x and y addressed with 32-bit offsets
+    a.g2.o_bytes = off32 ? (unsigned int)M * (unsigned int)d * 2u : 0u;
     a.g2.etab = nullptr;
     a.g2.queues = (int*)(plan + 3);
     a.dh = nullptr; a.lddh = 0; a.dgu = nullptr;
     a.panel1 = panel_width(f / 128, (size_t)2 * d * f * 2, (size_t)256 * d * 2);
     a.panel2 = panel_width(d / 256, (size_t)d * f * 2, (size_t)256 * f * 2);
     if (const int forced = g_force_panel.load(std::memory_order_relaxed)) a.panel1 = a.panel2 = forced;
-    {
-        moe::LaunchScope k("ffn_plan_kernel", s);
-        hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, offsets, (int)G, E_loc, M, bm,
-                           plan_capacity(M), plan, a.ready);
-        moe_status st = k.done();
-        if (st != MOE_OK) return st;
-    }
-    const long long max_blocks = M / bm + G;
+    const PlanArgs plan_args = {offsets, S, E_loc, M, bm, plan_capacity(M), plan, a.ready, row_map, row_gate, listed ? list : nullptr,
+                                row_gate ? gate : nullptr, ebase};
+    moe_status st = launch_plan(plan_args, s);
+    if (st != MOE_OK) return st;
+    const long long max_blocks = M / bm + E_loc;
     // (the adaptive kernel chains tiles over their last two slabs: at least four 64-wide slabs, f >= 256; d always is)
-    if (bm == 256 && !fp8 && f >= 256 && g_force_kernels.load(std::memory_order_relaxed) != 1) return launch_both_adaptive(a, max_blocks, s);
+    if (bm == 256 && !fp8 && f >= 256 && g_force_kernels.load(std::memory_order_relaxed) != 1)
+        return !listed ? launch_both_adaptive<ROWS_PLAIN>(a, max_blocks, s)
+               : off32 ? launch_both_adaptive<ROWS_LIST32>(a, max_blocks, s) : launch_both_adaptive<ROWS_LIST64>(a, max_blocks, s);
     if (fp8) {
         if (bm == 256) return launch_both<256, true>(a, max_blocks, s);
         if (bm == 128) return launch_both<128, true>(a, max_blocks, s);
@@ -1555,7 +1700,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     int4* plan_w = (int4*)(ws + L.plan_w);
     int* counters = (int*)(ws + L.counters);
     int4* etab = (int4*)(ws + L.etab);
-    int* src_row = (int*)(ws + L.src_row);
+    int *src_row = (int*)(ws + L.src_row), *src_pos = (int*)(ws + L.src_pos);
     __bf16 *wdt = (__bf16*)(ws + L.wdt), *wgut = (__bf16*)(ws + L.wgut), *dh = (__bf16*)(ws + L.dh), *dgu = (__bf16*)(ws + L.dgu);
     __bf16 *h = (__bf16*)(ws + L.h), *tx = (__bf16*)(ws + L.tx), *tdy = (__bf16*)(ws + L.tdy), *th = (__bf16*)(ws + L.th);
     __bf16 *tdg = (__bf16*)(ws + L.tdg), *tdu = (__bf16*)(ws + L.tdu), *dwdt = (__bf16*)(ws + L.dwdt);
@@ -1565,15 +1710,14 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
 
     // ---- plans (row blocks of the schedule; row blocks of the weight gradients: one group of f rows per expert),
     //      expert-major column numbering, transposed weights
-    {
-        moe::LaunchScope k("ffn_plan_kernel", s);
-        hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, offsets, (int)G, E_loc, M, 256, plan_capacity(M), plan_rows,
-                           (int*)(ws + L.ready_rows));
-        if ((st = k.done()) != MOE_OK) return st;
-    }
+    const bool listed = S > 1 && E_loc > 1;      // else the rows already lie expert by expert
+    int32_t* list = listed ? (int32_t*)(ws + L.list) : nullptr;
+    int* ebase = (int*)(ws + L.ebase);
+    const PlanArgs rows_plan = {offsets, S, E_loc, M, 256, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr, ebase};
+    if ((st = launch_plan(rows_plan, s)) != MOE_OK) return st;
     {
         moe::LaunchScope k("bwd_prep_kernel", s);
-        hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, offsets, S, E_loc, M, f, L.cols_cap, P, etab, src_row, counters,
+        hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, offsets, S, E_loc, M, f, L.cols_cap, P, etab, src_row, src_pos, counters,
                            (int32_t*)(ws + L.w_offsets));
         if ((st = k.done()) != MOE_OK) return st;
     }
@@ -1605,12 +1749,13 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.plan = plan_rows;
     a.ready = (int*)(ws + L.ready_rows);
     a.d = d; a.f = f;
-    a.row_map = nullptr; a.row_gate = nullptr;
+    a.list = list; a.gate = nullptr;
     a.panel1 = a.panel2 = 1 << 20;
     a.dh = dh; a.lddh = L.f_pad; a.dgu = dgu;
     a.queues1 = counters + 8;
     a.g2.etab = nullptr;
-    const long long row_blocks = M / 256 + G;
+    const long long row_blocks = M / 256 + E_loc;
+    const bool off32 = (unsigned long long)M * d * 2 < 0xFFFFFF00ull;
 
     // ---- dh = dy Wd: rows x f_pad, K = d
     a.g2.A = (const __bf16*)dy; a.g2.lda = d;
@@ -1618,16 +1763,27 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.g2.O = dh; a.g2.ldo = L.f_pad;
     a.g2.K = d; a.g2.NU = L.f_pad / 256;
     a.g2.queues = counters + 0;
-    if ((st = launch_adaptive<2, false, 0>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dh_kernel")) != MOE_OK) return st;
+    a.g2.o_bytes = 0;
+    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dh_kernel")
+       : off32   ? launch_adaptive<2, ROWS_LIST32, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dh_kernel")
+                 : launch_adaptive<2, ROWS_LIST64, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dh_kernel");
+    if (st != MOE_OK) return st;
     // ---- g, u recomputed; dg, du, h
-    if ((st = launch_adaptive<1, false, 1>(a, row_blocks * (f / 128), s, "ffn_bwd_act_kernel")) != MOE_OK) return st;
+    st = !listed ? launch_adaptive<1, ROWS_PLAIN, ROWS_PLAIN, 1>(a, row_blocks * (f / 128), s, "ffn_bwd_act_kernel")
+       : off32   ? launch_adaptive<1, ROWS_LIST32, ROWS_PLAIN, 1>(a, row_blocks * (f / 128), s, "ffn_bwd_act_kernel")
+                 : launch_adaptive<1, ROWS_LIST64, ROWS_PLAIN, 1>(a, row_blocks * (f / 128), s, "ffn_bwd_act_kernel");
+    if (st != MOE_OK) return st;
     // ---- dx = [dg | du] [Wg ; Wu]: rows x d, K = 2f
     a.g2.A = dgu; a.g2.lda = 2 * f;
     a.g2.B = wgut; a.g2.ldb = 2 * f; a.g2.strideB = (long long)d * 2 * f;
     a.g2.O = (__bf16*)dx; a.g2.ldo = d;
     a.g2.K = 2 * f; a.g2.NU = d / 256;
     a.g2.queues = counters + 16;
-    if ((st = launch_adaptive<2, false, 0>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dx_kernel")) != MOE_OK) return st;
+    a.g2.o_bytes = off32 ? (unsigned int)M * (unsigned int)d * 2u : 0u;
+    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dx_kernel")
+       : off32   ? launch_adaptive<2, ROWS_PLAIN, ROWS_LIST32>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dx_kernel")
+                 : launch_adaptive<2, ROWS_PLAIN, ROWS_LIST64>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dx_kernel");
+    if (st != MOE_OK) return st;
 
     // ---- transposed, expert-major copies of the operands of the weight gradients
     {
@@ -1635,18 +1791,15 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
         const int cb = (L.cols_cap + 63) / 64;
         hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (d + 63) / 64), dim3(256), 0, s, (const __bf16*)x, d, d, src_row, L.cols_cap, tx, (long long)L.cols_cap);
         hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (d + 63) / 64), dim3(256), 0, s, (const __bf16*)dy, d, d, src_row, L.cols_cap, tdy, (long long)L.cols_cap);
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)h, f, f, src_row, L.cols_cap, th, (long long)L.cols_cap);
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)dgu, 2 * f, f, src_row, L.cols_cap, tdg, (long long)L.cols_cap);
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)dgu + f, 2 * f, f, src_row, L.cols_cap, tdu, (long long)L.cols_cap);
+        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)h, f, f, src_pos, L.cols_cap, th, (long long)L.cols_cap);
+        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)dgu, 2 * f, f, src_pos, L.cols_cap, tdg, (long long)L.cols_cap);
+        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)dgu + f, 2 * f, f, src_pos, L.cols_cap, tdu, (long long)L.cols_cap);
         if ((st = k.done()) != MOE_OK) return st;
     }
     // ---- weight gradients: one group of f rows per expert, K = the expert's (padded) row count
-    {
-        moe::LaunchScope k("ffn_plan_kernel", s);
-        hipLaunchKernelGGL(ffn_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, (const int32_t*)(ws + L.w_offsets), E_loc * P, E_loc * P, wrows, 256,
-                           plan_capacity(wrows), plan_w, (int*)(ws + L.ready_w));
-        if ((st = k.done()) != MOE_OK) return st;
-    }
+    const PlanArgs w_plan = {(const int32_t*)(ws + L.w_offsets), 1, E_loc * P, wrows, 256, plan_capacity(wrows), plan_w, (int*)(ws + L.ready_w),
+                             nullptr, nullptr, nullptr, nullptr, ebase};
+    if ((st = launch_plan(w_plan, s)) != MOE_OK) return st;
     a.plan = plan_w;
     a.g2.etab = etab;
     a.g2.lda = L.cols_cap; a.g2.ldb = L.cols_cap; a.g2.strideB = 0;
@@ -1656,7 +1809,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
         {tdg, tx, (__bf16*)dw_gate, 24, "ffn_bwd_dwg_kernel"}, {tdu, tx, (__bf16*)dw_up, 32, "ffn_bwd_dwu_kernel"}, {th, tdy, dwdt, 40, "ffn_bwd_dwd_kernel"}};
     for (int i = 0; i < 3; ++i) {
         a.g2.A = wg[i].A; a.g2.B = wg[i].B; a.g2.O = P > 1 ? part : wg[i].O; a.g2.queues = counters + wg[i].q;
-        if ((st = launch_adaptive<2, false, 0>(a, w_blocks * a.g2.NU, s, wg[i].name)) != MOE_OK) return st;
+        if ((st = launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, w_blocks * a.g2.NU, s, wg[i].name)) != MOE_OK) return st;
         if (P > 1) {                                                     // partial sums of the P parts -> the gradient
             moe::LaunchScope k("bwd_reduce_parts_kernel", s);
             const long long n = (long long)f * d;

@@ -727,6 +727,41 @@ def test_ffn_mapped(lib, dtype, tile_rows):
         lib.moe_ffn_tile_override()
 
 
+@pytest.mark.parametrize("tile_rows", [0, 64, 256])
+@pytest.mark.parametrize("S,E_loc,M", [(300, 4, 5000), (2, 3, 257), (9, 2, 513), (700, 2, 40), (2, 2050, 6000), (40, 1, 900)])
+def test_ffn_slices_of_an_expert_share_tiles(lib, S, E_loc, M, tile_rows):
+    """Rows are worked on expert by expert whatever their slice: a schedule of many slices gives the bits of the same rows
+    sorted by expert in one slice (which needs no row list), plain and through a row map with weights.  Sizes: groups of a few
+    rows, ends of row blocks, more groups than the planning workgroup has threads, more experts than it keeps in LDS."""
+    say("ffn slices of an expert share tiles", S, E_loc, M, tile_rows)
+    d, f = 256, 256
+    g = torch.Generator(device=DEV)
+    g.manual_seed(S + M)
+    w = workloads.ffn_weights_on_device(E_loc, d, f, S, "bf16", DEV)
+    offsets = workloads.random_offsets(S * E_loc, M, seed=S * E_loc, empty_frac=0.3)
+    x = workloads.activations_on_device(M, d, M, DEV)
+    expert = (np.searchsorted(offsets, np.arange(M), side="right") - 1) % E_loc
+    order = dev(np.argsort(expert, kind="stable"))
+    off1 = np.concatenate([[0], np.cumsum(np.bincount(expert, minlength=E_loc))]).astype(np.int32)
+    row_map = torch.randperm(M, device=DEV, generator=g).to(torch.int32)
+    gate = torch.rand((M,), device=DEV, generator=g)
+    lib.moe_ffn_tile_override(tile_rows)
+    try:
+        y = lib.moe_expert_ffn_sliced(x, dev(offsets), S, E_loc, **w)
+        want = lib.moe_expert_ffn_sliced(x[order].contiguous(), dev(off1), 1, E_loc, **w)
+        ym = lib.moe_expert_ffn_sliced_mapped(x, dev(offsets), S, E_loc, row_map=row_map, row_gate=gate, **w)
+        gathered = lib.moe_expert_ffn_sliced_mapped(x[row_map.long()].contiguous(), dev(offsets), S, E_loc,
+                                                    row_map=torch.arange(M, dtype=torch.int32, device=DEV), row_gate=gate, **w)
+        torch.cuda.synchronize()
+    finally:
+        lib.moe_ffn_tile_override()
+    assert torch.equal(y[order].view(torch.int16), want.view(torch.int16))
+    assert torch.equal(ym[row_map.long()].view(torch.int16), gathered.view(torch.int16))
+    # and the weighted rows are the plain ones times the weight, up to the two roundings to bf16 (2^-8 of the value each)
+    plain = lib.moe_expert_ffn_sliced(x[row_map.long()].contiguous(), dev(offsets), S, E_loc, **w).float() * gate[:, None]
+    assert bool(((gathered.float() - plain).abs() <= 2.0 ** -7 * plain.abs() + 1e-30).all())
+
+
 # ------------------------------------------------------------------------------ FFN backward
 def check_backward(lib, E_loc, d, f, M, S, seed, what, spare=0, empty_frac=0.15):
     W = workloads.ffn_weights(E_loc, d, f, seed=seed)
