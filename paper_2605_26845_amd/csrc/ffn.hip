@@ -1216,6 +1216,221 @@ void ffn_fused_kernel(FfnArgs a) {
     ffn_adaptive_body<2, ROWS_PLAIN, ROWS, true>(a, smem);
 }
 
+// ---------------------------------------------------------------------------------- few rows per expert (decoding)
+// Bound by the weights' way from HBM: with at most a few dozen rows per expert a tile kernel has too few tiles for the chip
+// (f / 128 and d / 256 column tiles per expert) and too few bytes in flight per tile.  Here a workgroup takes a strip of
+// 16 * NC weight rows of one expert (phase 1: half of them gate, half up) and up to 64 of the expert's rows, and its W wavefronts
+// share the contraction: 64 values of K each in turn, weights and activations straight from memory into MFMA fragments, the
+// next two (D - 1) steps in flight while one is multiplied.  The W partial sums meet in LDS and are added in fp32 in a fixed order.
+// No plan: every workgroup finds its rows in the offsets by itself (a scan over the S groups of its expert), h lies in schedule
+// order, K-major (8 values of K of all rows side by side): a fragment load of phase 2 then covers runs of 16 rows x 16 bytes
+// instead of 16 rows that lie a power of two apart in the same memory channel (phase 2 of d = 4096, f = 14336 at 64 rows 69 ->
+// 48 us; d = 7168, f = 2048, four fp8 experts 42 -> 28 us).  For the same reason the strips start at different steps of K
+// (one expert, d 4096, f 14336, 5 rows: 86 -> 70 us).
+// One expert, d 4096, f 14336, 37 rows (352 MB of weights): 587 us in 64-row tiles -> 97 us; four fp8 experts, d 7168, f 2048,
+// 203 rows (176 MB): 439 -> 90 us.  5 rows of the former: 68 us, 5.2 TB/s; with more rows the activations' way from L2 counts too.
+struct SkinnyArgs {
+    const __bf16* x; __bf16* h; __bf16* y;
+    const void *wg, *wu, *wd;
+    const float *sg, *su, *sd;
+    const int32_t* offsets;
+    const int32_t* row_map; const float* row_gate;
+    int M, S, E, d, f;
+};
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+constexpr int SKINNY_ROWS = 64;        // rows per workgroup
+constexpr int SKINNY_MAX_SLICES = 1024;
+
+// W wavefronts, NC 16-row column tiles of weights, at most MT 16-row tiles of activations, D register buffers
+template <int PHASE, int W, int NC, int MT, int D, bool FP8>
+__global__ __launch_bounds__(W * 64)
+void ffn_skinny_kernel(SkinnyArgs a) {
+    static_assert(PHASE == 2 || NC % 2 == 0, "gate and up tiles in pairs");
+    constexpr int ESZ = FP8 ? 1 : 2, WL = FP8 ? 1 : 2;                     // 16-byte weight loads per lane, column tile and 64 values of K
+    constexpr int PASS = 32 / (W * NC) < 1 ? 1 : (32 / (W * NC) > MT ? MT : 32 / (W * NC));     // row tiles per reduction pass
+    constexpr int NH = PHASE == 1 ? NC / 2 : NC;                           // column tiles of the output
+    __shared__ int s_row[SKINNY_ROWS];
+    __shared__ int s_scan[W];
+    __shared__ f32x4 s_red[W * NC * PASS * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g4 = lane >> 4;
+    const int strip = blockIdx.x, e = blockIdx.y;
+    const int K = PHASE == 1 ? a.d : a.f, NO = PHASE == 1 ? a.f : a.d;     // contraction, output columns
+    const int col0 = strip * 16 * NH;
+    const int KT = K / 64, n = (KT - wave + W - 1) / W;                    // steps in all, and of this wavefront (K >= 128)
+    const int rot = (int)(((unsigned)strip * 3u + (unsigned)e * 3u) % (unsigned)KT);
+
+    for (int first = (int)blockIdx.z * SKINNY_ROWS;; first += (int)gridDim.z * SKINNY_ROWS) {
+        // ---- positions first .. first + 63 of the expert's rows
+        int total = 0;
+        for (int s0 = 0; s0 < a.S; s0 += W * 64) {
+            const int s = s0 + tid;
+            int lo = 0, rows = 0;
+            if (s < a.S) {
+                const int gi = s * a.E + e;
+                lo = min(max(a.offsets[gi], 0), a.M);
+                rows = min(max(a.offsets[gi + 1], lo), a.M) - lo;
+            }
+            int incl = rows;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(incl, off);
+                if (lane >= off) incl += o;
+            }
+            if (lane == 63) s_scan[wave] = incl;
+            __syncthreads();
+            int base = total;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int t = s_scan[w];
+                if (w < wave) base += t;
+                total += t;
+            }
+            const int p0 = base + incl - rows;
+            for (int p = max(p0, first); p < min(p0 + rows, first + SKINNY_ROWS); ++p) s_row[p - first] = lo + (p - p0);
+            __syncthreads();
+        }
+        const int rows = min(total - first, SKINNY_ROWS);
+        if (rows <= 0) return;
+
+        auto mapped = [&](int m) __attribute__((always_inline)) -> int {
+            if (!a.row_map) return m;
+            const int r = a.row_map[m];
+            return (unsigned)r < (unsigned)a.M ? r : 0;
+        };
+        auto work = [&](auto tag) __attribute__((always_inline)) {
+            constexpr int T = decltype(tag)::value;                        // 16-row tiles of this workgroup's rows
+            f32x4 acc[NC][T];
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+#pragma unroll
+                for (int t = 0; t < T; ++t) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // Lane (r16, g4) holds row r16 of a 16-row tile and 8 consecutive values of K per MFMA step.  The order of K inside a
+            // step is free as long as both operands agree: fp8 lanes fetch 16 consecutive codes, the two steps' worth.
+            unsigned int xoff[T];                                          // (M * K * 2 < 2^32 is a condition of this route)
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int m = s_row[min(t * 16 + r16, rows - 1)];          // rows past the end repeat the last one and are not stored
+                xoff[t] = PHASE == 1 ? ((unsigned int)mapped(m) * (unsigned int)K + (unsigned int)g4 * (FP8 ? 16 : 8)) * 2u
+                                     : ((unsigned int)g4 * (FP8 ? 2 : 1) * (unsigned int)a.M + (unsigned int)m) * 16u;
+            }
+            const void* const xbase = PHASE == 1 ? (const void*)a.x : (const void*)a.h;
+            const unsigned int xbytes = (unsigned int)a.M * (unsigned int)K * 2u;
+            // bytes per value of K, and from the first MFMA step of 64 values to the second
+            const unsigned int xstep = PHASE == 1 ? 2u : 2u * (unsigned int)a.M;
+            const unsigned int xhalf = PHASE == 1 ? (FP8 ? 16u : 64u) : (FP8 ? 16u : 64u) * (unsigned int)a.M;
+            const unsigned int woff = ((unsigned int)r16 * (unsigned int)K) * ESZ + (unsigned int)g4 * 16u;
+            const unsigned int wbytes = 16u * (unsigned int)K * ESZ;
+            const unsigned char* wbase[NC];
+            const float* sbase[2] = {nullptr, nullptr};                    // scale row of the strip's 128 x 128 blocks (gate / up or down)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const void* w = PHASE == 2 ? a.wd : (c < NH ? a.wg : a.wu);
+                wbase[c] = (const unsigned char*)w + ((size_t)e * NO + col0 + (c % NH) * 16) * (size_t)K * ESZ;
+            }
+            if (FP8) {
+                const size_t srow = ((size_t)e * (NO / 128) + col0 / 128) * (size_t)(K / 128);
+                sbase[0] = (PHASE == 2 ? a.sd : a.sg) + srow;
+                sbase[1] = (PHASE == 2 ? a.sd : a.su) + srow;
+            }
+            struct Buf { u32x4 w[NC][WL], x[T][2]; float sc[2]; };
+            Buf buf[D];
+            // steps past the last one read through an empty descriptor: zeros, and no memory traffic
+            auto load = [&](Buf& b, int i) __attribute__((always_inline)) {
+                const bool live = i < n;
+                int kc = wave + W * i + rot;                               // (a step past the last one may lie up to W * D further: not read)
+                kc = kc >= KT ? kc - KT : kc;
+                const unsigned int k0 = (unsigned int)kc * 64u;
+                const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc((void*)xbase, 0, live ? xbytes : 0u, 0x00020000);
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)wbase[c], 0, live ? wbytes : 0u, 0x00020000);
+#pragma unroll
+                    for (int j = 0; j < WL; ++j) b.w[c][j] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + k0 * ESZ + j * 64, 0, 0);
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) b.x[t][j] = __builtin_amdgcn_raw_buffer_load_b128(rx, xoff[t] + k0 * xstep + j * xhalf, 0, 0);
+                if (FP8) {
+                    const int kb = (int)(min(k0, (unsigned int)K - 64u) >> 7);
+                    b.sc[0] = sbase[0][kb];
+                    if (PHASE == 1) b.sc[1] = sbase[1][kb];
+                }
+            };
+            auto multiply = [&](const Buf& b) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        u32x4 wv;
+                        if (FP8) {
+                            const u32x4 q = b.w[c][0];
+                            wv = dequant8(j == 0 ? u32x2{q.x, q.y} : u32x2{q.z, q.w}, b.sc[PHASE == 1 && c >= NH ? 1 : 0]);
+                        } else {
+                            wv = b.w[c][FP8 ? 0 : j];
+                        }
+#pragma unroll
+                        for (int t = 0; t < T; ++t)
+                            acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv),
+                                                                                __builtin_bit_cast(bf16x8, b.x[t][j]), acc[c][t], 0, 0, 0);
+                    }
+            };
+#pragma unroll
+            for (int i = 0; i < D - 1; ++i) load(buf[i], i);
+            for (int i = 0; i < n; i += D) {
+#pragma unroll
+                for (int u = 0; u < D; ++u) {
+                    load(buf[(u + D - 1) % D], i + u + D - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    multiply(buf[u]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            // ---- partial sums of the wavefronts; acc[c][t][v]: weight row 4 * g4 + v of column tile c, row r16 of row tile t
+#pragma unroll
+            for (int t0 = 0; t0 < T; t0 += PASS) {
+                if (t0 > 0) __syncthreads();
+#pragma unroll
+                for (int t = t0; t < t0 + PASS && t < T; ++t)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) s_red[((t - t0) * NC + c) * (W * 64) + wave * 64 + lane] = acc[c][t];
+                __syncthreads();
+                const int here = min(PASS, T - t0);
+                for (int it = tid; it < here * NH * 64; it += W * 64) {
+                    const int l = it & 63, c = (it >> 6) % NH, t = (it >> 6) / NH;
+                    const int pos = (t0 + t) * 16 + (l & 15);
+                    f32x4 s0 = s_red[(t * NC + c) * (W * 64) + l], s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int w = 1; w < W; ++w) s0 += s_red[(t * NC + c) * (W * 64) + w * 64 + l];
+                    if (PHASE == 1) {
+#pragma unroll
+                        for (int w = 0; w < W; ++w) s1 += s_red[(t * NC + c + NH) * (W * 64) + w * 64 + l];
+                    }
+                    if (pos < rows) {
+                        const int m = s_row[pos];
+                        const int col = col0 + c * 16 + 4 * (l >> 4);
+                        if (PHASE == 1) {
+                            *reinterpret_cast<u32x2*>(a.h + ((size_t)(col >> 3) * a.M + m) * 8 + (col & 7)) =
+                                pack4(silu(s0[0]) * s1[0], silu(s0[1]) * s1[1], silu(s0[2]) * s1[2], silu(s0[3]) * s1[3]);
+                        } else {
+                            const float gate = a.row_gate ? a.row_gate[m] : 1.0f;
+                            *reinterpret_cast<u32x2*>(a.y + (size_t)mapped(m) * a.d + col) =
+                                pack4(gate * s0[0], gate * s0[1], gate * s0[2], gate * s0[3]);
+                        }
+                    }
+                }
+            }
+        };
+        const int tiles = (rows + 15) / 16;
+        if (MT == 1 || tiles == 1)      work(std::integral_constant<int, 1>{});
+        else if (MT == 2 || tiles == 2) work(std::integral_constant<int, (MT < 2 ? MT : 2)>{});
+        else if (MT == 3 || tiles == 3) work(std::integral_constant<int, (MT < 3 ? MT : 3)>{});
+        else                            work(std::integral_constant<int, MT>{});
+        __syncthreads();                                                   // s_row and s_red are used again
+    }
+}
+
 // Expands block-scaled E4M3 codes [rows][cols] to bf16, eight values per thread and step (HBM bound: 3 bytes per weight).
 __global__ __launch_bounds__(256)
 void ffn_expand_fp8_kernel(const unsigned char* __restrict__ codes, const float* __restrict__ scales, __bf16* __restrict__ out,
@@ -1342,6 +1557,29 @@ moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
     moe_status st = launch_gemm<1, ROWS, FP8>(a, max_blocks * (a.f / 128), s);
     if (st != MOE_OK) return st;
     return launch_gemm<2, ROWS, FP8>(a, max_blocks * (a.d / BN), s);
+}
+
+template <int PHASE, int W, int NC, int D, bool FP8>
+moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
+    const int strips = (PHASE == 1 ? a.f / (8 * NC) : a.d / (16 * NC));
+    const dim3 grid(strips, a.E, std::min((a.M + SKINNY_ROWS - 1) / SKINNY_ROWS, 8));
+    moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
+    // (fewer rows in the whole call than a workgroup takes: the variants with fewer row tiles need fewer registers)
+    if (a.M <= 16)      hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, 1, D, FP8>), grid, dim3(W * 64), 0, s, a);
+    else if (a.M <= 32) hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, 2, D, FP8>), grid, dim3(W * 64), 0, s, a);
+    else                hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, 4, D, FP8>), grid, dim3(W * 64), 0, s, a);
+    return k.done();
+}
+
+// Weight rows per workgroup: 64 (the 64 rows of activations are then fetched as often as the weights), but 16 in phase 2 when
+// the strips of 64 would leave half the compute units idle: d = 4096, f = 14336, one expert, phase 2 at 37 rows: 64 rows 75 us,
+// 16 rows 39 us; d = 7168, f = 2048, four fp8 experts, 203 rows: 28 us, 59 us.
+template <bool FP8>
+moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
+    moe_status st = launch_skinny<1, 4, 4, 2, FP8>(a, s);
+    if (st != MOE_OK) return st;
+    if ((long long)(a.d / 64) * a.E >= num_cus() / 2) return launch_skinny<2, 4, 4, 2, FP8>(a, s);
+    return launch_skinny<2, 4, 1, 4, FP8>(a, s);
 }
 
 moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
@@ -1604,6 +1842,24 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
         if (st != MOE_OK) return st;
         return moe_expert_ffn_sliced_mapped(x, offsets, M, S, E_loc, d, f, MOE_W_BF16, wg, wu, wd, nullptr, nullptr, nullptr,
                                             row_map, row_gate, y, workspace, base_bytes, hip_stream);
+    }
+
+    // Few rows per expert: the weights are streamed, once per 64 rows, by the kernels made for that.  Where that ends depends on
+    // how many tiles the tile kernels would have for the chip (the column tiles of phase 2, E_loc * d / 256).  Measured at
+    // 16 / 64 / 128 / 256 rows per expert, us, tiles against streaming:
+    //    16 column tiles (E 1, d 4096, f 14336)        572 / 399 / 576 / 561     74 / 117 / 213 / 373
+    //    32              (E 4, d 2048, f 1408)          95 /  84 / 103 / 122     25 /  34 /  64 / 109
+    //   112              (E 4, d 7168, f 2048)         319 / 291 / 222 / 341     79 / 150 / 230 / 397
+    //   112, fp8         (E 4, d 7168, f 2048)         399 / 365 / 316 / 432     48 / 108 / 162 / 277
+    //   224              (E 8, d 7168, f 2048)         332 / 264 / 294 / 550    156 / 274 / 444 / 777
+    const long long tiles2 = (long long)E_loc * (d / 256);
+    const long long most = std::min(256LL, std::max(48LL, (fp8 ? 24576LL : 12288LL) / tiles2));
+    // (32-bit offsets into x and h; every workgroup scans the slices of its expert)
+    if (g_force_rows.load(std::memory_order_relaxed) == 0 && M <= most * E_loc && S <= SKINNY_MAX_SLICES && E_loc <= 4096 &&
+        (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull) {
+        const SkinnyArgs k = {(const __bf16*)x, (__bf16*)workspace, (__bf16*)y, w_gate, w_up, w_down, s_gate, s_up, s_down,
+                              offsets, row_map, row_gate, M, S, E_loc, d, f};
+        return fp8 ? launch_both_skinny<true>(k, s) : launch_both_skinny<false>(k, s);
     }
 
     // rows per tile by the rows an expert has on average (its slices are merged)

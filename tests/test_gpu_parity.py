@@ -752,14 +752,51 @@ def test_ffn_slices_of_an_expert_share_tiles(lib, S, E_loc, M, tile_rows):
         ym = lib.moe_expert_ffn_sliced_mapped(x, dev(offsets), S, E_loc, row_map=row_map, row_gate=gate, **w)
         gathered = lib.moe_expert_ffn_sliced_mapped(x[row_map.long()].contiguous(), dev(offsets), S, E_loc,
                                                     row_map=torch.arange(M, dtype=torch.int32, device=DEV), row_gate=gate, **w)
+        plain = lib.moe_expert_ffn_sliced(x[row_map.long()].contiguous(), dev(offsets), S, E_loc, **w)      # (by the same kernels)
         torch.cuda.synchronize()
     finally:
         lib.moe_ffn_tile_override()
     assert torch.equal(y[order].view(torch.int16), want.view(torch.int16))
     assert torch.equal(ym[row_map.long()].view(torch.int16), gathered.view(torch.int16))
     # and the weighted rows are the plain ones times the weight, up to the two roundings to bf16 (2^-8 of the value each)
-    plain = lib.moe_expert_ffn_sliced(x[row_map.long()].contiguous(), dev(offsets), S, E_loc, **w).float() * gate[:, None]
+    plain = plain.float() * gate[:, None]
     assert bool(((gathered.float() - plain).abs() <= 2.0 ** -7 * plain.abs() + 1e-30).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("E_loc,d,f,sizes", [
+    (1, 256, 128, [[1]]), (1, 512, 1408, [[15]]), (2, 256, 384, [[16, 17]]), (1, 1280, 256, [[20], [0], [13], [30]]),
+    (3, 256, 640, [[0, 65, 1], [64, 0, 0], [0, 0, 47]]), (2, 512, 128, [[3, 1]] * 300), (8, 4096, 256, [[9, 0, 33, 1, 64, 2, 0, 40]] * 2),
+    (4, 256, 256, [[600, 3, 0, 80]]), (2, 8192, 128, [[129, 40]])])
+def test_ffn_few_rows_per_expert(lib, dtype, E_loc, d, f, sizes):
+    """The kernels that stream the weights: every row against the oracle, and through a row map with weights.  Sizes: ends of the
+    16-row tiles and of the 64-row chunks, more chunks than the grid has (600 rows of one expert), experts without rows, more
+    slices than a workgroup has threads, steps of K that do not divide by the wavefronts (2, 4, 6, 10, 20, 22), both strip
+    widths of phase 2 (64 from E_loc * d / 64 >= half the compute units on: the 8 x 4096 and 2 x 8192 cases)."""
+    say("ffn few rows per expert", dtype, E_loc, d, f, len(sizes))
+    offsets = np.concatenate([[0], np.cumsum(np.array(sizes).ravel())]).astype(np.int32)
+    M, S = int(offsets[-1]), len(sizes)
+    W = workloads.ffn_weights(E_loc, d, f, seed=d + f, dtype=dtype)
+    x = workloads.activations(M + 3, d, seed=M)
+    w = upload_weights(W)
+    y0 = torch.full((M + 3, d), 3.0, dtype=torch.bfloat16, device=DEV)
+    y = lib.moe_expert_ffn_sliced(dev_bf16(x), dev(offsets), S, E_loc, y=y0, **w)
+    torch.cuda.synchronize()
+    ref = oracle.expert_ffn_sliced(x, offsets, E_loc, W)
+    yb = host_bf16_bits(y)
+    check_ffn_error(ffn_error(yb[:M], ref, offsets), dtype)
+    assert (oracle.decode_bf16(yb[M:]) == 3.0).all()                                  # rows past the end untouched
+    # row m at row_map[m], weighted: the same row products, so the plain result times the weight up to two roundings to bf16
+    rng = np.random.default_rng(M)
+    row_map, gate = rng.permutation(M).astype(np.int32), rng.random(M, dtype=np.float32)
+    xm = np.empty_like(x[:M])
+    xm[row_map] = x[:M]
+    ones = lib.moe_expert_ffn_sliced_mapped(dev_bf16(xm), dev(offsets), S, E_loc, row_map=dev(row_map), **w)
+    ym = lib.moe_expert_ffn_sliced_mapped(dev_bf16(xm), dev(offsets), S, E_loc, row_map=dev(row_map), row_gate=dev(gate), **w)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_bf16_bits(ones)[row_map], yb[:M])
+    plain = oracle.decode_bf16(yb[:M]) * gate[:, None]
+    assert (np.abs(oracle.decode_bf16(host_bf16_bits(ym)[row_map]) - plain) <= 2.0 ** -7 * np.abs(plain) + 1e-30).all()
 
 
 # ------------------------------------------------------------------------------ FFN backward
