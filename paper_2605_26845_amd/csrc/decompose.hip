@@ -15,6 +15,7 @@
 //     in order, each by one breadth-first search over alternating paths on 128-bit lane masks.
 #include "common.hpp"
 #include <limits.h>
+#include <type_traits>
 
 namespace {
 
@@ -76,6 +77,17 @@ __device__ __forceinline__ unsigned long long ballot64(bool p) { return __builti
 // between a lane's store and another lane's load, only that the compiler keeps that order and that pending
 // LDS traffic has drained.  (__syncthreads() would also wait for every outstanding global store.)
 __device__ __forceinline__ void lds_fence() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// f(0) .. f(n - 1), U at a time.  (The compiler does not unroll loops of unknown length around cross-lane operations.)
+template <int U, typename F>
+__device__ __forceinline__ void blocked_loop(int n, F f) {
+    int i = 0;
+    for (; i + U <= n; i += U) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) f(i + k);
+    }
+    for (; i < n; ++i) f(i);
+}
 
 // lane-distributed arrays: element idx lives in lane idx & 63, slot idx >> 6 (one slot: 0 <= idx < 64, and an index
 // outside that range matches no lane in set_at)
@@ -210,8 +222,7 @@ __device__ __forceinline__ void build_masks(const T* R, int N, int lane, Mask<NP
 #pragma unroll
     for (int s = 0; s < NPL; ++s) tm[s].clear();
     const Mask<NPL> cols = below<NPL>(N);
-#pragma unroll 4
-    for (int i = 0; i < N; ++i) {
+    blocked_loop<4>(N, [&](int i) __attribute__((always_inline)) {
         Mask<NPL> row;
 #pragma unroll
         for (int s = 0; s < NPL; ++s) {
@@ -221,7 +232,7 @@ __device__ __forceinline__ void build_masks(const T* R, int N, int lane, Mask<NP
 #pragma unroll
         for (int s = 0; s < NPL; ++s)
             if (lane == (i & 63) && s == (i >> 6)) tm[s] = row;
-    }
+    });
 }
 
 // One level of the alternating breadth-first search used by both the lexicographic pass and
@@ -432,6 +443,151 @@ __device__ __forceinline__ void emit_matching(const int (&sigma)[NPL], int durat
     }
 }
 
+// ------------------------------------------------------------------------------ greedy search
+// One shortest augmenting path from the unmatched row r, in Dijkstra form: dist_j = length of the shortest alternating path
+// found so far from row r to column j in the reduced costs u_i + v_j - R_ij of the duals at the start of the search (they
+// are updated once, at its end).  Of the columns at the least distance one without an owner is taken first: it ends the
+// search (128 ranks: 872 -> 471 steps per matching, 64 ranks: 252 -> 204).  Returns the number of steps; D_end = length of the path.
+// PACKED: distance, "has an owner" and column number share one 32-bit key, so that the wave minimum yields all three, and a
+// scanned column is one whose key and potential carry the bit CLOSED: no lane masks, no ballots, no selects in a step.
+// A candidate is at most D + u + v and D at most max u + max v (the edge from r to any column without an owner), so keys
+// stay below CLOSED / 2 while max u + max v < MOST; beyond that the plain form runs.
+template <int NPL> struct Packed {
+    static constexpr int COL_BITS = NPL == 1 ? 6 : 7, SHIFT = COL_BITS + 1;
+    static constexpr int OWNED = 1 << COL_BITS, CLOSED = 1 << 30;
+    static constexpr int MOST = 1 << (29 - SHIFT - 1);
+};
+__device__ __forceinline__ int scalar_min(int a, int b) {
+    int r;
+    asm("s_min_i32 %0, %1, %2" : "=s"(r) : "s"(a), "s"(b) : "scc");
+    return r;
+}
+// wave_min_rows with the last steps on the scalar unit (the compiler takes them back to vector registers for a three-way minimum)
+template <int NW>
+__device__ __forceinline__ int wave_min_scalar(int x) {
+    x = min_dpp<0xB1>(x);
+    x = min_dpp<0x4E>(x);
+    x = min_dpp<0x141>(x);
+    x = min_dpp<0x140>(x);
+    int m = __builtin_amdgcn_readlane(x, 0);
+    if (NW > 1) {
+        const int b = __builtin_amdgcn_readlane(x, 16);
+        if (NW > 2) {
+            const int c = __builtin_amdgcn_readlane(x, 32), d = __builtin_amdgcn_readlane(x, 48);
+            m = scalar_min(scalar_min(m, b), scalar_min(c, d));
+        } else {
+            m = scalar_min(m, b);
+        }
+    }
+    return m;
+}
+template <int NPL, int NW, bool PACKED, typename T>
+__device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 16 : 1], int N, int r, int lane, int (&u)[NPL],
+                                          int (&v)[NPL], int (&p)[NPL], int (&sigma)[NPL], int& D_end) {
+    typedef Packed<NPL> P;
+    const Mask<NPL> cols = below<NPL>(N);
+    int key[NPL], way[NPL], pot[NPL], at[NPL];
+    Mask<NPL> used, vacant;            // plain form: scanned columns (those that do not exist count as scanned); columns without an owner
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) {
+        const int j = lane + 64 * s;
+        key[s] = INT_MAX;
+        way[s] = -1;
+        at[s] = j < N ? j : N - 1;
+        if (PACKED) pot[s] = j < N ? (int)((unsigned)v[s] << P::SHIFT) + (p[s] >= 0 ? P::OWNED : 0) + j : P::CLOSED;
+        else        { pot[s] = v[s]; used.w[s] = ~cols.w[s]; vacant.w[s] = ballot64(p[s] < 0) & cols.w[s]; }
+    }
+    int i0 = r, j0 = -1, D = 0, steps = 0;
+    while (steps < N) {
+        int entry[NPL], local = INT_MAX;
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) {
+            if constexpr (NW == 1) entry[s] = Rc[i0 & 15]; else entry[s] = (int)R[i0 * N + at[s]];
+        }
+        const int base = D + bcast<NPL>(u, i0);                          // row i0 entered the tree at distance D
+        int keyed[NPL];
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) {
+            if constexpr (PACKED) {
+                const int c = pot[s] + (int)((unsigned)base << P::SHIFT) - (int)((unsigned)entry[s] << P::SHIFT);
+                way[s] = c < key[s] ? j0 : way[s];
+                key[s] = min(key[s], c);
+                local = min(local, key[s]);
+            } else {
+                const bool open = !__builtin_amdgcn_inverse_ballot_w64(used.w[s]);
+                const int c = open ? base + pot[s] - entry[s] : INT_MAX;
+                way[s] = c < key[s] ? j0 : way[s];
+                key[s] = min(key[s], c);
+                keyed[s] = open ? key[s] : INT_MAX;
+                local = min(local, keyed[s]);
+            }
+        }
+        const int m = wave_min_scalar<NW>(local);                        // (finite: row r is unmatched, so a column is vacant)
+        ++steps;
+        if constexpr (PACKED) {
+            D = m >> P::SHIFT;
+            j0 = m & (P::OWNED - 1);
+            if (!(m & P::OWNED)) break;
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) {
+                const int shut = key[s] == m ? P::CLOSED : 0;
+                key[s] += shut;
+                pot[s] += shut;
+            }
+        } else {
+            D = m;
+            Mask<NPL> eq;
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) eq.w[s] = ballot64(keyed[s] == m);
+            const Mask<NPL> ends = eq & vacant;
+            const bool last = ends.any();
+            j0 = last ? ends.first() : eq.first();
+            used.set(j0);
+            if (last) break;
+        }
+        i0 = bcast<NPL>(p, j0);
+    }
+    // duals: a scanned column j rises by D - dist_j, its row falls by the same amount, row r falls by D
+    // (tree edges stay tight, everything stays feasible, the new path is tight)
+    int du[NPL];
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) {
+        const int sg = sigma[s];                                         // the column of this lane's row, if it has one
+        const int src = sg < 0 ? 0 : sg;
+        int kc = __shfl(key[0], src & 63);
+        if (NPL > 1) { const int k1 = __shfl(key[NPL - 1], src & 63); kc = (src >> 6) ? k1 : kc; }
+        bool rin;
+        if constexpr (PACKED) {
+            rin = sg >= 0 && (kc & P::CLOSED);
+            kc = (kc & (P::CLOSED - 1)) >> P::SHIFT;
+        } else {
+            rin = sg >= 0 && used.test(src);
+        }
+        du[s] = lane + 64 * s == r ? D : (rin ? D - kc : 0);
+    }
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) {
+        if constexpr (PACKED) {
+            if (lane + 64 * s < N && (key[s] & P::CLOSED)) v[s] += D - ((key[s] & (P::CLOSED - 1)) >> P::SHIFT);
+        } else {
+            if (__builtin_amdgcn_inverse_ballot_w64(used.w[s] & cols.w[s])) v[s] += D - key[s];
+        }
+        u[s] -= du[s];
+    }
+    // flip the path back to row r
+    for (int guard = 0; guard <= N; ++guard) {
+        const int j1 = bcast<NPL>(way, j0);
+        int i = r;
+        if (j1 >= 0) i = bcast<NPL>(p, j1);
+        set_at<NPL>(p, j0, i, lane);
+        set_at<NPL>(sigma, i, j0, lane);
+        if (j1 < 0) break;
+        j0 = j1;
+    }
+    D_end = D;
+    return steps;
+}
+
 // ------------------------------------------------------------------------------ greedy kernel
 template <int NPL, typename T, int NW>            // NW: 16-lane rows that hold columns (1, 2 or 4)
 __global__ __launch_bounds__(MOE_WAVE)
@@ -488,181 +644,109 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
 #pragma unroll
             for (int i = 0; i < 16; ++i) Rc[i] = i < N ? (int)col[i * N] : 0;
         }
+        // ---- column reduction: lower v_j until column j has a tight edge.  The matching before took its entries out of the
+        //      residual, which leaves room; the searches below get shorter by it (16 / 64 / 128 ranks: 43 / 378 / 1115 -> 30 / 252 /
+        //      872 steps per matching), and it costs no reduction across lanes.
+        {
+            int top[NPL];
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) top[s] = INT_MIN;
+            if constexpr (NW == 1) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    if (i < N) top[0] = max(top[0], Rc[i] - __builtin_amdgcn_readlane(u[0], i));
+            } else {
+#pragma unroll
+                for (int half = 0; half < NPL; ++half) {
+                    const int rows = min(N - 64 * half, 64);
+                    blocked_loop<8>(rows, [&](int i) __attribute__((always_inline)) {
+                        const T* row = R + (64 * half + i) * N;
+                        const int ui = __builtin_amdgcn_readlane(u[half], i);
+#pragma unroll
+                        for (int s = 0; s < NPL; ++s) top[s] = max(top[s], (int)row[lane + 64 * s < N ? lane + 64 * s : N - 1] - ui);
+                    });
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) v[s] = lane + 64 * s < N ? top[s] : 0;
+        }
         // ---- row reduction: lower u_r until row r has a tight edge, and take that edge if its column is free.
         //      (Duals stay feasible, matched edges are tight; most rows are settled here and skip the search.)
-        if constexpr (NPL == 1) {
-            // u_r <- max_j (R_rj - v_j) does not depend on the other rows: only the set of taken columns (a scalar
-            // mask) links the iterations, so their LDS reads and reductions overlap
-            const bool incol = lane < N;
-            const T* Rcol = R + (incol ? lane : N - 1);
-            unsigned long long taken = 0;
-            auto reduce_row = [&](int r, int entry) __attribute__((always_inline)) {
-                const int x = incol ? entry - v[0] : INT_MIN;             // lanes without a column never win or tie
-                const int m = wave_max_rows<NW>(x);
-                const unsigned long long avail = ballot64(x == m) & ~taken;
-                // branch-free, so that the reductions of consecutive rows overlap: no free tight column = column -1
-                const int pick = __builtin_ffsll((long long)avail) - 1;
-                taken |= avail & (0ULL - avail);
-                if (lane == pick) p[0] = r;
-                if (lane == r) { u[0] = m; sigma[0] = pick; }
+        // u_r <- max_j (R_rj - v_j) does not depend on the other rows: only the sets of taken columns (scalar masks) link the
+        // iterations, so their LDS reads and reductions overlap
+        {
+            Mask<NPL> vacant = below<NPL>(N);
+            auto reduce_row = [&](auto half_tag, int r, const int (&entry)[NPL]) __attribute__((always_inline)) {
+                constexpr int H = decltype(half_tag)::value;                  // rows 64 * H ...: lane r of slot H holds row 64 * H + r
+                int x[NPL], local = INT_MIN;
+#pragma unroll
+                for (int s = 0; s < NPL; ++s) {
+                    x[s] = lane + 64 * s < N ? entry[s] - v[s] : INT_MIN;     // lanes without a column never win or tie
+                    local = max(local, x[s]);
+                }
+                const int m = wave_max_rows<NW>(local);
+                // branch-free, so that the reductions of consecutive rows overlap: no vacant tight column = column -1
+                int pick = -1;
+                bool found = false;
+#pragma unroll
+                for (int s = 0; s < NPL; ++s) {
+                    const unsigned long long avail = ballot64(x[s] == m) & vacant.w[s];
+                    const unsigned long long take = found ? 0ULL : avail & (0ULL - avail);
+                    vacant.w[s] &= ~take;
+                    if (__builtin_amdgcn_inverse_ballot_w64(take)) p[s] = 64 * H + r;
+                    pick = take ? 64 * s + __builtin_ctzll(take) : pick;
+                    found = found || take != 0;
+                }
+                if (lane == r) { u[H] = m; sigma[H] = pick; }
             };
             if constexpr (NW == 1) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    if (r < N) reduce_row(r, Rc[r]);
+                    if (r < N) { const int entry[1] = {Rc[r]}; reduce_row(std::integral_constant<int, 0>{}, r, entry); }
             } else {
-#pragma unroll 4
-                for (int r = 0; r < N; ++r) reduce_row(r, (int)Rcol[r * N]);
-            }
-        } else {
-            Mask<NPL> free_cols = below<NPL>(N);                       // columns nobody has taken yet
-            for (int r = 0; r < N; ++r) {
-                const T* row = R + r * N;
-                int x[NPL], local = INT_MIN;
+                auto rows = [&](auto half_tag) __attribute__((always_inline)) {
+                    constexpr int H = decltype(half_tag)::value;
+                    const int n = min(N - 64 * H, 64);
+                    blocked_loop<4>(n, [&](int r) __attribute__((always_inline)) {
+                        const T* row = R + (64 * H + r) * N;
+                        int entry[NPL];
 #pragma unroll
-                for (int s = 0; s < NPL; ++s) {
-                    const int j = lane + 64 * s;
-                    x[s] = j < N ? (int)row[j] - v[s] : INT_MIN;        // lanes without a column never win or tie
-                    local = max(local, x[s]);
-                }
-                const int m = wave_max(local);
-                set_at<NPL>(u, r, m, lane);
-                int pick = -1;
-#pragma unroll
-                for (int s = NPL - 1; s >= 0; --s) {
-                    const unsigned long long f = ballot64(x[s] == m) & free_cols.w[s];
-                    if (f) pick = 64 * s + __builtin_ctzll(f);
-                }
-                if (pick >= 0) {
-                    free_cols.reset(pick);
-                    set_at<NPL>(p, pick, r, lane);
-                    set_at<NPL>(sigma, r, pick, lane);
-                }
+                        for (int s = 0; s < NPL; ++s) entry[s] = (int)row[lane + 64 * s < N ? lane + 64 * s : N - 1];
+                        reduce_row(half_tag, r, entry);
+                    });
+                };
+                rows(std::integral_constant<int, 0>{});
+                if constexpr (NPL > 1) rows(std::integral_constant<int, NPL - 1>{});
             }
         }
         // ---- maximum-weight perfect matching: one shortest augmenting path per row still unmatched
-        if constexpr (NPL == 1) {
-            // One column per lane: Dijkstra form of the search.  dist_j = length of the shortest alternating path found
-            // so far from row r to column j in reduced costs u_i + v_j - R_ij of the duals at the start of the search
-            // (they are updated once, at its end); the set of scanned columns is a scalar bit mask.
-            const bool incol = lane < N;
-            const unsigned long long beyond = N >= 64 ? 0ULL : ~0ULL << N;     // lanes that hold no column count as scanned
-            const T* Rcol = R + (incol ? lane : N - 1);
-            unsigned long long todo = ballot64(incol && sigma[0] < 0);
-            while (todo) {
-                const int r = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                int dist = INT_MAX, way[1] = {-1};
-                unsigned long long used = beyond;
-                int i0 = r, j0 = -1, D = 0;
-                for (int step = 0; step < N; ++step) {
-                    const int base = D + rdlane(u[0], i0);               // row i0 entered the tree at distance D
-                    const bool open = !__builtin_amdgcn_inverse_ballot_w64(used);
-                    int entry;
-                    if constexpr (NW == 1) entry = Rc[i0 & 15]; else entry = (int)Rcol[i0 * N];
-                    const int cand = open ? base + v[0] - entry : INT_MAX;
-                    way[0] = cand < dist ? j0 : way[0];
-                    dist = min(dist, cand);
-                    const int key = open ? dist : INT_MAX;
-                    D = wave_min_rows<NW>(key);                          // (finite: row r is unmatched, so a column is free)
-                    const int j1 = __builtin_ctzll(ballot64(key == D));
-                    used |= 1ULL << j1;
-                    j0 = j1;
-                    i0 = rdlane(p[0], j1);
-                    ++n_steps;
-                    if (i0 < 0) break;
-                }
-                ++n_searches;
-                used &= ~beyond;
-                // duals: a scanned column j rises by D - dist_j, its row falls by the same amount, row r falls by D
-                // (tree edges stay tight, everything stays feasible, the new path is tight)
-                const int sg = sigma[0];
-                const int dcol = __shfl(dist, sg < 0 ? 0 : sg);
-                const bool rin = sg >= 0 && ((used >> sg) & 1ULL);
-                if (__builtin_amdgcn_inverse_ballot_w64(used)) v[0] += D - dist;
-                if (lane == r) u[0] -= D; else if (rin) u[0] -= D - dcol;
-                // flip the path back to row r
-                for (int guard = 0; guard <= N; ++guard) {
-                    int j1 = bcast<NPL>(way, j0);
-                    int i = r;
-                    if (j1 >= 0) i = bcast<NPL>(p, j1);
-                    set_at<NPL>(p, j0, i, lane);
-                    set_at<NPL>(sigma, i, j0, lane);
-                    if (j1 < 0) break;
-                    j0 = j1;
-                }
-            }
-        } else {
-            // The same search with NPL columns per lane; the sets of scanned columns are NPL uniform masks.
+        {
             const Mask<NPL> cols = below<NPL>(N);
             Mask<NPL> todo;
 #pragma unroll
             for (int s = 0; s < NPL; ++s) todo.w[s] = ballot64(sigma[s] < 0) & cols.w[s];
+            // upper bound of max u + max v: a search raises no v by more than its length, and no u
+            auto dual_bound = [&]() __attribute__((always_inline)) {
+                int mu = INT_MIN, mv = INT_MIN;
+#pragma unroll
+                for (int s = 0; s < NPL; ++s)
+                    if (lane + 64 * s < N) { mu = max(mu, u[s]); mv = max(mv, v[s]); }
+                mu = wave_max(mu); mv = wave_max(mv);
+                return mu < Packed<NPL>::MOST && mv < Packed<NPL>::MOST ? max(mu, 0) + max(mv, 0) : Packed<NPL>::MOST;
+            };
+            int bound = dual_bound();
             while (todo.any()) {
                 const int r = todo.first();
                 todo.reset(r);
-                int dist[NPL], way[NPL];
-                Mask<NPL> used;                                          // columns that do not exist count as scanned
-#pragma unroll
-                for (int s = 0; s < NPL; ++s) { dist[s] = INT_MAX; way[s] = -1; used.w[s] = ~cols.w[s]; }
-                int i0 = r, j0 = -1, D = 0;
-                for (int step = 0; step < N; ++step) {
-                    const int base = D + bcast<NPL>(u, i0);              // row i0 entered the tree at distance D
-                    const T* row = R + i0 * N;
-                    int key[NPL], local = INT_MAX;
-#pragma unroll
-                    for (int s = 0; s < NPL; ++s) {
-                        const int j = lane + 64 * s;
-                        const bool open = !__builtin_amdgcn_inverse_ballot_w64(used.w[s]);
-                        const int entry = (int)row[j < N ? j : N - 1];
-                        const int cand = open ? base + v[s] - entry : INT_MAX;
-                        way[s] = cand < dist[s] ? j0 : way[s];
-                        dist[s] = min(dist[s], cand);
-                        key[s] = open ? dist[s] : INT_MAX;
-                        local = min(local, key[s]);
-                    }
-                    D = wave_min(local);                                 // (finite: row r is unmatched, so a column is free)
-                    int j1 = -1;
-#pragma unroll
-                    for (int s = NPL - 1; s >= 0; --s) {
-                        const unsigned long long m = ballot64(key[s] == D);
-                        if (m) j1 = 64 * s + __builtin_ctzll(m);
-                    }
-                    used.set(j1);
-                    j0 = j1;
-                    i0 = bcast<NPL>(p, j1);
-                    ++n_steps;
-                    if (i0 < 0) break;
+                int D;
+                if (bound < Packed<NPL>::MOST) {
+                    n_steps += search_row<NPL, NW, true>(R, Rc, N, r, lane, u, v, p, sigma, D);
+                    bound += D;
+                    if (bound >= Packed<NPL>::MOST) bound = dual_bound();
+                } else {
+                    n_steps += search_row<NPL, NW, false>(R, Rc, N, r, lane, u, v, p, sigma, D);
                 }
                 ++n_searches;
-                // duals: a scanned column j rises by D - dist_j, its row falls by the same amount, row r falls by D
-#pragma unroll
-                for (int s = 0; s < NPL; ++s) used.w[s] &= cols.w[s];
-                int du[NPL];
-#pragma unroll
-                for (int s = 0; s < NPL; ++s) {
-                    const int sg = sigma[s];                             // the column of this lane's row, if it has one
-                    const int src = sg < 0 ? 0 : sg;
-                    int dcol = __shfl(dist[0], src & 63);
-                    if (NPL > 1) { const int d1 = __shfl(dist[NPL - 1], src & 63); dcol = (src >> 6) ? d1 : dcol; }
-                    const bool rin = sg >= 0 && used.test(src);
-                    du[s] = lane + 64 * s == r ? D : (rin ? D - dcol : 0);
-                }
-#pragma unroll
-                for (int s = 0; s < NPL; ++s) {
-                    if (__builtin_amdgcn_inverse_ballot_w64(used.w[s])) v[s] += D - dist[s];
-                    u[s] -= du[s];
-                }
-                // flip the path back to row r
-                for (int guard = 0; guard <= N; ++guard) {
-                    int j1 = bcast<NPL>(way, j0);
-                    int i = r;
-                    if (j1 >= 0) i = bcast<NPL>(p, j1);
-                    set_at<NPL>(p, j0, i, lane);
-                    set_at<NPL>(sigma, i, j0, lane);
-                    if (j1 < 0) break;
-                    j0 = j1;
-                }
             }
         }
         // ---- canonical optimum: lexicographically smallest perfect matching of the tight graph

@@ -153,6 +153,23 @@ def test_decompose_special_cases(lib):
         lib.moe_decompose_greedy(torch.zeros((1, 129, 129), dtype=torch.int32, device=DEV), 4)
 
 
+@pytest.mark.parametrize("N,limit", [(2, 21), (16, 21), (31, 21), (64, 21), (65, 20), (128, 20)])
+def test_greedy_keys_of_32_bits(lib, N, limit):
+    """The search packs distance and column into one key while the duals stay below 2^limit and keeps them apart beyond: entries
+    just below, around and above half of that (max u + max v of the first matching is the largest entry), one row or column far
+    above the rest, and a matrix whose later matchings fall below the limit again."""
+    say("greedy keys of 32 bits", N, limit)
+    rng = np.random.default_rng(N)
+    mats = np.stack([rng.integers(h // 2, h, (N, N)) for h in (1 << (limit - 2), 1 << (limit - 1), (1 << limit) - 1, 1 << limit, 1 << (limit + 1))]
+                    + [rng.integers(0, 50, (N, N)) for _ in range(4)]).astype(np.int32)
+    mats[5, 0] += (1 << limit) - 60                                       # one row / column above the rest
+    mats[6, :, N - 1] += (1 << limit) - 25
+    mats[7, N // 2] += 1 << (limit + 2)
+    mats[8, 0, 0] = (1 << 30) // N                                        # gone after the first matching
+    for kmax in (4, 2 * N):
+        check_decomposition(lib, "greedy", mats, kmax, False)
+
+
 def test_greedy_16_bit_residual(lib):
     """How the residual is held on chip (32 bits, or 16 bits with a second launch for the matrices that do not fit)
     does not change a byte of the result."""
