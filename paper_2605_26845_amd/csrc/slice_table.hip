@@ -145,7 +145,11 @@ void st_count_kernel(const int32_t* __restrict__ ids, int N, int per_src, int E,
         const int first = x0 + tid * ST_ITEMS;
         int e[ST_ITEMS];
 #pragma unroll
-        for (int k = 0; k < ST_ITEMS; ++k) e[k] = x0 == 0 ? e_first[k] : (first + k < per_src ? src[first + k] : -1);
+        for (int k = 0; k < ST_ITEMS; ++k) {
+            e[k] = e_first[k];                                         // the next pass's are in flight during this one
+            const unsigned int ahead = (unsigned int)first + ST_THREADS * ST_ITEMS + k;
+            e_first[k] = ahead < (unsigned int)per_src ? src[ahead] : -1;
+        }
         int cnt = 0;
 #pragma unroll
         for (int k = 0; k < ST_ITEMS; ++k) cnt += (e[k] >= e_lo && e[k] < e_hi) ? 1 : 0;
@@ -219,90 +223,137 @@ void st_count_kernel(const int32_t* __restrict__ ids, int N, int per_src, int E,
 // the source's assignments as st_count_kernel did.  Windows are consecutive stretches of the arrival order, so the
 // rank of an assignment inside its (window, expert) group is the number of earlier assignments of that expert minus
 // those that fell into earlier windows; what no matching shipped is appended source by source.
+// One wavefront's LDS accesses execute in order; this keeps the compiler to that order between its lanes.
+__device__ __forceinline__ void wave_lds_order() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// The workgroup's wavefronts take one stretch of the assignments each and walk it twice: once to count, so that each knows
+// what the ones before it hold, and once to place, without a barrier between them, the next chunk's ids in flight; few
+// assignments are for this rank, so a chunk's are put side by side first.  (One barrier-separated pass of the workgroup per
+// 1024 assignments: 64 sources of 65 536 assignments 174 us.)
 constexpr int PLACE_MAX_ELOC = 64;
+constexpr int PLACE_CHUNK = 256;
 __global__ __launch_bounds__(ST_THREADS)
 void st_place_kernel(const int32_t* __restrict__ ids, int N, int per_src, int E, int e_loc, int r,
                      const int32_t* __restrict__ traffic, int kmax, const int32_t* __restrict__ offsets,
                      const int2* __restrict__ win_ws, const int32_t* __restrict__ wcnt_ws, const int32_t* __restrict__ res_cnt,
                      const int32_t* __restrict__ wcount, int32_t* __restrict__ row_arrival, int32_t* __restrict__ row_assignment) {
-    __shared__ ScanSmem sm;
     __shared__ int2 lds_win[WIN_CAP];
     __shared__ int pre[CNT_CAP];                       // assignments of expert el in windows before w, at [w * e_loc + el]
-    __shared__ int cntw[ST_WAVES][PLACE_MAX_ELOC];     // this chunk: assignments of expert el seen by wavefront w
-    __shared__ int run_el[PLACE_MAX_ELOC], res_base[PLACE_MAX_ELOC];
+    __shared__ int run[ST_WAVES][PLACE_MAX_ELOC];      // assignments of expert el: of wavefront w, then those before its next one
+    __shared__ int mine_of[ST_WAVES];                  // assignments of wavefront w for this rank
+    __shared__ int res_base[PLACE_MAX_ELOC];
     __shared__ int src_base;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ unsigned short found[ST_WAVES][PLACE_CHUNK];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = blockIdx.x;
     const int W = wcount[s];
     const int2* my_ws = win_ws + (size_t)s * kmax;
     const bool win_in_lds = W <= WIN_CAP;
+    const int32_t* src = ids + (size_t)s * per_src;
+    const int e_lo = r * e_loc;
+    // this wavefront's stretch of the source's assignments
+    const unsigned int total = (unsigned int)per_src, stretch = (total + ST_WAVES * PLACE_CHUNK - 1) / (ST_WAVES * PLACE_CHUNK) * PLACE_CHUNK;
+    const unsigned int begin = min((unsigned int)wave * stretch, total), end = min(begin + stretch, total);
+    constexpr int U = PLACE_CHUNK / MOE_WAVE;
+    auto fetch = [&](int (&e)[U], unsigned int x0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const unsigned int x = x0 + k * MOE_WAVE + lane;
+            e[k] = x < end ? src[x] : -1;
+        }
+    };
+
     for (int x = tid; x < W && x < WIN_CAP; x += ST_THREADS) lds_win[x] = my_ws[x];
+    for (int x = tid; x < (W + 1) * e_loc; x += ST_THREADS) pre[x] = wcnt_ws[(size_t)s * (kmax + 1) * e_loc + x];
+    if (tid < PLACE_MAX_ELOC) res_base[tid] = 0;
+    if (tid == 0) src_base = 0;
+    run[wave][lane] = 0;
+    __syncthreads();
+    // ---- what lies before: windows of this source, sources before this one, wavefronts before this one
     if (tid < e_loc) {
-        const int32_t* c = wcnt_ws + (size_t)s * (kmax + 1) * e_loc;
         int acc = 0;
-        for (int w = 0; w <= W; ++w) { pre[w * e_loc + tid] = acc; acc += c[w * e_loc + tid]; }
+        for (int w = 0; w <= W; ++w) { const int c = pre[w * e_loc + tid]; pre[w * e_loc + tid] = acc; acc += c; }
+    }
+    if (lane < e_loc) {
         int rb = 0;
-        for (int s2 = 0; s2 < s; ++s2) rb += res_cnt[(size_t)s2 * e_loc + tid];
-        res_base[tid] = rb;
-        run_el[tid] = 0;
+        for (int s2 = wave; s2 < s; s2 += ST_WAVES) rb += res_cnt[(size_t)s2 * e_loc + lane];
+        if (rb) atomicAdd(&res_base[lane], rb);
     }
-    if (tid == 0) {
-        int b = 0;
-        for (int s2 = 0; s2 < s; ++s2) b += traffic[(size_t)s2 * N + r];
-        src_base = b;
+    for (int s2 = tid; s2 < s; s2 += ST_THREADS) atomicAdd(&src_base, traffic[(size_t)s2 * N + r]);
+    {
+        int e[U], next[U], mine = 0;
+        fetch(next, begin);
+        for (unsigned int x0 = begin; x0 < end; x0 += PLACE_CHUNK) {
+#pragma unroll
+            for (int k = 0; k < U; ++k) e[k] = next[k];
+            fetch(next, x0 + PLACE_CHUNK);
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const bool is = e[k] >= e_lo && e[k] < e_lo + e_loc;
+                if (is) atomicAdd(&run[wave][e[k] - e_lo], 1);
+                mine += __popcll(__ballot(is));
+            }
+        }
+        if (lane == 0) mine_of[wave] = mine;
     }
-    cntw[wave][lane] = 0;
+    __syncthreads();
+    if (tid < e_loc) {
+        int acc = 0;
+#pragma unroll
+        for (int w = 0; w < ST_WAVES; ++w) { const int c = run[w][tid]; run[w][tid] = acc; acc += c; }
+    }
+    int q_base = 0;
+    for (int w = 0; w < wave; ++w) q_base += mine_of[w];
     __syncthreads();
 
-    int q_base = 0;
-    const int32_t* src = ids + (size_t)s * per_src;
-    for (int x0 = 0; x0 < per_src; x0 += ST_THREADS) {
-        const int x = x0 + tid;
-        const int e = x < per_src ? src[x] : -1;
-        const bool mine = (unsigned)e < (unsigned)E && e / e_loc == r;
-        int excl, tot;
-        unsigned long long dummy_i, dummy_t;
-        block_scan(sm, mine, 0ULL, tid, excl, dummy_i, tot, dummy_t);
-        const int el = mine ? e % e_loc : 0;
-        // rank among this wavefront's assignments of the same expert, and the wavefront's count per expert
-        int rank_w = 0;
-        unsigned long long todo = __ballot(mine);
-        while (todo) {
-            const int leader = __builtin_ctzll(todo);
-            const int k = __builtin_amdgcn_readlane(el, leader);
-            const unsigned long long peers = __ballot(mine && el == k);
-            if (mine && el == k) rank_w = __popcll(peers & ((1ULL << lane) - 1ULL));
-            if (lane == leader) cntw[wave][k] = __popcll(peers);
-            todo &= ~peers;
+    // ---- second walk, every wavefront by itself (its row of `run` and of `found` is its own)
+    int e[U], next[U];
+    fetch(next, begin);
+    for (unsigned int x0 = begin; x0 < end; x0 += PLACE_CHUNK) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) e[k] = next[k];
+        fetch(next, x0 + PLACE_CHUNK);
+        int n = 0;                                     // the chunk's assignments for this rank, side by side
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const bool is = e[k] >= e_lo && e[k] < e_lo + e_loc;
+            const unsigned long long b = __ballot(is);
+            if (is) found[wave][n + __popcll(b & ((1ULL << lane) - 1ULL))] = (unsigned short)((k * MOE_WAVE + lane) | ((e[k] - e_lo) << 8));
+            n += __popcll(b);
         }
-        __syncthreads();
-        int before = 0;
-        if (mine) {
-            before = run_el[el] + rank_w;
-            for (int w = 0; w < wave; ++w) before += cntw[w][el];
-        }
-        __syncthreads();
-        if (tid < PLACE_MAX_ELOC) {
-            int add = 0;
-            for (int w = 0; w < ST_WAVES; ++w) { add += cntw[w][tid]; cntw[w][tid] = 0; }
-            if (tid < e_loc) run_el[tid] += add;
-        }
-        if (mine) {
-            const int q = q_base + excl;
-            int lo = 0, hi = W;
-            while (lo < hi) {
-                int mid = (lo + hi) >> 1;
-                int cum = win_in_lds ? lds_win[mid].y : my_ws[mid].y;
-                if (cum > q) hi = mid; else lo = mid + 1;
+        wave_lds_order();
+        for (int at = 0; at < n; at += MOE_WAVE) {
+            const bool mine = at + lane < n;
+            const int entry = mine ? found[wave][at + lane] : 0;
+            const int el = entry >> 8, x = (int)x0 + (entry & 255);
+            // rank among this group's assignments of the same expert; the expert's count so far
+            int before = 0;
+            unsigned long long todo = __ballot(mine);
+            while (todo) {
+                const int k = __builtin_amdgcn_readlane(el, __builtin_ctzll(todo));
+                const unsigned long long peers = __ballot(mine && el == k);
+                if (mine && el == k) before = run[wave][k] + __popcll(peers & ((1ULL << lane) - 1ULL));
+                if (lane == __builtin_ctzll(todo)) run[wave][k] += __popcll(peers);
+                todo &= ~peers;
+                wave_lds_order();
             }
-            const bool left = s != r && lo >= W;
-            const int slice = s == r ? 0 : (left ? kmax + 1 : (win_in_lds ? lds_win[lo].x : my_ws[lo].x));
-            const int pos = offsets[(size_t)slice * e_loc + el] + (left ? res_base[el] : 0) + before - pre[lo * e_loc + el];
-            if (row_arrival) row_arrival[pos] = src_base + q;
-            if (row_assignment) row_assignment[pos] = s * per_src + x;
+            if (mine) {
+                const int q = q_base + at + lane;
+                int lo = 0, hi = W;
+                while (lo < hi) {
+                    int mid = (lo + hi) >> 1;
+                    int cum = win_in_lds ? lds_win[mid].y : my_ws[mid].y;
+                    if (cum > q) hi = mid; else lo = mid + 1;
+                }
+                const bool left = s != r && lo >= W;
+                const int slice = s == r ? 0 : (left ? kmax + 1 : (win_in_lds ? lds_win[lo].x : my_ws[lo].x));
+                const int pos = offsets[(size_t)slice * e_loc + el] + (left ? res_base[el] : 0) + before - pre[lo * e_loc + el];
+                if (row_arrival) row_arrival[pos] = src_base + q;
+                if (row_assignment) row_assignment[pos] = s * per_src + x;
+            }
         }
-        q_base += tot;
-        __syncthreads();
+        q_base += n;
+        wave_lds_order();
     }
 }
 

@@ -393,6 +393,29 @@ def test_slice_table_walk_passes(lib, T, topk):
     assert np.array_equal(off.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("T,topk,E", [(1, 1, 5), (255, 1, 20), (256, 1, 20), (257, 1, 320), (1365, 3, 20), (4096, 1, 20), (4097, 1, 20), (33000, 2, 20)])
+def test_slice_table_rows_walk(lib, T, topk, E):
+    """The row map's walk: assignments per source below, at and above a chunk (256) and a chunk of every wavefront (4096), all or
+    few of them for the rank, 1 to 64 experts."""
+    say("slice table rows walk", T, topk, E)
+    N, r, kmax = 5, 3, 6
+    rng = np.random.default_rng(T + E)
+    ids = rng.integers(-2, E + 2, size=(N, T, topk)).astype(np.int32)
+    ids[1] = r * (E // N)                                                       # one source sends everything to one expert of r
+    traffic, _ = oracle.route_histogram(ids, E)
+    rp, rd, _ = oracle.decompose_greedy(traffic, kmax, zero_diag=True)
+    k = len(rd)
+    perms = np.zeros((kmax, N), dtype=np.uint8); perms[:k] = rp
+    dur = np.zeros(kmax, dtype=np.int32); dur[:k] = rd // 2                     # half of it is left over
+    M = int(traffic[:, r].sum())
+    off, arr, asg = lib.moe_slice_table_rows(dev(ids), E, r, dev(traffic), dev(perms), dev(dur), dev(np.array([k], dtype=np.int32)), kmax, M)
+    torch.cuda.synchronize()
+    ref_off, ref_rows = oracle.slice_table(ids, E, r, traffic, rp, rd // 2, kmax)
+    assert np.array_equal(off.cpu().numpy(), ref_off) and np.array_equal(asg.cpu().numpy(), ref_rows)
+    arrival = np.cumsum((ids.ravel() // (E // N) == r) & (ids.ravel() >= 0) & (ids.ravel() < E)) - 1
+    assert np.array_equal(arr.cpu().numpy(), arrival[ref_rows])
+
+
 def test_slice_table_rows_shapes_and_errors(lib):
     say("slice table rows shapes")
     rng = np.random.default_rng(8)
