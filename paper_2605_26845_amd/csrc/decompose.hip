@@ -177,23 +177,7 @@ __device__ __forceinline__ Mask<NPL> bcast_mask(const Mask<NPL> (&m)[NPL], int r
 
 // ------------------------------------------------------------------------------ shared pieces
 // Copy one matrix into LDS (optionally with the diagonal forced to zero).
-// 16-bit residual (the caller vouches for entries below 65536): returns false if an entry does not fit.
-__device__ __forceinline__ bool load_matrix(const int32_t* __restrict__ A, uint16_t* R, int N, bool zero_diag, int lane) {
-    const int total = N * N;
-    bool ok = true;
-    for (int x = lane; x < total; x += MOE_WAVE) {
-        const int v = A[x];
-        ok = ok && (unsigned)v < 65536u;
-        R[x] = (uint16_t)v;
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (zero_diag) {
-        for (int i = lane; i < N; i += MOE_WAVE) R[i * N + i] = 0;
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    }
-    return __ballot(!ok) == 0;
-}
-__device__ __forceinline__ bool load_matrix(const int32_t* __restrict__ A, int32_t* R, int N, bool zero_diag, int lane) {
+__device__ __forceinline__ void load_matrix(const int32_t* __restrict__ A, int32_t* R, int N, bool zero_diag, int lane) {
     const int total = N * N;
     if ((total & 3) == 0 && (((uintptr_t)A) & 15) == 0) {
         const int4* src = reinterpret_cast<const int4*>(A);
@@ -207,7 +191,6 @@ __device__ __forceinline__ bool load_matrix(const int32_t* __restrict__ A, int32
         for (int i = lane; i < N; i += MOE_WAVE) R[i * N + i] = 0;
         lds_fence();
     }
-    return true;
 }
 template <typename T>
 __device__ __forceinline__ void store_matrix(const T* R, int32_t* __restrict__ out, int N, int lane) {
@@ -482,7 +465,7 @@ __device__ __forceinline__ int wave_min_scalar(int x) {
     return m;
 }
 template <int NPL, int NW, bool PACKED, typename T>
-__device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 16 : 1], int N, int r, int lane, int (&u)[NPL],
+__device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 16 : 1], int N, int ld, int r, int lane, int (&u)[NPL],
                                           int (&v)[NPL], int (&p)[NPL], int (&sigma)[NPL], int& D_end) {
     typedef Packed<NPL> P;
     const Mask<NPL> cols = below<NPL>(N);
@@ -502,7 +485,7 @@ __device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 
         int entry[NPL], local = INT_MAX;
 #pragma unroll
         for (int s = 0; s < NPL; ++s) {
-            if constexpr (NW == 1) entry[s] = Rc[i0 & 15]; else entry[s] = (int)R[i0 * N + at[s]];
+            if constexpr (NW == 1) entry[s] = Rc[i0 & 15]; else entry[s] = (int)R[i0 * ld + at[s]];
         }
         const int base = D + bcast<NPL>(u, i0);                          // row i0 entered the tree at distance D
         int keyed[NPL];
@@ -588,6 +571,118 @@ __device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 
     return steps;
 }
 
+// ------------------------------------------------------------------------------ greedy: residual and reductions
+// Rows of the residual lie `ld` elements apart in LDS, an odd number of 4-byte words: lanes that read the same column of
+// consecutive rows then hit different banks, and what is done for every row is done with a row per lane, without a reduction
+// across lanes (a column per lane and a wave maximum per row: 64 ranks 320 cycles per row, now about 20; 128 ranks the same).
+template <typename T> __host__ __device__ constexpr int greedy_ld(int N) {
+    return sizeof(T) == 4 ? (N | 1) : (((N + 1) / 2) | 1) * 2;
+}
+template <typename T> __host__ __device__ constexpr size_t greedy_lds_bytes(int N) {       // residual, one word per column
+    return (size_t)N * greedy_ld<T>(N) * sizeof(T) + (size_t)((N + 63) & ~63) * sizeof(int);
+}
+// Copies one matrix into LDS; returns false if an entry does not fit T (16 bits: the caller vouches for entries below 65536).
+template <typename T>
+__device__ __forceinline__ bool load_residual(const int32_t* __restrict__ A, T* R, int N, int ld, bool zero_diag, int lane) {
+    bool ok = true;
+    for (int j = lane; j < N; j += MOE_WAVE) {
+#pragma unroll 8
+        for (int i = 0; i < N; ++i) {
+            const int v = A[i * N + j];
+            if (sizeof(T) == 2) ok = ok && (unsigned)v < 65536u;
+            R[i * ld + j] = (T)v;
+        }
+    }
+    lds_fence();
+    if (zero_diag) {
+        for (int i = lane; i < N; i += MOE_WAVE) R[i * ld + i] = 0;
+        lds_fence();
+    }
+    return sizeof(T) == 4 || __ballot(!ok) == 0;
+}
+// u_r = max_j (R_rj - v_j)
+template <int NPL, typename T>
+__device__ __forceinline__ void row_maxima(const T* R, int N, int ld, int lane, const int (&v)[NPL], int (&u)[NPL]) {
+    const T* row[NPL];
+    int top[NPL];
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) { row[s] = R + min(lane + 64 * s, N - 1) * ld; top[s] = INT_MIN; }
+#pragma unroll
+    for (int h = 0; h < NPL; ++h)
+        blocked_loop<8>(min(N - 64 * h, 64), [&](int j) __attribute__((always_inline)) {
+            const int vj = __builtin_amdgcn_readlane(v[h], j);
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) top[s] = max(top[s], (int)row[s][64 * h + j] - vj);
+        });
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) u[s] = lane + 64 * s < N ? top[s] : 0;
+}
+// row r's tight columns {j : u_r + v_j = R_rj}
+template <int NPL, typename T>
+__device__ __forceinline__ void tight_masks(const T* R, int N, int ld, int lane, const int (&u)[NPL], const int (&v)[NPL], Mask<NPL> (&tm)[NPL]) {
+    const T* row[NPL];
+    const Mask<NPL> cols = below<NPL>(N);
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) { row[s] = R + min(lane + 64 * s, N - 1) * ld; tm[s].clear(); }
+#pragma unroll
+    for (int h = 0; h < 2 * NPL; ++h) {                                     // 32 columns at a time
+        unsigned int bits[NPL];
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) bits[s] = 0;
+        for (int j0 = 0; j0 < min(N - 32 * h, 32); j0 += 8) {
+            unsigned int part[NPL];
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) part[s] = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int j = min(32 * h + j0 + k, N - 1);
+                const int vj = __builtin_amdgcn_readlane(v[h / 2], j & 63);
+#pragma unroll
+                for (int s = 0; s < NPL; ++s) part[s] |= (int)row[s][j] - vj == u[s] ? 1u << k : 0u;
+            }
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) bits[s] |= part[s] << j0;
+        }
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) tm[s].w[h / 2] |= (unsigned long long)bits[s] << (32 * (h & 1));
+    }
+#pragma unroll
+    for (int s = 0; s < NPL; ++s)
+#pragma unroll
+        for (int k = 0; k < NPL; ++k) tm[s].w[k] = lane + 64 * s < N ? tm[s].w[k] & cols.w[k] : 0ULL;
+}
+// A maximal matching of the graph `tm`: every unmatched row asks for its first vacant column, the smallest row that asks gets
+// it, until nobody asks.  `slot`: one LDS word per column.
+template <int NPL>
+__device__ __forceinline__ void match_greedily(const Mask<NPL> (&tm)[NPL], int N, int lane, int* slot, int (&sigma)[NPL], int (&p)[NPL]) {
+    Mask<NPL> vacant = below<NPL>(N);
+    for (int round = 0; round < N; ++round) {
+        int pick[NPL];
+        unsigned long long asks = 0;
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) {
+            const Mask<NPL> c = tm[s] & vacant;                                  // (empty for lanes without a row)
+            pick[s] = sigma[s] < 0 && c.any() ? c.first() : -1;
+            asks |= ballot64(pick[s] >= 0);
+            slot[lane + 64 * s] = INT_MAX;
+        }
+        if (!asks) break;
+        lds_fence();
+#pragma unroll
+        for (int s = 0; s < NPL; ++s)
+            if (pick[s] >= 0) atomicMin(&slot[pick[s]], lane + 64 * s);
+        lds_fence();
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) {
+            if (pick[s] >= 0 && slot[pick[s]] == lane + 64 * s) sigma[s] = pick[s];
+            const int owner = slot[lane + 64 * s];
+            if (owner != INT_MAX) p[s] = owner;
+            vacant.w[s] &= ~ballot64(owner != INT_MAX);
+        }
+        lds_fence();
+    }
+}
+
 // ------------------------------------------------------------------------------ greedy kernel
 template <int NPL, typename T, int NW>            // NW: 16-lane rows that hold columns (1, 2 or 4)
 __global__ __launch_bounds__(MOE_WAVE)
@@ -605,28 +700,26 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
     unsigned long long t_cycles = 0, t_real = 0;
     int n_steps = 0, n_searches = 0;
     if (profiled) { t_cycles = __builtin_readcyclecounter(); t_real = wall_clock64(); }
-    if (!load_matrix(mats + (size_t)b * N * N, R, N, flags & MOE_DECOMP_ZERO_DIAGONAL, lane)) {
+    const int ld = greedy_ld<T>(N);
+    int* slot = reinterpret_cast<int*>(R + N * ld);
+    if (!load_residual(mats + (size_t)b * N * N, R, N, ld, flags & MOE_DECOMP_ZERO_DIAGONAL, lane)) {
         if (lane == 0) counts[b] = NOT_DONE;            // an entry does not fit 16 bits: left to the second pass
         return;
     }
 
     // feasible start: u_i = row maximum, v_j = 0  (u_i + v_j >= R_ij)
     int u[NPL], v[NPL], p[NPL], sigma[NPL];
-#pragma unroll
-    for (int s = 0; s < NPL; ++s) { u[s] = 0; v[s] = 0; p[s] = -1; sigma[s] = -1; }
     int nnz = 0;
-    for (int i = 0; i < N; ++i) {
-        int m = 0, pos = 0;
 #pragma unroll
-        for (int s = 0; s < NPL; ++s) {
-            int j = lane + 64 * s;
-            int x = j < N ? R[i * N + j] : 0;
-            m = max(m, x);
-            pos += __popcll(ballot64(x > 0));
+    for (int s = 0; s < NPL; ++s) {
+        const int i = lane + 64 * s;
+        int positive = 0, top = 0;
+        if (i < N) {
+#pragma unroll 8
+            for (int j = 0; j < N; ++j) { const int x = (int)R[i * ld + j]; positive += x > 0; top = max(top, x); }
         }
-        m = wave_max(m);
-        nnz += pos;
-        set_at<NPL>(u, i, m, lane);
+        u[s] = top; v[s] = 0; p[s] = -1; sigma[s] = -1;
+        nnz += wave_sum(positive);
     }
 
     Fnv fnv{FNV_OFFSET};
@@ -642,7 +735,7 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
         if constexpr (NW == 1) {
             const T* col = R + (lane < N ? lane : N - 1);
 #pragma unroll
-            for (int i = 0; i < 16; ++i) Rc[i] = i < N ? (int)col[i * N] : 0;
+            for (int i = 0; i < 16; ++i) Rc[i] = i < N ? (int)col[i * ld] : 0;
         }
         // ---- column reduction: lower v_j until column j has a tight edge.  The matching before took its entries out of the
         //      residual, which leaves room; the searches below get shorter by it (16 / 64 / 128 ranks: 43 / 378 / 1115 -> 30 / 252 /
@@ -660,7 +753,7 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
                 for (int half = 0; half < NPL; ++half) {
                     const int rows = min(N - 64 * half, 64);
                     blocked_loop<8>(rows, [&](int i) __attribute__((always_inline)) {
-                        const T* row = R + (64 * half + i) * N;
+                        const T* row = R + (64 * half + i) * ld;
                         const int ui = __builtin_amdgcn_readlane(u[half], i);
 #pragma unroll
                         for (int s = 0; s < NPL; ++s) top[s] = max(top[s], (int)row[lane + 64 * s < N ? lane + 64 * s : N - 1] - ui);
@@ -670,55 +763,12 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
 #pragma unroll
             for (int s = 0; s < NPL; ++s) v[s] = lane + 64 * s < N ? top[s] : 0;
         }
-        // ---- row reduction: lower u_r until row r has a tight edge, and take that edge if its column is free.
-        //      (Duals stay feasible, matched edges are tight; most rows are settled here and skip the search.)
-        // u_r <- max_j (R_rj - v_j) does not depend on the other rows: only the sets of taken columns (scalar masks) link the
-        // iterations, so their LDS reads and reductions overlap
-        {
-            Mask<NPL> vacant = below<NPL>(N);
-            auto reduce_row = [&](auto half_tag, int r, const int (&entry)[NPL]) __attribute__((always_inline)) {
-                constexpr int H = decltype(half_tag)::value;                  // rows 64 * H ...: lane r of slot H holds row 64 * H + r
-                int x[NPL], local = INT_MIN;
-#pragma unroll
-                for (int s = 0; s < NPL; ++s) {
-                    x[s] = lane + 64 * s < N ? entry[s] - v[s] : INT_MIN;     // lanes without a column never win or tie
-                    local = max(local, x[s]);
-                }
-                const int m = wave_max_rows<NW>(local);
-                // branch-free, so that the reductions of consecutive rows overlap: no vacant tight column = column -1
-                int pick = -1;
-                bool found = false;
-#pragma unroll
-                for (int s = 0; s < NPL; ++s) {
-                    const unsigned long long avail = ballot64(x[s] == m) & vacant.w[s];
-                    const unsigned long long take = found ? 0ULL : avail & (0ULL - avail);
-                    vacant.w[s] &= ~take;
-                    if (__builtin_amdgcn_inverse_ballot_w64(take)) p[s] = 64 * H + r;
-                    pick = take ? 64 * s + __builtin_ctzll(take) : pick;
-                    found = found || take != 0;
-                }
-                if (lane == r) { u[H] = m; sigma[H] = pick; }
-            };
-            if constexpr (NW == 1) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (r < N) { const int entry[1] = {Rc[r]}; reduce_row(std::integral_constant<int, 0>{}, r, entry); }
-            } else {
-                auto rows = [&](auto half_tag) __attribute__((always_inline)) {
-                    constexpr int H = decltype(half_tag)::value;
-                    const int n = min(N - 64 * H, 64);
-                    blocked_loop<4>(n, [&](int r) __attribute__((always_inline)) {
-                        const T* row = R + (64 * H + r) * N;
-                        int entry[NPL];
-#pragma unroll
-                        for (int s = 0; s < NPL; ++s) entry[s] = (int)row[lane + 64 * s < N ? lane + 64 * s : N - 1];
-                        reduce_row(half_tag, r, entry);
-                    });
-                };
-                rows(std::integral_constant<int, 0>{});
-                if constexpr (NPL > 1) rows(std::integral_constant<int, NPL - 1>{});
-            }
-        }
+        // ---- row reduction: lower u_r until row r has a tight edge; most rows then find a vacant tight column and skip the search.
+        //      (Duals stay feasible, matched edges are tight.)
+        Mask<NPL> tm[NPL];
+        row_maxima<NPL, T>(R, N, ld, lane, v, u);
+        tight_masks<NPL, T>(R, N, ld, lane, u, v, tm);
+        match_greedily<NPL>(tm, N, lane, slot, sigma, p);
         // ---- maximum-weight perfect matching: one shortest augmenting path per row still unmatched
         {
             const Mask<NPL> cols = below<NPL>(N);
@@ -740,34 +790,17 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
                 todo.reset(r);
                 int D;
                 if (bound < Packed<NPL>::MOST) {
-                    n_steps += search_row<NPL, NW, true>(R, Rc, N, r, lane, u, v, p, sigma, D);
+                    n_steps += search_row<NPL, NW, true>(R, Rc, N, ld, r, lane, u, v, p, sigma, D);
                     bound += D;
                     if (bound >= Packed<NPL>::MOST) bound = dual_bound();
                 } else {
-                    n_steps += search_row<NPL, NW, false>(R, Rc, N, r, lane, u, v, p, sigma, D);
+                    n_steps += search_row<NPL, NW, false>(R, Rc, N, ld, r, lane, u, v, p, sigma, D);
                 }
                 ++n_searches;
             }
         }
         // ---- canonical optimum: lexicographically smallest perfect matching of the tight graph
-        Mask<NPL> tm[NPL];
-        {
-            int vv[NPL];
-#pragma unroll
-            for (int s = 0; s < NPL; ++s) vv[s] = v[s];
-            if constexpr (NW == 1) {
-                tm[0].clear();
-                const unsigned long long colmask = below<NPL>(N).w[0];
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (i < N) {
-                        const unsigned long long row = ballot64(__builtin_amdgcn_readlane(u[0], i) + vv[0] == Rc[i]) & colmask;
-                        if (lane == i) tm[0].w[0] = row;
-                    }
-            } else {
-                build_masks<NPL, T>(R, N, lane, tm, [&](int x, int i, int s) { return bcast<NPL>(u, i) + vv[s] == x; });
-            }
-        }
+        tight_masks<NPL, T>(R, N, ld, lane, u, v, tm);
         lex_smallest<NPL, false, NPL == 1 && NW <= 2>(tm, N, lane, sigma, p, 0);
         // ---- ship whole entries; the matching lasts as long as its heaviest pair
         int dmax = 0, pos = 0;
@@ -775,7 +808,7 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
         for (int s = 0; s < NPL; ++s) {
             int i = lane + 64 * s;
             int x = 0;
-            if (i < N) { x = R[i * N + sigma[s]]; R[i * N + sigma[s]] = 0; }
+            if (i < N) { x = R[i * ld + sigma[s]]; R[i * ld + sigma[s]] = 0; }
             dmax = max(dmax, x);
             pos += __popcll(ballot64(x > 0));
         }
@@ -789,7 +822,11 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
         counts[b] = t;
         if (hashes) hashes[b] = fnv.h;
     }
-    if (residual) store_matrix(R, residual + (size_t)b * N * N, N, lane);
+    if (residual) {
+        int32_t* out = residual + (size_t)b * N * N;
+        for (int j = lane; j < N; j += MOE_WAVE)
+            for (int i = 0; i < N; ++i) out[i * N + j] = (int)R[i * ld + j];
+    }
     if (profiled && lane == 0) {
         prof[4 * (size_t)b + 0] = __builtin_readcyclecounter() - t_cycles;
         prof[4 * (size_t)b + 1] = wall_clock64() - t_real;
@@ -1258,14 +1295,22 @@ extern "C" moe_status moe_decompose_greedy(const int32_t* mats, int B, int N, in
     const int kflags = flags & MOE_DECOMP_ZERO_DIAGONAL;
     unsigned long long* prof = g_prof.load(std::memory_order_relaxed);
     const int prof_cap = g_prof_cap.load(std::memory_order_relaxed);
-    const size_t lds32 = (size_t)N * N * sizeof(int32_t);
+    const size_t lds32 = greedy_lds_bytes<int32_t>(N);
     auto wide = N <= 16 ? greedy_kernel<1, int32_t, 1> : N <= 32 ? greedy_kernel<1, int32_t, 2>
               : N <= 64 ? greedy_kernel<1, int32_t, 4> : greedy_kernel<2, int32_t, 4>;
+    static moe::DeviceOnce attr;                        // (more than 64 KiB from 128 ranks on)
+    int dev;
+    if (attr.needed(dev)) {
+        hipError_t e = hipFuncSetAttribute((const void*)greedy_kernel<2, int32_t, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)greedy_lds_bytes<int32_t>(MOE_MAX_RANKS));
+        if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
+        attr.mark(dev);
+    }
     if (narrow) {
         auto kern = N <= 16 ? greedy_kernel<1, uint16_t, 1> : N <= 32 ? greedy_kernel<1, uint16_t, 2>
                   : N <= 64 ? greedy_kernel<1, uint16_t, 4> : greedy_kernel<2, uint16_t, 4>;
         moe::LaunchScope k("greedy_kernel", s);
-        hipLaunchKernelGGL(kern, dim3(B), dim3(MOE_WAVE), lds32 / 2, s, mats, N, kmax, kflags, perms, durations, counts, residual,
+        hipLaunchKernelGGL(kern, dim3(B), dim3(MOE_WAVE), greedy_lds_bytes<uint16_t>(N), s, mats, N, kmax, kflags, perms, durations, counts, residual,
                            (unsigned long long*)hashes, prof, prof_cap);
         st = k.done();
         if (st != MOE_OK) return st;
