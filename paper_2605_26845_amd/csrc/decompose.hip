@@ -617,9 +617,10 @@ __device__ __forceinline__ void row_maxima(const T* R, int N, int ld, int lane, 
 #pragma unroll
     for (int s = 0; s < NPL; ++s) u[s] = lane + 64 * s < N ? top[s] : 0;
 }
-// row r's tight columns {j : u_r + v_j = R_rj}
-template <int NPL, typename T>
-__device__ __forceinline__ void tight_masks(const T* R, int N, int ld, int lane, const int (&u)[NPL], const int (&v)[NPL], Mask<NPL> (&tm)[NPL]) {
+// row r's tight columns {j : u_r + v_j = R_rj}; BY_OWNER: bit i stands for the column of row i instead
+template <int NPL, bool BY_OWNER, typename T>
+__device__ __forceinline__ void tight_masks(const T* R, int N, int ld, int lane, const int (&u)[NPL], const int (&v)[NPL],
+                                            const int (&sigma)[NPL], Mask<NPL> (&tm)[NPL]) {
     const T* row[NPL];
     const Mask<NPL> cols = below<NPL>(N);
 #pragma unroll
@@ -635,8 +636,9 @@ __device__ __forceinline__ void tight_masks(const T* R, int N, int ld, int lane,
             for (int s = 0; s < NPL; ++s) part[s] = 0;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const int j = min(32 * h + j0 + k, N - 1);
-                const int vj = __builtin_amdgcn_readlane(v[h / 2], j & 63);
+                int j = min(32 * h + j0 + k, N - 1);
+                if (BY_OWNER) j = __builtin_amdgcn_readlane(sigma[h / 2], j & 63);
+                const int vj = BY_OWNER ? bcast<NPL>(v, j) : __builtin_amdgcn_readlane(v[h / 2], j & 63);
 #pragma unroll
                 for (int s = 0; s < NPL; ++s) part[s] |= (int)row[s][j] - vj == u[s] ? 1u << k : 0u;
             }
@@ -680,6 +682,94 @@ __device__ __forceinline__ void match_greedily(const Mask<NPL> (&tm)[NPL], int N
             vacant.w[s] &= ~ballot64(owner != INT_MAX);
         }
         lds_fence();
+    }
+}
+
+// lex_smallest for matrices of more than 64 ranks, where its searches were a third of the time (128 ranks, 32 matchings, 1024 matrices: 7.6 -> 7.4 ms with this form): bit i of adj[r] says that row r may take
+// the column of row i, so that a level of the search is one AND of every row's mask with the rows reached, and nothing has to
+// be looked up per column; rows remember only the level they were reached at, and the few searches that succeed (3 of 37 per
+// matching at 128 ranks) find their way back by the levels.  A re-routing renames the columns along its path in every row's mask.
+template <int NPL>
+__device__ __forceinline__ void lex_smallest_by_rows(const Mask<NPL> (&tm)[NPL], Mask<NPL> (&adj)[NPL], int N, int lane, int (&sigma)[NPL],
+                                                     int (&p)[NPL]) {
+    const Mask<NPL> all = below<NPL>(N);
+    int first_row = 0;
+    for (int round = 0; round <= N; ++round) {
+        Mask<NPL> need = rows_with_candidates<NPL>(tm, N, lane, sigma, first_row);
+        bool changed = false;
+        while (need.any() && !changed) {
+            const int i = need.first();
+            need.reset(i);
+            const int cur = bcast<NPL>(sigma, i);
+            Mask<NPL> cand = bcast_mask<NPL>(tm, i) & below<NPL>(cur);
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) cand.w[s] &= ~(ballot64((unsigned int)p[s] < (unsigned int)i) & all.w[s]);
+            if (!cand.any()) continue;
+            // rows that can be moved so that the column of row i is taken
+            Mask<NPL> open = rows_after<NPL>(i, N), reached;
+            reached.clear();
+            reached.set(i);
+            int level[NPL];
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) level[s] = INT_MAX;
+            set_at<NPL>(level, i, 0, lane);
+            const int best = bcast<NPL>(p, cand.first());
+            for (int l = 1; l <= N; ++l) {
+                Mask<NPL> vm;
+#pragma unroll
+                for (int s = 0; s < NPL; ++s) {
+                    vm.w[s] = ballot64((adj[s] & reached).any()) & open.w[s];
+                    if (__builtin_amdgcn_inverse_ballot_w64(vm.w[s])) level[s] = l;
+                    open.w[s] &= ~vm.w[s];
+                }
+                if (!vm.any()) break;
+#pragma unroll
+                for (int s = 0; s < NPL; ++s) reached.w[s] |= vm.w[s];
+                if (reached.test(best)) break;
+            }
+            int to = -1;                                     // owner of the smallest candidate column that can be vacated
+            while (cand.any() && to < 0) {
+                const int c = cand.first();
+                cand.reset(c);
+                const int o = bcast<NPL>(p, c);
+                if (reached.test(o)) to = o;
+            }
+            if (to < 0) continue;
+            // i takes the column of `to`, which takes the column of a row of a lower level, and so on down to i's
+            int path[NPL], len = 0;
+#pragma unroll
+            for (int s = 0; s < NPL; ++s) path[s] = 0;
+            for (int o = to; o != i && len < N; ++len) {
+                set_at<NPL>(path, len, o, lane);
+                const int l = bcast<NPL>(level, o);
+                Mask<NPL> lower = bcast_mask<NPL>(adj, o);
+#pragma unroll
+                for (int s = 0; s < NPL; ++s) lower.w[s] &= ballot64(level[s] < l);
+                o = lower.first();
+            }
+            int row = i;
+            for (int k = 0; k <= len; ++k) {
+                const int o = k < len ? bcast<NPL>(path, k) : i;
+                const int c = k < len ? bcast<NPL>(sigma, o) : cur;
+                set_at<NPL>(sigma, row, c, lane);
+                set_at<NPL>(p, c, row, lane);
+                if (k < len) {
+                    Mask<NPL> a, b;
+                    a.clear(); a.set(row);
+                    b.clear(); b.set(o);
+#pragma unroll
+                    for (int s = 0; s < NPL; ++s)
+                        if ((adj[s] & a).any() != (adj[s] & b).any()) {
+#pragma unroll
+                            for (int w = 0; w < NPL; ++w) adj[s].w[w] ^= a.w[w] | b.w[w];
+                        }
+                }
+                row = o;
+            }
+            changed = true;
+            first_row = i + 1;
+        }
+        if (!changed) break;
     }
 }
 
@@ -767,7 +857,7 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
         //      (Duals stay feasible, matched edges are tight.)
         Mask<NPL> tm[NPL];
         row_maxima<NPL, T>(R, N, ld, lane, v, u);
-        tight_masks<NPL, T>(R, N, ld, lane, u, v, tm);
+        tight_masks<NPL, false, T>(R, N, ld, lane, u, v, sigma, tm);
         match_greedily<NPL>(tm, N, lane, slot, sigma, p);
         // ---- maximum-weight perfect matching: one shortest augmenting path per row still unmatched
         {
@@ -800,8 +890,14 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
             }
         }
         // ---- canonical optimum: lexicographically smallest perfect matching of the tight graph
-        tight_masks<NPL, T>(R, N, ld, lane, u, v, tm);
-        lex_smallest<NPL, false, NPL == 1 && NW <= 2>(tm, N, lane, sigma, p, 0);
+        tight_masks<NPL, false, T>(R, N, ld, lane, u, v, sigma, tm);
+        if constexpr (NPL > 1) {
+            Mask<NPL> adj[NPL];
+            tight_masks<NPL, true, T>(R, N, ld, lane, u, v, sigma, adj);
+            lex_smallest_by_rows<NPL>(tm, adj, N, lane, sigma, p);
+        } else {
+            lex_smallest<NPL, false, NW <= 2>(tm, N, lane, sigma, p, 0);
+        }
         // ---- ship whole entries; the matching lasts as long as its heaviest pair
         int dmax = 0, pos = 0;
 #pragma unroll
