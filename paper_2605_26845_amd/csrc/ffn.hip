@@ -1605,10 +1605,14 @@ __host__ __device__ inline int bwd_kpad(int rows, int P) {
 // Parts the contraction of a weight gradient is split into.  The gradients have few output tiles (E_loc * f / 256 row
 // blocks times d / 256 column units) and a very long contraction (all rows of the expert): unsplit, a small layer does
 // not fill the chip and a large one runs in a few coarse rounds.  Parts produce partial sums that are added in fp32.
+// Two rounds of tiles on 256 compute units are enough: a part costs a writing and a reading of the gradient.  Whole call, us, for
+// 1 / 2 / 4 / 8 / 16 parts: 192 tiles (E 4, d 2048, f 1408, 36 833 rows) 2904 / 2492 / 2316 / 2335 / 2555; 896 tiles (E 1, d 4096, f 14336,
+// 9000 rows) 8229 / 8319 / 8630 / 9241 / 10694; 96 tiles (E 8, d 1024, f 768, 20 000 rows) 1047 / 792 / 700 / 731 / 909; 48 tiles (E 1, d 2048,
+// f 1408, 30 000 rows) 3091 / 2990 / 2092 / 1751 / 1701.
 int bwd_split(int M, int E_loc, int d, int f) {
     const long long tiles = (long long)E_loc * ((f + 255) / 256) * (d / 256);
     int P = 1;
-    while (P < BWD_MAX_SPLIT && tiles * P < 8 * 256 && (long long)M / E_loc / (2 * P) >= 1024) P *= 2;
+    while (P < BWD_MAX_SPLIT && tiles * P < 2 * 256 && (long long)M / E_loc / (2 * P) >= 512) P *= 2;
     return P;
 }
 

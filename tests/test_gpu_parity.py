@@ -869,6 +869,12 @@ def test_ffn_backward_small(lib, E_loc, d, f, M, S):
     check_backward(lib, E_loc, d, f, M, S, seed=d + f + M, what="small", spare=5)
 
 
+@pytest.mark.parametrize("E_loc,M", [(1, 1023), (1, 1024), (1, 2100), (2, 4500), (1, 9000)])
+def test_ffn_backward_parts(lib, E_loc, M):
+    """1, 2, 4 and 8 parts of the contraction of the weight gradients (at least 512 rows each)."""
+    check_backward(lib, E_loc, 256, 256, M, 3, M, "parts")
+
+
 def test_ffn_backward_edge_cases(lib):
     say("ffn backward edge cases")
     # an expert without rows (zero weight gradients), a single row, no rows at all
