@@ -212,7 +212,8 @@ moe_status moe_slice_table_rows(const int32_t* ids, int N, int T, int topk, int 
  *   s_gate,s_up in  float [E_loc][f/128][d/128], s_down float [E_loc][d/128][f/128]
  *                   (MOE_W_FP8_E4M3_B128 only, else NULL): weight = decode(code) * scale
  *   y          out  bf16 [M][d]; rows >= offsets[last] are left untouched
- *   workspace       moe_ffn_workspace_bytes(M, d, f) bytes (holds the hidden activations).  With
+ *   workspace       moe_ffn_workspace_bytes(M, d, f) bytes (holds the hidden activations and, for up to
+ *                   4096 rows, a copy of x; a call whose workspace lacks room for the copy reads x itself).  With
  *                   MOE_W_FP8_E4M3_B128 the caller may add moe_ffn_expanded_weights_bytes(E_loc, d, f)
  *                   bytes: when there are at least 2048 rows per local expert on average the weights
  *                   are then expanded to bf16 once per call (the same values the kernels would form

@@ -1217,9 +1217,9 @@ void ffn_fused_kernel(FfnArgs a) {
 }
 
 // ---------------------------------------------------------------------------------- few rows per expert (decoding)
-// Bound by the weights' way from HBM: with at most a few dozen rows per expert a tile kernel has too few tiles for the chip
+// Bound by the weights' way from HBM: with few rows per expert a tile kernel has too few tiles for the chip
 // (f / 128 and d / 256 column tiles per expert) and too few bytes in flight per tile.  Here a workgroup takes a strip of
-// 16 * NC weight rows of one expert (phase 1: half of them gate, half up) and up to 64 of the expert's rows, and its W wavefronts
+// 16 * NC weight rows of one expert (phase 1: half of them gate, half up) and up to 16 * MT of the expert's rows, and its W wavefronts
 // share the contraction: 64 values of K each in turn, weights and activations straight from memory into MFMA fragments, the
 // next two (D - 1) steps in flight while one is multiplied.  The W partial sums meet in LDS and are added in fp32 in a fixed order.
 // No plan: every workgroup finds its rows in the offsets by itself (a scan over the S groups of its expert), h lies in schedule
@@ -1228,9 +1228,10 @@ void ffn_fused_kernel(FfnArgs a) {
 // 48 us; d = 7168, f = 2048, four fp8 experts 42 -> 28 us).  For the same reason the strips start at different steps of K
 // (one expert, d 4096, f 14336, 5 rows: 86 -> 70 us).
 // One expert, d 4096, f 14336, 37 rows (352 MB of weights): 587 us in 64-row tiles -> 97 us; four fp8 experts, d 7168, f 2048,
-// 203 rows (176 MB): 439 -> 90 us.  5 rows of the former: 68 us, 5.2 TB/s; with more rows the activations' way from L2 counts too.
+// 203 rows (176 MB): 445 -> 95 us.  5 rows of the former: 68 us, 5.2 TB/s; with more rows the activations' way from L2 counts too.
 struct SkinnyArgs {
     const __bf16* x; __bf16* h; __bf16* y;
+    const __bf16* xk;                  // the rows of x in schedule order, K-major as h, or null: phase 1 reads x
     const void *wg, *wu, *wd;
     const float *sg, *su, *sd;
     const int32_t* offsets;
@@ -1238,8 +1239,22 @@ struct SkinnyArgs {
     int M, S, E, d, f;
 };
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-constexpr int SKINNY_ROWS = 64;        // rows per workgroup
 constexpr int SKINNY_MAX_SLICES = 1024;
+
+// xk[k / 8][m][8] = row m's x: 8 lanes fetch 128 bytes of a row, the 8 rows of a wavefront lie side by side in the result
+__global__ __launch_bounds__(256)
+void ffn_kmajor_kernel(const __bf16* __restrict__ x, const int32_t* __restrict__ row_map, const int32_t* __restrict__ last, int M, int d,
+                       __bf16* __restrict__ xk) {
+    const int m = blockIdx.x * 32 + (threadIdx.x >> 3), k8 = blockIdx.y * 8 + (threadIdx.x & 7);       // (d is a multiple of 64)
+    if (m >= M) return;
+    int row = m;
+    if (row_map) {
+        if (m >= *last) return;                                           // the map ends with the last group
+        row = row_map[m];
+        row = (unsigned)row < (unsigned)M ? row : 0;
+    }
+    *reinterpret_cast<u32x4*>(xk + ((size_t)k8 * M + m) * 8) = *reinterpret_cast<const u32x4*>(x + (size_t)row * d + k8 * 8);
+}
 
 // W wavefronts, NC 16-row column tiles of weights, at most MT 16-row tiles of activations, D register buffers
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
@@ -1249,7 +1264,8 @@ void ffn_skinny_kernel(SkinnyArgs a) {
     constexpr int ESZ = FP8 ? 1 : 2, WL = FP8 ? 1 : 2;                     // 16-byte weight loads per lane, column tile and 64 values of K
     constexpr int PASS = 32 / (W * NC) < 1 ? 1 : (32 / (W * NC) > MT ? MT : 32 / (W * NC));     // row tiles per reduction pass
     constexpr int NH = PHASE == 1 ? NC / 2 : NC;                           // column tiles of the output
-    __shared__ int s_row[SKINNY_ROWS];
+    constexpr int ROWS = 16 * MT;                                          // rows per workgroup
+    __shared__ int s_row[ROWS];
     __shared__ int s_scan[W];
     __shared__ f32x4 s_red[W * NC * PASS * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1260,8 +1276,8 @@ void ffn_skinny_kernel(SkinnyArgs a) {
     const int KT = K / 64, n = (KT - wave + W - 1) / W;                    // steps in all, and of this wavefront (K >= 128)
     const int rot = (int)(((unsigned)strip * 3u + (unsigned)e * 3u) % (unsigned)KT);
 
-    for (int first = (int)blockIdx.z * SKINNY_ROWS;; first += (int)gridDim.z * SKINNY_ROWS) {
-        // ---- positions first .. first + 63 of the expert's rows
+    for (int first = (int)blockIdx.z * ROWS;; first += (int)gridDim.z * ROWS) {
+        // ---- positions first .. first + ROWS - 1 of the expert's rows
         int total = 0;
         for (int s0 = 0; s0 < a.S; s0 += W * 64) {
             const int s = s0 + tid;
@@ -1287,10 +1303,10 @@ void ffn_skinny_kernel(SkinnyArgs a) {
                 total += t;
             }
             const int p0 = base + incl - rows;
-            for (int p = max(p0, first); p < min(p0 + rows, first + SKINNY_ROWS); ++p) s_row[p - first] = lo + (p - p0);
+            for (int p = max(p0, first); p < min(p0 + rows, first + ROWS); ++p) s_row[p - first] = lo + (p - p0);
             __syncthreads();
         }
-        const int rows = min(total - first, SKINNY_ROWS);
+        const int rows = min(total - first, ROWS);
         if (rows <= 0) return;
 
         auto mapped = [&](int m) __attribute__((always_inline)) -> int {
@@ -1307,18 +1323,19 @@ void ffn_skinny_kernel(SkinnyArgs a) {
                 for (int t = 0; t < T; ++t) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
             // Lane (r16, g4) holds row r16 of a 16-row tile and 8 consecutive values of K per MFMA step.  The order of K inside a
             // step is free as long as both operands agree: fp8 lanes fetch 16 consecutive codes, the two steps' worth.
+            const bool kmajor = PHASE == 2 || a.xk;
             unsigned int xoff[T];                                          // (M * K * 2 < 2^32 is a condition of this route)
 #pragma unroll
             for (int t = 0; t < T; ++t) {
                 const int m = s_row[min(t * 16 + r16, rows - 1)];          // rows past the end repeat the last one and are not stored
-                xoff[t] = PHASE == 1 ? ((unsigned int)mapped(m) * (unsigned int)K + (unsigned int)g4 * (FP8 ? 16 : 8)) * 2u
-                                     : ((unsigned int)g4 * (FP8 ? 2 : 1) * (unsigned int)a.M + (unsigned int)m) * 16u;
+                xoff[t] = !kmajor ? ((unsigned int)mapped(m) * (unsigned int)K + (unsigned int)g4 * (FP8 ? 16 : 8)) * 2u
+                                  : ((unsigned int)g4 * (FP8 ? 2 : 1) * (unsigned int)a.M + (unsigned int)m) * 16u;
             }
-            const void* const xbase = PHASE == 1 ? (const void*)a.x : (const void*)a.h;
+            const void* const xbase = PHASE == 2 ? (const void*)a.h : (const void*)(a.xk ? a.xk : a.x);
             const unsigned int xbytes = (unsigned int)a.M * (unsigned int)K * 2u;
             // bytes per value of K, and from the first MFMA step of 64 values to the second
-            const unsigned int xstep = PHASE == 1 ? 2u : 2u * (unsigned int)a.M;
-            const unsigned int xhalf = PHASE == 1 ? (FP8 ? 16u : 64u) : (FP8 ? 16u : 64u) * (unsigned int)a.M;
+            const unsigned int xstep = kmajor ? 2u * (unsigned int)a.M : 2u;
+            const unsigned int xhalf = (FP8 ? 16u : 64u) * (kmajor ? (unsigned int)a.M : 1u);
             const unsigned int woff = ((unsigned int)r16 * (unsigned int)K) * ESZ + (unsigned int)g4 * 16u;
             const unsigned int wbytes = 16u * (unsigned int)K * ESZ;
             const unsigned char* wbase[NC];
@@ -1426,6 +1443,8 @@ void ffn_skinny_kernel(SkinnyArgs a) {
         if (MT == 1 || tiles == 1)      work(std::integral_constant<int, 1>{});
         else if (MT == 2 || tiles == 2) work(std::integral_constant<int, (MT < 2 ? MT : 2)>{});
         else if (MT == 3 || tiles == 3) work(std::integral_constant<int, (MT < 3 ? MT : 3)>{});
+        else if (MT == 4 || tiles == 4) work(std::integral_constant<int, (MT < 4 ? MT : 4)>{});
+        else if (MT == 6 || tiles <= 6) work(std::integral_constant<int, (MT < 6 ? MT : 6)>{});
         else                            work(std::integral_constant<int, MT>{});
         __syncthreads();                                                   // s_row and s_red are used again
     }
@@ -1452,6 +1471,10 @@ size_t plan_bytes(int M) { return (((size_t)(plan_capacity(M) + PLAN_HDR) * size
 size_t list_bytes(int M) { return ((((size_t)M + LIST_PAD) * sizeof(int32_t)) + 255) & ~(size_t)255; }
 constexpr size_t EBASE_BYTES = (((size_t)MAX_GROUPS + 1) * sizeof(int) + 255) & ~(size_t)255;
 size_t ready_bytes(int M) { return (((size_t)plan_capacity(M) * sizeof(int)) + 255) & ~(size_t)255; }
+
+size_t ffn_base_bytes(int M, int f) { return h_bytes(M, f) + plan_bytes(M) + ready_bytes(M) + 2 * list_bytes(M) + EBASE_BYTES; }
+constexpr int KMAJOR_ROWS = 4096;          // the K-major copy of x is for calls of at most this many rows
+size_t kmajor_bytes(int M, int d) { return M <= KMAJOR_ROWS ? (((size_t)M * d * 2) + 255) & ~(size_t)255 : 0; }
 
 std::atomic<int> g_force_rows{0};          // moe_ffn_tile_override: 0 = rows per tile chosen per call, else 64 / 128 / 256
 std::atomic<int> g_force_kernels{0};       //                        1 = never the adaptive-shape kernels, 2 = adaptive-shape kernels, one launch per phase
@@ -1559,16 +1582,27 @@ moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
     return launch_gemm<2, ROWS, FP8>(a, max_blocks * (a.d / BN), s);
 }
 
+template <int PHASE, int W, int NC, int MT, int D, bool FP8>
+moe_status launch_skinny_tiles(const SkinnyArgs& a, hipStream_t s) {
+    const int strips = (PHASE == 1 ? a.f / (8 * NC) : a.d / (16 * NC));
+    const dim3 grid(strips, a.E, std::min((a.M + 16 * MT - 1) / (16 * MT), 8));
+    moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
+    hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, MT, D, FP8>), grid, dim3(W * 64), 0, s, a);
+    return k.done();
+}
 template <int PHASE, int W, int NC, int D, bool FP8>
 moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
-    const int strips = (PHASE == 1 ? a.f / (8 * NC) : a.d / (16 * NC));
-    const dim3 grid(strips, a.E, std::min((a.M + SKINNY_ROWS - 1) / SKINNY_ROWS, 8));
-    moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
     // (fewer rows in the whole call than a workgroup takes: the variants with fewer row tiles need fewer registers)
-    if (a.M <= 16)      hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, 1, D, FP8>), grid, dim3(W * 64), 0, s, a);
-    else if (a.M <= 32) hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, 2, D, FP8>), grid, dim3(W * 64), 0, s, a);
-    else                hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, 4, D, FP8>), grid, dim3(W * 64), 0, s, a);
-    return k.done();
+    if (a.M <= 16) return launch_skinny_tiles<PHASE, W, NC, 1, D, FP8>(a, s);
+    if (a.M <= 32) return launch_skinny_tiles<PHASE, W, NC, 2, D, FP8>(a, s);
+    // 128 rows per workgroup (one wavefront per SIMD) halve the readings of the weights: more than 64 rows per expert as long as
+    // that leaves a workgroup for every other compute unit, or an uneven spread of fewer bf16 rows over experts with large weights.
+    // 64 / 128 rows, us: E 1, d 4096, f 14336, 128 rows: 214 / 171; E 1, d 2048, f 1408, 128 / 384 rows: 30 / 40, 58 / 46; E 4, d 7168,
+    // f 2048, 51 rows on average: 143 / 125, in fp8 103 / 107.
+    const long long groups = (long long)a.E * (a.f / 32) * ((a.M / a.E + 127) / 128);
+    if ((a.M > 64LL * a.E && groups >= num_cus() / 2) || (!FP8 && a.E > 1 && a.M > 32LL * a.E && (long long)a.d * a.f >= (8LL << 20)))
+        return launch_skinny_tiles<PHASE, W, NC, 8, 2, FP8>(a, s);
+    return launch_skinny_tiles<PHASE, W, NC, 4, D, FP8>(a, s);
 }
 
 // Weight rows per workgroup: 64 (the 64 rows of activations are then fetched as often as the weights), but 16 in phase 2 when
@@ -1576,8 +1610,14 @@ moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
 // 16 rows 39 us; d = 7168, f = 2048, four fp8 experts, 203 rows: 28 us, 59 us.
 template <bool FP8>
 moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
-    moe_status st = launch_skinny<1, 4, 4, 2, FP8>(a, s);
-    if (st != MOE_OK) return st;
+    moe_status st;
+    if (a.xk) {
+        moe::LaunchScope k("ffn_kmajor_kernel", s);
+        hipLaunchKernelGGL(ffn_kmajor_kernel, dim3((a.M + 31) / 32, a.d / 64), dim3(256), 0, s, a.x, a.row_map, a.offsets + (size_t)a.S * a.E,
+                           a.M, a.d, (__bf16*)a.xk);
+        if ((st = k.done()) != MOE_OK) return st;
+    }
+    if ((st = launch_skinny<1, 4, 4, 2, FP8>(a, s)) != MOE_OK) return st;
     if ((long long)(a.d / 64) * a.E >= num_cus() / 2) return launch_skinny<2, 4, 4, 2, FP8>(a, s);
     return launch_skinny<2, 4, 1, 4, FP8>(a, s);
 }
@@ -1785,7 +1825,8 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
 extern "C" size_t moe_ffn_workspace_bytes(int M, int d, int f) {
     if (M < 0 || d < 1 || f < 1) return 0;
     // hidden activations, plan, ready counters, row list, router weights in list order, row bases of the experts
-    return h_bytes(M, f) + plan_bytes(M) + ready_bytes(M) + 2 * list_bytes(M) + EBASE_BYTES;
+    // (all that a call must have), and room for the K-major rows of x of a small call
+    return ffn_base_bytes(M, f) + kmajor_bytes(M, d);
 }
 
 extern "C" moe_status moe_ffn_tile_override(int tile_rows, int kernels, int panel_groups) {
@@ -1823,7 +1864,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     // every operand is moved in 16-byte pieces
     if ((((uintptr_t)x | (uintptr_t)y | (uintptr_t)w_gate | (uintptr_t)w_up | (uintptr_t)w_down | (uintptr_t)workspace) & 15) != 0)
         return MOE_ERR_INVALID_ARG;
-    const size_t base_bytes = moe_ffn_workspace_bytes(M, d, f);
+    const size_t base_bytes = ffn_base_bytes(M, f);
     if (!workspace || workspace_bytes < base_bytes) return MOE_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
 
@@ -1848,20 +1889,28 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
                                             row_map, row_gate, y, workspace, base_bytes, hip_stream);
     }
 
-    // Few rows per expert: the weights are streamed, once per 64 rows, by the kernels made for that.  Where that ends depends on
-    // how many tiles the tile kernels would have for the chip (the column tiles of phase 2, E_loc * d / 256).  Measured at
-    // 16 / 64 / 128 / 256 rows per expert, us, tiles against streaming:
-    //    16 column tiles (E 1, d 4096, f 14336)        572 / 399 / 576 / 561     74 / 117 / 213 / 373
-    //    32              (E 4, d 2048, f 1408)          95 /  84 / 103 / 122     25 /  34 /  64 / 109
-    //   112              (E 4, d 7168, f 2048)         319 / 291 / 222 / 341     79 / 150 / 230 / 397
-    //   112, fp8         (E 4, d 7168, f 2048)         399 / 365 / 316 / 432     48 / 108 / 162 / 277
-    //   224              (E 8, d 7168, f 2048)         332 / 264 / 294 / 550    156 / 274 / 444 / 777
+    // Few rows per expert: the weights are streamed, once per 64 or 128 rows, by the kernels made for that.  Where that ends
+    // depends on how many tiles the tile kernels would have for the chip (the column tiles of phase 2, E_loc * d / 256).
+    // Measured at 16 / 64 / 128 / 256 / 384 rows per expert, us, weights not in any cache, tiles against streaming:
+    //    16 column tiles (E 1, d 4096, f 14336)        576 / 543 / 510 / 493 / 545     76 / 110 / 153 / 279 / 405
+    //    32              (E 4, d 2048, f 1408)         125 / 117 / 119 / 137 / 143     30 /  44 /  54 /  83 / 109
+    //   112              (E 4, d 7168, f 2048)         321 / 246 / 263 / 357 / 279     84 / 134 / 204 / 316 / 442
+    //   112, fp8         (E 4, d 7168, f 2048)         468 / 377 / 372 / 497 / 347     62 / 113 / 167 / 263 / 368
+    //   224              (E 8, d 7168, f 2048)         329 / 269 / 295 / 542 / 500    158 / 252 / 359 / 606 / 865
+    // (512 rows: E 1, d 4096, f 14336 584, 505; E 4, d 2048, f 1408 153, 141; but E 8, d = f = 512 65, 73.)
     const long long tiles2 = (long long)E_loc * (d / 256);
-    const long long most = std::min(256LL, std::max(48LL, (fp8 ? 24576LL : 12288LL) / tiles2));
+    const long long most = fp8 ? std::min(640LL, std::max(64LL, 36864LL / tiles2))
+                               : std::min((long long)d * f >= (2LL << 20) ? 512LL : 384LL, std::max(64LL, 27000LL / tiles2));
     // (32-bit offsets into x and h; every workgroup scans the slices of its expert)
     if (g_force_rows.load(std::memory_order_relaxed) == 0 && M <= most * E_loc && S <= SKINNY_MAX_SLICES && E_loc <= 4096 &&
         (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull) {
-        const SkinnyArgs k = {(const __bf16*)x, (__bf16*)workspace, (__bf16*)y, w_gate, w_up, w_down, s_gate, s_up, s_down,
+        // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
+        // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
+        // 325, 79 / 112 / 154 / 280; E 4, d 2048, f 1408, 128 / 256 rows: 54 / 90, 57 / 84; not so E 4, d 7168, f 2048, 128 rows: 204, 213.
+        __bf16* xk = nullptr;
+        const bool pays = d % 2048 == 0 && M >= ((long long)E_loc * f >= 8192 ? 48LL : 160LL) * E_loc;
+        if (pays && kmajor_bytes(M, d) > 0 && workspace_bytes - base_bytes >= kmajor_bytes(M, d)) xk = (__bf16*)((char*)workspace + base_bytes);
+        const SkinnyArgs k = {(const __bf16*)x, (__bf16*)workspace, (__bf16*)y, xk, w_gate, w_up, w_down, s_gate, s_up, s_down,
                               offsets, row_map, row_gate, M, S, E_loc, d, f};
         return fp8 ? launch_both_skinny<true>(k, s) : launch_both_skinny<false>(k, s);
     }

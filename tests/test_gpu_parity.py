@@ -807,12 +807,14 @@ def test_ffn_slices_of_an_expert_share_tiles(lib, S, E_loc, M, tile_rows):
 @pytest.mark.parametrize("E_loc,d,f,sizes", [
     (1, 256, 128, [[1]]), (1, 512, 1408, [[15]]), (2, 256, 384, [[16, 17]]), (1, 1280, 256, [[20], [0], [13], [30]]),
     (3, 256, 640, [[0, 65, 1], [64, 0, 0], [0, 0, 47]]), (2, 512, 128, [[3, 1]] * 300), (8, 4096, 256, [[9, 0, 33, 1, 64, 2, 0, 40]] * 2),
-    (4, 256, 256, [[600, 3, 0, 80]]), (2, 8192, 128, [[129, 40]])])
+    (4, 256, 256, [[600, 3, 0, 80]]), (2, 8192, 128, [[129, 40]]), (1, 256, 4096, [[128]]), (1, 256, 4096, [[100], [29]]),
+    (2, 2048, 384, [[166, 0], [30, 137]]), (1, 2048, 4096, [[200]]), (2, 512, 2048, [[1100, 0]]), (8, 256, 128, [[1100, 0, 0, 5, 0, 0, 0, 1]]),
+    (2, 4096, 2048, [[81, 2]])])
 def test_ffn_few_rows_per_expert(lib, dtype, E_loc, d, f, sizes):
     """The kernels that stream the weights: every row against the oracle, and through a row map with weights.  Sizes: ends of the
-    16-row tiles and of the 64-row chunks, more chunks than the grid has (600 rows of one expert), experts without rows, more
-    slices than a workgroup has threads, steps of K that do not divide by the wavefronts (2, 4, 6, 10, 20, 22), both strip
-    widths of phase 2 (64 from E_loc * d / 64 >= half the compute units on: the 8 x 4096 and 2 x 8192 cases)."""
+    16-row tiles and of the 64-row and 128-row chunks (128: f >= 2048 here), more chunks than the grid has (1100 rows of one
+    expert), experts without rows, more slices than a workgroup has threads, steps of K that do not divide by the wavefronts (2, 4, 6,
+    10, 20, 22), x as it is and K-major (the 166 + 167 and the 200 rows of d = 2048), both strip widths of phase 2 (64 from E_loc * d / 64 >= half the compute units on: the 8 x 4096, 2 x 8192 and 2 x 4096 cases)."""
     say("ffn few rows per expert", dtype, E_loc, d, f, len(sizes))
     offsets = np.concatenate([[0], np.cumsum(np.array(sizes).ravel())]).astype(np.int32)
     M, S = int(offsets[-1]), len(sizes)
