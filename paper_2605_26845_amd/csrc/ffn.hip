@@ -1585,7 +1585,8 @@ moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
 moe_status launch_skinny_tiles(const SkinnyArgs& a, hipStream_t s) {
     const int strips = (PHASE == 1 ? a.f / (8 * NC) : a.d / (16 * NC));
-    const dim3 grid(strips, a.E, std::min((a.M + 16 * MT - 1) / (16 * MT), 8));
+    // workgroups for the chunks that one expert may have; with several experts most of them find no rows, and those that do walk on
+    const dim3 grid(strips, a.E, std::min((a.M + 16 * MT - 1) / (16 * MT), std::max(8, 64 / a.E)));
     moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
     hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, MT, D, FP8>), grid, dim3(W * 64), 0, s, a);
     return k.done();
@@ -1597,10 +1598,10 @@ moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
     if (a.M <= 32) return launch_skinny_tiles<PHASE, W, NC, 2, D, FP8>(a, s);
     // 128 rows per workgroup (one wavefront per SIMD) halve the readings of the weights: more than 64 rows per expert as long as
     // that leaves a workgroup for every other compute unit, or an uneven spread of fewer bf16 rows over experts with large weights.
-    // 64 / 128 rows, us: E 1, d 4096, f 14336, 128 rows: 214 / 171; E 1, d 2048, f 1408, 128 / 384 rows: 30 / 40, 58 / 46; E 4, d 7168,
+    // 64 / 128 rows, us: E 1, d 4096, f 14336, 128 rows: 214 / 171; E 1, d 2048, f 1408, 128 / 384 rows: 30 / 40, 58 / 46; E 1, d 256, f 512, 1024 / 1536 rows: 18 / 24, 28 / 25; E 4, d 7168,
     // f 2048, 51 rows on average: 143 / 125, in fp8 103 / 107.
     const long long groups = (long long)a.E * (a.f / 32) * ((a.M / a.E + 127) / 128);
-    if ((a.M > 64LL * a.E && groups >= num_cus() / 2) || (!FP8 && a.E > 1 && a.M > 32LL * a.E && (long long)a.d * a.f >= (8LL << 20)))
+    if ((a.M > 64LL * a.E && groups >= num_cus() / 2 + (a.E == 1)) || (!FP8 && a.E > 1 && a.M > 32LL * a.E && (long long)a.d * a.f >= (8LL << 20)))
         return launch_skinny_tiles<PHASE, W, NC, 8, 2, FP8>(a, s);
     return launch_skinny_tiles<PHASE, W, NC, 4, D, FP8>(a, s);
 }
@@ -1649,10 +1650,13 @@ __host__ __device__ inline int bwd_kpad(int rows, int P) {
 // 1 / 2 / 4 / 8 / 16 parts: 192 tiles (E 4, d 2048, f 1408, 36 833 rows) 2904 / 2492 / 2316 / 2335 / 2555; 896 tiles (E 1, d 4096, f 14336,
 // 9000 rows) 8229 / 8319 / 8630 / 9241 / 10694; 96 tiles (E 8, d 1024, f 768, 20 000 rows) 1047 / 792 / 700 / 731 / 909; 48 tiles (E 1, d 2048,
 // f 1408, 30 000 rows) 3091 / 2990 / 2092 / 1751 / 1701.
+// Where the contraction is long (8192 rows and more to a part) a part costs next to nothing, and one more doubling pays when
+// the rounds of tiles are at most 7/8 full: E 1, d 4096, f 14336 (896 tiles), 72 408 rows, 1 / 2 / 4 / 8 parts: 59.5 / 56.7 / 56.9 / 57.0 ms.
 int bwd_split(int M, int E_loc, int d, int f) {
     const long long tiles = (long long)E_loc * ((f + 255) / 256) * (d / 256);
     int P = 1;
     while (P < BWD_MAX_SPLIT && tiles * P < 2 * 256 && (long long)M / E_loc / (2 * P) >= 512) P *= 2;
+    while (P < BWD_MAX_SPLIT && (long long)M / E_loc / (2 * P) >= 8192 && tiles * P * 8 <= (tiles * P + 255) / 256 * 256 * 7) P *= 2;
     return P;
 }
 
@@ -1890,19 +1894,22 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     }
 
     // Few rows per expert: the weights are streamed, once per 64 or 128 rows, by the kernels made for that.  Where that ends
-    // depends on how many tiles the tile kernels would have for the chip (the column tiles of phase 2, E_loc * d / 256).
-    // Measured at 16 / 64 / 128 / 256 / 384 rows per expert, us, weights not in any cache, tiles against streaming:
-    //    16 column tiles (E 1, d 4096, f 14336)        576 / 543 / 510 / 493 / 545     76 / 110 / 153 / 279 / 405
-    //    32              (E 4, d 2048, f 1408)         125 / 117 / 119 / 137 / 143     30 /  44 /  54 /  83 / 109
-    //   112              (E 4, d 7168, f 2048)         321 / 246 / 263 / 357 / 279     84 / 134 / 204 / 316 / 442
-    //   112, fp8         (E 4, d 7168, f 2048)         468 / 377 / 372 / 497 / 347     62 / 113 / 167 / 263 / 368
-    //   224              (E 8, d 7168, f 2048)         329 / 269 / 295 / 542 / 500    158 / 252 / 359 / 606 / 865
-    // (512 rows: E 1, d 4096, f 14336 584, 505; E 4, d 2048, f 1408 153, 141; but E 8, d = f = 512 65, 73.)
-    const long long tiles2 = (long long)E_loc * (d / 256);
-    const long long most = fp8 ? std::min(640LL, std::max(64LL, 36864LL / tiles2))
-                               : std::min((long long)d * f >= (2LL << 20) ? 512LL : 384LL, std::max(64LL, 27000LL / tiles2));
+    // depends on how many column tiles the tile kernels would have for the chip (both phases: E_loc * (d / 256 + f / 128)).
+    // Measured at 64 / 128 / 320 / 448 rows per expert, us, weights not in any cache, the best tiles against streaming:
+    //    76 column tiles (E 4, d 2048, f 1408)         117 / 119 / 117 / 109     44 /  54 /  98 / 118
+    //   128              (E 1, d 4096, f 14336)        543 / 510 / 454 / 502    110 / 153 / 377 / 482
+    //   160              (E 8, d 1024, f 2048)          -  /  -  / 143 / 145     -  /  -  / 173 / 226
+    //   176              (E 4, d 7168, f 2048)         246 / 263 / 304 / 293    134 / 204 / 380 / 500
+    //   352              (E 8, d 7168, f 2048)         269 / 295 / 380 / 488    252 / 359 / 740 / 1000
+    //   152, fp8         (E 8, d 2048, f 1408)          -  /  -  / 211 / 182     -  /  -  / 166 / 212
+    //   176, fp8         (E 4, d 7168, f 2048)         377 / 372 / 438 / 354    113 / 167 / 332 / 420
+    // A small call in all streams whatever its rows per expert (M * d * f up to 2^29: a tile kernel's few tiles are then a chain of
+    // their own latencies): E 1, d 256, f 512, 256 / 1024 / 4096 rows 37 / 42 / 44, 17 / 18 / 41; E 1, d 1024, f 512, 1024 rows
+    // 59, 33; E 4, d = f = 512, 448 rows per expert 45, 43; beyond it loses: E 1, d 1024, f 512, 4096 rows 73, 81.
+    const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
+    const long long most = fp8 ? std::min(640LL, std::max(64LL, 60000LL / col_tiles)) : std::min(384LL, std::max(64LL, 40000LL / col_tiles));
     // (32-bit offsets into x and h; every workgroup scans the slices of its expert)
-    if (g_force_rows.load(std::memory_order_relaxed) == 0 && M <= most * E_loc && S <= SKINNY_MAX_SLICES && E_loc <= 4096 &&
+    if (g_force_rows.load(std::memory_order_relaxed) == 0 && (M <= most * E_loc || (long long)M * d * f <= (1LL << 29)) && S <= SKINNY_MAX_SLICES && E_loc <= 4096 &&
         (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull) {
         // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
         // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
@@ -1915,9 +1922,11 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
         return fp8 ? launch_both_skinny<true>(k, s) : launch_both_skinny<false>(k, s);
     }
 
-    // rows per tile by the rows an expert has on average (its slices are merged)
+    // Rows per tile by the rows an expert has on average (its slices are merged).  256-row tiles (the adaptive kernels in bf16) /
+    // 128-row tiles, us: bf16 E 8, d 7168, f 2048, 320 / 576 rows 380 / 506, 532 / 693; E 4, d 2048, f 1408, 320 / 576 rows 117 / 129, 143 /
+    // 132; E 1, d 1024, f 512, 320 / 900 rows 54 / 71, 66 / 66; fp8 E 4, d 7168, f 2048, 448 / 576 / 900 rows 457 / 492 / 455, 354 / 555 / 471.
     const long long avg = M / E_loc;
-    int bm = avg >= 768 ? 256 : (avg >= 96 ? 128 : 64);
+    int bm = avg >= (fp8 || f < 256 ? 576 : 256) ? 256 : (avg >= 96 ? 128 : 64);
     if (const int forced = g_force_rows.load(std::memory_order_relaxed)) bm = forced;
 
     FfnArgs a;
