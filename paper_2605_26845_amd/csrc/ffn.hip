@@ -1585,8 +1585,11 @@ moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
 moe_status launch_skinny_tiles(const SkinnyArgs& a, hipStream_t s) {
     const int strips = (PHASE == 1 ? a.f / (8 * NC) : a.d / (16 * NC));
-    // workgroups for the chunks that one expert may have; with several experts most of them find no rows, and those that do walk on
-    const dim3 grid(strips, a.E, std::min((a.M + 16 * MT - 1) / (16 * MT), std::max(8, 64 / a.E)));
+    // The chunks of an expert's rows are spread over as many workgroups as the chip holds at once, 8 at least (M bounds the rows, they
+    // may be fewer, and an expert may hold most of them); a workgroup walks on from there.
+    const int resident = num_cus() * (MT == 8 ? 1 : 2);
+    const long long fill = resident / ((long long)strips * a.E);
+    const dim3 grid(strips, a.E, (int)std::min<long long>((a.M + 16 * MT - 1) / (16 * MT), std::max(8LL, fill)));
     moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
     hipLaunchKernelGGL((ffn_skinny_kernel<PHASE, W, NC, MT, D, FP8>), grid, dim3(W * 64), 0, s, a);
     return k.done();
