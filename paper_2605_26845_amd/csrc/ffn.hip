@@ -1906,13 +1906,13 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     //   352              (E 8, d 7168, f 2048)         269 / 295 / 380 / 488    252 / 359 / 740 / 1000
     //   152, fp8         (E 8, d 2048, f 1408)          -  /  -  / 211 / 182     -  /  -  / 166 / 212
     //   176, fp8         (E 4, d 7168, f 2048)         377 / 372 / 438 / 354    113 / 167 / 332 / 420
-    // A small call in all streams whatever its rows per expert (M * d * f up to 2^29: a tile kernel's few tiles are then a chain of
-    // their own latencies): E 1, d 256, f 512, 256 / 1024 / 4096 rows 37 / 42 / 44, 17 / 18 / 41; E 1, d 1024, f 512, 1024 rows
+    // A small call in all streams up to 2048 rows per expert (M * d * f up to 2^29: a tile kernel's few tiles are then a chain of
+    // their own latencies): E 1, d 256, f 512, 256 / 1024 / 2048 / 4096 rows 37 / 39 / 41 / 43, 17 / 24 / 25 / 45; E 1, d 1024, f 512, 1024 rows
     // 59, 33; E 4, d = f = 512, 448 rows per expert 45, 43; beyond it loses: E 1, d 1024, f 512, 4096 rows 73, 81.
     const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
     const long long most = fp8 ? std::min(640LL, std::max(64LL, 60000LL / col_tiles)) : std::min(384LL, std::max(64LL, 40000LL / col_tiles));
     // (32-bit offsets into x and h; every workgroup scans the slices of its expert)
-    if (g_force_rows.load(std::memory_order_relaxed) == 0 && (M <= most * E_loc || (long long)M * d * f <= (1LL << 29)) && S <= SKINNY_MAX_SLICES && E_loc <= 4096 &&
+    if (g_force_rows.load(std::memory_order_relaxed) == 0 && (M <= most * E_loc || ((long long)M * d * f <= (1LL << 29) && M <= 2048LL * E_loc)) && S <= SKINNY_MAX_SLICES && E_loc <= 4096 &&
         (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull) {
         // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
         // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
