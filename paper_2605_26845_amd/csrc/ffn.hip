@@ -12,7 +12,8 @@
 // registers to be dequantised) and read back as 16-byte MFMA fragments.  The weights feed the MFMA
 // "A" port so that each lane ends up with 4 consecutive output columns of one row and can store
 // 8 bytes at a time.  bf16 schedules with large groups run the adaptive-shape kernels (ffn_fused_kernel /
-// ffn_adaptive_kernel), the others (and fp8 weights) the fixed-shape ffn_gemm_kernel.
+// ffn_adaptive_kernel), the others (and fp8 weights) the fixed-shape ffn_gemm_kernel; few rows per expert, and small calls,
+// run ffn_skinny_kernel, which streams the weights.
 // moe_expert_ffn_backward_sliced (the backward pass: the exchange of Section 2.1 repeated for the gradients) runs the
 // same adaptive-shape kernels on other operands.
 #include "common.hpp"

@@ -217,15 +217,16 @@ void st_count_kernel(const int32_t* __restrict__ ids, int N, int per_src, int E,
     }
 }
 
-// Row map of the receiving rank: for every row of the schedule (slice-major, then local expert, then source, then
-// arrival order) its arrival index (position among the assignments destined to r, sources in rank order, each in
-// its (token, slot) order) and its assignment index s * T * topk + t * topk + slot.  One workgroup per source walks
-// the source's assignments as st_count_kernel did.  Windows are consecutive stretches of the arrival order, so the
-// rank of an assignment inside its (window, expert) group is the number of earlier assignments of that expert minus
-// those that fell into earlier windows; what no matching shipped is appended source by source.
 // One wavefront's LDS accesses execute in order; this keeps the compiler to that order between its lanes.
 __device__ __forceinline__ void wave_lds_order() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Row map of the receiving rank: for every row of the schedule (slice-major, then local expert, then source, then
+// arrival order) its arrival index (position among the assignments destined to r, sources in rank order, each in
+// its (token, slot) order) and its assignment index s * T * topk + t * topk + slot.  One workgroup per source walks
+// the source's assignments once more.  Windows are consecutive stretches of the arrival order, so the
+// rank of an assignment inside its (window, expert) group is the number of earlier assignments of that expert minus
+// those that fell into earlier windows; what no matching shipped is appended source by source.
+//
 // The workgroup's wavefronts take one stretch of the assignments each and walk it twice: once to count, so that each knows
 // what the ones before it hold, and once to place, without a barrier between them, the next chunk's ids in flight; few
 // assignments are for this rank, so a chunk's are put side by side first.  (One barrier-separated pass of the workgroup per
