@@ -263,6 +263,8 @@ moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t* offsets, i
  *     dw_down[e] = dy^T h  [d][f] ;  dw_gate[e] = dg^T x  [f][d] ;  dw_up[e] = du^T x  [f][d]
  * bf16 inputs, fp32 accumulation; dh, dg, du and h are rounded to bf16 once (g and u are recomputed
  * from x, nothing is kept from the forward call), the outputs are bf16.
+ * The weight gradients of few output tiles are summed in 2 to 16 parts of at least 1024 rows per expert on
+ * average; a part is accumulated in fp32 and rounded to bf16, the parts are added in fp32.
  *   x, dy      in   bf16 [M][d]   grouped rows as in moe_expert_ffn_sliced
  *   offsets    in   int32 [S*E_loc + 1]
  *   w_gate, w_up in bf16 [E_loc][f][d], w_down in bf16 [E_loc][d][f]   (bf16 weights only)

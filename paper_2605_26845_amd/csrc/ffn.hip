@@ -1649,18 +1649,17 @@ __host__ __device__ inline int bwd_kpad(int rows, int P) {
 
 // Parts the contraction of a weight gradient is split into.  The gradients have few output tiles (E_loc * f / 256 row
 // blocks times d / 256 column units) and a very long contraction (all rows of the expert): unsplit, a small layer does
-// not fill the chip and a large one runs in a few coarse rounds.  Parts produce partial sums that are added in fp32.
-// Two rounds of tiles on 256 compute units are enough: a part costs a writing and a reading of the gradient.  Whole call, us, for
-// 1 / 2 / 4 / 8 / 16 parts: 192 tiles (E 4, d 2048, f 1408, 36 833 rows) 2904 / 2492 / 2316 / 2335 / 2555; 896 tiles (E 1, d 4096, f 14336,
-// 9000 rows) 8229 / 8319 / 8630 / 9241 / 10694; 96 tiles (E 8, d 1024, f 768, 20 000 rows) 1047 / 792 / 700 / 731 / 909; 48 tiles (E 1, d 2048,
-// f 1408, 30 000 rows) 3091 / 2990 / 2092 / 1751 / 1701.
-// Where the contraction is long (8192 rows and more to a part) a part costs next to nothing, and one more doubling pays when
-// the rounds of tiles are at most 7/8 full: E 1, d 4096, f 14336 (896 tiles), 72 408 rows, 1 / 2 / 4 / 8 parts: 59.5 / 56.7 / 56.9 / 57.0 ms.
+// not fill the chip and a large one runs in a few coarse rounds.  Parts produce partial sums that are rounded to bf16 and
+// then added in fp32 in part order.  Each rounding costs accuracy (1 -> 2 parts: relative error of a gradient 1.7e-3 -> 2.4e-3 on N(0, 1)
+// data), so a part has at least 1024 rows: an expert with fewer than 2048 is one fp32 accumulation.
+// Eight rounds of tiles on 256 compute units.  With equal experts two would do, but the launch waits for the tiles of the expert
+// with the most rows, whose contraction is as much longer as the expert is more popular than the average.  Whole call, ms, two
+// rounds / eight: E 64, d 1024, f 512 (512 tiles), Zipf popularity, 3000 / 6000 / 20 000 rows per expert on average 7.9 / 4.4, 12.3 / 6.2,
+// 42.0 / 21.4, equal experts 2.6 / 2.7, 4.7 / 4.9, 15.1 / 15.3; E 4, d 2048, f 1408 (192 tiles), Zipf, 40 000 rows 9.0 / 8.2.
 int bwd_split(int M, int E_loc, int d, int f) {
     const long long tiles = (long long)E_loc * ((f + 255) / 256) * (d / 256);
     int P = 1;
-    while (P < BWD_MAX_SPLIT && tiles * P < 2 * 256 && (long long)M / E_loc / (2 * P) >= 512) P *= 2;
-    while (P < BWD_MAX_SPLIT && (long long)M / E_loc / (2 * P) >= 8192 && tiles * P * 8 <= (tiles * P + 255) / 256 * 256 * 7) P *= 2;
+    while (P < BWD_MAX_SPLIT && tiles * P < 8 * 256 && (long long)M / E_loc / (2 * P) >= 1024) P *= 2;
     return P;
 }
 
@@ -1743,7 +1742,7 @@ void bwd_gather_transpose_kernel(const __bf16* __restrict__ src, int lds_, int C
     }
 }
 
-// out[e][r] = sum over p of part[e * P + p][r] (n values per expert), added in fp32 in part order; 8 values per thread
+// out[e][r] = sum over p of part[e * P + p][r] (n bf16 values per expert and part), added in fp32 in part order; 8 values per thread
 __global__ __launch_bounds__(256)
 void bwd_reduce_parts_kernel(const __bf16* __restrict__ part, int P, long long n, int E, __bf16* __restrict__ out) {
     typedef __attribute__((ext_vector_type(8))) __bf16 b8;

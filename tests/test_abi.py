@@ -63,6 +63,19 @@ def test_host_side_argument_checks_need_no_gpu():
     assert L.moe_kernel_timing_read(None, None, None, 0) == 0
 
 
+@pytest.mark.parametrize("E_loc,d,f,first", [(1, 1024, 1024, [2048, 4096, 8192, 16384]), (64, 1024, 512, [2048, 4096]), (1, 4096, 14336, [2048, 4096])])
+def test_parts_of_the_weight_gradients(E_loc, d, f, first):
+    """The contraction of a weight gradient is cut into parts of at least 1024 rows per expert (a part's sum is rounded to bf16), up to
+    16 of them and 2048 output tiles: the rows per expert from which on the workspace holds twice the partial sums."""
+    L = moe.load()
+    need = lambda rows: L.moe_ffn_backward_workspace_bytes(rows * E_loc, E_loc, d, f)
+    # (a row adds to the transposed operands, dh, dg, du and h, and in steps of 128 rows to their padding)
+    part = 2 * E_loc * d * f * 2
+    jumps = [r for r in range(32, 20001, 32) if need(r) - need(r - 32) > part]
+    assert jumps == first
+    assert need(first[0]) - need(first[0] - 1) > part > need(first[0] - 1) - need(first[0] - 32)
+
+
 def test_probe_argument_checks_need_no_gpu():
     L = moe.load()
     sink = ctypes.c_void_p(4096)

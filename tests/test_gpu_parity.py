@@ -871,10 +871,28 @@ def test_ffn_backward_small(lib, E_loc, d, f, M, S):
     check_backward(lib, E_loc, d, f, M, S, seed=d + f + M, what="small", spare=5)
 
 
-@pytest.mark.parametrize("E_loc,M", [(1, 1023), (1, 1024), (1, 2100), (2, 4500), (1, 9000)])
+@pytest.mark.parametrize("E_loc,M", [(1, 1023), (1, 1024), (1, 2100), (2, 4500), (1, 4200), (1, 9000), (1, 16500)])
 def test_ffn_backward_parts(lib, E_loc, M):
-    """1, 2, 4 and 8 parts of the contraction of the weight gradients (at least 512 rows each)."""
+    """1, 1, 2, 2, 4, 8 and 16 parts of the contraction of the weight gradients (at least 1024 rows each)."""
     check_backward(lib, E_loc, 256, 256, M, 3, M, "parts")
+
+
+@pytest.mark.parametrize("M", [1024, 1500, 2047])
+def test_ffn_backward_sums_below_2048_rows_are_exact(lib, M):
+    """An expert with fewer than 2048 rows is one fp32 accumulation: with the same x in every row and dy of +1 for the first half
+    (and three more rows), -1 for the rest, dw_down is a small multiple of h, which a partial sum rounded to bf16 would lose
+    (half the rows times h keeps 8 bits).  Every fp32 sum here is a multiple of h below 2^11 h: exact."""
+    say("ffn backward exact sums", M)
+    d, f = 256, 256
+    w = upload_weights(workloads.ffn_weights(1, d, f, seed=M))
+    x = dev_bf16(workloads.activations(1, d, seed=M)).expand(M, d).contiguous()
+    dy = torch.full((M, d), -1.0, dtype=torch.bfloat16, device=DEV)
+    dy[: M // 2 + 3] = 1.0
+    run = lambda n: lib.moe_expert_ffn_backward_sliced(x[:n], dy[:n], dev(np.array([0, n], dtype=np.int32)), 1, 1, w["w_gate"], w["w_up"], w["w_down"])
+    h = run(1)["dw_down"].float()                                          # one row, dy = 1: h itself
+    got = run(M)["dw_down"]
+    torch.cuda.synchronize()
+    assert torch.equal(got, (h * (2 * (M // 2 + 3) - M)).to(torch.bfloat16))
 
 
 def test_ffn_backward_edge_cases(lib):
