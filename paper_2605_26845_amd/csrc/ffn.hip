@@ -1515,7 +1515,7 @@ template <> struct Shape<128> { static constexpr int WMW = 2, MB = 2, BK = 32, N
 template <> struct Shape<64>  { static constexpr int WMW = 2, MB = 1, BK = 32, NST = 3, PER_CU = 2; };
 
 template <int PHASE, int ROWS, bool FP8>
-moe_status launch_gemm(const FfnArgs& a, long long max_tiles, hipStream_t s) {
+moe_status launch_gemm(const FfnArgs& a, hipStream_t s) {
     typedef Shape<ROWS> S;
     constexpr size_t lds = (size_t)S::NST * (ROWS + BN) * S::BK * 2;
     static moe::DeviceOnce attr;
@@ -1526,13 +1526,14 @@ moe_status launch_gemm(const FfnArgs& a, long long max_tiles, hipStream_t s) {
         if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
         attr.mark(dev);
     }
-    const long long slots = (long long)num_cus() * S::PER_CU;
-    const int grid = (int)(max_tiles < slots ? max_tiles : slots);
+    // Every slot, also when there are fewer tiles (see launch_adaptive): us, a workgroup per tile / every slot, fp8: E 1, d 4096,
+    // f 14336, 512 / 640 / 1024 rows 901 / 628, 886 / 585, 930 / 689; E 4, d 7168, f 2048, 512 rows 535 / 413; E 4, d 2048, f 1408, 1024 rows 215 / 156.
     moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(S::WMW * 128), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(num_cus() * S::PER_CU), dim3(S::WMW * 128), lds, s, a);
     return k.done();
 }
 
+// `max_tiles`: workgroups wanted, at most one per compute unit is launched
 template <int PHASE, int AROWS, int OROWS, int EPI = 0>
 moe_status launch_adaptive(const FfnArgs& a, long long max_tiles, hipStream_t s, const char* name = nullptr) {
     static moe::DeviceOnce attr;
@@ -1577,10 +1578,10 @@ moe_status launch_both_adaptive(const FfnArgs& a, long long max_blocks, hipStrea
 }
 
 template <int ROWS, bool FP8>
-moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
-    moe_status st = launch_gemm<1, ROWS, FP8>(a, max_blocks * (a.f / 128), s);
+moe_status launch_both(const FfnArgs& a, hipStream_t s) {
+    moe_status st = launch_gemm<1, ROWS, FP8>(a, s);
     if (st != MOE_OK) return st;
-    return launch_gemm<2, ROWS, FP8>(a, max_blocks * (a.d / BN), s);
+    return launch_gemm<2, ROWS, FP8>(a, s);
 }
 
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
@@ -1975,13 +1976,13 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
         return !listed ? launch_both_adaptive<ROWS_PLAIN>(a, max_blocks, s)
                : off32 ? launch_both_adaptive<ROWS_LIST32>(a, max_blocks, s) : launch_both_adaptive<ROWS_LIST64>(a, max_blocks, s);
     if (fp8) {
-        if (bm == 256) return launch_both<256, true>(a, max_blocks, s);
-        if (bm == 128) return launch_both<128, true>(a, max_blocks, s);
-        return launch_both<64, true>(a, max_blocks, s);
+        if (bm == 256) return launch_both<256, true>(a, s);
+        if (bm == 128) return launch_both<128, true>(a, s);
+        return launch_both<64, true>(a, s);
     }
-    if (bm == 256) return launch_both<256, false>(a, max_blocks, s);
-    if (bm == 128) return launch_both<128, false>(a, max_blocks, s);
-    return launch_both<64, false>(a, max_blocks, s);
+    if (bm == 256) return launch_both<256, false>(a, s);
+    if (bm == 128) return launch_both<128, false>(a, s);
+    return launch_both<64, false>(a, s);
 }
 
 extern "C" moe_status moe_expert_ffn_sliced(const void* x, const int32_t* offsets, int M, int S, int E_loc, int d, int f,
@@ -2075,7 +2076,13 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.dh = dh; a.lddh = L.f_pad; a.dgu = dgu;
     a.queues1 = counters + 8;
     a.g2.etab = nullptr;
-    const long long row_blocks = M / 256 + E_loc;
+    // Workgroups of the kernels over rows.  A workgroup takes its next ticket while it multiplies its first slab; were there no more
+    // workgroups than tiles, those whose own queue holds tiles would take a second one before those that have to look through the
+    // other queues have found their first, and the launch would last two tiles.  Twice as many see to it that first tickets go out
+    // first; where a tile is long (K >= 4096) every compute unit gets one, since what the idle ones cost the queues, some 8 us,
+    // does not count.  Whole call, us, one per tile / two per tile / every unit: E 1, d 4096, f 14336, 3000 rows 3970 / 3365 / 3365, 700 rows
+    // 2190 / 2050 / 1695; E 1, d 2048, f 1408, 700 rows 395 / 310 / 390; E 1, d = f = 256, 1500 rows 256 / 222 / 312.
+    auto workgroups = [&](int units, int K) -> long long { return K >= 4096 ? num_cus() : 2LL * (M / 256 + E_loc) * units; };
     const bool off32 = (unsigned long long)M * d * 2 < 0xFFFFFF00ull;
 
     // ---- dh = dy Wd: rows x f_pad, K = d
@@ -2085,14 +2092,14 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.g2.K = d; a.g2.NU = L.f_pad / 256;
     a.g2.queues = counters + 0;
     a.g2.o_bytes = 0;
-    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dh_kernel")
-       : off32   ? launch_adaptive<2, ROWS_LIST32, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dh_kernel")
-                 : launch_adaptive<2, ROWS_LIST64, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dh_kernel");
+    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dh_kernel")
+       : off32   ? launch_adaptive<2, ROWS_LIST32, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dh_kernel")
+                 : launch_adaptive<2, ROWS_LIST64, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dh_kernel");
     if (st != MOE_OK) return st;
     // ---- g, u recomputed; dg, du, h
-    st = !listed ? launch_adaptive<1, ROWS_PLAIN, ROWS_PLAIN, 1>(a, row_blocks * (f / 128), s, "ffn_bwd_act_kernel")
-       : off32   ? launch_adaptive<1, ROWS_LIST32, ROWS_PLAIN, 1>(a, row_blocks * (f / 128), s, "ffn_bwd_act_kernel")
-                 : launch_adaptive<1, ROWS_LIST64, ROWS_PLAIN, 1>(a, row_blocks * (f / 128), s, "ffn_bwd_act_kernel");
+    st = !listed ? launch_adaptive<1, ROWS_PLAIN, ROWS_PLAIN, 1>(a, workgroups(f / 128, d), s, "ffn_bwd_act_kernel")
+       : off32   ? launch_adaptive<1, ROWS_LIST32, ROWS_PLAIN, 1>(a, workgroups(f / 128, d), s, "ffn_bwd_act_kernel")
+                 : launch_adaptive<1, ROWS_LIST64, ROWS_PLAIN, 1>(a, workgroups(f / 128, d), s, "ffn_bwd_act_kernel");
     if (st != MOE_OK) return st;
     // ---- dx = [dg | du] [Wg ; Wu]: rows x d, K = 2f
     a.g2.A = dgu; a.g2.lda = 2 * f;
@@ -2101,9 +2108,9 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.g2.K = 2 * f; a.g2.NU = d / 256;
     a.g2.queues = counters + 16;
     a.g2.o_bytes = off32 ? (unsigned int)M * (unsigned int)d * 2u : 0u;
-    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dx_kernel")
-       : off32   ? launch_adaptive<2, ROWS_PLAIN, ROWS_LIST32>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dx_kernel")
-                 : launch_adaptive<2, ROWS_PLAIN, ROWS_LIST64>(a, row_blocks * a.g2.NU, s, "ffn_bwd_dx_kernel");
+    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel")
+       : off32   ? launch_adaptive<2, ROWS_PLAIN, ROWS_LIST32>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel")
+                 : launch_adaptive<2, ROWS_PLAIN, ROWS_LIST64>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel");
     if (st != MOE_OK) return st;
 
     // ---- transposed, expert-major copies of the operands of the weight gradients
