@@ -1515,7 +1515,7 @@ template <> struct Shape<128> { static constexpr int WMW = 2, MB = 2, BK = 32, N
 template <> struct Shape<64>  { static constexpr int WMW = 2, MB = 1, BK = 32, NST = 3, PER_CU = 2; };
 
 template <int PHASE, int ROWS, bool FP8>
-moe_status launch_gemm(const FfnArgs& a, hipStream_t s) {
+moe_status launch_gemm(const FfnArgs& a, long long max_tiles, hipStream_t s) {
     typedef Shape<ROWS> S;
     constexpr size_t lds = (size_t)S::NST * (ROWS + BN) * S::BK * 2;
     static moe::DeviceOnce attr;
@@ -1526,10 +1526,16 @@ moe_status launch_gemm(const FfnArgs& a, hipStream_t s) {
         if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
         attr.mark(dev);
     }
-    // Every slot, also when there are fewer tiles (see launch_adaptive): us, a workgroup per tile / every slot, fp8: E 1, d 4096,
-    // f 14336, 512 / 640 / 1024 rows 901 / 628, 886 / 585, 930 / 689; E 4, d 7168, f 2048, 512 rows 535 / 413; E 4, d 2048, f 1408, 1024 rows 215 / 156.
+    // Two workgroups per tile, as far as the chip holds them.  A workgroup takes its next ticket early; were there no more workgroups than
+    // tiles, those whose own queue holds tiles would take second ones before those that have to look through the other queues
+    // have found their first.  Many more than tiles cost the queues some 20 us.  Whole call, us, one per tile / two / four / every slot: fp8
+    // E 1, d = f = 4096, 512 rows 417 / 260 / 287 / 300; E 4, d 7168, f 2048, 512 rows 528 / 410 / 409 / 413; E 4, d 2048, f 1408, 1024 rows 214 /
+    // 153 / 153 / 153; bf16 E 8, d 2048, f 1408, 16 rows 127 / 99 / 123 / 141; E 24, d = f = 256, 64 rows 41 / 47 / 67 / 93 (of 260 calls
+    // two were faster than one by more than 10 % in 180 and slower by more than 10 %, a third at most, in 14).
+    const long long slots = (long long)num_cus() * S::PER_CU;
+    const int grid = (int)std::min(2 * max_tiles, slots);
     moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
-    hipLaunchKernelGGL(kern, dim3(num_cus() * S::PER_CU), dim3(S::WMW * 128), lds, s, a);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(S::WMW * 128), lds, s, a);
     return k.done();
 }
 
@@ -1578,10 +1584,10 @@ moe_status launch_both_adaptive(const FfnArgs& a, long long max_blocks, hipStrea
 }
 
 template <int ROWS, bool FP8>
-moe_status launch_both(const FfnArgs& a, hipStream_t s) {
-    moe_status st = launch_gemm<1, ROWS, FP8>(a, s);
+moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
+    moe_status st = launch_gemm<1, ROWS, FP8>(a, max_blocks * (a.f / 128), s);
     if (st != MOE_OK) return st;
-    return launch_gemm<2, ROWS, FP8>(a, s);
+    return launch_gemm<2, ROWS, FP8>(a, max_blocks * (a.d / BN), s);
 }
 
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
@@ -1976,13 +1982,13 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
         return !listed ? launch_both_adaptive<ROWS_PLAIN>(a, max_blocks, s)
                : off32 ? launch_both_adaptive<ROWS_LIST32>(a, max_blocks, s) : launch_both_adaptive<ROWS_LIST64>(a, max_blocks, s);
     if (fp8) {
-        if (bm == 256) return launch_both<256, true>(a, s);
-        if (bm == 128) return launch_both<128, true>(a, s);
-        return launch_both<64, true>(a, s);
+        if (bm == 256) return launch_both<256, true>(a, max_blocks, s);
+        if (bm == 128) return launch_both<128, true>(a, max_blocks, s);
+        return launch_both<64, true>(a, max_blocks, s);
     }
-    if (bm == 256) return launch_both<256, false>(a, s);
-    if (bm == 128) return launch_both<128, false>(a, s);
-    return launch_both<64, false>(a, s);
+    if (bm == 256) return launch_both<256, false>(a, max_blocks, s);
+    if (bm == 128) return launch_both<128, false>(a, max_blocks, s);
+    return launch_both<64, false>(a, max_blocks, s);
 }
 
 extern "C" moe_status moe_expert_ffn_sliced(const void* x, const int32_t* offsets, int M, int S, int E_loc, int d, int f,
@@ -2076,12 +2082,10 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.dh = dh; a.lddh = L.f_pad; a.dgu = dgu;
     a.queues1 = counters + 8;
     a.g2.etab = nullptr;
-    // Workgroups of the kernels over rows.  A workgroup takes its next ticket while it multiplies its first slab; were there no more
-    // workgroups than tiles, those whose own queue holds tiles would take a second one before those that have to look through the
-    // other queues have found their first, and the launch would last two tiles.  Twice as many see to it that first tickets go out
-    // first; where a tile is long (K >= 4096) every compute unit gets one, since what the idle ones cost the queues, some 8 us,
-    // does not count.  Whole call, us, one per tile / two per tile / every unit: E 1, d 4096, f 14336, 3000 rows 3970 / 3365 / 3365, 700 rows
-    // 2190 / 2050 / 1695; E 1, d 2048, f 1408, 700 rows 395 / 310 / 390; E 1, d = f = 256, 1500 rows 256 / 222 / 312.
+    // Workgroups of the kernels over rows: two per tile (see launch_gemm), but one on every compute unit where a tile is long
+    // (K >= 4096), since what the idle ones cost the queues, some 8 us, does not count there.  Whole call, us, one per tile / two per
+    // tile / every unit: E 1, d 4096, f 14336, 3000 rows 3970 / 3365 / 3365, 700 rows 2190 / 2050 / 1695; E 1, d 2048, f 1408, 700 rows 395 /
+    // 310 / 390; E 1, d = f = 256, 1500 rows 256 / 222 / 312.
     auto workgroups = [&](int units, int K) -> long long { return K >= 4096 ? num_cus() : 2LL * (M / 256 + E_loc) * units; };
     const bool off32 = (unsigned long long)M * d * 2 < 0xFFFFFF00ull;
 
