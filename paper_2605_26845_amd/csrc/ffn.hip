@@ -1526,14 +1526,15 @@ moe_status launch_gemm(const FfnArgs& a, long long max_tiles, hipStream_t s) {
         if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
         attr.mark(dev);
     }
-    // Two workgroups per tile, as far as the chip holds them.  A workgroup takes its next ticket early; were there no more workgroups than
-    // tiles, those whose own queue holds tiles would take second ones before those that have to look through the other queues
-    // have found their first.  Many more than tiles cost the queues some 20 us.  Whole call, us, one per tile / two / four / every slot: fp8
-    // E 1, d = f = 4096, 512 rows 417 / 260 / 287 / 300; E 4, d 7168, f 2048, 512 rows 528 / 410 / 409 / 413; E 4, d 2048, f 1408, 1024 rows 214 /
-    // 153 / 153 / 153; bf16 E 8, d 2048, f 1408, 16 rows 127 / 99 / 123 / 141; E 24, d = f = 256, 64 rows 41 / 47 / 67 / 93 (of 260 calls
-    // two were faster than one by more than 10 % in 180 and slower by more than 10 %, a third at most, in 14).
-    const long long slots = (long long)num_cus() * S::PER_CU;
-    const int grid = (int)std::min(2 * max_tiles, slots);
+    // Where there are fewer tiles than compute units, up to four workgroups per tile, but no more than compute units.  A workgroup
+    // takes its next ticket early; were there no more workgroups than tiles, those whose own queue holds tiles would take second ones
+    // before those that have to look through the other queues have found their first.  A second workgroup on a compute unit takes
+    // tickets away from one that is empty, and many idle ones cost the queues some 20 us.  Whole call, us, one per tile / two per tile, as
+    // far as the chip holds them / every slot / this: fp8 E 1, d = f = 4096, 96 rows 402 / 311 / - / 227, 512 rows 417 / 260 / 300 / 260; E 64, d 1024, f 512, 4
+    // rows 90 / 126 / - / 89; E 4, d 2048, f 1408, 1024 rows 214 / 153 / 153 / 153; bf16 E 8, d 2048, f 1408, 16 rows 127 / 99 / 141 / 99; E 24, d = f = 256, 64
+    // rows 41 / 47 / 93 / 47.  (546 calls, mean time over the best of these: 1.27, 1.08, -, 1.04.)
+    const long long slots = (long long)num_cus() * S::PER_CU, cus = num_cus();
+    const int grid = (int)std::min(max_tiles >= cus ? max_tiles : std::min(cus, max_tiles <= cus / 4 ? 4 * max_tiles : 2 * max_tiles), slots);
     moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(S::WMW * 128), lds, s, a);
     return k.done();
