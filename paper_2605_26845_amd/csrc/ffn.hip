@@ -1621,6 +1621,7 @@ moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
 // Weight rows per workgroup: 64 (the 64 rows of activations are then fetched as often as the weights), but 16 in phase 2 when
 // the strips of 64 would leave half the compute units idle: d = 4096, f = 14336, one expert, phase 2 at 37 rows: 64 rows 75 us,
 // 16 rows 39 us; d = 7168, f = 2048, four fp8 experts, 203 rows: 28 us, 59 us.
+int skinny_strips2(int E_loc, int d) { return (long long)(d / 64) * E_loc >= num_cus() / 2 ? d / 64 : d / 16; }     // strips per expert in phase 2
 template <bool FP8>
 moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
     moe_status st;
@@ -1631,8 +1632,38 @@ moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
         if ((st = k.done()) != MOE_OK) return st;
     }
     if ((st = launch_skinny<1, 4, 4, 2, FP8>(a, s)) != MOE_OK) return st;
-    if ((long long)(a.d / 64) * a.E >= num_cus() / 2) return launch_skinny<2, 4, 4, 2, FP8>(a, s);
+    if (skinny_strips2(a.E, a.d) == a.d / 64) return launch_skinny<2, 4, 4, 2, FP8>(a, s);
     return launch_skinny<2, 4, 1, 4, FP8>(a, s);
+}
+
+// Whether a call's weights are streamed (once per 64 or 128 rows) or its rows worked on in tiles.  Only M, an upper bound of the rows, is
+// known here, and not how unequal the experts are: the lines were fitted to 4000 calls (E 1 .. 128, d 256 .. 7168, f 256 .. 14336) with
+// equal experts, Zipf popularity and all rows at one expert.  Of the first two kinds 2 in 3000 calls take the slower way by more than a
+// factor 1.8, none of the Zipf ones by more than 1.3.
+// - Rows per expert at most a constant over the column tiles the tile kernels would have for the chip (both phases), at least 64.  One
+//   or two experts stream further, since nothing is lost to the remainder of one expert's rows behind another's.  us, streaming / tiles,
+//   at 128 / 256 / 384 rows per expert: bf16 E 4, d 2048, f 1408 (76 column tiles) 50 / 99, 75 / 104, 109 / 120; E 8, d 7168, f 2048 (352) 356 / 298, 598 /
+//   344, 879 / 365; E 1, d 4096, f 14336 (128) 154 / 450, 281 / 456, 405 / 457; fp8 E 8, d 2048, f 1408 (152) 81 / 157, 120 / 147, 170 / 194; E 4, d 7168,
+//   f 2048 (176) 144 / 321, 258 / 345, 359 / 321; E 1, d 4096, f 14336 128 / 577, 241 / 560, 350 / 570.
+// - A small call in all streams up to 2048 rows (a tile kernel's few tiles are then a chain of their own latencies): E 1, d 256, f 512,
+//   1024 / 2048 rows 18 / 43, 26 / 41; E 4, d = f = 512, 448 rows per expert 27 / 45.
+// - More than 8 experts: the most popular one's rows are chunks behind each other, so 3072 rows at most (E 16, d = f = 256, Zipf, 4096 rows 59 /
+//   40, 8192 rows 98 / 42); and as every expert gets workgroups for up to 8 chunks, most of which find no rows (some 5 ns each on
+//   the whole chip), a limit to those beyond the first: E 64, d 1024, f 512, 256 / 512 rows 79 / 85, 112 / 88; E 128, d 2048, f 768, 128 / 512 rows 204 / 219, 451 /
+//   261; fp8, whose tiles cost more, twice as many: E 64, 2048 rows 98 / 110.
+bool streams(int M, int S, int E_loc, int d, int f, bool fp8) {
+    // (32-bit offsets into x and h; every workgroup scans the slices of its expert)
+    if (S > SKINNY_MAX_SLICES || E_loc > 4096 || (unsigned long long)M * std::max(d, f) * 2 >= 0xFFFFFF00ull) return false;
+    const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
+    const long long most = E_loc <= 2 ? (fp8 ? std::min(1536LL, std::max(64LL, 90000 / col_tiles)) : std::min(768LL, std::max(64LL, 45000 / col_tiles)))
+                                      : (fp8 ? std::min(640LL, std::max(64LL, 60000 / col_tiles)) : std::min(384LL, std::max(64LL, 36000 / col_tiles)));
+    if (M > most * E_loc && !(M <= 2048 && (long long)M * d * f <= (1LL << 30))) return false;
+    if (E_loc > 8) {
+        const long long strips = f / 32 + skinny_strips2(E_loc, d);
+        const long long spare = E_loc * strips * (std::min(8, (M + 63) / 64) - 1);
+        if (M > 3072 || spare > (fp8 ? 64 : 36) * (long long)num_cus()) return false;
+    }
+    return true;
 }
 
 moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
@@ -1904,24 +1935,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
                                             row_map, row_gate, y, workspace, base_bytes, hip_stream);
     }
 
-    // Few rows per expert: the weights are streamed, once per 64 or 128 rows, by the kernels made for that.  Where that ends
-    // depends on how many column tiles the tile kernels would have for the chip (both phases: E_loc * (d / 256 + f / 128)).
-    // Measured at 64 / 128 / 320 / 448 rows per expert, us, weights not in any cache, the best tiles against streaming:
-    //    76 column tiles (E 4, d 2048, f 1408)         117 / 119 / 117 / 109     44 /  54 /  98 / 118
-    //   128              (E 1, d 4096, f 14336)        543 / 510 / 454 / 502    110 / 153 / 377 / 482
-    //   160              (E 8, d 1024, f 2048)          -  /  -  / 143 / 145     -  /  -  / 173 / 226
-    //   176              (E 4, d 7168, f 2048)         246 / 263 / 304 / 293    134 / 204 / 380 / 500
-    //   352              (E 8, d 7168, f 2048)         269 / 295 / 380 / 488    252 / 359 / 740 / 1000
-    //   152, fp8         (E 8, d 2048, f 1408)          -  /  -  / 211 / 182     -  /  -  / 166 / 212
-    //   176, fp8         (E 4, d 7168, f 2048)         377 / 372 / 438 / 354    113 / 167 / 332 / 420
-    // A small call in all streams up to 2048 rows per expert (M * d * f up to 2^29: a tile kernel's few tiles are then a chain of
-    // their own latencies): E 1, d 256, f 512, 256 / 1024 / 2048 / 4096 rows 37 / 39 / 41 / 43, 17 / 24 / 25 / 45; E 1, d 1024, f 512, 1024 rows
-    // 59, 33; E 4, d = f = 512, 448 rows per expert 45, 43; beyond it loses: E 1, d 1024, f 512, 4096 rows 73, 81.
-    const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
-    const long long most = fp8 ? std::min(640LL, std::max(64LL, 60000LL / col_tiles)) : std::min(384LL, std::max(64LL, 40000LL / col_tiles));
-    // (32-bit offsets into x and h; every workgroup scans the slices of its expert)
-    if (g_force_rows.load(std::memory_order_relaxed) == 0 && (M <= most * E_loc || ((long long)M * d * f <= (1LL << 29) && M <= 2048LL * E_loc)) && S <= SKINNY_MAX_SLICES && E_loc <= 4096 &&
-        (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull) {
+    if (g_force_rows.load(std::memory_order_relaxed) == 0 && streams(M, S, E_loc, d, f, fp8)) {
         // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
         // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
         // 325, 79 / 112 / 154 / 280; E 4, d 2048, f 1408, 128 / 256 rows: 54 / 90, 57 / 84; not so E 4, d 7168, f 2048, 128 rows: 204, 213.

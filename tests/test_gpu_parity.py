@@ -841,6 +841,39 @@ def test_ffn_few_rows_per_expert(lib, dtype, E_loc, d, f, sizes):
     assert (np.abs(oracle.decode_bf16(host_bf16_bits(ym)[row_map]) - plain) <= 2.0 ** -7 * np.abs(plain) + 1e-30).all()
 
 
+@pytest.mark.parametrize("dtype,E_loc,d,f,M,S,streamed", [
+    ("bf16", 1, 256, 512, 2048, 1, True), ("bf16", 1, 2048, 1408, 768, 3, True), ("bf16", 1, 2048, 1408, 4096, 1, False), ("fp8", 1, 4096, 1408, 768, 10, True),
+    ("bf16", 8, 2048, 1408, 8 * 192, 10, True), ("bf16", 8, 2048, 1408, 8 * 256, 10, False), ("bf16", 16, 256, 256, 4096, 2, False), ("fp8", 64, 256, 256, 8192, 10, False),
+    ("bf16", 64, 1024, 512, 512, 1, False), ("bf16", 64, 1024, 512, 256, 1, True), ("fp8", 64, 1024, 512, 2048, 1, True), ("fp8", 64, 1024, 512, 4096, 1, False),
+    ("bf16", 2, 256, 256, 30, 1025, False)])
+def test_ffn_choice_of_kernels(lib, dtype, E_loc, d, f, M, S, streamed):
+    """Which calls stream the weights and which work in tiles (these run the planning kernel): many experts and a skewed spread of the
+    rows must not meet the streaming kernels' re-reading of the weights.  Both ways agree where all rows belong to one expert."""
+    say("ffn choice of kernels", dtype, E_loc, d, f, M, S)
+    w = workloads.ffn_weights_on_device(E_loc, d, f, M, dtype, DEV)
+    x = workloads.activations_on_device(M, d, S, DEV)
+    sizes = np.zeros((S, E_loc), dtype=np.int64)
+    sizes[:, E_loc // 2] = M // S
+    sizes[0, E_loc // 2] += M - sizes.sum()
+    offsets = dev(np.concatenate([[0], np.cumsum(sizes.ravel())]).astype(np.int32))
+    lib.moe_kernel_timing_enable(True)
+    try:
+        y = lib.moe_expert_ffn_sliced(x, offsets, S, E_loc, **w)
+        torch.cuda.synchronize()
+        names = lib.moe_kernel_timing_read()
+    finally:
+        lib.moe_kernel_timing_enable(False)
+    assert ("ffn_plan_kernel" not in names) == streamed
+    lib.moe_ffn_tile_override(128)
+    try:
+        tiles = lib.moe_expert_ffn_sliced(x, offsets, S, E_loc, **w)
+        torch.cuda.synchronize()
+    finally:
+        lib.moe_ffn_tile_override()
+    # the same values, h and y rounded to bf16 after sums in another order: single roundings of either differ
+    assert float((y.float() - tiles.float()).norm() / tiles.float().norm()) <= 2.0 ** -8
+
+
 # ------------------------------------------------------------------------------ FFN backward
 def check_backward(lib, E_loc, d, f, M, S, seed, what, spare=0, empty_frac=0.15):
     W = workloads.ffn_weights(E_loc, d, f, seed=seed)
