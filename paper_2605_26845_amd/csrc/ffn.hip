@@ -17,6 +17,7 @@
 // moe_expert_ffn_backward_sliced (the backward pass: the exchange of Section 2.1 repeated for the gradients) runs the
 // same adaptive-shape kernels on other operands.
 #include "common.hpp"
+#include "rows.hpp"
 #include <type_traits>
 #include <algorithm>
 
@@ -77,7 +78,8 @@ __device__ __forceinline__ int mapped_row(const FfnArgs& a, int p) { return a.li
 // ---------------------------------------------------------------------------------- plan kernel
 // Orders the rows by expert (see FfnArgs), writes the row list where the order differs from the schedule's, and splits
 // every expert's rows into row blocks of bm rows.  Malformed offsets cannot make it write outside its tables: boundaries
-// are clamped to [0, M] and to non-decreasing order, positions to M, and entries beyond `cap` are dropped.
+// are clamped to [0, M] and to non-decreasing order, positions are saturated sums that never pass M (rows.hpp), and entries
+// beyond `cap` are dropped.
 // Plan entry = (first position, end of the expert's positions, local expert, shape class of the block: 0 for more than
 // 128 rows, else 1).
 // The partial last blocks of the experts come first in the table and the full blocks after them: a partial block's
@@ -103,6 +105,30 @@ __device__ __forceinline__ int plan_scan(int v, int tid, int* wave_tot, int& tot
         total += wave_tot[w];
     }
     return base + incl - v;
+}
+
+// exclusive prefix over the workgroup of row counts 0 .. M each, every sum saturated at M
+__device__ __forceinline__ int plan_scan_rows(int rows, int M, int tid, int* wave_tot, int& total) {
+    const int lane = tid & 63, wave = tid >> 6;
+    int incl = rows;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off);
+        if (lane >= off) incl = add_rows(incl, o, M);
+    }
+    int excl = __shfl_up(incl, 1);                       // (a saturated sum less the own count would not be the sum before it)
+    if (lane == 0) excl = 0;
+    __syncthreads();
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    int base = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < PLAN_THREADS / 64; ++w) {
+        if (w < wave) base = add_rows(base, wave_tot[w], M);
+        total = add_rows(total, wave_tot[w], M);
+    }
+    return add_rows(base, excl, M);
 }
 
 // two prefixes behind one pair of barriers
@@ -155,18 +181,14 @@ void ffn_plan_kernel(PlanArgs a) {
     for (int i0 = 0; i0 < G; i0 += PLAN_THREADS) {
         const int i = i0 + tid, e = i / a.S, s = i - e * a.S;
         int lo = 0, rows = 0;
-        if (i < G) {
-            const int g = s * a.e_loc + e;
-            lo = min(max(a.offsets[g], 0), M);
-            rows = min(max(a.offsets[g + 1], lo), M) - lo;
-        }
+        if (i < G) rows = group_rows(a.offsets, s * a.e_loc + e, M, lo);
         int total;
-        const int excl = plan_scan(rows, tid, wave_tot, total);
-        const int pos = min(base + excl, M);
+        const int excl = plan_scan_rows(rows, M, tid, wave_tot, total);
+        const int pos = add_rows(base, excl, M);
         if (table && i < G && s == 0) eb[e] = pos;
         if (a.list) {
             g_pos[tid] = pos; g_row[tid] = lo;
-            if (tid == 0) g_pos[PLAN_THREADS] = min(base + total, M);
+            if (tid == 0) g_pos[PLAN_THREADS] = add_rows(base, total, M);
             __syncthreads();
             const int last = g_pos[PLAN_THREADS];
             for (int p = g_pos[0] + (int)blockIdx.x * PLAN_THREADS + tid; p < last; p += (int)gridDim.x * PLAN_THREADS) {
@@ -182,10 +204,10 @@ void ffn_plan_kernel(PlanArgs a) {
             }
             __syncthreads();                                              // the next pass overwrites the entries
         }
-        base += total;
+        base = add_rows(base, total, M);
     }
     if (!table) return;
-    const int used = min(base, M);
+    const int used = base;
     if (tid == 0) eb[a.e_loc] = used;
     if (a.list && tid < LIST_PAD) a.list[used + tid] = 0;                 // (used <= M: inside the list)
     __threadfence_block();
@@ -1715,43 +1737,41 @@ int bwd_split(int M, int E_loc, int d, int f) {
 __global__ __launch_bounds__(PLAN_THREADS)
 void bwd_prep_kernel(const int32_t* __restrict__ offsets, int S, int e_loc, int M, int f, int cols_cap, int P, int4* __restrict__ etab,
                      int* __restrict__ src_row, int* __restrict__ src_pos, int* __restrict__ counters, int32_t* __restrict__ w_offsets) {
-    __shared__ int k0_of[MAX_GROUPS / 16], p0_of[MAX_GROUPS / 16];      // (e_loc <= 4096)
+    __shared__ int k0_of[MAX_GROUPS / 16], p0_of[MAX_GROUPS / 16 + 1];      // (e_loc <= 4096)
     const int tid = threadIdx.x;
-    auto bound = [&](int g) { return min(max(offsets[g], 0), M); };
     for (int i = tid; i < cols_cap; i += PLAN_THREADS) src_row[i] = src_pos[i] = -1;
     for (int i = tid; i < BWD_GEMMS * 8; i += PLAN_THREADS) counters[i] = 0;
     for (int v = tid; v <= e_loc * P; v += PLAN_THREADS) w_offsets[v] = v * f;  // row groups of the weight gradients: f rows per part
     for (int e = tid; e < e_loc; e += PLAN_THREADS) {
-        int rows = 0;
-        for (int sl = 0; sl < S; ++sl) { const int g = sl * e_loc + e; rows += max(bound(g + 1) - bound(g), 0); }
+        int rows = 0, lo;
+        for (int sl = 0; sl < S; ++sl) rows = add_rows(rows, group_rows(offsets, sl * e_loc + e, M, lo), M);
         p0_of[e] = rows;
-        k0_of[e] = bwd_kpad(rows, P);
     }
     __syncthreads();
     if (tid == 0) {
         int run = 0, run_pos = 0;
         for (int e = 0; e < e_loc; ++e) {
-            const int rows = p0_of[e];
+            const int next_pos = add_rows(run_pos, p0_of[e], M), k = bwd_kpad(next_pos - run_pos, P), kp = k / P;
             p0_of[e] = run_pos;
-            run_pos += rows;
-            const int k = k0_of[e], kp = k / P;
+            run_pos = next_pos;
             for (int p = 0; p < P; ++p) etab[e * P + p] = make_int4(run + p * kp, kp, (e * P + p) * f, 0);
             k0_of[e] = run;
             run += k;
         }
+        p0_of[e_loc] = run_pos;
     }
     __syncthreads();
-    // one wavefront per expert at a time walks its groups in slice order
+    // one wavefront per expert at a time walks its groups in slice order, as far as its positions go (all its rows, unless the
+    // offsets are malformed)
     const int wave = tid >> 6, lane = tid & 63;
     for (int e = wave; e < e_loc; e += PLAN_THREADS / 64) {
-        const int k0 = k0_of[e], p0 = p0_of[e];
-        int base = k0;
-        for (int sl = 0; sl < S; ++sl) {
-            const int g = sl * e_loc + e;
-            const int lo = bound(g), n = max(bound(g + 1) - lo, 0);
-            for (int r = lane; r < n; r += 64)
-                if (base + r < cols_cap) { src_row[base + r] = lo + r; src_pos[base + r] = p0 + (base - k0) + r; }
-            base += n;
+        const int k0 = k0_of[e], p0 = p0_of[e], rows = p0_of[e + 1] - p0;
+        int at = 0;
+        for (int sl = 0; sl < S && at < rows; ++sl) {
+            int lo;
+            const int n = min(group_rows(offsets, sl * e_loc + e, M, lo), rows - at);
+            for (int r = lane; r < n; r += 64) { src_row[k0 + at + r] = lo + r; src_pos[k0 + at + r] = p0 + at + r; }
+            at += n;
         }
     }
 }
