@@ -2075,6 +2075,14 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     const int P = L.P, wrows = E_loc * P * f;
     moe_status st;
 
+    if (M == 0 || G == 0) {
+        // no rows: the weight gradients are zero, dx is empty
+        moe::LaunchScope k("bwd_zero_kernel", s);
+        const size_t words = (size_t)E_loc * f * d / 2;
+        for (void* p : {dw_gate, dw_up, dw_down}) hipLaunchKernelGGL(bwd_zero_kernel, dim3(1024), dim3(256), 0, s, (unsigned int*)p, words);
+        return k.done();
+    }
+
     // ---- plans (row blocks of the schedule; row blocks of the weight gradients: one group of f rows per expert),
     //      expert-major column numbering, transposed weights
     const bool listed = S > 1 && E_loc > 1;      // else the rows already lie expert by expert
@@ -2100,13 +2108,6 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
         hipLaunchKernelGGL(bwd_transpose_kernel, dim3((f + 63) / 64, (d + 63) / 64, E_loc), blk, 0, s, (const __bf16*)w_up, f, d, d, wgut,
                            (long long)2 * f, (long long)d * 2 * f, f);
         if ((st = k.done()) != MOE_OK) return st;
-    }
-    if (M == 0 || G == 0) {
-        // no rows: the weight gradients are zero, dx is empty
-        moe::LaunchScope k("bwd_zero_kernel", s);
-        const size_t words = (size_t)E_loc * f * d / 2;
-        for (void* p : {dw_gate, dw_up, dw_down}) hipLaunchKernelGGL(bwd_zero_kernel, dim3(1024), dim3(256), 0, s, (unsigned int*)p, words);
-        return k.done();
     }
 
     FfnArgs a;

@@ -904,6 +904,26 @@ def test_ffn_backward_small(lib, E_loc, d, f, M, S):
     check_backward(lib, E_loc, d, f, M, S, seed=d + f + M, what="small", spare=5)
 
 
+@pytest.mark.parametrize("S,M,E_loc", [(0, 0, 3), (0, 40, 3), (0, 40, 1100), (0, 40, 2100), (5, 0, 3)])
+def test_ffn_backward_without_groups(lib, S, M, E_loc):
+    """No slices (also with more experts than the planning workgroup has threads, or keeps in LDS) or no rows: zero weight gradients and
+    nothing else is launched, since without groups there are no row boundaries to plan from."""
+    say("ffn backward without groups", S, M, E_loc)
+    d, f = 256, 256
+    w = [torch.ones(sh, dtype=torch.bfloat16, device=DEV) for sh in ((E_loc, f, d), (E_loc, f, d), (E_loc, d, f))]
+    x = torch.ones((M, d), dtype=torch.bfloat16, device=DEV)
+    offsets = torch.zeros((S * E_loc + 1,), dtype=torch.int32, device=DEV)
+    lib.moe_kernel_timing_enable(True)
+    try:
+        out = lib.moe_expert_ffn_backward_sliced(x, x.clone(), offsets, S, E_loc, *w)
+        torch.cuda.synchronize()
+        names = lib.moe_kernel_timing_read()
+    finally:
+        lib.moe_kernel_timing_enable(False)
+    assert set(names) == {"bwd_zero_kernel"}
+    assert not any(bool(out[k].any()) for k in ("dw_gate", "dw_up", "dw_down"))
+
+
 @pytest.mark.parametrize("E_loc,M", [(1, 1023), (1, 1024), (1, 2100), (2, 4500), (1, 4200), (1, 9000), (1, 16500)])
 def test_ffn_backward_parts(lib, E_loc, M):
     """1, 1, 2, 2, 4, 8 and 16 parts of the contraction of the weight gradients (at least 1024 rows each)."""
