@@ -176,8 +176,9 @@ void ffn_plan_kernel(PlanArgs a) {
     const int G = a.S * a.e_loc, M = a.M, bm = a.bm;
     int* const eb = a.e_loc <= PLAN_EXPERTS_LDS ? eb_lds : a.ebase;      // first position of every expert (workgroup 0)
     const bool table = blockIdx.x == 0;
-    // ---- the groups in expert-major order: entry i = group (slice i % S, expert i / S)
-    int base = 0;
+    // ---- the groups in expert-major order: entry i = group (slice i % S, expert i / S).  Listed positions count from 0; without a list
+    //      a position is a schedule row, and they begin where the first group does
+    int base = a.list ? 0 : first_row(a.offsets, M);
     for (int i0 = 0; i0 < G; i0 += PLAN_THREADS) {
         const int i = i0 + tid, e = i / a.S, s = i - e * a.S;
         int lo = 0, rows = 0;
@@ -1735,7 +1736,7 @@ int bwd_split(int M, int E_loc, int d, int f) {
 // The contraction of expert e is split into P parts ("virtual experts" v = e * P + p with partial results of their own):
 // etab[v] = (k0_e + p * K_e / P, K_e / P, v * f, 0).  Also clears the tile queue counters of the launches that follow.
 __global__ __launch_bounds__(PLAN_THREADS)
-void bwd_prep_kernel(const int32_t* __restrict__ offsets, int S, int e_loc, int M, int f, int cols_cap, int P, int4* __restrict__ etab,
+void bwd_prep_kernel(const int32_t* __restrict__ offsets, int S, int e_loc, int M, int listed, int f, int cols_cap, int P, int4* __restrict__ etab,
                      int* __restrict__ src_row, int* __restrict__ src_pos, int* __restrict__ counters, int32_t* __restrict__ w_offsets) {
     __shared__ int k0_of[MAX_GROUPS / 16], p0_of[MAX_GROUPS / 16 + 1];      // (e_loc <= 4096)
     const int tid = threadIdx.x;
@@ -1749,7 +1750,7 @@ void bwd_prep_kernel(const int32_t* __restrict__ offsets, int S, int e_loc, int 
     }
     __syncthreads();
     if (tid == 0) {
-        int run = 0, run_pos = 0;
+        int run = 0, run_pos = listed ? 0 : first_row(offsets, M);           // (as in the plan)
         for (int e = 0; e < e_loc; ++e) {
             const int next_pos = add_rows(run_pos, p0_of[e], M), k = bwd_kpad(next_pos - run_pos, P), kp = k / P;
             p0_of[e] = run_pos;
@@ -2092,7 +2093,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     if ((st = launch_plan(rows_plan, s)) != MOE_OK) return st;
     {
         moe::LaunchScope k("bwd_prep_kernel", s);
-        hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, offsets, S, E_loc, M, f, L.cols_cap, P, etab, src_row, src_pos, counters,
+        hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, offsets, S, E_loc, M, (int)listed, f, L.cols_cap, P, etab, src_row, src_pos, counters,
                            (int32_t*)(ws + L.w_offsets));
         if ((st = k.done()) != MOE_OK) return st;
     }

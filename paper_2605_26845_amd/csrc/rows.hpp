@@ -19,6 +19,9 @@ MOE_ROWS_FN int group_rows(const int32_t* offsets, int g, int M, int& lo) {
     return b - a;
 }
 
+// first row of the first group
+MOE_ROWS_FN int first_row(const int32_t* offsets, int M) { const int a = offsets[0]; return a < 0 ? 0 : (a > M ? M : a); }
+
 // a + b, at most M (0 <= a, b <= M < 2^31)
 MOE_ROWS_FN int add_rows(int a, int b, int M) {
     const unsigned int sum = (unsigned int)a + (unsigned int)b;

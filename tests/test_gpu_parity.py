@@ -874,6 +874,34 @@ def test_ffn_choice_of_kernels(lib, dtype, E_loc, d, f, M, S, streamed):
     assert float((y.float() - tiles.float()).norm() / tiles.float().norm()) <= 2.0 ** -8
 
 
+@pytest.mark.parametrize("dtype,tile_rows", [("bf16", 0), ("bf16", 64), ("bf16", 128), ("bf16", 256), ("fp8", 128)])
+@pytest.mark.parametrize("S,E_loc", [(1, 3), (4, 1), (3, 2), (1, 1)])
+def test_ffn_first_group_later(lib, dtype, tile_rows, S, E_loc):
+    """A schedule whose first group begins behind row 0: its rows are the same as in a buffer that begins there, by every kernel and
+    whether the rows are listed (several slices and experts) or not; the rows before it stay untouched."""
+    say("ffn first group later", dtype, tile_rows, S, E_loc)
+    d, f, skip, M = 256, 256, 37, 700
+    w = workloads.ffn_weights_on_device(E_loc, d, f, S + E_loc, dtype, DEV)
+    offsets = workloads.random_offsets(S * E_loc, M, seed=S + 7 * E_loc)
+    x = workloads.activations_on_device(M + skip, d, 5, DEV)
+    lib.moe_ffn_tile_override(tile_rows)
+    try:
+        y = lib.moe_expert_ffn_sliced(x, dev(offsets + skip), S, E_loc, y=torch.full_like(x, 3.0), **w)
+        want = lib.moe_expert_ffn_sliced(x[skip:].clone(), dev(offsets), S, E_loc, **w)
+        torch.cuda.synchronize()
+    finally:
+        lib.moe_ffn_tile_override()
+    assert torch.equal(y[skip:].view(torch.int16), want.view(torch.int16)) and bool((y[:skip] == 3.0).all())
+    if dtype == "bf16" and tile_rows == 0:
+        dy = workloads.activations_on_device(M + skip, d, 6, DEV)
+        got = lib.moe_expert_ffn_backward_sliced(x, dy, dev(offsets + skip), S, E_loc, **w)
+        want = lib.moe_expert_ffn_backward_sliced(x[skip:].clone(), dy[skip:].clone(), dev(offsets), S, E_loc, **w)
+        torch.cuda.synchronize()
+        assert torch.equal(got["dx"][skip:], want["dx"])
+        for k in ("dw_gate", "dw_up", "dw_down"):
+            assert torch.equal(got[k], want[k]), k
+
+
 # ------------------------------------------------------------------------------ FFN backward
 def check_backward(lib, E_loc, d, f, M, S, seed, what, spare=0, empty_frac=0.15):
     W = workloads.ffn_weights(E_loc, d, f, seed=seed)
