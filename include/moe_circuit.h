@@ -213,7 +213,8 @@ moe_status moe_slice_table_rows(const int32_t* ids, int N, int T, int topk, int 
  *                   (MOE_W_FP8_E4M3_B128 only, else NULL): weight = decode(code) * scale
  *   y          out  bf16 [M][d]; rows >= offsets[last] are left untouched
  *   workspace       moe_ffn_workspace_bytes(M, d, f) bytes (holds the hidden activations and, for up to
- *                   4096 rows, a copy of x; a call whose workspace lacks room for the copy reads x itself).  With
+ *                   4096 rows, a copy of x; a call whose workspace lacks room for the copy reads x itself;
+ *                   never less for a larger M, so one sized for the largest M serves every call).  With
  *                   MOE_W_FP8_E4M3_B128 the caller may add moe_ffn_expanded_weights_bytes(E_loc, d, f)
  *                   bytes: when there are at least 2048 rows per local expert on average the weights
  *                   are then expanded to bf16 once per call (the same values the kernels would form

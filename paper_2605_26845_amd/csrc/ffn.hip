@@ -1498,7 +1498,7 @@ size_t ready_bytes(int M) { return (((size_t)plan_capacity(M) * sizeof(int)) + 2
 
 size_t ffn_base_bytes(int M, int f) { return h_bytes(M, f) + plan_bytes(M) + ready_bytes(M) + 2 * list_bytes(M) + EBASE_BYTES; }
 constexpr int KMAJOR_ROWS = 4096;          // the K-major copy of x is for calls of at most this many rows
-size_t kmajor_bytes(int M, int d) { return M <= KMAJOR_ROWS ? (((size_t)M * d * 2) + 255) & ~(size_t)255 : 0; }
+size_t kmajor_bytes(int M, int d) { return (((size_t)M * d * 2) + 255) & ~(size_t)255; }
 
 std::atomic<int> g_force_rows{0};          // moe_ffn_tile_override: 0 = rows per tile chosen per call, else 64 / 128 / 256
 std::atomic<int> g_force_kernels{0};       //                        1 = never the adaptive-shape kernels, 2 = adaptive-shape kernels, one launch per phase
@@ -1896,8 +1896,9 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
 extern "C" size_t moe_ffn_workspace_bytes(int M, int d, int f) {
     if (M < 0 || d < 1 || f < 1) return 0;
     // hidden activations, plan, ready counters, row list, router weights in list order, row bases of the experts
-    // (all that a call must have), and room for the K-major rows of x of a small call
-    return ffn_base_bytes(M, f) + kmajor_bytes(M, d);
+    // (all that a call must have), and room for the K-major rows of x of a small call; a larger M has room for the smaller
+    // calls too, so that the size never falls when M grows
+    return ffn_base_bytes(M, f) + kmajor_bytes(std::min(M, KMAJOR_ROWS), d);
 }
 
 extern "C" moe_status moe_ffn_tile_override(int tile_rows, int kernels, int panel_groups) {
@@ -1966,7 +1967,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
         // 325, 79 / 112 / 154 / 280; E 4, d 2048, f 1408, 128 / 256 rows: 54 / 90, 57 / 84; not so E 4, d 7168, f 2048, 128 rows: 204, 213.
         __bf16* xk = nullptr;
         const bool pays = d % 2048 == 0 && M >= ((long long)E_loc * f >= 8192 ? 48LL : 160LL) * E_loc;
-        if (pays && kmajor_bytes(M, d) > 0 && workspace_bytes - base_bytes >= kmajor_bytes(M, d)) xk = (__bf16*)((char*)workspace + base_bytes);
+        if (pays && M <= KMAJOR_ROWS && workspace_bytes - base_bytes >= kmajor_bytes(M, d)) xk = (__bf16*)((char*)workspace + base_bytes);
         const SkinnyArgs k = {(const __bf16*)x, (__bf16*)workspace, (__bf16*)y, xk, w_gate, w_up, w_down, s_gate, s_up, s_down,
                               offsets, row_map, row_gate, M, S, E_loc, d, f};
         return fp8 ? launch_both_skinny<true>(k, s) : launch_both_skinny<false>(k, s);

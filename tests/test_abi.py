@@ -63,6 +63,14 @@ def test_host_side_argument_checks_need_no_gpu():
     assert L.moe_kernel_timing_read(None, None, None, 0) == 0
 
 
+@pytest.mark.parametrize("d,f", [(256, 128), (4096, 14336), (7168, 2048)])
+def test_ffn_workspace_grows_with_the_rows(d, f):
+    """One workspace, sized for the largest number of rows, serves every smaller call."""
+    L = moe.load()
+    sizes = [L.moe_ffn_workspace_bytes(M, d, f) for M in (0, 1, 2, 100, 4095, 4096, 4097, 4200, 5000, 8192, 70000)]
+    assert sizes == sorted(sizes)
+
+
 @pytest.mark.parametrize("E_loc,d,f,first", [(1, 1024, 1024, [2048, 4096, 8192, 16384]), (64, 1024, 512, [2048, 4096]), (1, 4096, 14336, [2048, 4096])])
 def test_parts_of_the_weight_gradients(E_loc, d, f, first):
     """The contraction of a weight gradient is cut into parts of at least 1024 rows per expert (a part's sum is rounded to bf16), up to
