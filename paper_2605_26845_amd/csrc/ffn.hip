@@ -1632,15 +1632,16 @@ moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
     if (a.M <= 16) return launch_skinny_tiles<PHASE, W, NC, 1, D, FP8>(a, s);
     if (a.M <= 32) return launch_skinny_tiles<PHASE, W, NC, 2, D, FP8>(a, s);
     // 128 rows per workgroup (one wavefront per SIMD) halve the readings of the weights, as long as enough workgroups are left for the
-    // chip.  With one expert: more than 64 rows, and a workgroup for more than every other compute unit.  With several the most popular
-    // one's chunks of 64 would outnumber the others' by far: from 32 rows per expert on average (fp8, where a reading is half the bytes:
-    // 64), and workgroups for three units in eight.
-    // 64 / 128 rows, us: E 1, d 4096, f 14336, 128 rows 191 / 154; E 1, d 2048, f 1408, 128 / 384 rows 29 / 38, 53 / 42; E 1, d 256, f 512, 1024 / 1536 rows
-    // 18 / 25, 29 / 26; Zipf popularity: E 4, d = f = 512, 256 rows per expert 35 / 25; E 8, d 768, f 384, 96 rows 39 / 30; E 16, d 2048, f 1408, 32 rows 113 /
-    // 99; equal experts: fp8 E 8, d 512, f 1024, 64 rows 31 / 23; fp8 E 4, d 7168, f 2048, Zipf, 48 / 64 rows 89 / 93, 110 / 108.
-    // (It is not always the better one: Zipf, E 12, d 768, f 384, 32 rows 20 / 28.)
+    // chip: for more than every other compute unit with one expert, for three units in eight with several, whose rows are unequal.
+    // From more than 64 rows per expert on average; from 32 with 5 to 16 experts, the popular ones of which have several chunks of 64, and
+    // in bf16 where a second reading of the weights is long (a matrix of 16 MiB).  64 / 128 rows, us: E 1, d 4096, f 14336, 128 rows
+    // 191 / 154; E 1, d 2048, f 1408, 128 / 384 rows 29 / 38, 53 / 42; E 1, d 256, f 512, 1024 / 1536 rows 18 / 25, 29 / 26; Zipf popularity: E 4, d = f =
+    // 512, 256 rows per expert 35 / 25; E 4, d 2048, f 1408, 48 / 64 / 96 rows 35 / 42, 44 / 47, 52 / 50; E 4, d 7168, f 2048, 48 rows 126 / 112, in fp8 89 / 93;
+    // E 8, d 768, f 384, 96 rows 39 / 30; E 16, d 2048, f 1408, 32 rows 113 / 99, in fp8 89 / 79; fp8 E 32, d 2048, f 768, 32 rows 109 / 127.
     const long long groups = (long long)a.E * (a.f / 32) * ((a.M / a.E + 127) / 128);
-    if (a.E == 1 ? a.M > 64 && 2 * groups > num_cus() : a.M >= (FP8 ? 64LL : 32LL) * a.E && 8 * groups >= 3 * num_cus())
+    const bool fills = a.E == 1 ? 2 * groups > num_cus() : 8 * groups >= 3 * num_cus();
+    const bool early = a.E > 4 ? a.E <= 16 && a.M >= 32LL * a.E : !FP8 && a.E > 1 && a.M > 32LL * a.E && (long long)a.d * a.f >= (8LL << 20);
+    if (fills && (a.M > 64LL * a.E || early))
         return launch_skinny_tiles<PHASE, W, NC, 8, 2, FP8>(a, s);
     return launch_skinny_tiles<PHASE, W, NC, 4, D, FP8>(a, s);
 }
