@@ -1974,11 +1974,12 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
         return fp8 ? launch_both_skinny<true>(k, s) : launch_both_skinny<false>(k, s);
     }
 
-    // Rows per tile by the rows an expert has on average (its slices are merged).  256-row tiles (the adaptive kernels in bf16) /
-    // 128-row tiles, us: bf16 E 8, d 7168, f 2048, 320 / 576 rows 380 / 506, 532 / 693; E 4, d 2048, f 1408, 320 / 576 rows 117 / 129, 143 /
-    // 132; E 1, d 1024, f 512, 320 / 900 rows 54 / 71, 66 / 66; fp8 E 4, d 7168, f 2048, 448 / 576 / 900 rows 457 / 492 / 455, 354 / 555 / 471.
+    // Rows per tile by the rows an expert has on average (its slices are merged).  256-row tiles (in bf16 the adaptive kernels) need half as
+    // many readings of the weights, 128-row tiles fit ragged ends better: time of 128-row tiles over 256-row tiles, mean over calls of
+    // E 1 .. 128, d 256 .. 7168, f 256 .. 14336, at 192 / 256 / 384 / 512 / 768 rows: bf16 1.10 / 1.14 / 1.17 / 1.22 / 1.26, fp8 1.13 / 1.06 / 1.15 / 1.10 /
+    // 1.12 (single calls from 0.63 to 1.8: one or two experts prefer 128 rows up to 320).  f = 128 has no adaptive kernel.
     const long long avg = M / E_loc;
-    int bm = avg >= (fp8 || f < 256 ? 576 : 256) ? 256 : (avg >= 96 ? 128 : 64);
+    int bm = avg >= (f < 256 ? 576 : 256) ? 256 : (avg >= 96 ? 128 : 64);
     if (const int forced = g_force_rows.load(std::memory_order_relaxed)) bm = forced;
 
     FfnArgs a;
