@@ -327,17 +327,18 @@ void st_place_kernel(const int32_t* __restrict__ ids, int N, int per_src, int E,
             const bool mine = at + lane < n;
             const int entry = mine ? found[wave][at + lane] : 0;
             const int el = entry >> 8, x = (int)x0 + (entry & 255);
-            // rank among this group's assignments of the same expert; the expert's count so far
-            int before = 0;
-            unsigned long long todo = __ballot(mine);
-            while (todo) {
-                const int k = __builtin_amdgcn_readlane(el, __builtin_ctzll(todo));
-                const unsigned long long peers = __ballot(mine && el == k);
-                if (mine && el == k) before = run[wave][k] + __popcll(peers & ((1ULL << lane) - 1ULL));
-                if (lane == __builtin_ctzll(todo)) run[wave][k] += __popcll(peers);
-                todo &= ~peers;
-                wave_lds_order();
+            // rank among this group's assignments of the same expert (those that agree in every bit of its number: expert by
+            // expert 64 experts of one rank, 1024 assignments, took 42 us in place of 34); the expert's count so far
+            unsigned long long peers = __ballot(mine);
+            for (int bit = 0; (1 << bit) < e_loc; ++bit) {
+                const bool one = (el >> bit) & 1;
+                const unsigned long long ones = __ballot(one);
+                peers &= one ? ones : ~ones;
             }
+            const int before = run[wave][el] + __popcll(peers & ((1ULL << lane) - 1ULL));
+            wave_lds_order();
+            if (mine && lane == __builtin_ctzll(peers)) run[wave][el] = before + __popcll(peers);
+            wave_lds_order();
             if (mine) {
                 const int q = q_base + at + lane;
                 int lo = 0, hi = W;
