@@ -809,12 +809,15 @@ def test_ffn_slices_of_an_expert_share_tiles(lib, S, E_loc, M, tile_rows):
     (3, 256, 640, [[0, 65, 1], [64, 0, 0], [0, 0, 47]]), (2, 512, 128, [[3, 1]] * 300), (8, 4096, 256, [[9, 0, 33, 1, 64, 2, 0, 40]] * 2),
     (4, 256, 256, [[600, 3, 0, 80]]), (2, 8192, 128, [[129, 40]]), (1, 256, 4096, [[128]]), (1, 256, 4096, [[100], [29]]),
     (2, 2048, 384, [[166, 0], [30, 137]]), (1, 2048, 4096, [[200]]), (2, 512, 2048, [[1100, 0]]), (8, 256, 128, [[1100, 0, 0, 5, 0, 0, 0, 1]]),
-    (2, 4096, 2048, [[81, 2]])])
+    (2, 4096, 2048, [[81, 2]]), (1, 256, 128, [[17]]), (1, 512, 640, [[29]]), (2, 256, 256, [[18, 11]]), (6, 512, 1024, [[40, 0, 130, 33, 1, 9]]),
+    (6, 512, 1024, [[100, 0, 0, 290, 1, 9]])])
 def test_ffn_few_rows_per_expert(lib, dtype, E_loc, d, f, sizes):
     """The kernels that stream the weights: every row against the oracle, and through a row map with weights.  Sizes: ends of the
-    16-row tiles and of the 64-row and 128-row chunks (128: f >= 2048 here), more chunks than the grid has (1100 rows of one
-    expert), experts without rows, more slices than a workgroup has threads, steps of K that do not divide by the wavefronts (2, 4, 6,
-    10, 20, 22), x as it is and K-major (the 166 + 167 and the 200 rows of d = 2048), both strip widths of phase 2 (64 from E_loc * d / 64 >= half the compute units on: the 8 x 4096, 2 x 8192 and 2 x 4096 cases)."""
+    16-row tiles and of the 64-row and 128-row chunks (128: the cases of one or two experts with f >= 2048 and of six), calls of up to 16 and up
+    to 32 rows with their own kernels (32: up to 15, 17, 29 and 18 + 11 rows), more chunks than the grid has (1100 rows of one expert),
+    experts without rows, more slices than a workgroup has threads, steps of K that do not divide by the wavefronts (2, 4, 6, 10, 20,
+    22), x as it is and K-major (the 166 + 167 and the 200 rows of d = 2048), both strip widths of phase 2 (64 from E_loc * d / 64 >= half the
+    compute units on: the 8 x 4096, 2 x 8192 and 2 x 4096 cases)."""
     say("ffn few rows per expert", dtype, E_loc, d, f, len(sizes))
     offsets = np.concatenate([[0], np.cumsum(np.array(sizes).ravel())]).astype(np.int32)
     M, S = int(offsets[-1]), len(sizes)
@@ -974,6 +977,39 @@ def test_ffn_backward_sums_below_2048_rows_are_exact(lib, M):
     got = run(M)["dw_down"]
     torch.cuda.synchronize()
     assert torch.equal(got, (h * (2 * (M // 2 + 3) - M)).to(torch.bfloat16))
+
+
+def test_ffn_backward_rows_addressed_with_64_bits(lib):
+    """x and dy above 4 GiB with several slices and experts: the rows of the plan are listed, and gathered (dh, dg, du, h) and scattered
+    (dx) with 64-bit addresses.  Every row and gradient against float32 products of the GPU."""
+    say("ffn backward, listed rows above 4 GiB")
+    E_loc, d, f, S = 2, 8192, 256, 3
+    M = (1 << 32) // (2 * d) + 1500
+    offsets = workloads.random_offsets(S * E_loc, M, seed=51, empty_frac=0.0)
+    w = {k: v for k, v in workloads.ffn_weights_on_device(E_loc, d, f, 52, "bf16", DEV).items()}
+    x, dy = workloads.activations_on_device(M, d, 53, DEV), workloads.activations_on_device(M, d, 54, DEV)
+    out = lib.moe_expert_ffn_backward_sliced(x, dy, dev(offsets), S, E_loc, **w)
+    torch.cuda.synchronize()
+
+    def check(got, ref, what):
+        diff = (got.float() - ref).abs_()
+        check_ffn_error(float(diff.max() / ref.abs().max()), "bf16", what)
+        assert float(diff.norm() / ref.norm()) <= 1.2e-2, what               # (four roundings to bf16 of 2^-9 each, as elsewhere)
+
+    for e in range(E_loc):
+        wg, wu, wd = (w[k][e].float() for k in ("w_gate", "w_up", "w_down"))
+        dWg, dWu, dWd = torch.zeros_like(wg), torch.zeros_like(wu), torch.zeros_like(wd)
+        for s in range(S):
+            lo, hi = int(offsets[s * E_loc + e]), int(offsets[s * E_loc + e + 1])
+            xs, ds = x[lo:hi].float(), dy[lo:hi].float()
+            g, u, dh = xs @ wg.t(), xs @ wu.t(), ds @ wd
+            sig = torch.sigmoid(g)
+            du, dg = dh * g * sig, dh * u * sig * (1 + g * (1 - sig))
+            check(out["dx"][lo:hi], dg @ wg + du @ wu, "dx of slice %d, expert %d" % (s, e))
+            dWg += dg.t() @ xs; dWu += du.t() @ xs; dWd += ds.t() @ (g * sig * u)
+            del xs, ds
+        for k, ref in (("dw_gate", dWg), ("dw_up", dWu), ("dw_down", dWd)):
+            check(out[k][e], ref, "%s[%d]" % (k, e))
 
 
 def test_ffn_backward_edge_cases(lib):
