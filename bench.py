@@ -710,7 +710,8 @@ def decomposition_extras(moe, torch, np, workloads, dev, cpu=True):
         p = prof.cpu().numpy().astype(np.float64)
         clock_ghz = float((p[:, 0] / np.maximum(p[:, 1], 1.0)).mean() * 0.1)          # cycles per 10 ns tick
         steps = float(p[:, 2].mean())
-        lds = N * N * (4 if bits == 32 else 2)
+        # residual in rows of an odd number of 4-byte words, and one word per column
+        lds = N * ((N | 1) * 4 if bits == 32 else ((N + 1) // 2 | 1) * 4) + 4 * ((N + 63) // 64 * 64)
         per_cu = min(LDS_BYTES_PER_CU // lds, 32)
         # ALU bound: every step of a search relaxes one row of the residual, N columns at about 6 vector integer
         # operations each (load, add, subtract, compare, two selects) plus the 6-stage minimum reduction; all lanes of
