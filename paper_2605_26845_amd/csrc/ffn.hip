@@ -1598,10 +1598,18 @@ moe_status launch_fused(const FfnArgs& a, long long max_tiles, hipStream_t s) {
     return k.done();
 }
 
+// One workgroup per tile of the larger phase, half as many more with one expert: its row blocks make few chunks, so that more of the
+// workgroups find their own queue empty and come late to the others (see launch_gemm).  us, 1 / 1.5 / 2 per tile: E 1, d 2048, f 1408, 384 / 2048
+// rows 119 / 84 / 85, 132 / 96 / 103; E 1, d 1024, f 512, 2048 rows 73 / 51 / 53; E 1, d = f = 4096, 512 / 640 rows 260 / 207 / 212, 212 / 246 / 213; E 4, d = f =
+// 512, 2048 rows per expert 57 / 66 / 74.  Mean over the best of the three: one expert 1.09 / 1.02 / 1.02, two 1.02 / 1.02 / 1.03, more 1.01 / 1.02 / 1.04.
+// Not below d = 1024: where a tile takes a few microseconds and M may be a bound above the rows, the idle ones show (8 ranks, d 256, f 512, M
+// 4096: 80 -> 82 us for the layer as a whole).
 template <int ROWS>
-moe_status launch_both_adaptive(const FfnArgs& a, long long max_blocks, hipStream_t s) {
-    if (g_force_kernels.load(std::memory_order_relaxed) != 2)
-        return launch_fused<ROWS>(a, max_blocks * std::max(a.f / 128, a.d / 256), s);
+moe_status launch_both_adaptive(const FfnArgs& a, long long max_blocks, int E_loc, hipStream_t s) {
+    if (g_force_kernels.load(std::memory_order_relaxed) != 2) {
+        const long long tiles = max_blocks * std::max(a.f / 128, a.d / 256);
+        return launch_fused<ROWS>(a, E_loc == 1 && a.d >= 1024 ? tiles + tiles / 2 : tiles, s);
+    }
     moe_status st = launch_adaptive<1, ROWS, ROWS_PLAIN>(a, max_blocks * (a.f / 128), s);
     if (st != MOE_OK) return st;
     return launch_adaptive<2, ROWS_PLAIN, ROWS>(a, max_blocks * (a.d / 256), s);
@@ -2022,8 +2030,8 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     const long long max_blocks = M / bm + E_loc;
     // (the adaptive kernel chains tiles over their last two slabs: at least four 64-wide slabs, f >= 256; d always is)
     if (bm == 256 && !fp8 && f >= 256 && g_force_kernels.load(std::memory_order_relaxed) != 1)
-        return !listed ? launch_both_adaptive<ROWS_PLAIN>(a, max_blocks, s)
-               : off32 ? launch_both_adaptive<ROWS_LIST32>(a, max_blocks, s) : launch_both_adaptive<ROWS_LIST64>(a, max_blocks, s);
+        return !listed ? launch_both_adaptive<ROWS_PLAIN>(a, max_blocks, E_loc, s)
+               : off32 ? launch_both_adaptive<ROWS_LIST32>(a, max_blocks, E_loc, s) : launch_both_adaptive<ROWS_LIST64>(a, max_blocks, E_loc, s);
     if (fp8) {
         if (bm == 256) return launch_both<256, true>(a, max_blocks, s);
         if (bm == 128) return launch_both<128, true>(a, max_blocks, s);
