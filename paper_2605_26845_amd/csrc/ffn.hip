@@ -1674,8 +1674,8 @@ moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
 
 // Whether a call's weights are streamed (once per 64 or 128 rows) or its rows worked on in tiles.  Only M, an upper bound of the rows, is
 // known here, and not how unequal the experts are: the lines were fitted to 4000 calls (E 1 .. 128, d 256 .. 7168, f 256 .. 14336) with
-// equal experts, Zipf popularity and all rows at one expert.  Of the first two kinds 2 in 3000 calls take the slower way by more than a
-// factor 1.8, none of the Zipf ones by more than 1.3.
+// equal experts, Zipf popularity and all rows at one expert.  Of the first two kinds 3 in 3000 calls take more than 1.8 times what the better way
+// would, none of the Zipf ones more than 1.45 times (means 1.02); all rows at one expert: 2.4 times at most, mean 1.04.
 // - Rows per expert at most a constant over the column tiles the tile kernels would have for the chip (both phases), at least 64.  One
 //   or two experts stream further, since nothing is lost to the remainder of one expert's rows behind another's.  us, streaming / tiles,
 //   at 128 / 256 / 384 rows per expert: bf16 E 4, d 2048, f 1408 (76 column tiles) 50 / 99, 75 / 104, 109 / 120; E 8, d 7168, f 2048 (352) 356 / 298, 598 /
