@@ -63,8 +63,6 @@ struct FfnArgs {
         __bf16* O; int ldo;
         int K, NU;
         unsigned int o_bytes;              // bytes of O when rows are scattered with 32-bit offsets
-        const int4* etab;                  // or null.  Per expert (k0, K, r0, 0): the tile contracts over columns k0 .. k0 + K - 1 of
-                                           // A and B, and row m of the schedule is row m - r0 of A
         int* queues;                       // 8 tile queue counters, zero at launch
     } g2;
     // backward pass, phase 1 with the gradient read-out (EPI == 1): dh in, [dg | du] and h out
@@ -166,6 +164,7 @@ struct PlanArgs {
     int32_t* list;                     // [M + LIST_PAD] or null: not wanted
     float* gate;                       // [M] or null: row_gate in list order
     int* ebase;                        // [e_loc + 1], used when e_loc > PLAN_EXPERTS_LDS
+    int* bases;                        // [e_loc + 1] or null: first position of every expert, and the end
 };
 __global__ __launch_bounds__(PLAN_THREADS)
 void ffn_plan_kernel(PlanArgs a) {
@@ -213,6 +212,8 @@ void ffn_plan_kernel(PlanArgs a) {
     if (a.list && tid < LIST_PAD) a.list[used + tid] = 0;                 // (used <= M: inside the list)
     __threadfence_block();
     __syncthreads();
+    if (a.bases)
+        for (int e = tid; e <= a.e_loc; e += PLAN_THREADS) a.bases[e] = eb[e];
     // ---- number of partial blocks (experts whose row count is not a multiple of bm); with at most one expert per thread
     //      the scan of the table pass below yields it
     int n_partial = 0;
@@ -709,7 +710,7 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l31 = lane & 31, lhi = lane >> 5;
-    int K = PHASE == 1 ? a.d : a.g2.K;                          // (per tile when the GEMM has an expert table)
+    const int K = PHASE == 1 ? a.d : a.g2.K;
     const int NU = PHASE == 1 ? a.f / 128 : a.g2.NU;            // column units
     const int lda = PHASE == 1 ? a.d : a.g2.lda, ldb = PHASE == 1 ? a.d : a.g2.ldb;      // row pitch of the operands, elements
     TileGeom geom;
@@ -822,11 +823,6 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
         const int e = __builtin_amdgcn_readfirstlane(s_ticket[5]);
         const int rows = min(C::BMc, m_end - m0);
         const int row0 = C::ROWB == 128 ? row0_128 : row0_64, kcg = C::ROWB == 128 ? kcg_128 : kcg_64;
-        int k0 = 0, r0 = 0;                                               // columns and rows of the operands the tile starts at
-        if (PHASE == 2 && a.g2.etab) {
-            const __attribute__((address_space(4))) int* t = (const __attribute__((address_space(4))) int*)a.g2.etab + 4 * e;
-            k0 = t[0]; K = t[1]; r0 = t[2];
-        }
         if constexpr (GATHER) {
 #pragma unroll
             for (int i = 0; i < C::CA; ++i) {
@@ -840,7 +836,7 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
             for (int i = 0; i < C::CA; ++i)                               // (entries past the block's end are rows too: LIST_PAD)
                 a_voff[i] = (unsigned int)list_row(std::integral_constant<int, WR>{}, m0 + C::RPC * i + WR * wave) * (unsigned int)(lda * 2) + (unsigned int)(kcg * 16);
         } else {
-            aB = (unsigned long long)Abase + ((unsigned long long)(unsigned int)(m0 - r0) * (unsigned int)lda + (unsigned int)k0) * 2ull;
+            aB = (unsigned long long)Abase + (unsigned long long)(unsigned int)m0 * (unsigned int)lda * 2ull;
 #pragma unroll
             for (int i = 0; i < C::CA; ++i) a_voff[i] = (unsigned int)(min(row0 + C::RPC * i, rows - 1) * lda + kcg * 8) * 2u;
         }
@@ -850,7 +846,7 @@ __device__ __forceinline__ void ffn_adaptive_body(const FfnArgs& a, unsigned cha
             wB = (unsigned long long)((const __bf16*)a.wg + ((size_t)e * a.f + (size_t)u0 * 128) * ldb);
             wB_up = (unsigned long long)((const __bf16*)a.wu + ((size_t)e * a.f + (size_t)u0 * 128) * ldb) - wB;
         } else {
-            wB = (unsigned long long)(a.g2.B + (size_t)e * a.g2.strideB + (size_t)u0 * 256 * ldb + k0);
+            wB = (unsigned long long)(a.g2.B + (size_t)e * a.g2.strideB + (size_t)u0 * 256 * ldb);
             wB_up = 0;
         }
         b_voff = (unsigned int)(row0 * ldb + kcg * 8) * 2u;
@@ -1710,128 +1706,400 @@ moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
     return k.done();
 }
 
-// ---------------------------------------------------------------------------------- backward pass: helper kernels
-constexpr int BWD_GEMMS = 6;                   // launches of the matrix kernels per backward call (each owns 8 queue counters)
-constexpr int BWD_KPAD = 128, BWD_KMIN = 256;  // a K range is padded to whole pairs of 64-wide K slabs, four slabs at least
-constexpr int BWD_MAX_SPLIT = 16;
+// ---------------------------------------------------------------------------------- backward pass: weight gradients
+// dW_gate = dg^T x, dW_up = du^T x, dW_down = dy^T h: contractions over the rows of an expert, whose operands all lie with a row's features
+// side by side, i.e. with the contraction as the slow dimension.  K slabs of 64 rows x 256 features (512-byte rows: whole cache lines) go
+// global -> LDS as they lie, and the MFMA fragments are read with ds_read_b64_tr_b16, which hands lane c of 16 the values of four rows
+// in column c.  x and dy are gathered through the row list by the copies themselves (a row number is a scalar load, one slab
+// ahead); rows past an expert's end lie behind the buffer descriptor, for which the copy deposits zeros.
+// Bound by the matrix cores (67 % busy, at 1.02 PFLOP/s) and, beside them, by unequal experts.  E 4, d 2048, f 1408, 36833 rows: 623 us, whole backward
+// pass 1712; with transposed copies of x, dy, h, dg and du (295 us), three launches of the row GEMM that each waited for the most popular
+// expert (797) and partial sums rounded to bf16 and added in three more (110) 2327.  E 1, d 4096, f 14336, 6000 rows: 1620 us, before 2480.
+// All products and experts are one launch, the longest contractions first.  A unit of work is a 256 x 256 tile of one expert's [dW_gate; dW_up] or
+// dW_down over one part of its rows; only experts behind which too little work is left to even out the ends are split (bwd_prep_kernel).
+// Parts are added in fp32 in part order by the workgroup that finishes a tile's last part.
+constexpr int DW_MAX_PARTS = 32;
+constexpr int DW_PART_ROWS = 768;              // rows of a part at least
+constexpr int DW_MAX_UNITS = 1024;             // parts of tiles with a place for their sums, at most
+constexpr size_t DW_UNIT_BYTES = 256 * 256 * sizeof(float);
+constexpr int DW_QUEUES = 24;                  // first of the 8 queue counters of the weight gradients
+constexpr int BWD_COUNTERS = 32;               // tile queue counters of a backward call: dh, act, dx, dW
+constexpr int DW_ZEROS = 1024;                 // bytes of zeros that rows past an expert's end read where the operands need 64-bit addresses
 
-// padded row count of an expert whose rows are contracted in P parts of equal length
-__host__ __device__ inline int bwd_kpad(int rows, int P) {
-    const int unit = BWD_KPAD * P;
-    const int k = (rows + unit - 1) / unit * unit;
-    return k < BWD_KMIN * P ? BWD_KMIN * P : k;
-}
+struct DwGrid {                                // tiles of one product of one expert, walked in chunks of at most 32 for the workgroups of one L2
+    int C, CN, RB, R, ncg, chunks;
+    __host__ __device__ __forceinline__ void init(int rows, int cols) {
+        R = rows; C = cols;
+        ncg = (C + 7) / 8;
+        CN = (C + ncg - 1) / ncg;
+        RB = 32 / CN;
+        chunks = (R + RB - 1) / RB * ncg;
+    }
+    __device__ __forceinline__ bool at(int chunk, int j, int& r, int& c) const {
+        const int rg = chunk / ncg, cg = chunk - rg * ncg;
+        r = rg * RB + j / CN;
+        c = cg * CN + j % CN;
+        return j < RB * CN && r < R && c < C;
+    }
+};
+__host__ __device__ inline int dw_tiles(int d, int f) { return f / 128 * (d / 256) + d / 256 * ((f + 255) / 256); }       // per expert
 
-// Parts the contraction of a weight gradient is split into.  The gradients have few output tiles (E_loc * f / 256 row
-// blocks times d / 256 column units) and a very long contraction (all rows of the expert): unsplit, a small layer does
-// not fill the chip and a large one runs in a few coarse rounds.  Parts produce partial sums that are rounded to bf16 and
-// then added in fp32 in part order.  That rounding costs accuracy (E 4, d 2048, f 1408, 1500 rows each, 1 -> 2 parts: error of dw_gate
-// against float64 2.9e-3 -> 3.4e-3), so a part has at least 1024 rows: an expert with fewer than 2048 is one fp32 accumulation.
-// Eight rounds of tiles on 256 compute units.  With equal experts two would do, but the launch waits for the tiles of the expert
-// with the most rows, whose contraction is as much longer as the expert is more popular than the average.  Whole call, ms, two
-// rounds / eight: E 64, d 1024, f 512 (512 tiles), Zipf popularity, 3000 / 6000 / 20 000 rows per expert on average 7.9 / 4.4, 12.3 / 6.2,
-// 42.0 / 21.4, equal experts 2.6 / 2.7, 4.7 / 4.9, 15.1 / 15.3; E 4, d 2048, f 1408 (192 tiles), Zipf, 40 000 rows 9.0 / 8.2.
-int bwd_split(int M, int E_loc, int d, int f) {
-    const long long tiles = (long long)E_loc * ((f + 255) / 256) * (d / 256);
-    int P = 1;
-    while (P < BWD_MAX_SPLIT && tiles * P < 8 * 256 && (long long)M / E_loc / (2 * P) >= 1024) P *= 2;
-    return P;
-}
+struct DwArgs {
+    const __bf16 *x, *dy;              // [M][d], rows listed (or in order)
+    const __bf16 *dgu, *h;             // [M][2 f], [M][f] in position order
+    const int32_t* list;
+    const int4* entries;               // [0].x = number; then per part of an expert's rows (position, rows, expert, part), (parts, first unit, 0, 0)
+    int* queues;
+    int* arrived;                      // [units] parts of the tile that are done (at the tile's first unit)
+    f32x4* part;                       // [units][256 * 256 / 4]
+    const unsigned char* zeros;
+    __bf16 *dwg, *dwu, *dwd;
+    int M, d, f;
+};
 
-// One workgroup.  Expert-major numbering of the schedule's rows (the weight gradients contract over all rows of an
-// expert, which lie in one group per slice): expert e owns columns k0_e .. k0_e + K_e - 1 of the transposed operands,
-// K_e = its row count padded as above; src_row[c] = schedule row behind column c, src_pos[c] = its position in the row
-// order of the plan (h, dg and du lie in that order), both -1 for padding.
-// The contraction of expert e is split into P parts ("virtual experts" v = e * P + p with partial results of their own):
-// etab[v] = (k0_e + p * K_e / P, K_e / P, v * f, 0).  Also clears the tile queue counters of the launches that follow.
+// One workgroup.  The order in which the weight gradients of the experts are worked on (most rows first) and the parts each is contracted
+// in: one, unless the work from this expert to the end is less than its own rows on every compute unit.  Then the number of parts
+// is the one with which that work takes the least time in rounds of equal units, a part costing `fix` rows to open and `split` rows to add up.
+// (Simulated lists of unequal and equal experts end 1.4 % after the best of 17 rules on average, unsplit ones 54 %.)
 __global__ __launch_bounds__(PLAN_THREADS)
-void bwd_prep_kernel(const int32_t* __restrict__ offsets, int S, int e_loc, int M, int listed, int f, int cols_cap, int P, int4* __restrict__ etab,
-                     int* __restrict__ src_row, int* __restrict__ src_pos, int* __restrict__ counters, int32_t* __restrict__ w_offsets) {
-    __shared__ int k0_of[MAX_GROUPS / 16], p0_of[MAX_GROUPS / 16 + 1];      // (e_loc <= 4096)
+void bwd_prep_kernel(const int* __restrict__ bases, int e_loc, int tiles, int cus, int cap, int4* __restrict__ entries, int* __restrict__ counters,
+                     int* __restrict__ arrived, unsigned int* __restrict__ zeros) {
+    __shared__ int rows_of[MAX_GROUPS / 16], parts_of[MAX_GROUPS / 16];
     const int tid = threadIdx.x;
-    for (int i = tid; i < cols_cap; i += PLAN_THREADS) src_row[i] = src_pos[i] = -1;
-    for (int i = tid; i < BWD_GEMMS * 8; i += PLAN_THREADS) counters[i] = 0;
-    for (int v = tid; v <= e_loc * P; v += PLAN_THREADS) w_offsets[v] = v * f;  // row groups of the weight gradients: f rows per part
+    for (int i = tid; i < BWD_COUNTERS; i += PLAN_THREADS) counters[i] = 0;
+    for (int i = tid; i < cap; i += PLAN_THREADS) arrived[i] = 0;
+    for (int i = tid; i < DW_ZEROS / 4; i += PLAN_THREADS) zeros[i] = 0;
+    for (int e = tid; e < e_loc; e += PLAN_THREADS) rows_of[e] = bases[e + 1] - bases[e];
+    __syncthreads();
+    auto before = [&](int j, int e) { return rows_of[j] > rows_of[e] || (rows_of[j] == rows_of[e] && j < e); };
     for (int e = tid; e < e_loc; e += PLAN_THREADS) {
-        int rows = 0, lo;
-        for (int sl = 0; sl < S; ++sl) rows = add_rows(rows, group_rows(offsets, sl * e_loc + e, M, lo), M);
-        p0_of[e] = rows;
+        const int rows = rows_of[e];
+        long long rest = 0;                                               // rows of this expert and of those after it
+        for (int j = 0; j < e_loc; ++j) rest += before(j, e) ? 0 : rows_of[j];
+        int best = 1;
+        if (rest * tiles < (long long)rows * cus && 2 * tiles <= cap) {
+            constexpr float fix = 100.f, split = 380.f;
+            float least = 0.f;
+            for (int P = 1; P <= DW_MAX_PARTS && P * tiles <= cap && (P == 1 || rows / P >= DW_PART_ROWS); ++P) {
+                const float unit = (float)((rows + P * 64 - 1) / (P * 64) * 64) + fix + (P > 1 ? split : 0.f);
+                const float t = ceilf((float)rest * (float)tiles * (float)P / ((float)rows * (float)cus) - 1e-3f) * unit;
+                if (P == 1 || t < least) { least = t; best = P; }
+            }
+        }
+        parts_of[e] = best;
     }
     __syncthreads();
+    for (int e = tid; e < e_loc; e += PLAN_THREADS) {
+        int at = 0, unit = 0, P = parts_of[e];
+        for (int j = 0; j < e_loc; ++j) {
+            if (!before(j, e)) continue;
+            at += parts_of[j];
+            unit += parts_of[j] > 1 ? parts_of[j] * tiles : 0;
+        }
+        const int slots = P;
+        if (P > 1 && unit + P * tiles > cap) P = 1;                       // (no room for its sums: one part, and the other entries are empty)
+        const int rows = rows_of[e], len = (rows + P * 64 - 1) / (P * 64) * 64;
+        for (int p = 0; p < slots; ++p) {
+            const int lo = min(p * len, rows);
+            entries[1 + 2 * (at + p)] = make_int4(bases[e] + lo, min(len, rows - lo), p < P ? e : -1, p);
+            entries[2 + 2 * (at + p)] = make_int4(P, unit, 0, 0);
+        }
+    }
     if (tid == 0) {
-        int run = 0, run_pos = listed ? 0 : first_row(offsets, M);           // (as in the plan)
-        for (int e = 0; e < e_loc; ++e) {
-            const int next_pos = add_rows(run_pos, p0_of[e], M), k = bwd_kpad(next_pos - run_pos, P), kp = k / P;
-            p0_of[e] = run_pos;
-            run_pos = next_pos;
-            for (int p = 0; p < P; ++p) etab[e * P + p] = make_int4(run + p * kp, kp, (e * P + p) * f, 0);
-            k0_of[e] = run;
-            run += k;
-        }
-        p0_of[e_loc] = run_pos;
-    }
-    __syncthreads();
-    // one wavefront per expert at a time walks its groups in slice order, as far as its positions go (all its rows, unless the
-    // offsets are malformed)
-    const int wave = tid >> 6, lane = tid & 63;
-    for (int e = wave; e < e_loc; e += PLAN_THREADS / 64) {
-        const int k0 = k0_of[e], p0 = p0_of[e], rows = p0_of[e + 1] - p0;
-        int at = 0;
-        for (int sl = 0; sl < S && at < rows; ++sl) {
-            int lo;
-            const int n = min(group_rows(offsets, sl * e_loc + e, M, lo), rows - at);
-            for (int r = lane; r < n; r += 64) { src_row[k0 + at + r] = lo + r; src_pos[k0 + at + r] = p0 + at + r; }
-            at += n;
-        }
+        int n = 0;
+        for (int e = 0; e < e_loc; ++e) n += parts_of[e];
+        entries[0] = make_int4(n, 0, 0, 0);
     }
 }
 
-// dst[c][col] (pitch ldd, c < C) = src[src_row[col]][c] (pitch lds_), zero where src_row[col] < 0: the rows of a
-// row-major operand become the K-contiguous columns of its transpose, in expert-major order.  HBM bound.  64 x 64 tiles
-// through LDS; both sides move 16 bytes per thread (C and lds_ are multiples of 8, cols and ldd of 64).
-__global__ __launch_bounds__(256)
-void bwd_gather_transpose_kernel(const __bf16* __restrict__ src, int lds_, int C, const int* __restrict__ src_row, int cols,
-                                 __bf16* __restrict__ dst, long long ldd) {
-    __shared__ unsigned short tile[64][72];                              // [feature][column], padded rows
-    const int col0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-    const int part = threadIdx.x & 7, line = threadIdx.x >> 3;           // 8 threads per 64-value line, 32 lines per pass
-    typedef unsigned short us8 __attribute__((ext_vector_type(8)));
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        const int r = line + 32 * p, col = col0 + r;
-        const int m = col < cols ? src_row[col] : -1;
-        us8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (m >= 0 && c0 + part * 8 < C) v = *reinterpret_cast<const us8*>(reinterpret_cast<const unsigned short*>(src) + (size_t)m * lds_ + c0 + part * 8);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) tile[part * 8 + k][r] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        const int c = c0 + line + 32 * p;
-        if (c < C && col0 + part * 8 < cols)
-            *reinterpret_cast<us8*>(reinterpret_cast<unsigned short*>(dst) + (size_t)c * ldd + col0 + part * 8) =
-                *reinterpret_cast<const us8*>(&tile[line + 32 * p][part * 8]);
-    }
-}
+template <bool LISTED, bool WIDE>
+__global__ __launch_bounds__(512, 1)
+void ffn_bwd_dw_kernel(DwArgs a) {
+    constexpr int ROWB = 512, OPERAND = 64 * ROWB, SLAB = 2 * OPERAND;    // bytes of a slab row, of an operand's slab, of both
+    constexpr int LPS = 8, NSTORE = 16;                                   // copies per wavefront and slab, stores per wavefront and tile
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    // next unit (entry, product, row tile, column tile; entry -1 = none).  Shares its bytes with wavefront 0's output staging: written by that wavefront
+    // after its read-out, read by all between the two barriers ahead of the next one.
+    int* const s_ticket = reinterpret_cast<int*>(smem + STAGE_OFF);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;                              // 4 x 2 wavefronts of 64 x 128
+    const int l31 = lane & 31, lhi = lane >> 5;
+    const int my_xcd = blockIdx.x & 7;
 
-// out[e][r] = sum over p of part[e * P + p][r] (n bf16 values per expert and part), added in fp32 in part order; 8 values per thread
-__global__ __launch_bounds__(256)
-void bwd_reduce_parts_kernel(const __bf16* __restrict__ part, int P, long long n, int E, __bf16* __restrict__ out) {
-    typedef __attribute__((ext_vector_type(8))) __bf16 b8;
-    const long long n8 = n / 8, total = n8 * E;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-        const long long e = i / n8, r = (i - e * n8) * 8;
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int p = 0; p < P; ++p) {
-            const b8 v = *reinterpret_cast<const b8*>(part + ((e * P + p) * n + r));
-#pragma unroll
-            for (int k = 0; k < 8; ++k) acc[k] += (float)v[k];
+    typedef const __attribute__((address_space(4))) int* scalar_ints;
+    auto fetch = [&]() __attribute__((always_inline)) {
+        int q = my_xcd, entry = -1, product = 0, r = 0, c = 0;
+        DwGrid gu, dn;                                                    // tiles of [dW_gate; dW_up] (2 f rows, d columns) and of dW_down (d rows, f columns)
+        gu.init(a.f / 128, a.d / 256);
+        dn.init(a.d / 256, (a.f + 255) / 256);
+        const int per = gu.chunks + dn.chunks, n_chunks = ((scalar_ints)a.entries)[0] * per;
+        for (int tries = 0; tries < 8;) {
+            const int k = atomicAdd(&a.queues[q], 1), chunk = (k >> 5) * 8 + q;
+            if (chunk >= n_chunks) { ++tries; q = (q + 1) & 7; continue; }
+            const int en = chunk / per, rem = chunk - en * per;
+            product = rem >= gu.chunks;
+            const bool tile = product ? dn.at(rem - gu.chunks, k & 31, r, c) : gu.at(rem, k & 31, r, c);
+            if (tile && ((scalar_ints)a.entries)[4 * (1 + 2 * __builtin_amdgcn_readfirstlane(en)) + 2] >= 0) { entry = en; break; }
         }
-        b8 o;
+        s_ticket[0] = entry; s_ticket[1] = product; s_ticket[2] = r; s_ticket[3] = c;
+    };
+    if (tid == 0) fetch();
+    __syncthreads();
+    if (s_ticket[0] < 0) return;
+
+    // ---- per-unit state.  "Plain" operand: dgu or h, rows in position order; "listed" operand: x or dy.  What only the read-out needs is
+    //      looked up again there (scalar registers are short).
+    int entry = 0, row_tile = 0, col_tile = 0, product = 0, pos0 = 0, rows = 0;
+    unsigned long long pbase = 0, lbase = 0;           // first row and first column of the plain operand, first column of the listed one
+    unsigned int lbytes = 0;                           // of the listed operand from there
+    // Byte offsets of the 16-byte pieces this lane copies: row 8 * wave + 2 * i + lhi of a slab, piece l31.  64-byte unit c of row r sits at position
+    // c ^ (r & 3), so that the four rows and two units that 32 lanes of a transposed read touch lie in different banks
+    unsigned int pvoff[4], lvoff[LISTED ? 2 : 4];
+    auto setup = [&]() __attribute__((always_inline)) {
+        entry = __builtin_amdgcn_readfirstlane(s_ticket[0]);
+        product = __builtin_amdgcn_readfirstlane(s_ticket[1]);
+        row_tile = __builtin_amdgcn_readfirstlane(s_ticket[2]); col_tile = __builtin_amdgcn_readfirstlane(s_ticket[3]);
+        const scalar_ints t = (scalar_ints)a.entries + 4 * (1 + 2 * entry);
+        pos0 = t[0]; rows = t[1];
+        const int pc = 256 * (product ? col_tile : row_tile), lc = 256 * (product ? row_tile : col_tile);
+        const unsigned int ppitch = (unsigned int)(product ? a.f : 2 * a.f) * 2u, lpitch = (unsigned int)a.d * 2u;
+        pbase = (unsigned long long)(product ? a.h : a.dgu) + (unsigned long long)(unsigned int)pos0 * ppitch + (unsigned int)pc * 2u;
+        lbase = (unsigned long long)(product ? a.dy : a.x) + (unsigned int)lc * 2u;
+        if (!LISTED) lbase += (unsigned long long)(unsigned int)pos0 * lpitch;
+        lbytes = (unsigned int)a.M * lpitch - (unsigned int)lc * 2u;      // (read where M * d * 2 < 2^32 only)
+        const bool half = product && pc + 128 >= a.f;                     // only the first 128 columns exist: the others repeat them and are not stored
 #pragma unroll
-        for (int k = 0; k < 8; ++k) o[k] = (__bf16)acc[k];
-        *reinterpret_cast<b8*>(out + (e * n + r)) = o;
+        for (int i = 0; i < 4; ++i) {
+            const int u = (l31 >> 2) ^ (2 * (i & 1) + lhi);
+            const unsigned int row = (unsigned int)(8 * wave + 2 * i + lhi);
+            pvoff[i] = row * ppitch + (unsigned int)((half ? u & 3 : u) * 64 + (l31 & 3) * 16);
+            if (!LISTED || i < 2) lvoff[i] = (LISTED ? 0u : row * lpitch) + (unsigned int)(u * 64 + (l31 & 3) * 16);
+        }
+    };
+    int lr[8];                                                            // rows of the listed operand that this wavefront copies next
+    auto list_rows = [&](int s) __attribute__((always_inline)) {
+        if constexpr (LISTED) {
+            const scalar_ints l = (scalar_ints)a.list + __builtin_amdgcn_readfirstlane(pos0 + min(s * 64 + 8 * wave, rows));   // (the list goes on for LIST_PAD entries)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) lr[k] = l[k];
+        }
+    };
+    // Copies are written out: the compiler would hold every transposed read of LDS until all copies in flight have landed.  (No register
+    // is written; the waits that cover the copies are wait_vmcnt's.)
+    auto copy = [&](unsigned long long base, unsigned int bytes, unsigned int voff, int to) __attribute__((always_inline)) {
+        const u32x4 rs = {(unsigned int)base, (unsigned int)(base >> 32), bytes, 0x00020000u};
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(voff), "s"(rs) : "memory");
+    };
+    auto slab_bytes = [&](int s, unsigned int pitch) __attribute__((always_inline)) -> unsigned int {       // rows past the end: zeros are deposited
+        const int left = min(rows - s * 64, 64);
+        return left > 0 ? (unsigned int)(left - 1) * pitch + 512u : 0u;
+    };
+    const int lds0 = (int)(unsigned int)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)smem + wave * (8 * ROWB);
+    auto copy_plain = [&](int s, int buf, int i) __attribute__((always_inline)) {
+        const unsigned int pitch = (unsigned int)(product ? a.f : 2 * a.f) * 2u;
+        copy(pbase + (unsigned long long)(unsigned int)(s * 64) * pitch, slab_bytes(s, pitch), pvoff[i], lds0 + buf * SLAB + 2 * i * ROWB);
+    };
+    auto copy_listed = [&](int s, int buf, int i) __attribute__((always_inline)) {
+        const unsigned int pitch = (unsigned int)a.d * 2u;
+        const int to = lds0 + buf * SLAB + OPERAND + 2 * i * ROWB;
+        if constexpr (!LISTED) {
+            copy(lbase + (unsigned long long)(unsigned int)(s * 64) * pitch, slab_bytes(s, pitch), lvoff[i], to);
+        } else {
+            const unsigned int row = (unsigned int)(lhi ? lr[2 * i + 1] : lr[2 * i]);
+            const bool live = s * 64 + 8 * wave + 2 * i + lhi < rows;
+            if constexpr (WIDE) {
+                const unsigned char* const from = live ? (const unsigned char*)lbase + (unsigned long long)row * pitch + lvoff[i & 1] : a.zeros + l31 * 16;
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory");
+            } else {
+                copy(lbase, lbytes, live ? row * pitch + lvoff[i & 1] : 0xFFFFFF00u, to);
+            }
+        }
+    };
+    auto prologue = [&]() __attribute__((always_inline)) {                // slabs 0 and 1 (past the end: zeros, from no memory)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            list_rows(s);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) copy_plain(s, s, i);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) copy_listed(s, s, i);
+        }
+        list_rows(2);
+    };
+    // fragment of 32 columns x 16 rows: two transposed reads of 4 rows each; lane -> rows 8 * lhi + 4 * j + (lane & 15) / 4, columns
+    // 16 * (lane / 16 & 1) + 4 * (lane & 3) of the block
+    const int frag = (8 * lhi + ((lane & 15) >> 2)) * ROWB + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    const int sw = (lane >> 2) & 3;
+    int foff[6];                                                          // 4 column blocks of the n operand, 2 of the m operand
+#pragma unroll
+    for (int q = 0; q < 4; ++q) foff[q] = frag + (((wn * 4 + q) ^ sw) << 6);
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) foff[4 + mb] = frag + (((wm * 2 + mb) ^ sw) << 6);
+
+    bool counted = false;
+    setup();
+    prologue();
+    while (true) {
+        f32x16 acc[2][4];
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[mb][q][v] = 0.f;
+        // issued so far, oldest first: slab 0, slab 1, the output of the unit before
+        if (counted) wait_vmcnt<LPS + NSTORE>(); else wait_vmcnt<LPS>();
+        lds_barrier();
+        const int n_area = product ? 0 : OPERAND, m_area = OPERAND - n_area, NS = (rows + 63) >> 6;
+        auto load_frag = [&](bf16x8& to, int i, int buf, int u) __attribute__((always_inline)) {
+            typedef __attribute__((address_space(3))) bf16x4* lds4;
+            unsigned char* const at = smem + foff[i] + buf * SLAB + (i < 4 ? n_area : m_area) + u * 16 * ROWB;
+            const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4)at), hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds4)(at + 4 * ROWB));
+            to = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        };
+        bf16x8 frags[2][6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) load_frag(frags[0][i], i, 0, 0);
+        // Slab s.  The barrier ahead of its last K step publishes slab s + 1 and frees its own buffer, into which the plain operand of slab s + 2
+        // (NEW) is copied at once; the listed operand follows in the first K step of the next slab (OLD: slab s + 1's half is due here).
+        auto slab = [&](int s, auto new_tag, auto old_tag, auto final_tag) __attribute__((always_inline)) {
+            constexpr bool NEW = decltype(new_tag)::value, OLD = decltype(old_tag)::value, FINAL = decltype(final_tag)::value;
+            const int buf = s & 1;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int cur = u & 1, nxt = cur ^ 1;
+                const bool last = u == 3, reads = !(last && FINAL);
+                if (last && !FINAL) { wait_vmcnt<0>(); lds_barrier(); }
+                const int rbuf = last ? buf ^ 1 : buf, ru = last ? 0 : u + 1;
+                const bool copies = last ? NEW : (OLD && u == 0);
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    if (reads) load_frag(frags[nxt][i], i, rbuf, ru);
+                    if (copies && i < 4) { if (last) copy_plain(s + 2, buf, i); else copy_listed(s + 1, buf ^ 1, i); }
+                }
+                if (OLD && u == 0) list_rows(s + 2);
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        acc[mb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frags[cur][q], frags[cur][4 + mb], acc[mb][q], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     // MFMA
+                    if (reads && i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);                 // LDS reads
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        {
+            const std::true_type T{};
+            const std::false_type F{};
+            const int draw = max(NS - 5, 0);                              // (late: the longest contractions come first, and a unit drawn early waits for its holder)
+            if (draw == 0 && tid == 0) fetch();
+            if (NS > 2)       slab(0, T, F, F);
+            else if (NS == 2) slab(0, F, F, F);
+            int s = 1;
+            for (; s + 2 < NS; ++s) {
+                if (s == draw && tid == 0) fetch();
+                slab(s, T, T, F);
+            }
+            if (NS > 2) slab(NS - 2, F, T, F);
+            if (NS > 0) slab(NS - 1, F, F, T);
+        }
+        lds_barrier();                   // every fragment is in registers: both buffers are free; the next ticket is visible
+        const int eentry = entry, erow = row_tile, ecol = col_tile, eproduct = product;
+        const bool more = __builtin_amdgcn_readfirstlane(s_ticket[0]) >= 0;
+        if (more) { setup(); prologue(); }                                // the next unit's first slabs fly during the read-out
+        lds_barrier();                   // the ticket has been read: its bytes may stage output
+
+        // ---- a part: its sums go to memory where every die sees them; the workgroup that finds the others there adds them up, in part order
+        const scalar_ints t = (scalar_ints)a.entries + 4 * (1 + 2 * eentry);
+        const int ee = t[2], epart = t[3], eparts = t[4];
+        bool store = true;
+        counted = false;
+        if (eparts > 1) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)a.part, 0, 0xFFFFFFFF, 0x00020000);
+            const int eunit = t[5] + (eproduct ? a.f / 128 * (a.d / 256) + erow * ((a.f + 255) / 256) + ecol : erow * (a.d / 256) + ecol) * eparts;
+            const unsigned int first = (unsigned int)eunit * (unsigned int)DW_UNIT_BYTES + (unsigned int)wave * 32768u;
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const f32x4 v = {acc[mb][q][g * 4], acc[mb][q][g * 4 + 1], acc[mb][q][g * 4 + 2], acc[mb][q][g * 4 + 3]};
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, lane * 16,
+                                                               first + (unsigned int)epart * (unsigned int)DW_UNIT_BYTES + (unsigned int)((mb * 4 + q) * 4 + g) * 1024u, DEVICE_SCOPE);
+                    }
+            wait_vmcnt<0>();
+            lds_barrier();
+            if (tid == 0) s_ticket[0] = __hip_atomic_fetch_add(&a.arrived[eunit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            lds_barrier();
+            store = __builtin_amdgcn_readfirstlane(s_ticket[0]) == eparts - 1;
+            lds_barrier();
+            if (store) {
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        f32x16 sum;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) sum[v] = 0.f;
+                        for (int p = 0; p < eparts; ++p) {
+#pragma unroll
+                            for (int g = 0; g < 4; ++g) {
+                                const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16,
+                                                    first + (unsigned int)p * (unsigned int)DW_UNIT_BYTES + (unsigned int)((mb * 4 + q) * 4 + g) * 1024u, DEVICE_SCOPE));
+#pragma unroll
+                                for (int k = 0; k < 4; ++k) sum[g * 4 + k] += v[k];
+                            }
+                        }
+                        acc[mb][q] = sum;
+                    }
+            }
+        }
+        if (store) {
+            // acc[mb][q][v]: row l31 of row block mb, column 8 * (v >> 2) + 4 * lhi + (v & 3) of column block q: 32 rows x 64 columns at a time
+            // through a private staging area, so that whole cache lines are stored
+            int lane_e = lane;
+            asm volatile("" : "+v"(lane_e));                              // (address arithmetic stays here)
+            const int el31 = lane_e & 31, elhi = lane_e >> 5, sr = lane_e >> 3, sc = lane_e & 7;
+            auto swz = [](int r) { return (r >> 1) & 7; };
+            unsigned char* const stage = smem + STAGE_OFF + wave * STAGE_WAVE;
+            unsigned char* const wr = stage + el31 * 128 + elhi * 8;
+            const int row = erow * 256 + wm * 64, col = ecol * 256 + wn * 128;
+            __bf16* out;
+            if (eproduct)       out = a.dwd + ((size_t)ee * a.d + row) * a.f + col;
+            else if (row < a.f) out = a.dwg + ((size_t)ee * a.f + row) * a.d + col;       // (f is a multiple of 128: a wavefront's rows are all of one matrix)
+            else                out = a.dwu + ((size_t)ee * a.f + row - a.f) * a.d + col;
+            const int pitch = (eproduct ? a.f : a.d) * 2;
+            const unsigned long long ob = (unsigned long long)out;
+            const unsigned int ob_lo = (unsigned int)__builtin_amdgcn_readfirstlane((unsigned int)ob);
+            const unsigned int ob_hi = (unsigned int)__builtin_amdgcn_readfirstlane((unsigned int)(ob >> 32));
+            const bool exists = !eproduct || col < a.f;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(((unsigned long long)ob_hi << 32) | ob_lo), 0,
+                                                                                __builtin_amdgcn_readfirstlane(exists ? 64 * pitch : 0), 0x00020000);
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+#pragma unroll
+                for (int hq = 0; hq < 2; ++hq) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)
+                            *reinterpret_cast<u32x2*>(wr + (((q * 4 + g) ^ swz(el31)) << 4)) =
+                                pack4(acc[mb][hq * 2 + q][g * 4], acc[mb][hq * 2 + q][g * 4 + 1], acc[mb][hq * 2 + q][g * 4 + 2], acc[mb][hq * 2 + q][g * 4 + 3]);
+                    u32x4 v[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const u32x4*>(stage + (i * 8 + sr) * 128 + ((sc ^ swz(i * 8 + sr)) << 4));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) __builtin_amdgcn_raw_buffer_store_b128(v[i], rs, (mb * 32 + i * 8 + sr) * pitch + hq * 128 + sc * 16, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            counted = eparts == 1;
+        }
+        if (!more) break;
     }
 }
 
@@ -1859,44 +2127,49 @@ void bwd_transpose_kernel(const __bf16* __restrict__ src, int R, int C, int Cpad
     }
 }
 
+template <bool LISTED, bool WIDE>
+moe_status launch_dw(const DwArgs& a, long long most_units, hipStream_t s) {
+    static moe::DeviceOnce attr;
+    auto kern = ffn_bwd_dw_kernel<LISTED, WIDE>;
+    int dev;
+    if (attr.needed(dev)) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ADAPTIVE_LDS);
+        if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
+        attr.mark(dev);
+    }
+    moe::LaunchScope k("ffn_bwd_dw_kernel", s);
+    hipLaunchKernelGGL(kern, dim3((int)std::min<long long>(most_units, num_cus())), dim3(512), ADAPTIVE_LDS, s, a);
+    return k.done();
+}
+
 inline size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct BwdLayout {                              // byte offsets into the workspace of a backward call
-    size_t plan_rows, ready_rows, plan_w, ready_w, list, ebase, counters, etab, w_offsets, src_row, src_pos, wdt, wgut, dh, dgu, h, tx, tdy, th, tdg, tdu, dwdt, part, total;
-    int f_pad, cols_cap, P;
+    size_t plan_rows, ready_rows, list, ebase, bases, counters, entries, arrived, zeros, wdt, wgut, dh, dgu, h, part, total;
+    int f_pad, units;                           // units: places for partial sums that the weight gradients would use; a call runs with fewer too
 };
 BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
     BwdLayout L;
     L.f_pad = (f + 255) / 256 * 256;
-    L.P = bwd_split(M, E_loc, d, f);
-    L.cols_cap = (M + BWD_KPAD - 1) / BWD_KPAD * BWD_KPAD + BWD_KMIN * L.P * E_loc;
-    const int wrows = E_loc * L.P * f;
+    L.units = (int)std::min<long long>(DW_MAX_UNITS, M < 2 * DW_PART_ROWS ? 0 : (long long)M / DW_PART_ROWS * dw_tiles(d, f));
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += al256(bytes); return at; };
     L.plan_rows = take((size_t)(plan_capacity(M) + PLAN_HDR) * sizeof(int4));
     L.ready_rows = take((size_t)plan_capacity(M) * sizeof(int));
-    L.plan_w = take((size_t)(plan_capacity(wrows) + PLAN_HDR) * sizeof(int4));
-    L.ready_w = take((size_t)plan_capacity(wrows) * sizeof(int));
     L.list = take(list_bytes(M));
     L.ebase = take(EBASE_BYTES);
-    L.counters = take((size_t)BWD_GEMMS * 8 * sizeof(int));
-    L.etab = take((size_t)E_loc * L.P * sizeof(int4));
-    L.w_offsets = take((size_t)(E_loc * L.P + 1) * sizeof(int32_t));
-    L.src_row = take((size_t)L.cols_cap * sizeof(int));
-    L.src_pos = take((size_t)L.cols_cap * sizeof(int));
+    L.bases = take((size_t)(E_loc + 1) * sizeof(int));
+    L.counters = take((size_t)BWD_COUNTERS * sizeof(int));
+    L.entries = take(((size_t)1 + 2 * ((size_t)E_loc + DW_MAX_UNITS)) * sizeof(int4));
+    L.arrived = take((size_t)DW_MAX_UNITS * sizeof(int));
+    L.zeros = take(DW_ZEROS);
     L.wdt = take((size_t)E_loc * L.f_pad * d * 2);
     L.wgut = take((size_t)E_loc * d * 2 * f * 2);
     L.dh = take((size_t)M * L.f_pad * 2);
     L.dgu = take((size_t)M * 2 * f * 2);
     L.h = take((size_t)M * f * 2);
-    L.tx = take((size_t)d * L.cols_cap * 2);
-    L.tdy = take((size_t)d * L.cols_cap * 2);
-    L.th = take((size_t)f * L.cols_cap * 2);
-    L.tdg = take((size_t)f * L.cols_cap * 2);
-    L.tdu = take((size_t)f * L.cols_cap * 2);
-    L.dwdt = take((size_t)E_loc * f * d * 2);
-    L.part = take(L.P > 1 ? (size_t)E_loc * L.P * f * d * 2 : 0);
-    L.total = o;
+    L.part = o;                                  // (last: what the workspace has beyond it)
+    L.total = o + (size_t)L.units * DW_UNIT_BYTES;
     return L;
 }
 
@@ -2017,14 +2290,13 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     a.g2.K = f; a.g2.NU = d / 256;
     const bool off32 = (unsigned long long)M * d * 2 < 0xFFFFFF00ull;       // x and y addressed with 32-bit offsets
     a.g2.o_bytes = off32 ? (unsigned int)M * (unsigned int)d * 2u : 0u;
-    a.g2.etab = nullptr;
     a.g2.queues = (int*)(plan + 3);
     a.dh = nullptr; a.lddh = 0; a.dgu = nullptr;
     a.panel1 = panel_width(f / 128, (size_t)2 * d * f * 2, (size_t)256 * d * 2);
     a.panel2 = panel_width(d / 256, (size_t)d * f * 2, (size_t)256 * f * 2);
     if (const int forced = g_force_panel.load(std::memory_order_relaxed)) a.panel1 = a.panel2 = forced;
     const PlanArgs plan_args = {offsets, S, E_loc, M, bm, plan_capacity(M), plan, a.ready, row_map, row_gate, listed ? list : nullptr,
-                                row_gate ? gate : nullptr, ebase};
+                                row_gate ? gate : nullptr, ebase, nullptr};
     moe_status st = launch_plan(plan_args, s);
     if (st != MOE_OK) return st;
     const long long max_blocks = M / bm + E_loc;
@@ -2063,28 +2335,20 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     if (!w_gate || !w_up || !w_down || !dw_gate || !dw_up || !dw_down) return MOE_ERR_INVALID_ARG;
     if (d % 256 != 0 || f % 128 != 0 || f < 256) return MOE_ERR_UNSUPPORTED_SHAPE;
     const long long G = (long long)S * E_loc;
-    if (G > MAX_GROUPS || E_loc > MAX_GROUPS / 16 || (long long)E_loc * BWD_MAX_SPLIT * f >= (1LL << 31)) return MOE_ERR_UNSUPPORTED_SHAPE;
+    if (G > MAX_GROUPS || E_loc > MAX_GROUPS / 16 || (long long)E_loc * f >= (1LL << 27) || M + 256LL * E_loc >= (1LL << 22)) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (d > (1 << 22) || f > (1 << 21) || (long long)d * f >= (1LL << 30)) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (M > 0 && (!x || !dy || !dx)) return MOE_ERR_INVALID_ARG;
     if ((((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx | (uintptr_t)w_gate | (uintptr_t)w_up | (uintptr_t)w_down | (uintptr_t)dw_gate |
           (uintptr_t)dw_up | (uintptr_t)dw_down | (uintptr_t)workspace) & 15) != 0)
         return MOE_ERR_INVALID_ARG;
     const BwdLayout L = bwd_layout(M, E_loc, d, f);
-    // 32-bit byte offsets inside one 256-row tile of the transposed operands (row pitch = cols_cap)
-    if ((long long)L.cols_cap * 512 * 2 >= (1LL << 32)) return MOE_ERR_UNSUPPORTED_SHAPE;
-    if (!workspace || workspace_bytes < L.total) return MOE_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < L.part) return MOE_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     int4* plan_rows = (int4*)(ws + L.plan_rows);
-    int4* plan_w = (int4*)(ws + L.plan_w);
     int* counters = (int*)(ws + L.counters);
-    int4* etab = (int4*)(ws + L.etab);
-    int *src_row = (int*)(ws + L.src_row), *src_pos = (int*)(ws + L.src_pos);
     __bf16 *wdt = (__bf16*)(ws + L.wdt), *wgut = (__bf16*)(ws + L.wgut), *dh = (__bf16*)(ws + L.dh), *dgu = (__bf16*)(ws + L.dgu);
-    __bf16 *h = (__bf16*)(ws + L.h), *tx = (__bf16*)(ws + L.tx), *tdy = (__bf16*)(ws + L.tdy), *th = (__bf16*)(ws + L.th);
-    __bf16 *tdg = (__bf16*)(ws + L.tdg), *tdu = (__bf16*)(ws + L.tdu), *dwdt = (__bf16*)(ws + L.dwdt);
-    __bf16* part = (__bf16*)(ws + L.part);
-    const int P = L.P, wrows = E_loc * P * f;
+    __bf16* h = (__bf16*)(ws + L.h);
     moe_status st;
 
     if (M == 0 || G == 0) {
@@ -2095,17 +2359,18 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
         return k.done();
     }
 
-    // ---- plans (row blocks of the schedule; row blocks of the weight gradients: one group of f rows per expert),
-    //      expert-major column numbering, transposed weights
+    // ---- row blocks of the schedule, order and parts of the weight gradients, transposed weights
     const bool listed = S > 1 && E_loc > 1;      // else the rows already lie expert by expert
     int32_t* list = listed ? (int32_t*)(ws + L.list) : nullptr;
-    int* ebase = (int*)(ws + L.ebase);
-    const PlanArgs rows_plan = {offsets, S, E_loc, M, 256, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr, ebase};
+    int* bases = (int*)(ws + L.bases);
+    const PlanArgs rows_plan = {offsets, S, E_loc, M, 256, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr,
+                                (int*)(ws + L.ebase), bases};
     if ((st = launch_plan(rows_plan, s)) != MOE_OK) return st;
+    const int tiles = dw_tiles(d, f), units = (int)std::min<size_t>(L.units, (workspace_bytes - L.part) / DW_UNIT_BYTES);
     {
         moe::LaunchScope k("bwd_prep_kernel", s);
-        hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, offsets, S, E_loc, M, (int)listed, f, L.cols_cap, P, etab, src_row, src_pos, counters,
-                           (int32_t*)(ws + L.w_offsets));
+        hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, bases, E_loc, tiles, num_cus(), units, (int4*)(ws + L.entries), counters,
+                           (int*)(ws + L.arrived), (unsigned int*)(ws + L.zeros));
         if ((st = k.done()) != MOE_OK) return st;
     }
     {
@@ -2133,7 +2398,6 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.panel1 = a.panel2 = 1 << 20;
     a.dh = dh; a.lddh = L.f_pad; a.dgu = dgu;
     a.queues1 = counters + 8;
-    a.g2.etab = nullptr;
     // Workgroups of the kernels over rows: two per tile (see launch_gemm), but one on every compute unit where a tile is long
     // (K >= 4096), since what the idle ones cost the queues, some 8 us, does not count there.  Whole call, us, one per tile / two per
     // tile / every unit: E 1, d 4096, f 14336, 3000 rows 3970 / 3365 / 3365, 700 rows 2190 / 2050 / 1695; E 1, d 2048, f 1408, 700 rows 395 /
@@ -2169,42 +2433,17 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
                  : launch_adaptive<2, ROWS_PLAIN, ROWS_LIST64>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel");
     if (st != MOE_OK) return st;
 
-    // ---- transposed, expert-major copies of the operands of the weight gradients
-    {
-        moe::LaunchScope k("bwd_gather_transpose_kernel", s);
-        const int cb = (L.cols_cap + 63) / 64;
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (d + 63) / 64), dim3(256), 0, s, (const __bf16*)x, d, d, src_row, L.cols_cap, tx, (long long)L.cols_cap);
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (d + 63) / 64), dim3(256), 0, s, (const __bf16*)dy, d, d, src_row, L.cols_cap, tdy, (long long)L.cols_cap);
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)h, f, f, src_pos, L.cols_cap, th, (long long)L.cols_cap);
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)dgu, 2 * f, f, src_pos, L.cols_cap, tdg, (long long)L.cols_cap);
-        hipLaunchKernelGGL(bwd_gather_transpose_kernel, dim3(cb, (f + 63) / 64), dim3(256), 0, s, (const __bf16*)dgu + f, 2 * f, f, src_pos, L.cols_cap, tdu, (long long)L.cols_cap);
-        if ((st = k.done()) != MOE_OK) return st;
-    }
-    // ---- weight gradients: one group of f rows per expert, K = the expert's (padded) row count
-    const PlanArgs w_plan = {(const int32_t*)(ws + L.w_offsets), 1, E_loc * P, wrows, 256, plan_capacity(wrows), plan_w, (int*)(ws + L.ready_w),
-                             nullptr, nullptr, nullptr, nullptr, ebase};
-    if ((st = launch_plan(w_plan, s)) != MOE_OK) return st;
-    a.plan = plan_w;
-    a.g2.etab = etab;
-    a.g2.lda = L.cols_cap; a.g2.ldb = L.cols_cap; a.g2.strideB = 0;
-    a.g2.ldo = d; a.g2.K = BWD_KMIN; a.g2.NU = d / 256;
-    const long long w_blocks = wrows / 256 + E_loc * P;
-    struct { const __bf16 *A, *B; __bf16* O; int q; const char* name; } wg[3] = {
-        {tdg, tx, (__bf16*)dw_gate, 24, "ffn_bwd_dwg_kernel"}, {tdu, tx, (__bf16*)dw_up, 32, "ffn_bwd_dwu_kernel"}, {th, tdy, dwdt, 40, "ffn_bwd_dwd_kernel"}};
-    for (int i = 0; i < 3; ++i) {
-        a.g2.A = wg[i].A; a.g2.B = wg[i].B; a.g2.O = P > 1 ? part : wg[i].O; a.g2.queues = counters + wg[i].q;
-        if ((st = launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, w_blocks * a.g2.NU, s, wg[i].name)) != MOE_OK) return st;
-        if (P > 1) {                                                     // partial sums of the P parts -> the gradient
-            moe::LaunchScope k("bwd_reduce_parts_kernel", s);
-            const long long n = (long long)f * d;
-            const int blocks = (int)std::min<long long>((n / 8 * E_loc + 255) / 256, 8LL * num_cus());
-            hipLaunchKernelGGL(bwd_reduce_parts_kernel, dim3(blocks), dim3(256), 0, s, part, P, n, E_loc, wg[i].O);
-            if ((st = k.done()) != MOE_OK) return st;
-        }
-    }
-    // dWd^T [E][f][d] -> dw_down [E][d][f]
-    moe::LaunchScope k("bwd_transpose_kernel", s);
-    hipLaunchKernelGGL(bwd_transpose_kernel, dim3((f + 63) / 64, (d + 63) / 64, E_loc), dim3(256), 0, s, dwdt, f, d, d, (__bf16*)dw_down,
-                       (long long)f, (long long)d * f, 0);
-    return k.done();
+    // ---- weight gradients
+    DwArgs w;
+    w.x = (const __bf16*)x; w.dy = (const __bf16*)dy; w.dgu = dgu; w.h = h;
+    w.list = list;
+    w.entries = (const int4*)(ws + L.entries);
+    w.queues = counters + DW_QUEUES;
+    w.arrived = (int*)(ws + L.arrived);
+    w.part = (f32x4*)(ws + L.part);
+    w.zeros = (const unsigned char*)(ws + L.zeros);
+    w.dwg = (__bf16*)dw_gate; w.dwu = (__bf16*)dw_up; w.dwd = (__bf16*)dw_down;
+    w.M = M; w.d = d; w.f = f;
+    const long long most = (long long)E_loc * tiles + units;
+    return !listed ? launch_dw<false, false>(w, most, s) : off32 ? launch_dw<true, false>(w, most, s) : launch_dw<true, true>(w, most, s);
 }

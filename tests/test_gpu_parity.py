@@ -1012,6 +1012,41 @@ def test_ffn_backward_rows_addressed_with_64_bits(lib):
             check(out[k][e], ref, "%s[%d]" % (k, e))
 
 
+@pytest.mark.parametrize("f,S,sizes", [
+    (256, 1, [64]), (384, 1, [129]),                                     # one expert: whole slabs, a remainder; rows in order
+    (384, 2, [0, 1, 63, 64, 65, 127, 128, 192]),                         # slabs of 64 rows and their remainders, one slab, two, three; listed rows
+    (256, 3, [1536, 200, 1600]), (640, 1, [1535, 5]), (256, 2, [40000])])    # the last experts split over parts with a remainder, or just not
+def test_ffn_backward_weight_gradient_slabs(lib, f, S, sizes):
+    """Ends of the contraction over an expert's rows, and rows that belong to other experts and hold infinities: they must not be touched, not
+    even multiplied by zero."""
+    say("ffn backward weight gradient slabs", f, S, sizes)
+    d, E_loc = 256, len(sizes)
+    W = workloads.ffn_weights(E_loc, d, f, seed=f + S)
+    w = upload_weights(W)
+    parts = np.array([[n // S + (s < n % S) for n in sizes] for s in range(S)])
+    off = np.concatenate([[0], np.cumsum(parts.ravel())]).astype(np.int32)
+    M = int(off[-1])
+    x, dy = workloads.activations(M, d, seed=f + 1), workloads.activations(M, d, seed=f + 2)
+    ref = oracle.expert_ffn_backward_sliced(x, dy, off, E_loc, W)[1:]
+    bad = E_loc // 2 if E_loc > 1 else -1                             # this expert's rows
+    xd, dyd = dev_bf16(x), dev_bf16(dy)
+    for s in range(S):
+        if bad >= 0:
+            xd[off[s * E_loc + bad]:off[s * E_loc + bad + 1]] = float("inf")
+            dyd[off[s * E_loc + bad]:off[s * E_loc + bad + 1]] = float("inf")
+    out = lib.moe_expert_ffn_backward_sliced(xd, dyd, dev(off), S, E_loc, w["w_gate"], w["w_up"], w["w_down"])
+    torch.cuda.synchronize()
+    for name, want in zip(("dw_gate", "dw_up", "dw_down"), ref):
+        got = oracle.decode_bf16(host_bf16_bits(out[name]))
+        for e in range(E_loc):
+            if e == bad:
+                continue
+            if sizes[e] == 0:
+                assert not got[e].any(), (name, e)
+            else:
+                check_ffn_error(float(np.abs(got[e] - want[e]).max() / np.abs(want[e]).max()), "bf16", "%s[%d] of %s" % (name, e, sizes))
+
+
 def test_ffn_backward_edge_cases(lib):
     say("ffn backward edge cases")
     # an expert without rows (zero weight gradients), a single row, no rows at all
