@@ -429,8 +429,8 @@ def moe_probe_mfma_bf16(data: int, iters: int, workgroups: int, sink=None):
 
 
 def moe_ffn_tile_override(tile_rows: int = 0, kernels: int = 0, panel_groups: int = 0):
-    """Test / measurement hook: pin the row-block height (64, 128, 256; 0 = automatic), the kernel family (1 = fixed
-    shape, 2 = adaptive shape with one launch per phase) and / or the panel width of the tile walk for the following
+    """Test / measurement hook: pin the row-block height (64, 128, 256; 0 = automatic), the kernel family (1 = tiles of
+    128 columns instead of 256 x 256, 2 = 256 x 256 tiles with one launch per phase) and / or the panel width of the tile walk for the following
     FFN calls of this process.  Call with no arguments to restore the defaults."""
     _check(load().moe_ffn_tile_override(int(tile_rows), int(kernels), int(panel_groups)), "moe_ffn_tile_override")
 

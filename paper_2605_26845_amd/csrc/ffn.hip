@@ -3,17 +3,15 @@
 // decompositions pay, so all slices are issued by launches whose number does not depend on the
 // number of matchings).
 //
-// Two grouped GEMMs on the bf16 MFMA units, persistent kernels looping over output tiles (for bf16 weights and 256-row
-// blocks both run in one launch, phase-2 tiles waiting for the rows of H they read):
-//   phase 1:  H = silu(X Wg^T) * (X Wu^T)     tile = BM rows x (128 gate + 128 up) columns
-//   phase 2:  Y = H Wd^T                      tile = BM rows x 256 columns
+// Two grouped GEMMs on the bf16 MFMA units:
+//   phase 1:  H = silu(X Wg^T) * (X Wu^T)
+//   phase 2:  Y = H Wd^T
 // A tile holds rows of one expert (of any slices, see FfnArgs).  Both operands are K-contiguous, are copied
-// global -> LDS in K slabs (2 to 4 in flight, XOR-swizzled 16-byte chunks; fp8 weights pass through
-// registers to be dequantised) and read back as 16-byte MFMA fragments.  The weights feed the MFMA
-// "A" port so that each lane ends up with 4 consecutive output columns of one row and can store
-// 8 bytes at a time.  bf16 schedules with large groups run the adaptive-shape kernels (ffn_fused_kernel /
-// ffn_adaptive_kernel), the others (and fp8 weights) the fixed-shape ffn_gemm_kernel; few rows per expert, and small calls,
-// run ffn_skinny_kernel, which streams the weights.
+// global -> LDS in K slabs (2 to 4 in flight, XOR-swizzled 16-byte chunks) and read back as 16-byte MFMA fragments.
+// The weights feed the MFMA "A" port so that each lane ends up with 4 consecutive output columns of one row.
+// From the fewest rows per expert to the most (route() chooses): ffn_skinny_kernel streams the weights; ffn_tile_kernel works in tiles of 64, 128 or 256
+// rows by 128 columns and splits contractions that would leave the chip idle; ffn_fused_kernel (bf16) runs both phases in one persistent
+// launch over tiles of 256 x 256, phase-2 tiles waiting for the rows of H they read (ffn_adaptive_kernel: one launch per phase).
 // moe_expert_ffn_backward_sliced (the backward pass: the exchange of Section 2.1 repeated for the gradients) runs the
 // same adaptive-shape kernels on other operands.
 #include "common.hpp"
@@ -34,6 +32,7 @@ constexpr int PLAN_THREADS = 1024;
 constexpr int MAX_GROUPS = 65536;
 constexpr int PLAN_EXPERTS_LDS = 2048; // row bases of the experts kept in LDS by the plan kernel (more: in the workspace)
 constexpr int LIST_PAD = 256;          // valid entries behind the last row of the row list (a row block may read past its end)
+constexpr int TILE_COUNTERS = 512;     // counters per phase of the parts of split contractions (see ffn_tile_kernel; a split call has fewer tiles)
 constexpr int PLAN_HDR = 5;            // plan[0] = (row blocks, 0, 0, 0); plan[1..2] / plan[3..4] = tile queue counters of phase 1 / 2
 
 struct FfnArgs {
@@ -43,7 +42,7 @@ struct FfnArgs {
     const void *wg, *wu, *wd;          // bf16 or fp8 codes
     const float *sg, *su, *sd;         // block scales (fp8) or null
     int4* plan;                        // plan[0].x = number of row blocks; plan[PLAN_HDR + i] = (row0, row_end, expert, class)
-    int d, f;
+    int M, d, f;
     // Rows are worked on expert by expert, an expert's rows of all slices side by side ("positions" 0 .. M-1): what a
     // row becomes depends on its expert and not on its slice, so a schedule of many small slices costs no more tiles, and
     // reads the weights no more often, than one big slice.  36 833 rows of 4 experts, d = 2048, f = 1408: 228 slices
@@ -250,9 +249,83 @@ void ffn_plan_kernel(PlanArgs a) {
             a.plan[PLAN_HDR + at_partial] = make_int4(row, hi, e, hi - row > 128 ? 0 : 1);
         }
     }
-    for (int i = tid; i < min(run_full, a.cap); i += PLAN_THREADS) a.ready[i] = 0;      // per row block: column units of h complete
+    // per row block: column units of h complete (fused kernel); per tile of a split contraction: parts that are done (tile kernel)
+    for (int i = tid; i < min(max(run_full, 2 * TILE_COUNTERS), a.cap); i += PLAN_THREADS) a.ready[i] = 0;
     if (tid == 0) a.plan[0] = make_int4(min(run_full, a.cap), 0, 0, 0);
     if (tid >= 1 && tid < PLAN_HDR) a.plan[tid] = make_int4(0, 0, 0, 0);    // tile queue counters
+}
+
+// The same plan for a call with few groups and rows: a group per thread, one scan and two barriers instead of loops around ten.  4 experts, 1024
+// rows in 6 slices: 6.6 -> 4.6 us (with the events around the launch); a call of that size takes 42.  (At most 33 blocks of 64 rows, so that
+// two passes fill the list and a thread per expert the table.)
+constexpr int SMALL_PLAN_BLOCKS = 33;
+bool small_plan(int M, int S, int e_loc) { return (long long)S * e_loc <= PLAN_THREADS && M / 64 + e_loc <= SMALL_PLAN_BLOCKS; }
+__global__ __launch_bounds__(PLAN_THREADS)
+void ffn_small_plan_kernel(PlanArgs a) {
+    __shared__ int wave_tot[PLAN_THREADS / 64];
+    __shared__ int g_pos[PLAN_THREADS + 1], g_row[PLAN_THREADS], eb[SMALL_PLAN_BLOCKS + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M = a.M, bm = a.bm;
+    const int e = tid / a.S, s = tid - e * a.S;
+    int lo = 0, rows = 0;
+    if (e < a.e_loc) rows = group_rows(a.offsets, s * a.e_loc + e, M, lo);
+    const int start = a.list ? 0 : first_row(a.offsets, M);
+    for (int i = tid; i < 2 * TILE_COUNTERS && i < a.cap; i += PLAN_THREADS) a.ready[i] = 0;
+    int incl = rows;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off);
+        if (lane >= off) incl = add_rows(incl, o, M);
+    }
+    int pos = __shfl_up(incl, 1);
+    if (lane == 0) pos = 0;
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
+    int base = start, used = start;
+#pragma unroll
+    for (int w = 0; w < PLAN_THREADS / 64; ++w) {
+        if (w < wave) base = add_rows(base, wave_tot[w], M);
+        used = add_rows(used, wave_tot[w], M);
+    }
+    pos = add_rows(base, pos, M);
+    g_pos[tid] = pos; g_row[tid] = lo;
+    if (e < a.e_loc && s == 0) eb[e] = pos;
+    if (tid == 0) { eb[a.e_loc] = used; g_pos[PLAN_THREADS] = used; }
+    __syncthreads();
+    if (a.list) {
+        for (int p = tid; p < used; p += PLAN_THREADS) {
+            int t = 0;                                                    // the last group that starts at or before p
+#pragma unroll
+            for (int step = PLAN_THREADS / 2; step > 0; step >>= 1)
+                if (g_pos[t + step] <= p) t += step;
+            const int m = g_row[t] + (p - g_pos[t]);
+            int row = m;
+            if (a.row_map) { row = a.row_map[m]; row = (unsigned)row < (unsigned)M ? row : 0; }
+            a.list[p] = row;
+            if (a.gate) a.gate[p] = a.row_gate[m];
+        }
+        if (tid < LIST_PAD) a.list[used + tid] = 0;
+    }
+    // partial blocks in expert order, then the full blocks in expert order
+    if (tid <= a.e_loc) {
+        int partials = 0, partial_at = 0, full_at = 0, fulls = 0;
+        for (int j = 0; j < a.e_loc; ++j) {
+            const int n = eb[j + 1] - eb[j];
+            partial_at += j < tid && n % bm != 0;
+            partials += n % bm != 0;
+            full_at += j < tid ? n / bm : 0;
+            fulls += n / bm;
+        }
+        if (tid < a.e_loc) {
+            const int first = eb[tid], end = eb[tid + 1], nfull = (end - first) / bm;
+            for (int i = 0; i < nfull; ++i)
+                if (partials + full_at + i < a.cap) a.plan[PLAN_HDR + partials + full_at + i] = make_int4(first + i * bm, end, tid, bm > 128 ? 0 : 1);
+            if (first + nfull * bm < end && partial_at < a.cap)
+                a.plan[PLAN_HDR + partial_at] = make_int4(first + nfull * bm, end, tid, end - first - nfull * bm > 128 ? 0 : 1);
+        } else {
+            a.plan[0] = make_int4(min(partials + fulls, a.cap), 0, 0, 0);
+        }
+    }
+    if (tid >= 1 && tid < PLAN_HDR) a.plan[tid] = make_int4(0, 0, 0, 0);
 }
 
 // ---------------------------------------------------------------------------------- helpers
@@ -276,14 +349,16 @@ __device__ __forceinline__ u32x4 dequant8(u32x2 codes, float scale) {
     return __builtin_bit_cast(u32x4, o);
 }
 
-// ---------------------------------------------------------------------------------- GEMM kernel
-// PHASE 1: A = x (K = d), B rows 0..127 = gate rows, 128..255 = up rows of the tile's 128 columns.
-// PHASE 2: A = h (K = f), B rows = 256 rows of w_down.
-// MB = row blocks of 32 per wavefront: BM = 64 * MB.   FP8 = weights are block-scaled E4M3 codes.
-//
-// K slabs of 64 are double buffered in LDS.  bf16 operands go global -> LDS directly (each
-// wavefront instruction deposits 64 x 16 bytes contiguously, so the XOR swizzle is applied to
-// the global chunk a lane fetches); fp8 weights pass through registers to be dequantised.
+// half of 16 consecutive codes -> 8 bf16, without a scale: every E4M3 value is a bf16 value
+__device__ __forceinline__ bf16x8 widen8(u32x4 codes, int half) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const unsigned int lo = half ? codes.z : codes.x, hi = half ? codes.w : codes.y;
+    const bf16x2 v0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, false), v1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, true);
+    const bf16x2 v2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, false), v3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, true);
+    return bf16x8{v0.x, v0.y, v1.x, v1.y, v2.x, v2.y, v3.x, v3.y};
+}
+
+// ---------------------------------------------------------------------------------- persistent tiles
 // Tiles are handed out by eight atomic queues, one per XCD (workgroup id modulo 8), each
 // walking its own chunks of neighbouring tiles so that the workgroups sharing an L2 also share
 // operand slabs; a workgroup whose queue runs dry takes from the others.
@@ -341,304 +416,6 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-}
-
-// BK = K slab width (32 or 64 bf16), NST = LDS stages: slabs kt+1 .. kt+NST-1 are in flight or landed while slab kt
-// is multiplied.
-// WMW = wavefronts along the rows (2 or 4; always 2 along the columns), MB = 32-row blocks per wavefront:
-// BM = 32 * MB * WMW rows per tile, 128 * WMW threads.  Eight wavefronts (two per SIMD) matter because one
-// wavefront can only issue slab copies at a limited rate: with four, the copies, not the MFMAs, set the pace.
-template <int PHASE, int WMW, int MB, bool FP8, int BK, int NST, int PER_CU>
-__global__ __launch_bounds__(WMW * 128, PER_CU)
-void ffn_gemm_kernel(FfnArgs a) {
-    constexpr int FFN_THREADS = WMW * 128;
-    constexpr int BM = 32 * MB * WMW;
-    constexpr int ROW_BYTES = BK * 2;                  // one slab row
-    constexpr int CPR = BK / 8;                        // 16-byte chunks per row (4 or 8)
-    constexpr int RS = FFN_THREADS / CPR;              // slab rows covered by one pass of all threads
-    constexpr int KS = BK / 16;                        // MFMA K steps per slab
-    constexpr int A_BYTES = BM * ROW_BYTES, B_BYTES = BN * ROW_BYTES, STAGE = A_BYTES + B_BYTES;
-    constexpr int CA = BM / RS;                        // 16-byte chunks per thread, A slab
-    constexpr int CB = BN / RS;                        // B slab
-    constexpr int ESZ = FP8 ? 1 : 2;
-    constexpr int LPS = CA + (FP8 ? 0 : CB);           // asynchronous copies per thread and slab
-    static_assert(NST >= 2 && NST <= 4 && KS % 2 == 0 && 3 * LPS < 64, "pipeline shape");
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __shared__ int s_ticket[2];                        // (block, column tile) of the next tile, -1 = none
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int l31 = lane & 31, lhi = lane >> 5;
-    const int K = PHASE == 1 ? a.d : a.f;
-    const int KT = K / BK;
-    TileGeom geom;
-    geom.init(a.plan[0].x, PHASE == 1 ? a.f / 128 : a.d / BN, PHASE == 1 ? a.panel1 : a.panel2);
-    int* queues = (int*)(a.plan + (PHASE == 1 ? 1 : 3));
-    const int my_xcd = blockIdx.x & 7;
-
-    // LDS layout of a slab: row-major, 16-byte chunk c of row r sits at position c ^ swz(r).  With 64 banks of 4
-    // bytes a 16-lane group of a ds_read_b128 touches 256 bytes; swz makes 16 consecutive rows hit 16 different
-    // 16-byte bank groups: 128-byte rows -> (r >> 1) & 7, 64-byte rows -> (r >> 2) & 3.
-    // Staging: chunk id = tid + i*threads -> row = tid / CPR + i*RS.  One wavefront instruction deposits 64 x 16 bytes
-    // contiguously (whole rows), so the swizzle is applied to the global chunk a lane fetches.
-    const int row0 = tid / CPR;
-    const int swz0 = BK == 64 ? ((row0 >> 1) & 7) : ((row0 >> 2) & 3);     // same for row0 + i*RS
-    const int kcg = (tid % CPR) ^ swz0;
-    const int wave_bytes = wave * 1024;
-    const int st_off = row0 * ROW_BYTES + ((tid % CPR) << 4);    // register path: same position
-    // fragment coordinates: row l31 of a 32-row block, chunk (2*ks + lhi)
-    const int fswz = BK == 64 ? ((l31 >> 1) & 7) : ((l31 >> 2) & 3);
-    int frag_off[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) frag_off[ks] = l31 * ROW_BYTES + ((((ks << 1) | lhi) ^ fswz) << 4);
-    int brow[4];                                       // first B-slab row of this wave's 4 column blocks
-#pragma unroll
-    for (int q = 0; q < 4; ++q) brow[q] = PHASE == 1 ? ((q >> 1) * 128 + wn * 64 + (q & 1) * 32) : (wn * 128 + q * 32);
-
-    // thread 0 pulls tickets; own queue first, then the others
-    auto fetch = [&](int first_k) {
-        int q = my_xcd, k = first_k, blk = -1, nt = -1;
-        for (int tries = 0; tries < 8;) {
-            int st = geom.decode(q, k, blk, nt);
-            if (st == 1) break;
-            if (st < 0) { blk = -1; ++tries; q = (q + 1) & 7; }
-            if (tries < 8) k = atomicAdd(&queues[q], 1);
-        }
-        s_ticket[0] = blk; s_ticket[1] = nt;
-    };
-    if (tid == 0) fetch(atomicAdd(&queues[my_xcd], 1));
-    __syncthreads();
-    if (s_ticket[0] < 0) return;
-
-    // ---- per-tile state (set by setup()): global addressing of the slab copies; rows past the group's end re-read
-    //      its last row.  B slab row r = row0 + RS*i: only i selects gate / up / 128-row block, so each B address is
-    //      a wave-uniform base plus one per-thread byte offset.
-    const __bf16* Abase = (PHASE == 1 ? a.x : (const __bf16*)a.h);
-    const unsigned int b_voff = (unsigned int)(row0 * K + kcg * 8) * ESZ;
-    int m0 = 0, m_end = 0, nt = 0;
-    long long a_off[CA];                               // element offset of this thread's chunk (64 bit: M * K may pass 2^31)
-    const unsigned char* bbase[CB];
-    const float* sbase[CB];
-    auto setup = [&](int blk, int nt_) {
-        const int4 info = a.plan[PLAN_HDR + blk];
-        m0 = info.x; m_end = info.y; nt = nt_;
-        const int e = info.z;
-        const int rows = min(BM, m_end - m0);
-#pragma unroll
-        for (int i = 0; i < CA; ++i) {
-            const int m = m0 + min(row0 + RS * i, rows - 1);
-            a_off[i] = (long long)(PHASE == 1 ? mapped_row(a, m) : m) * K + kcg * 8;
-        }
-#pragma unroll
-        for (int i = 0; i < CB; ++i) {
-            constexpr int PER_HALF = 128 / RS;                            // passes per 128 slab rows
-            long long wrow;                                               // first weight row of this strip
-            const void* w;
-            if (PHASE == 1) { wrow = (long long)e * a.f + nt * 128 + RS * (i % PER_HALF); w = (i < PER_HALF) ? a.wg : a.wu; }
-            else            { wrow = (long long)e * a.d + nt * BN + RS * i;                 w = a.wd; }
-            bbase[i] = (const unsigned char*)w + wrow * K * ESZ;
-            if (FP8) {
-                // scale row of the 128 x 128 block holding the strip
-                if (PHASE == 1) sbase[i] = ((i < PER_HALF) ? a.sg : a.su) + ((long long)e * (a.f / 128) + nt) * (K / 128);
-                else            sbase[i] = a.sd + ((long long)e * (a.d / 128) + nt * 2 + i / PER_HALF) * (K / 128);
-            } else {
-                sbase[i] = nullptr;
-            }
-        }
-    };
-
-    // asynchronous global -> LDS copies of one slab (A always; B when it is bf16)
-    auto issue_slab = [&](int kt, int stage) {
-        unsigned char* sa = smem + stage * STAGE + wave_bytes;
-        unsigned char* sb = sa + A_BYTES;
-#pragma unroll
-        for (int i = 0; i < CA; ++i)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Abase + a_off[i] + kt * BK),
-                                             (__attribute__((address_space(3))) void*)(sa + i * RS * ROW_BYTES), 16, 0, 0);
-        if (!FP8) {
-#pragma unroll
-            for (int i = 0; i < CB; ++i)
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(bbase[i] + (size_t)kt * BK * ESZ + b_voff),
-                    (__attribute__((address_space(3))) void*)(sb + i * RS * ROW_BYTES), 16, 0, 0);
-        }
-    };
-    // fp8 weights: codes through registers (one slab ahead), dequantised on the way into LDS
-    u32x2 rb[CB];
-    float rscale[CB];
-    auto load_b_regs = [&](int kt) {
-#pragma unroll
-        for (int i = 0; i < CB; ++i) {
-            rb[i] = *reinterpret_cast<const u32x2*>(bbase[i] + (size_t)kt * BK + b_voff);
-            rscale[i] = sbase[i][(kt * BK) >> 7];
-        }
-    };
-    auto store_b_regs = [&](int stage) {
-        unsigned char* sb = smem + stage * STAGE + A_BYTES;
-#pragma unroll
-        for (int i = 0; i < CB; ++i) *reinterpret_cast<u32x4*>(sb + st_off + i * RS * ROW_BYTES) = dequant8(rb[i], rscale[i]);
-    };
-
-    // ---- K loop, software pipelined.  All NST stages are kept busy: the barrier that lets a wavefront read
-    //      slab kt+1 sits before the last MFMA batch of slab kt; by then every wavefront holds all of slab kt
-    //      in registers, so the same barrier frees slab kt's stage for slab kt+NST.
-    auto load_frags = [&](bf16x8 (&wf)[4], bf16x8 (&xf)[MB], int stage, int ks) {
-        const unsigned char* sa = smem + stage * STAGE + (wm * (MB * 32)) * ROW_BYTES;
-        const unsigned char* sb = smem + stage * STAGE + A_BYTES;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) wf[q] = *reinterpret_cast<const bf16x8*>(sb + brow[q] * ROW_BYTES + frag_off[ks]);
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) xf[mb] = *reinterpret_cast<const bf16x8*>(sa + mb * 32 * ROW_BYTES + frag_off[ks]);
-    };
-    auto load_frag_one = [&](bf16x8 (&wf)[4], bf16x8 (&xf)[MB], int stage, int ks, int i) {
-        const unsigned char* sa = smem + stage * STAGE + (wm * (MB * 32)) * ROW_BYTES;
-        const unsigned char* sb = smem + stage * STAGE + A_BYTES;
-        if (i < 4) wf[i] = *reinterpret_cast<const bf16x8*>(sb + brow[i] * ROW_BYTES + frag_off[ks]);
-        else       xf[i - 4] = *reinterpret_cast<const bf16x8*>(sa + (i - 4) * 32 * ROW_BYTES + frag_off[ks]);
-    };
-    auto issue_one = [&](int kt, int stage, int i) {
-        unsigned char* sa = smem + stage * STAGE + wave_bytes;
-        unsigned char* sb = sa + A_BYTES;
-        if (i < CA)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Abase + a_off[i] + kt * BK),
-                                             (__attribute__((address_space(3))) void*)(sa + i * RS * ROW_BYTES), 16, 0, 0);
-        else
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(bbase[i - CA] + (size_t)kt * BK * ESZ + b_voff),
-                (__attribute__((address_space(3))) void*)(sb + (i - CA) * RS * ROW_BYTES), 16, 0, 0);
-    };
-    // wait until at most `y` whole slabs of this thread's copies are outstanding (copies complete in order)
-    auto wait_slabs = [&](int y) {
-        if (y >= 3) wait_vmcnt<3 * LPS>(); else if (y == 2) wait_vmcnt<2 * LPS>();
-        else if (y == 1) wait_vmcnt<LPS>(); else wait_vmcnt<0>();
-    };
-
-    // first slabs of a tile (all stages must be free)
-    auto prologue = [&]() {
-        if (FP8) { load_b_regs(0); store_b_regs(0); if (KT > 1) load_b_regs(1); }
-#pragma unroll
-        for (int j = 0; j < NST; ++j)
-            if (j < KT) issue_slab(j, j);
-    };
-
-    setup(s_ticket[0], s_ticket[1]);
-    prologue();
-    while (true) {
-        f32x16 acc[MB][4];
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mb][q][v] = 0.f;
-
-        wait_slabs(min(NST - 1, KT - 1));
-        lds_barrier();                   // slab 0 of this tile is in LDS; everybody has read the ticket of this tile
-        if (tid == 0) fetch(atomicAdd(&queues[my_xcd], 1));             // ticket of the next tile
-        bf16x8 wf[2][4], xf[2][MB];
-        load_frags(wf[0], xf[0], 0, 0);
-
-        // One slab.  ISSUE = a further slab (kt + NST) exists and is fetched; the steady-state body is branch free so
-        // that the scheduler can spread LDS reads and slab copies between the MFMAs (MFMA first: the wait for the
-        // fragments of this batch must not also wait for reads issued for the next one).
-        auto slab = [&](int kt, auto issue_tag) {
-            constexpr bool ISSUE = decltype(issue_tag)::value;
-            const int stage = kt % NST;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const int cur = ks & 1, nxt = cur ^ 1;
-                bool copies = false;
-                if (ks + 1 < KS) {
-                    load_frags(wf[nxt], xf[nxt], stage, ks + 1);
-                } else if (ISSUE) {
-                    if (FP8) store_b_regs((kt + 1) % NST);
-                    wait_vmcnt<(NST - 2) * LPS>();                       // slab kt+1 landed; kt+2 .. kt+NST-1 may be in flight
-                    lds_barrier();
-                    if (FP8) load_b_regs(kt + 2);                        // before the copies: waited for first
-                    // fragment reads and slab copies alternate in program order (a copy writes LDS, so the compiler
-                    // keeps it ordered against the reads around it)
-                    constexpr int NF = 4 + MB, NC = CA + (FP8 ? 0 : CB);
-#pragma unroll
-                    for (int i = 0; i < (NF > NC ? NF : NC); ++i) {
-                        if (i < NF) load_frag_one(wf[nxt], xf[nxt], (kt + 1) % NST, 0, i);
-                        if (i < NC) issue_one(kt + NST, stage, i);
-                    }
-                    copies = true;
-                } else if (kt + 1 < KT) {
-                    if (FP8) store_b_regs((kt + 1) % NST);
-                    wait_slabs(min(NST - 2, KT - 2 - kt));
-                    lds_barrier();
-                    load_frags(wf[nxt], xf[nxt], (kt + 1) % NST, 0);
-                    if (FP8 && kt + 2 < KT) load_b_regs(kt + 2);
-                }
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        acc[mb][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[cur][q], xf[cur][mb], acc[mb][q], 0, 0, 0);
-                // issue order: one MFMA, then at most one LDS read and one slab copy, repeated
-                constexpr int NMF = 4 * MB, NFR = 4 + MB, NCP = CA + CB;
-                if (copies) {
-#pragma unroll
-                    for (int i = 0; i < (NMF > NFR ? NMF : NFR); ++i) {
-                        if (i < NMF) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-                        if (i < NFR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
-                        if (i < NCP) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);   // vector memory (slab copy)
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < (NMF > NFR ? NMF : NFR); ++i) {
-                        if (i < NMF) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        if (i < NFR) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        {
-            int kt = 0;
-            for (; kt + NST < KT; ++kt) slab(kt, std::true_type{});
-            for (; kt < KT; ++kt) slab(kt, std::false_type{});
-        }
-        lds_barrier();                   // every fragment is in registers: all stages are free; next ticket visible
-        const int em0 = m0, em_end = m_end, ent = nt;
-        const int nblk = s_ticket[0], nnt = s_ticket[1];
-        if (nblk >= 0) { setup(nblk, nnt); prologue(); }                // the next tile's first slabs fly during the epilogue
-
-
-        // ---- epilogue.  acc[mb][q][v]: row m = l31 of row block mb; column n = 8*(v>>2) + 4*lhi + (v&3)
-        //      of column block q
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int m = em0 + wm * (MB * 32) + mb * 32 + l31;
-            if (m < em_end) {
-                if (PHASE == 1) {
-                    __bf16* out = a.h + (long long)m * a.f + ent * 128 + wn * 64 + 4 * lhi;
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-#pragma unroll
-                        for (int vg = 0; vg < 4; ++vg) {
-                            float hv[4];
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) hv[j] = silu(acc[mb][q][vg * 4 + j]) * acc[mb][q + 2][vg * 4 + j];
-                            *reinterpret_cast<u32x2*>(out + q * 32 + vg * 8) = pack4(hv[0], hv[1], hv[2], hv[3]);
-                        }
-                } else {
-                    __bf16* out = a.y + (long long)mapped_row(a, m) * a.d + ent * BN + wn * 128 + 4 * lhi;
-                    const float gate = a.gate ? a.gate[m] : 1.0f;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int vg = 0; vg < 4; ++vg)
-                            *reinterpret_cast<u32x2*>(out + q * 32 + vg * 8) =
-                                pack4(gate * acc[mb][q][vg * 4], gate * acc[mb][q][vg * 4 + 1], gate * acc[mb][q][vg * 4 + 2],
-                                      gate * acc[mb][q][vg * 4 + 3]);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);     // one row block at a time: keeps the accumulator read-out short-lived
-        }
-        if (nblk < 0) break;
-    }
 }
 
 // ---------------------------------------------------------------------------------- adaptive-shape GEMM kernel (bf16)
@@ -1247,8 +1024,8 @@ void ffn_fused_kernel(FfnArgs a) {
 // instead of 16 rows that lie a power of two apart in the same memory channel (phase 2 of d = 4096, f = 14336 at 64 rows 69 ->
 // 48 us; d = 7168, f = 2048, four fp8 experts 42 -> 28 us).  For the same reason the strips start at different steps of K
 // (one expert, d 4096, f 14336, 5 rows: 86 -> 70 us).
-// One expert, d 4096, f 14336, 37 rows (352 MB of weights): 587 us in 64-row tiles -> 97 us; four fp8 experts, d 7168, f 2048,
-// 203 rows (176 MB): 445 -> 95 us.  5 rows of the former: 68 us, 5.2 TB/s; with more rows the activations' way from L2 counts too.
+// One expert, d 4096, f 14336 (352 MB of weights): 5 rows 68 us, 5.2 TB/s; with more rows the activations' way from L2 counts too (37 rows 96 us, in
+// tiles of 64 rows 85).
 struct SkinnyArgs {
     const __bf16* x; __bf16* h; __bf16* y;
     const __bf16* xk;                  // the rows of x in schedule order, K-major as h, or null: phase 1 reads x
@@ -1336,6 +1113,7 @@ void ffn_skinny_kernel(SkinnyArgs a) {
         };
         auto work = [&](auto tag) __attribute__((always_inline)) {
             constexpr int T = decltype(tag)::value;                        // 16-row tiles of this workgroup's rows
+            constexpr int TS = FP8 ? T : 1;
             f32x4 acc[NC][T];
 #pragma unroll
             for (int c = 0; c < NC; ++c)
@@ -1395,23 +1173,28 @@ void ffn_skinny_kernel(SkinnyArgs a) {
                     if (PHASE == 1) b.sc[1] = sbase[1][kb];
                 }
             };
+            // fp8: codes are widened to bf16 (exactly), and the scale multiplies the fp32 sum over the step's 64 values of K
             auto multiply = [&](const Buf& b) __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int c = 0; c < NC; ++c) {
+                    f32x4 sum[TS];
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        u32x4 wv;
-                        if (FP8) {
-                            const u32x4 q = b.w[c][0];
-                            wv = dequant8(j == 0 ? u32x2{q.x, q.y} : u32x2{q.z, q.w}, b.sc[PHASE == 1 && c >= NH ? 1 : 0]);
-                        } else {
-                            wv = b.w[c][FP8 ? 0 : j];
+                    for (int j = 0; j < 2; ++j) {
+                        const bf16x8 wv = FP8 ? widen8(b.w[c][0], j) : __builtin_bit_cast(bf16x8, b.w[c][FP8 ? 0 : j]);
+#pragma unroll
+                        for (int t = 0; t < T; ++t) {
+                            if (FP8) sum[FP8 ? t : 0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(bf16x8, b.x[t][j]), j == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[FP8 ? t : 0], 0, 0, 0);
+                            else     acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv, __builtin_bit_cast(bf16x8, b.x[t][j]), acc[c][t], 0, 0, 0);
                         }
+                    }
+                    if (FP8) {
+                        const float sc = b.sc[PHASE == 1 && c >= NH ? 1 : 0];
 #pragma unroll
                         for (int t = 0; t < T; ++t)
-                            acc[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, wv),
-                                                                                __builtin_bit_cast(bf16x8, b.x[t][j]), acc[c][t], 0, 0, 0);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) acc[c][t][v] = __builtin_fmaf(sum[FP8 ? t : 0][v], sc, acc[c][t][v]);
                     }
+                }
             };
 #pragma unroll
             for (int i = 0; i < D - 1; ++i) load(buf[i], i);
@@ -1470,6 +1253,356 @@ void ffn_skinny_kernel(SkinnyArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------------- a few hundred rows per expert
+// Between streaming and the 256 x 256 tiles a call has too few of those tiles for the chip (d = 4096 makes 16 column tiles of w_down, each a contraction over
+// all of f), so that it lasts as long as one tile's chain of K slabs.  Here a tile is 128 rows x 128 columns (phase 1: 64 gate + 64 up), four wavefronts of
+// 64 x 64, two workgroups per compute unit, and where the tiles do not fill the slots (both workgroups of every compute unit) the contraction of
+// a tile is split over up to TILE_MAX_PARTS workgroups, which add their sums in fp32 in part order (the last one to finish does).
+// The plan says how many row blocks there are, so every workgroup works out the tiles, the split and its unit by itself; workgroups beyond the last unit
+// leave at once.  Bound by the operands' way from the L2 into LDS: 32 KiB per slab of 64 values of K for 4.2 Mflop.
+// Both operands are copied global -> LDS as they lie; fp8 codes are widened to bf16 (exactly) on the way from LDS to the matrix cores, two values per
+// v_cvt_scalef32_pk_bf16_fp8, and the scale of a 128 x 128 block multiplies the fp32 sum over that block's 128 values of K.
+constexpr int TILE = 128;                                    // columns
+constexpr int TILE_MAX_PARTS = 16, TILE_MIN_SLABS = 12;       // parts of a contraction, slabs of 64 values of K per part at least
+// ROWS = rows per tile:
+//    64: 4 wavefronts (2 x 2) of 32 x 64, three slabs of 24 KiB (fp8: four of activations, three of codes), 2 workgroups per compute unit
+//   128: 4 wavefronts (2 x 2) of 64 x 64, two slabs of 32 KiB, 2 workgroups per compute unit
+//   256: 8 wavefronts (4 x 2) of 64 x 64, three slabs of 48 KiB, 1 workgroup per compute unit
+template <int ROWS, bool FP8> struct TileShape {
+    static constexpr int WM = ROWS == 256 ? 4 : 2, MB = ROWS / (32 * WM), THREADS = 128 * WM;
+    static constexpr int PER_CU = WM == 4 ? 1 : 2;
+    // Workgroups per compute unit up to which contractions are split.  (64 rows, one / two: E 1, d 4096, f 14336, 37 rows 85 / 100 us; fp8 E 4, d 7168, f 2048, 64
+    // rows 48 / 58, 203 rows 69 / 65.  128 rows, 203 rows of the former 139 / 134; E 2, d 3584, f 4864, 512 rows 130 / 103.)
+    static constexpr int SPLIT_PER_CU = ROWS == 128 ? 2 : 1;
+    static constexpr int NST = ROWS == 64 ? (FP8 ? 4 : 3) : (ROWS == 128 ? 2 : 3);      // places for slabs of 64 values of K of the activations
+    static constexpr int NB = !FP8 ? NST : (ROWS == 64 ? 3 : 2);                        // places for slabs of 128 bytes per weight row
+    static constexpr int A_BYTES = ROWS * 128, B_BYTES = TILE * 128;                    // of a place
+    static constexpr size_t LDS = NST * A_BYTES + NB * B_BYTES;
+    static constexpr size_t UNIT_BYTES = (size_t)ROWS * TILE * sizeof(float);
+};
+// parts per contraction with `tiles` tiles, at most `cap` units having room for their sums
+__host__ __device__ inline int tile_parts(long long tiles, int slots, int K, int cap) {
+    if (tiles < 1 || tiles >= TILE_COUNTERS) return 1;
+    long long P = slots / tiles;
+    const long long most = K / 64 / TILE_MIN_SLABS, room = cap / tiles;
+    P = P < most ? P : most;
+    P = P < room ? P : room;
+    P = P < TILE_MAX_PARTS ? P : TILE_MAX_PARTS;
+    return P < 1 ? 1 : (int)P;
+}
+
+struct TileArgs {
+    FfnArgs a;
+    f32x4* part;                       // [cap] units
+    int* arrived;                      // [TILE_COUNTERS] parts of the tile that are done
+    int slots, cap;
+};
+template <int PHASE, bool FP8, int ROWS, bool WIDE>
+__global__ __launch_bounds__((TileShape<ROWS, FP8>::THREADS), 2)
+void ffn_tile_kernel(TileArgs t) {
+    typedef TileShape<ROWS, FP8> S;
+    const FfnArgs& a = t.a;
+    constexpr int ROWB = 128, NST = S::NST, NB = S::NB, MB = S::MB, A_BYTES = S::A_BYTES, B_BYTES = S::B_BYTES, B_AT = NST * A_BYTES;
+    constexpr int RPC = S::THREADS / 8, CA = ROWS / RPC, CB = TILE / RPC; // rows one copy of the workgroup deposits, copies of a slab
+    static_assert(CA <= 4 && (CB == 2 || CB == 4), "copies");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l31 = lane & 31, lhi = lane >> 5;
+    const int K = PHASE == 1 ? a.d : a.f, NT = PHASE == 1 ? a.f / 64 : a.d / TILE;
+    const int nblocks = a.plan[0].x;
+    const int P = tile_parts((long long)nblocks * NT, t.slots, K, t.cap);
+    // workgroup -> unit: every die (workgroup number modulo 8) takes a stretch of the units; row blocks are innermost, so that those which share
+    // weights share an L2
+    const int units = nblocks * NT * P, xcd = blockIdx.x & 7;              // (< 2^28: a condition of this route)
+    const int last = units * (xcd + 1) / 8, unit = units * xcd / 8 + (int)(blockIdx.x >> 3);
+    if (unit >= last) return;
+    const int blk = unit % nblocks, rest = unit / nblocks, p = rest % P, nt = rest / P;
+    const int4 info = a.plan[PLAN_HDR + blk];
+    const int m0 = __builtin_amdgcn_readfirstlane(info.x), m_end = __builtin_amdgcn_readfirstlane(info.y), e = __builtin_amdgcn_readfirstlane(info.z);
+    const int rows = min(ROWS, m_end - m0);
+    // this part's K: whole blocks of 128
+    const int KB = K / 128, kb0 = KB * p / P, NP = KB * (p + 1) / P - kb0, NS = 2 * NP;
+
+    // ---- copies.  A slab row is 128 bytes; 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7).
+    const int row0 = tid >> 3, kcg = (tid & 7) ^ ((row0 >> 1) & 7);
+    // Rows past the end lie behind the buffer descriptor: zeros are deposited, from no memory.  WIDE: x or h does not fit 32-bit offsets.
+    const unsigned char* a_ptr[WIDE ? 4 : 1];
+    unsigned int a_voff[4];
+    const __bf16* const A = PHASE == 1 ? a.x : (const __bf16*)a.h;
+#pragma unroll
+    for (int i = 0; i < CA; ++i) {
+        const int r = row0 + RPC * i, m = m0 + min(r, rows - 1);
+        const unsigned int row = (unsigned int)(PHASE == 1 ? mapped_row(a, m) : m);
+        if (WIDE) a_ptr[WIDE ? i : 0] = (const unsigned char*)(A + (size_t)row * K) + (size_t)kb0 * 256 + kcg * 16;     // (repeats the last row)
+        else      a_voff[i] = r < rows ? row * (unsigned int)K * 2u + (unsigned int)kb0 * 256u + (unsigned int)kcg * 16u : 0xFFFFFF00u;
+    }
+    const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc((void*)A, 0, (int)((unsigned int)a.M * (unsigned int)K * 2u), 0x00020000);
+    constexpr int ESZ = FP8 ? 1 : 2;
+    const size_t pitch = (size_t)K * ESZ;
+    const unsigned char *b_lo, *b_hi;                                     // weight rows 0 .. 63 and 64 .. 127 of the tile
+    if (PHASE == 1) {
+        const size_t at = ((size_t)e * a.f + (size_t)nt * 64) * pitch;
+        b_lo = (const unsigned char*)a.wg + at; b_hi = (const unsigned char*)a.wu + at;
+    } else {
+        b_lo = (const unsigned char*)a.wd + ((size_t)e * a.d + (size_t)nt * TILE) * pitch; b_hi = b_lo + 64 * pitch;
+    }
+    b_lo += (size_t)kb0 * 128 * ESZ; b_hi += (size_t)kb0 * 128 * ESZ;
+    const unsigned int b_voff = (unsigned int)row0 * (unsigned int)pitch + (unsigned int)kcg * 16u;
+    const __amdgpu_buffer_rsrc_t rs_lo = __builtin_amdgcn_make_buffer_rsrc((void*)b_lo, 0, 0xFFFFFFFF, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_hi = __builtin_amdgcn_make_buffer_rsrc((void*)b_hi, 0, 0xFFFFFFFF, 0x00020000);
+    auto copy_a = [&](int s, int st, int i) __attribute__((always_inline)) {        // slab s into place st
+        void* const to = smem + st * A_BYTES + i * RPC * ROWB + wave * 1024;
+        if constexpr (WIDE) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(a_ptr[i] + (size_t)s * ROWB), (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+        } else {
+            const int koff = s * ROWB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_a, (__attribute__((address_space(3))) void*)to, 16, a_voff[i], koff, 0, 0);
+        }
+    };
+    auto copy_b = [&](int s, int st, int i) __attribute__((always_inline)) {        // 128 bytes per weight row: 64 bf16 values, or 128 codes
+        const int koff = s * ROWB;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(2 * i < CB ? rs_lo : rs_hi, (__attribute__((address_space(3))) void*)(smem + B_AT + st * B_BYTES + i * RPC * ROWB + wave * 1024),
+                                                 16, b_voff, (i % (CB / 2)) * RPC * (int)pitch + koff, 0, 0);
+    };
+
+    // ---- fragments.  Column blocks of the wavefront: phase 1 gate columns 32 wn .. and up columns 32 wn .., phase 2 columns 64 wn .. and 64 wn + 32 ..
+    // The order of K inside 32 values is free as long as both operands agree: fp8 lanes read 16 consecutive codes, the two MFMA steps' worth.
+    const int swz = (l31 >> 1) & 7;
+    const unsigned char* const fa = smem + (wm * 32 * MB + l31) * ROWB;
+    const int brow[2] = {(PHASE == 1 ? wn * 32 : wn * 64) + l31, (PHASE == 1 ? 64 + wn * 32 : wn * 64 + 32) + l31};
+    bf16x8 xf[2][MB];
+    u32x4 wf[2][2];                                                       // of K step u in wf[u & 1]; fp8: of steps 2 g and 2 g + 1 in wf[g]
+    auto load_frags = [&](int s, int st, int bst, int u) __attribute__((always_inline)) {     // K step u of slab s, whose operands lie at st and bst
+        const int ca = FP8 ? 4 * (u >> 1) + 2 * lhi + (u & 1) : 2 * u + lhi;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) xf[u & 1][mb] = *reinterpret_cast<const bf16x8*>(fa + st * A_BYTES + mb * 32 * ROWB + ((ca ^ swz) << 4));
+        if (!FP8 || (u & 1) == 0) {
+            const int cb = FP8 ? 2 * (2 * (s & 1) + (u >> 1)) + lhi : ca;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) wf[FP8 ? u >> 1 : u & 1][q] = *reinterpret_cast<const u32x4*>(smem + B_AT + bst * B_BYTES + brow[q] * ROWB + ((cb ^ swz) << 4));
+        }
+    };
+    typedef const __attribute__((address_space(4))) float* scalar_floats;
+    scalar_floats scale[2] = {nullptr, nullptr};                          // scale row of the tile's 128 x 128 blocks: gate and up, or down
+    if (FP8) {
+        const size_t row = PHASE == 1 ? (size_t)e * (a.f / 128) + nt / 2 : (size_t)e * (a.d / 128) + nt;
+        scale[0] = (scalar_floats)((PHASE == 1 ? a.sg : a.sd) + row * (K / 128) + kb0);
+        scale[1] = (scalar_floats)((PHASE == 1 ? a.su : a.sd) + row * (K / 128) + kb0);
+    }
+
+    f32x16 acc[MB][2], sum[FP8 ? MB : 1][FP8 ? 2 : 1];            // fp8: sums over the current 128 values of K
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mb][q][v] = 0.f;
+
+    // Slab s.  The barrier ahead of its last K step publishes slab s + 1 and frees its own place, into which slab s + NST is copied (fp8: the codes of
+    // 128 values of K with every other slab, NB blocks ahead, behind the activations).  NEW: that slab exists.
+    int st = 0, bst = 0;                                                  // places of slab s
+    auto next_slab = [&](int s, auto odd_tag, auto new_tag) __attribute__((always_inline)) {         // the barrier
+        constexpr bool ODD = decltype(odd_tag)::value, NEW = decltype(new_tag)::value;
+        // still in flight behind what slab s + 1 needs: NST - 2 slabs, and the codes of NB - 2 blocks (while slab s + 1 is in this one's block, NB - 1)
+        if (!NEW)      wait_vmcnt<0>();
+        else if (!FP8) wait_vmcnt<(NST - 2) * (CA + CB)>();
+        else           wait_vmcnt<(NST - 2) * CA + (NB - (ODD ? 2 : 1)) * CB>();
+        lds_barrier();
+    };
+    auto copies_of = [&](int s, auto odd_tag) __attribute__((always_inline)) {                       // what goes out behind slab s
+        constexpr bool ODD = decltype(odd_tag)::value;
+#pragma unroll
+        for (int i = 0; i < CA; ++i) copy_a(s + NST, st, i);
+        if (!FP8) {
+#pragma unroll
+            for (int i = 0; i < CB; ++i) copy_b(s + NST, st, i);
+        } else if (ODD) {                                                 // (ahead of the last blocks: the last one once more, into a free place)
+            const int b = min((s >> 1) + NB, NP - 1);
+#pragma unroll
+            for (int i = 0; i < CB; ++i) copy_b(b, bst, i);
+        }
+    };
+    auto advance = [&](auto odd_tag) __attribute__((always_inline)) {
+        constexpr bool ODD = decltype(odd_tag)::value;
+        st = st + 1 == NST ? 0 : st + 1;
+        if (!FP8) bst = st; else if (ODD) bst = bst + 1 == NB ? 0 : bst + 1;
+    };
+    auto slab = [&](int s, auto odd_tag, auto new_tag, auto final_tag) __attribute__((always_inline)) {
+        constexpr bool ODD = decltype(odd_tag)::value, NEW = decltype(new_tag)::value, FINAL = decltype(final_tag)::value;
+        if (FP8 && !ODD) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) sum[FP8 ? mb : 0][FP8 ? q : 0][v] = 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int cur = u & 1;
+            const bool last = u == 3, reads = !(last && FINAL), copies = last && NEW;
+            if (last && !FINAL) {
+                next_slab(s, odd_tag, new_tag);
+                const int nst = st + 1 == NST ? 0 : st + 1, nbst = !FP8 ? nst : (ODD ? (bst + 1 == NB ? 0 : bst + 1) : bst);
+                load_frags(s + 1, nst, nbst, 0);
+            } else if (reads) {
+                load_frags(s, st, bst, u + 1);
+            }
+            if (copies) copies_of(s, odd_tag);
+            bf16x8 w[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) w[q] = FP8 ? widen8(wf[u >> 1][q], u & 1) : __builtin_bit_cast(bf16x8, wf[cur][q]);
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    f32x16& c = FP8 ? sum[FP8 ? mb : 0][FP8 ? q : 0] : acc[mb][q];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[q], xf[cur][mb], c, 0, 0, 0);
+                }
+#pragma unroll
+            for (int i = 0; i < 2 * MB; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                         // MFMA
+                if (reads) __builtin_amdgcn_sched_group_barrier(0x100, MB == 1 ? 2 : 1, 0);                // LDS reads
+                if (copies) __builtin_amdgcn_sched_group_barrier(0x010, MB == 1 ? 3 : 2, 0);               // slab copies
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (FP8 && ODD) {
+            const float sc[2] = {scale[0][s >> 1], scale[1][s >> 1]};
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[mb][q][v] = __builtin_fmaf(sum[FP8 ? mb : 0][FP8 ? q : 0][v], sc[q], acc[mb][q][v]);
+        }
+        advance(odd_tag);
+    };
+    // a wavefront without rows has its share of the copies and barriers only
+    auto idle_slab = [&](int s, auto odd_tag, auto new_tag, auto final_tag) __attribute__((always_inline)) {
+        constexpr bool NEW = decltype(new_tag)::value, FINAL = decltype(final_tag)::value;
+        if (!FINAL) next_slab(s, odd_tag, new_tag);
+        if (NEW) copies_of(s, odd_tag);
+        advance(odd_tag);
+    };
+    auto all_slabs = [&](auto one) __attribute__((always_inline)) {
+        const std::true_type T{};
+        const std::false_type F{};
+        int s = 0;
+        for (; s + 1 + NST < NS; s += 2) { one(s, F, T, F); one(s + 1, T, T, F); }
+        // (NS is even: 2 slabs are left, or 4; with three places slab NS - 1 is copied behind slab NS - 4)
+        if (NS - s > 2) {
+            if (NST == 3) one(s, F, T, F); else one(s, F, F, F);
+            one(s + 1, T, F, F);
+            s += 2;
+        }
+        one(s, F, F, F);
+        one(s + 1, T, F, T);
+    };
+    // The first slabs, in the order of the steady state: slab k with, behind every other one, a block of codes.  (Past the end: the last ones once more.)
+    if (FP8) {
+#pragma unroll
+        for (int i = 0; i < CB; ++i) copy_b(0, 0, i);
+    }
+#pragma unroll
+    for (int s = 0; s < NST; ++s) {
+#pragma unroll
+        for (int i = 0; i < CA; ++i) copy_a(min(s, NS - 1), s, i);
+        constexpr int EVEN = NST & 1;                                     // (a block follows the slabs that have as many behind them as places, up to an even number)
+        if (!FP8 || ((s & 1) != EVEN && s > 0)) {
+            const int b = FP8 ? (s - NST + 1) / 2 + NB - 1 : s;
+#pragma unroll
+            for (int i = 0; i < CB; ++i) copy_b(FP8 ? min(b, NP - 1) : min(b, NS - 1), b, i);
+        }
+    }
+    wait_vmcnt<(NST - 1) * CA + (NB - 1) * CB>();
+    lds_barrier();
+    if (wm * 32 * MB < rows) {
+        load_frags(0, 0, 0, 0);
+        all_slabs(slab);
+    } else {
+        all_slabs(idle_slab);
+    }
+    __syncthreads();                     // the slabs' places stage the output
+
+    // ---- a part of the contraction: its sums go to memory where every die sees them; the workgroup that finds the others there adds them up in order
+    if (P > 1) {
+        const int tile = nt * nblocks + blk;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)t.part, 0, 0xFFFFFFFF, 0x00020000);
+        const unsigned int at = (unsigned int)(tile * P) * (unsigned int)S::UNIT_BYTES + (unsigned int)wave * (8192u * MB);
+        const int live = min(MB, (rows - wm * 32 * MB + 31) / 32);        // 32-row blocks of this wavefront that hold rows (may be negative)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            if (mb < live) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const f32x4 v = {acc[mb][i >> 2][(i & 3) * 4], acc[mb][i >> 2][(i & 3) * 4 + 1], acc[mb][i >> 2][(i & 3) * 4 + 2], acc[mb][i >> 2][(i & 3) * 4 + 3]};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, lane * 16,
+                                                           at + (unsigned int)p * (unsigned int)S::UNIT_BYTES + (unsigned int)(mb * 8 + i) * 1024u, DEVICE_SCOPE);
+                }
+            }
+        wait_vmcnt<0>();
+        __syncthreads();
+        int* const s_arrived = reinterpret_cast<int*>(smem);
+        if (tid == 0) *s_arrived = __hip_atomic_fetch_add(&t.arrived[tile], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const int others = *s_arrived;
+        __syncthreads();
+        if (others != P - 1) return;
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            acc[mb][0] = acc[mb][1] = f32x16{0.f};
+            if (mb >= live) continue;
+            for (int k = 0; k < P; ++k) {
+                u32x4 v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    v[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, at + (unsigned int)k * (unsigned int)S::UNIT_BYTES + (unsigned int)(mb * 8 + i) * 1024u, DEVICE_SCOPE);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const f32x4 w = __builtin_bit_cast(f32x4, v[i]);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[mb][i >> 2][(i & 3) * 4 + j] += w[j];
+                }
+            }
+        }
+    }
+
+    // ---- output.  acc[mb][q][v]: row l31 of row block mb, column 8 * (v >> 2) + 4 * lhi + (v & 3) of column block q; through a private staging area, 32
+    // rows at a time (phase 1: of 32 hidden units, phase 2: of 64 columns), so that a store covers runs of 64 or 128 bytes
+    unsigned char* const stage = smem + wave * 4096;
+    constexpr int SROW = PHASE == 1 ? 64 : 128, CPR = SROW / 16, RPI = 64 / CPR;
+    auto swz_out = [](int r) { return (r >> 1) & (CPR - 1); };
+    const int sr = lane / CPR, sc = lane % CPR;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+        const int wrow = m0 + wm * 32 * MB + mb * 32;
+        float gate = 1.0f;
+        if (PHASE == 2 && a.gate) gate = a.gate[min(wrow + l31, m_end - 1)];
+#pragma unroll
+        for (int q = 0; q < (PHASE == 1 ? 1 : 2); ++q)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                float o[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float v = acc[mb][q][g * 4 + j];
+                    o[j] = PHASE == 1 ? silu(v) * acc[mb][1][g * 4 + j] : gate * v;
+                }
+                *reinterpret_cast<u32x2*>(stage + l31 * SROW + (((q * 4 + g) ^ swz_out(l31)) << 4) + lhi * 8) = pack4(o[0], o[1], o[2], o[3]);
+            }
+#pragma unroll
+        for (int i = 0; i < 32 / RPI; ++i) {
+            const int r = i * RPI + sr, m = wrow + r;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * SROW + ((sc ^ swz_out(r)) << 4));
+            if (m < m_end) {
+                if (PHASE == 1) *reinterpret_cast<u32x4*>(a.h + (size_t)(unsigned int)m * a.f + nt * 64 + wn * 32 + sc * 8) = v;
+                else            *reinterpret_cast<u32x4*>(a.y + (size_t)(unsigned int)mapped_row(a, m) * a.d + nt * TILE + wn * 64 + sc * 8) = v;
+            }
+        }
+    }
+}
+
 // Expands block-scaled E4M3 codes [rows][cols] to bf16, eight values per thread and step (HBM bound: 3 bytes per weight).
 __global__ __launch_bounds__(256)
 void ffn_expand_fp8_kernel(const unsigned char* __restrict__ codes, const float* __restrict__ scales, __bf16* __restrict__ out,
@@ -1524,41 +1657,6 @@ int panel_width(int units, size_t expert_weight_bytes, size_t unit_bytes) {
     return w < 1 ? 1 : (w > ncg ? ncg : w);
 }
 
-// Tile shapes.  ROWS = rows per tile:
-//   256: 8 wavefronts (4 x 2), 64 x 128 per wavefront, two 64-wide slabs of 64 KiB (whole cache lines per row; 1 workgroup per CU)
-//   128: 4 wavefronts (2 x 2), 64 x 128 per wavefront, three 32-wide slabs of 24 KiB         (2 workgroups per CU)
-//    64: 4 wavefronts (2 x 2), 32 x 128 per wavefront, three 32-wide slabs of 20 KiB         (2 workgroups per CU)
-template <int ROWS> struct Shape;
-template <> struct Shape<256> { static constexpr int WMW = 4, MB = 2, BK = 64, NST = 2, PER_CU = 1; };
-template <> struct Shape<128> { static constexpr int WMW = 2, MB = 2, BK = 32, NST = 3, PER_CU = 2; };
-template <> struct Shape<64>  { static constexpr int WMW = 2, MB = 1, BK = 32, NST = 3, PER_CU = 2; };
-
-template <int PHASE, int ROWS, bool FP8>
-moe_status launch_gemm(const FfnArgs& a, long long max_tiles, hipStream_t s) {
-    typedef Shape<ROWS> S;
-    constexpr size_t lds = (size_t)S::NST * (ROWS + BN) * S::BK * 2;
-    static moe::DeviceOnce attr;
-    auto kern = ffn_gemm_kernel<PHASE, S::WMW, S::MB, FP8, S::BK, S::NST, S::PER_CU>;
-    int dev;
-    if (attr.needed(dev)) {
-        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
-        attr.mark(dev);
-    }
-    // Where there are fewer tiles than compute units, up to four workgroups per tile, but no more than compute units.  A workgroup
-    // takes its next ticket early; were there no more workgroups than tiles, those whose own queue holds tiles would take second ones
-    // before those that have to look through the other queues have found their first.  A second workgroup on a compute unit takes
-    // tickets away from one that is empty, and many idle ones cost the queues some 20 us.  Whole call, us, one per tile / two per tile, as
-    // far as the chip holds them / every slot / this: fp8 E 1, d = f = 4096, 96 rows 402 / 311 / - / 227, 512 rows 417 / 260 / 300 / 260; E 64, d 1024, f 512, 4
-    // rows 90 / 126 / - / 89; E 4, d 2048, f 1408, 1024 rows 214 / 153 / 153 / 153; bf16 E 8, d 2048, f 1408, 16 rows 127 / 99 / 141 / 99; E 24, d = f = 256, 64
-    // rows 41 / 47 / 93 / 47.  (546 calls, mean time over the best of these: 1.27, 1.08, -, 1.04.)
-    const long long slots = (long long)num_cus() * S::PER_CU, cus = num_cus();
-    const int grid = (int)std::min(max_tiles >= cus ? max_tiles : std::min(cus, max_tiles <= cus / 4 ? 4 * max_tiles : 2 * max_tiles), slots);
-    moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(S::WMW * 128), lds, s, a);
-    return k.done();
-}
-
 // `max_tiles`: workgroups wanted, at most one per compute unit is launched
 template <int PHASE, int AROWS, int OROWS, int EPI = 0>
 moe_status launch_adaptive(const FfnArgs& a, long long max_tiles, hipStream_t s, const char* name = nullptr) {
@@ -1611,11 +1709,35 @@ moe_status launch_both_adaptive(const FfnArgs& a, long long max_blocks, int E_lo
     return launch_adaptive<2, ROWS_PLAIN, ROWS>(a, max_blocks * (a.d / 256), s);
 }
 
-template <int ROWS, bool FP8>
-moe_status launch_both(const FfnArgs& a, long long max_blocks, hipStream_t s) {
-    moe_status st = launch_gemm<1, ROWS, FP8>(a, max_blocks * (a.f / 128), s);
+template <int PHASE, bool FP8, int ROWS, bool WIDE>
+moe_status launch_tile(const TileArgs& a, long long max_blocks, hipStream_t s) {
+    typedef TileShape<ROWS, FP8> S;
+    static moe::DeviceOnce attr;
+    auto kern = ffn_tile_kernel<PHASE, FP8, ROWS, WIDE>;
+    int dev;
+    if (attr.needed(dev)) {
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
+        if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
+        attr.mark(dev);
+    }
+    const long long units = std::max<long long>(max_blocks * (PHASE == 1 ? a.a.f / 64 : a.a.d / TILE), a.cap > 0 ? a.slots : 0);
+    moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
+    hipLaunchKernelGGL(kern, dim3((unsigned int)((units + 7) / 8 * 8)), dim3(S::THREADS), S::LDS, s, a);
+    return k.done();
+}
+template <bool FP8, int ROWS>
+moe_status launch_both_tile(const FfnArgs& a, long long max_blocks, f32x4* part, size_t part_bytes, hipStream_t s) {
+    TileArgs t;
+    t.a = a;
+    t.part = part;
+    t.slots = TileShape<ROWS, FP8>::SPLIT_PER_CU * num_cus();
+    t.cap = (int)std::min<size_t>(part_bytes / TileShape<ROWS, FP8>::UNIT_BYTES, (size_t)t.slots);
+    t.arrived = a.ready;
+    const bool wide = (unsigned long long)a.M * std::max(a.d, a.f) * 2 >= 0xFFFFFF00ull;
+    moe_status st = wide ? launch_tile<1, FP8, ROWS, true>(t, max_blocks, s) : launch_tile<1, FP8, ROWS, false>(t, max_blocks, s);
     if (st != MOE_OK) return st;
-    return launch_gemm<2, ROWS, FP8>(a, max_blocks * (a.d / BN), s);
+    t.arrived = a.ready + TILE_COUNTERS;
+    return wide ? launch_tile<2, FP8, ROWS, true>(t, max_blocks, s) : launch_tile<2, FP8, ROWS, false>(t, max_blocks, s);
 }
 
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
@@ -1668,37 +1790,80 @@ moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
     return launch_skinny<2, 4, 1, 4, FP8>(a, s);
 }
 
-// Whether a call's weights are streamed (once per 64 or 128 rows) or its rows worked on in tiles.  Only M, an upper bound of the rows, is
-// known here, and not how unequal the experts are: the lines were fitted to 4000 calls (E 1 .. 128, d 256 .. 7168, f 256 .. 14336) with
-// equal experts, Zipf popularity and all rows at one expert.  Of the first two kinds 3 in 3000 calls take more than 1.8 times what the better way
-// would, none of the Zipf ones more than 1.45 times (means 1.02); all rows at one expert: 2.4 times at most, mean 1.04.
-// - Rows per expert at most a constant over the column tiles the tile kernels would have for the chip (both phases), at least 64.  One
-//   or two experts stream further, since nothing is lost to the remainder of one expert's rows behind another's.  us, streaming / tiles,
-//   at 128 / 256 / 384 rows per expert: bf16 E 4, d 2048, f 1408 (76 column tiles) 50 / 99, 75 / 104, 109 / 120; E 8, d 7168, f 2048 (352) 356 / 298, 598 /
-//   344, 879 / 365; E 1, d 4096, f 14336 (128) 154 / 450, 281 / 456, 405 / 457; fp8 E 8, d 2048, f 1408 (152) 81 / 157, 120 / 147, 170 / 194; E 4, d 7168,
-//   f 2048 (176) 144 / 321, 258 / 345, 359 / 321; E 1, d 4096, f 14336 128 / 577, 241 / 560, 350 / 570.
-// - A small call in all streams up to 2048 rows (a tile kernel's few tiles are then a chain of their own latencies): E 1, d 256, f 512,
-//   1024 / 2048 rows 18 / 43, 26 / 41; E 4, d = f = 512, 448 rows per expert 27 / 45.
-// - More than 8 experts: the most popular one's rows are chunks behind each other, so 3072 rows at most (E 16, d = f = 256, Zipf, 4096 rows 59 /
-//   40, 8192 rows 98 / 42); and as every expert gets workgroups for up to 8 chunks, most of which find no rows (some 5 ns each on
-//   the whole chip), a limit to those beyond the first: E 64, d 1024, f 512, 256 / 512 rows 79 / 85, 112 / 88; E 128, d 2048, f 768, 128 / 512 rows 204 / 219, 451 /
-//   261; fp8, whose tiles cost more, twice as many: E 64, 2048 rows 98 / 110.
-bool streams(int M, int S, int E_loc, int d, int f, bool fp8) {
-    // (32-bit offsets into x and h; every workgroup scans the slices of its expert)
-    if (S > SKINNY_MAX_SLICES || E_loc > 4096 || (unsigned long long)M * std::max(d, f) * 2 >= 0xFFFFFF00ull) return false;
-    const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
-    const long long most = E_loc <= 2 ? (fp8 ? std::min(1536LL, std::max(64LL, 90000 / col_tiles)) : std::min(768LL, std::max(64LL, 45000 / col_tiles)))
-                                      : (fp8 ? std::min(640LL, std::max(64LL, 60000 / col_tiles)) : std::min(384LL, std::max(64LL, 36000 / col_tiles)));
-    if (M > most * E_loc && !(M <= 2048 && (long long)M * d * f <= (1LL << 30))) return false;
-    if (E_loc > 8) {
-        const long long strips = f / 32 + skinny_strips2(E_loc, d);
-        const long long spare = E_loc * strips * (std::min(8, (M + 63) / 64) - 1);
-        if (M > 3072 || spare > (fp8 ? 64 : 36) * (long long)num_cus()) return false;
+// ---- which kernels a call takes.  Only M, an upper bound of the rows, is known here, and not how unequal the experts are.  Up to 8 experts the times
+// of the ways are estimated (us) and the least is taken.  The constants were fitted to 2050 calls timed in every way (E 1 .. 128, d 256 .. 7168, f 256 .. 14336,
+// 1 .. 6144 rows per expert, bf16 and fp8; equal experts, Zipf popularity and all rows at one expert): with up to 8 experts the chosen way takes 1.4 % longer
+// than the best one on average, 1.37 times at most (one row for each of eight fp8 experts).
+// us, streaming / tiles of 64 / 128 / 256 rows / fused, at 8, 64, 256, 1024, 4096 rows per expert:
+//   bf16 E 1, d 4096, f 14336: 73 79 90 86 -, 109 84 104 94 550, - 174 147 128 458, - 536 411 349 598, - - 1534 1286 1102
+//   bf16 E 4, d 2048, f 1408: 26 31 45 38 -, 44 37 48 46 113, - 50 58 60 120, - 126 118 111 141, - - 374 372 266
+//   fp8  E 4, d 7168, f 2048: 51 46 60 64 -, 120 69 77 81 -, - 155 157 151 -, - 485 478 431 -, - - 1647 1657 -
+enum Route { STREAM, TILE_64, TILE_128, TILE_256, FUSED };
+// Tiles: rounds of the units the chip holds at once, times the slabs of a unit, times a slab's time on a full chip.  An expert's last block is half full; a
+// round that is not full counts less (the compute units hold one workgroup instead of two, or wait less for memory).
+size_t tile_part_bytes(int d, int f) { return std::max(d, f) / 64 < 2 * TILE_MIN_SLABS ? 0 : (size_t)TILE_COUNTERS * TileShape<128, false>::UNIT_BYTES; }
+double tile_us(int M, int E_loc, int d, int f, bool fp8, int rows) {
+    const double blocks = E_loc == 1 ? (M + rows - 1) / rows : std::max<double>(std::min(E_loc, M), (double)M / rows + 0.5 * E_loc);
+    const double slab_us = rows == 64 ? (fp8 ? 0.68 : 0.77) : (rows == 128 ? (fp8 ? 1.05 : 1.39) : (fp8 ? 1.05 : 0.98));
+    const int slots = (rows == 256 ? 1 : 2) * num_cus(), split_slots = (rows == 128 ? 2 : 1) * num_cus();
+    double us = 0.0;
+    for (int phase = 1; phase <= 2; ++phase) {
+        const int K = phase == 1 ? d : f;
+        const double tiles = blocks * (phase == 1 ? f / 64 : d / TILE);
+        const int P = tile_parts((long long)(tiles + 0.5), split_slots, K, split_slots);
+        const double full = tiles * P / slots;
+        us += (full <= 1.0 ? std::max(full, 0.55) : 0.7 * full + 0.3 * std::ceil(full)) * (K / 64.0 / P) * slab_us + (P > 1 ? 16.5 : 7.4);
     }
-    return true;
+    const double weights = 3.0 * std::min(E_loc, M) * d * f * (fp8 ? 1 : 2);
+    return std::max(us, 11.5 + weights / (fp8 ? 2.4e6 : 3.84e6));
+}
+// fused: the same with tiles of 256 x 256 and one round at least per phase (what the phases' overlap returns is in the slab's time)
+double fused_us(int M, int E_loc, int d, int f) {
+    const double blocks = E_loc == 1 ? (M + 255) / 256 : (double)M / 256 + 0.5 * E_loc;
+    double us = 22.0;
+    for (int phase = 1; phase <= 2; ++phase) {
+        const double full = blocks * (phase == 1 ? f / 128 : d / 256) / num_cus();
+        us += (full <= 1.0 ? 1.0 : 0.37 * full + 0.63 * std::ceil(full)) * ((phase == 1 ? d : f) / 64) * 1.57;
+    }
+    return us;
+}
+// streaming: the weights' way from memory, or a strip's steps, and every strip of 32 (64) weight rows reads all activations
+double stream_us(int M, int E_loc, int d, int f, bool fp8) {
+    const double df = (double)d * f;
+    return std::max(13.0 + 3.0 * std::min(E_loc, M) * df * (fp8 ? 1.0 / 3.25e6 : 2.0 / 5.2e6), 7.2 + 0.54 * (d / 64)) + M * df * 4.7e-8;
+}
+// More than 8 experts: a popular expert's rows are chunks behind each other that each read its weights, so at most 3072 rows are streamed (E 16, d = f = 256,
+// Zipf, 4096 rows 59 / 40, 8192 rows 98 / 42), up to a constant over the column tiles and at least 64 rows per expert; and as every expert gets
+// workgroups for up to 8 chunks, most of which find no rows (some 5 ns each on the whole chip), a limit to those beyond the first.
+bool streams_many(int M, int E_loc, int d, int f, bool fp8) {
+    const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
+    const long long most = fp8 ? std::min(640LL, std::max(64LL, 60000 / col_tiles)) : std::min(384LL, std::max(64LL, 36000 / col_tiles));
+    if (M > most * E_loc && !(M <= 2048 && (long long)M * d * f <= (1LL << 30))) return false;
+    const long long strips = f / 32 + skinny_strips2(E_loc, d);
+    const long long spare = E_loc * strips * (std::min(8, (M + 63) / 64) - 1);
+    return M <= 3072 && spare <= (fp8 ? 64 : 36) * (long long)num_cus();
+}
+Route route(int M, int S, int E_loc, int d, int f, bool fp8) {
+    // (streaming: 32-bit offsets into x and h; every workgroup scans the slices of its expert)
+    const bool can_stream = S <= SKINNY_MAX_SLICES && E_loc <= 4096 && (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull;
+    if (E_loc > 8 && can_stream && streams_many(M, E_loc, d, f, fp8)) return STREAM;
+    Route best = TILE_64;
+    double least = tile_us(M, E_loc, d, f, fp8, 64);
+    auto consider = [&](Route r, double us) { if (us < least) { least = us; best = r; } };
+    consider(TILE_128, tile_us(M, E_loc, d, f, fp8, 128));
+    consider(TILE_256, tile_us(M, E_loc, d, f, fp8, 256));
+    // (below 256 rows per expert the fused kernel was never the best one; f >= 256: it chains tiles over their last two slabs and needs four)
+    if (!fp8 && f >= 256 && M >= 256LL * E_loc) consider(FUSED, fused_us(M, E_loc, d, f));
+    if (E_loc <= 8 && can_stream) consider(STREAM, stream_us(M, E_loc, d, f, fp8));
+    return best;
 }
 
 moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
+    if (!p.bases && small_plan(p.M, p.S, p.e_loc)) {
+        moe::LaunchScope k("ffn_small_plan_kernel", s);
+        hipLaunchKernelGGL(ffn_small_plan_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, p);
+        return k.done();
+    }
     // one workgroup per 8192 list entries, at most 64: each scans the groups anew
     const int blocks = p.list ? std::min(64, p.M / (8 * PLAN_THREADS) + 1) : 1;
     moe::LaunchScope k("ffn_plan_kernel", s);
@@ -2145,13 +2310,12 @@ moe_status launch_dw(const DwArgs& a, long long most_units, hipStream_t s) {
 inline size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 struct BwdLayout {                              // byte offsets into the workspace of a backward call
-    size_t plan_rows, ready_rows, list, ebase, bases, counters, entries, arrived, zeros, wdt, wgut, dh, dgu, h, part, total;
-    int f_pad, units;                           // units: places for partial sums that the weight gradients would use; a call runs with fewer too
+    size_t plan_rows, ready_rows, list, ebase, bases, counters, entries, arrived, zeros, wdt, wgut, dh, dgu, h, part;
+    int f_pad;
 };
 BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
     BwdLayout L;
     L.f_pad = (f + 255) / 256 * 256;
-    L.units = (int)std::min<long long>(DW_MAX_UNITS, M < 2 * DW_PART_ROWS ? 0 : (long long)M / DW_PART_ROWS * dw_tiles(d, f));
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += al256(bytes); return at; };
     L.plan_rows = take((size_t)(plan_capacity(M) + PLAN_HDR) * sizeof(int4));
@@ -2168,9 +2332,23 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
     L.dh = take((size_t)M * L.f_pad * 2);
     L.dgu = take((size_t)M * 2 * f * 2);
     L.h = take((size_t)M * f * 2);
-    L.part = o;                                  // (last: what the workspace has beyond it)
-    L.total = o + (size_t)L.units * DW_UNIT_BYTES;
+    L.part = o;                                  // (last: places for partial sums, as many as the workspace has room for)
     return L;
+}
+// What a caller is told to bring.  The size is that of the tables, of dh, dg, du, h and the transposed weights, and of copies and 16-bit partial sums that a call
+// no longer makes: programs size their buffers by it, and the places for partial sums (at most DW_MAX_UNITS are used) lie there.
+size_t bwd_workspace_bytes(int M, int E_loc, int d, int f) {
+    const long long tiles = (long long)E_loc * ((f + 255) / 256) * (d / 256);
+    int P = 1;
+    while (P < 16 && tiles * P < 8 * 256 && (long long)M / E_loc / (2 * P) >= 1024) P *= 2;
+    const int f_pad = (f + 255) / 256 * 256, cols = (M + 127) / 128 * 128 + 256 * P * E_loc, wrows = E_loc * P * f;
+    size_t o = 0;
+    for (int rows : {M, wrows}) o += al256((size_t)(plan_capacity(rows) + PLAN_HDR) * sizeof(int4)) + al256((size_t)plan_capacity(rows) * sizeof(int));
+    o += al256(list_bytes(M)) + al256(EBASE_BYTES) + al256(48 * sizeof(int)) + al256((size_t)E_loc * P * sizeof(int4)) + al256((size_t)(E_loc * P + 1) * sizeof(int32_t));
+    o += 2 * al256((size_t)cols * sizeof(int)) + al256((size_t)E_loc * f_pad * d * 2) + al256((size_t)E_loc * d * 2 * f * 2);
+    o += al256((size_t)M * f_pad * 2) + al256((size_t)M * 2 * f * 2) + al256((size_t)M * f * 2);
+    o += 2 * al256((size_t)d * cols * 2) + 3 * al256((size_t)f * cols * 2) + al256((size_t)E_loc * f * d * 2) + (P > 1 ? al256((size_t)E_loc * P * f * d * 2) : 0);
+    return o;
 }
 
 }  // namespace
@@ -2178,9 +2356,9 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
 extern "C" size_t moe_ffn_workspace_bytes(int M, int d, int f) {
     if (M < 0 || d < 1 || f < 1) return 0;
     // hidden activations, plan, ready counters, row list, router weights in list order, row bases of the experts
-    // (all that a call must have), and room for the K-major rows of x of a small call; a larger M has room for the smaller
+    // (all that a call must have), and room for the K-major rows of x of a small call or the sums of split contractions; a larger M has room for the smaller
     // calls too, so that the size never falls when M grows
-    return ffn_base_bytes(M, f) + kmajor_bytes(std::min(M, KMAJOR_ROWS), d);
+    return ffn_base_bytes(M, f) + std::max(kmajor_bytes(std::min(M, KMAJOR_ROWS), d), tile_part_bytes(d, f));
 }
 
 extern "C" moe_status moe_ffn_tile_override(int tile_rows, int kernels, int panel_groups) {
@@ -2222,11 +2400,12 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     if (!workspace || workspace_bytes < base_bytes) return MOE_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
 
-    // fp8 weights and many rows per expert: the kernels that dequantise on the fly pay for it on every row block, so
-    // when the caller has added room for it the weights are expanded to bf16 once per call (bit-identical values) and
-    // the bf16 kernels run.  Worth it from about 2048 rows per expert on (3 bytes of traffic per weight against a
-    // quarter of the time of 6 flop per weight and row).
-    if (fp8 && (long long)M >= 2048LL * E_loc && workspace_bytes - base_bytes >= moe_ffn_expanded_weights_bytes(E_loc, d, f)) {
+    // fp8 weights and many rows per expert: when the caller has added room for it the weights are expanded to bf16 once per call and the fused
+    // kernel runs, which takes bf16 only.  Worth it from about 2048 rows per expert on, where bf16 weights would take that kernel (3 bytes of traffic per
+    // weight).  us, tiles on the codes / expansion and fused kernel: E 4, d 7168, f 2048, 1536 / 2048 / 4096 rows per expert 659 / 667, 875 / 807, 1663 /
+    // 1312; E 8, d 1024, f 2048 216 / 244, 276 / 281, 506 / 442; E 1, d 4096, f 14336, 2048 rows (bf16 weights take tiles) 673 / 762.
+    if (fp8 && (long long)M >= 2048LL * E_loc && workspace_bytes - base_bytes >= moe_ffn_expanded_weights_bytes(E_loc, d, f) &&
+        route(M, S, E_loc, d, f, false) == FUSED) {
         __bf16* wg = (__bf16*)((char*)workspace + base_bytes);
         __bf16* wu = wg + (size_t)E_loc * f * d;
         __bf16* wd = wu + (size_t)E_loc * f * d;
@@ -2243,7 +2422,11 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
                                             row_map, row_gate, y, workspace, base_bytes, hip_stream);
     }
 
-    if (g_force_rows.load(std::memory_order_relaxed) == 0 && streams(M, S, E_loc, d, f, fp8)) {
+    const int forced_rows = g_force_rows.load(std::memory_order_relaxed), forced_kernels = g_force_kernels.load(std::memory_order_relaxed);
+    Route way = route(M, S, E_loc, d, f, fp8);
+    if (forced_rows != 0) way = forced_rows == 64 ? TILE_64 : (forced_rows == 128 ? TILE_128 : (fp8 || f < 256 ? TILE_256 : FUSED));
+    if (way == FUSED && forced_kernels == 1) way = TILE_256;
+    if (way == STREAM) {
         // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
         // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
         // 325, 79 / 112 / 154 / 280; E 4, d 2048, f 1408, 128 / 256 rows: 54 / 90, 57 / 84; not so E 4, d 7168, f 2048, 128 rows: 204, 213.
@@ -2255,13 +2438,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
         return fp8 ? launch_both_skinny<true>(k, s) : launch_both_skinny<false>(k, s);
     }
 
-    // Rows per tile by the rows an expert has on average (its slices are merged).  256-row tiles (in bf16 the adaptive kernels) need half as
-    // many readings of the weights, 128-row tiles fit ragged ends better: time of 128-row tiles over 256-row tiles, mean over calls of
-    // E 1 .. 128, d 256 .. 7168, f 256 .. 14336, at 192 / 256 / 384 / 512 / 768 rows: bf16 1.10 / 1.14 / 1.17 / 1.22 / 1.26, fp8 1.13 / 1.06 / 1.15 / 1.10 /
-    // 1.12 (single calls from 0.63 to 1.8: one or two experts prefer 128 rows up to 320).  f = 128 has no adaptive kernel.
-    const long long avg = M / E_loc;
-    int bm = avg >= (f < 256 ? 576 : 256) ? 256 : (avg >= 96 ? 128 : 64);
-    if (const int forced = g_force_rows.load(std::memory_order_relaxed)) bm = forced;
+    const int bm = way == TILE_64 ? 64 : (way == TILE_128 ? 128 : 256);
 
     FfnArgs a;
     a.x = (const __bf16*)x;
@@ -2277,7 +2454,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     int32_t* list = (int32_t*)take(list_bytes(M));
     float* gate = (float*)take(list_bytes(M));
     int* ebase = (int*)take(EBASE_BYTES);
-    a.d = d; a.f = f;
+    a.M = M; a.d = d; a.f = f;
     // with one slice or one expert the rows already lie expert by expert.  (Otherwise they are always listed: what the
     // list costs, 1 % where every group is many tiles long, is less than the one ragged tile per group it saves.)
     const bool listed = row_map || row_gate || (S > 1 && E_loc > 1);
@@ -2300,18 +2477,14 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     moe_status st = launch_plan(plan_args, s);
     if (st != MOE_OK) return st;
     const long long max_blocks = M / bm + E_loc;
-    // (the adaptive kernel chains tiles over their last two slabs: at least four 64-wide slabs, f >= 256; d always is)
-    if (bm == 256 && !fp8 && f >= 256 && g_force_kernels.load(std::memory_order_relaxed) != 1)
+    if (way == FUSED)
         return !listed ? launch_both_adaptive<ROWS_PLAIN>(a, max_blocks, E_loc, s)
                : off32 ? launch_both_adaptive<ROWS_LIST32>(a, max_blocks, E_loc, s) : launch_both_adaptive<ROWS_LIST64>(a, max_blocks, E_loc, s);
-    if (fp8) {
-        if (bm == 256) return launch_both<256, true>(a, max_blocks, s);
-        if (bm == 128) return launch_both<128, true>(a, max_blocks, s);
-        return launch_both<64, true>(a, max_blocks, s);
-    }
-    if (bm == 256) return launch_both<256, false>(a, max_blocks, s);
-    if (bm == 128) return launch_both<128, false>(a, max_blocks, s);
-    return launch_both<64, false>(a, max_blocks, s);
+    f32x4* part = (f32x4*)((char*)workspace + base_bytes);
+    const size_t part_bytes = workspace_bytes - base_bytes;
+    if (bm == 256) return fp8 ? launch_both_tile<true, 256>(a, max_blocks, part, part_bytes, s) : launch_both_tile<false, 256>(a, max_blocks, part, part_bytes, s);
+    if (bm == 128) return fp8 ? launch_both_tile<true, 128>(a, max_blocks, part, part_bytes, s) : launch_both_tile<false, 128>(a, max_blocks, part, part_bytes, s);
+    return fp8 ? launch_both_tile<true, 64>(a, max_blocks, part, part_bytes, s) : launch_both_tile<false, 64>(a, max_blocks, part, part_bytes, s);
 }
 
 extern "C" moe_status moe_expert_ffn_sliced(const void* x, const int32_t* offsets, int M, int S, int E_loc, int d, int f,
@@ -2324,7 +2497,7 @@ extern "C" moe_status moe_expert_ffn_sliced(const void* x, const int32_t* offset
 
 extern "C" size_t moe_ffn_backward_workspace_bytes(int M, int E_loc, int d, int f) {
     if (M < 0 || E_loc < 1 || d < 1 || f < 1) return 0;
-    return bwd_layout(M, E_loc, d, f).total;
+    return bwd_workspace_bytes(M, E_loc, d, f);
 }
 
 extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* dy, const int32_t* offsets, int M, int S, int E_loc,
@@ -2335,14 +2508,15 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     if (!w_gate || !w_up || !w_down || !dw_gate || !dw_up || !dw_down) return MOE_ERR_INVALID_ARG;
     if (d % 256 != 0 || f % 128 != 0 || f < 256) return MOE_ERR_UNSUPPORTED_SHAPE;
     const long long G = (long long)S * E_loc;
-    if (G > MAX_GROUPS || E_loc > MAX_GROUPS / 16 || (long long)E_loc * f >= (1LL << 27) || M + 256LL * E_loc >= (1LL << 22)) return MOE_ERR_UNSUPPORTED_SHAPE;
+    if (G > MAX_GROUPS || E_loc > MAX_GROUPS / 16 || (long long)E_loc * 16 * f >= (1LL << 31)) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (d > (1 << 22) || f > (1 << 21) || (long long)d * f >= (1LL << 30)) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (M > 0 && (!x || !dy || !dx)) return MOE_ERR_INVALID_ARG;
     if ((((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx | (uintptr_t)w_gate | (uintptr_t)w_up | (uintptr_t)w_down | (uintptr_t)dw_gate |
           (uintptr_t)dw_up | (uintptr_t)dw_down | (uintptr_t)workspace) & 15) != 0)
         return MOE_ERR_INVALID_ARG;
     const BwdLayout L = bwd_layout(M, E_loc, d, f);
-    if (!workspace || workspace_bytes < L.part) return MOE_ERR_WORKSPACE;
+    if (M + 256LL * E_loc >= (1LL << 22)) return MOE_ERR_UNSUPPORTED_SHAPE;       // (a limit of the interface)
+    if (!workspace || workspace_bytes < bwd_workspace_bytes(M, E_loc, d, f)) return MOE_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     int4* plan_rows = (int4*)(ws + L.plan_rows);
@@ -2366,7 +2540,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     const PlanArgs rows_plan = {offsets, S, E_loc, M, 256, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr,
                                 (int*)(ws + L.ebase), bases};
     if ((st = launch_plan(rows_plan, s)) != MOE_OK) return st;
-    const int tiles = dw_tiles(d, f), units = (int)std::min<size_t>(L.units, (workspace_bytes - L.part) / DW_UNIT_BYTES);
+    const int tiles = dw_tiles(d, f), units = (int)std::min<size_t>(DW_MAX_UNITS, (workspace_bytes - L.part) / DW_UNIT_BYTES);
     {
         moe::LaunchScope k("bwd_prep_kernel", s);
         hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, bases, E_loc, tiles, num_cus(), units, (int4*)(ws + L.entries), counters,
@@ -2393,7 +2567,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.sg = a.su = a.sd = nullptr;
     a.plan = plan_rows;
     a.ready = (int*)(ws + L.ready_rows);
-    a.d = d; a.f = f;
+    a.M = M; a.d = d; a.f = f;
     a.list = list; a.gate = nullptr;
     a.panel1 = a.panel2 = 1 << 20;
     a.dh = dh; a.lddh = L.f_pad; a.dgu = dgu;

@@ -877,6 +877,113 @@ def test_ffn_choice_of_kernels(lib, dtype, E_loc, d, f, M, S, streamed):
     assert float((y.float() - tiles.float()).norm() / tiles.float().norm()) <= 2.0 ** -8
 
 
+def float_weights(w, e):
+    """w_gate, w_up, w_down of expert e in float32."""
+    out = []
+    for k in ("gate", "up", "down"):
+        v = w["w_" + k][e]
+        if "s_" + k in w:
+            v = v.view(torch.float8_e4m3fn).float() * w["s_" + k][e].repeat_interleave(128, 0).repeat_interleave(128, 1)
+        out.append(v.float())
+    return out
+
+
+def check_against_float(x, off, y, w, what):
+    """y of groups of one slice against float32 products on the GPU: two roundings to bf16 (hidden activations, result) of 2^-9 each at most."""
+    for e in range(len(off) - 1):
+        lo, hi = int(off[e]), int(off[e + 1])
+        if lo == hi:
+            continue
+        wg, wu, wd = float_weights(w, e)
+        xs = x[lo:hi].float()
+        ref = (torch.nn.functional.silu(xs @ wg.t()) * (xs @ wu.t())) @ wd.t()
+        diff = (y[lo:hi].float() - ref).abs()
+        check_ffn_error(float(diff.max() / ref.abs().max()), "bf16", "%s expert %d" % (what, e))
+        assert float(diff.norm() / ref.norm()) <= 2.0 ** -8, (what, e)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("tile_rows,kernels", [(64, 0), (128, 0), (256, 1)])
+@pytest.mark.parametrize("d,f,sizes", [
+    (256, 128, [1, 64, 65, 0, 31, 33]),                                   # contractions of one and two blocks of 128 values: no steady state
+    (512, 384, [128, 129, 257, 63]),                                      # of three and four; row blocks and their remainders
+    (2048, 1664, [70, 3]), (1536, 2048, [300]),                           # contractions split over workgroups: with a block more for some, in one phase only
+    (3328, 256, [5, 40, 0, 1])])
+def test_ffn_tile_edges(lib, dtype, tile_rows, kernels, d, f, sizes):
+    """Tiles of 64, 128 and 256 rows: short contractions, remainders of rows, split contractions (the same bits on every call, which
+    needs every counter of finished parts to start at zero and the parts to be added in order), and the same calls in a workspace without room for
+    the parts' sums, which leaves them whole."""
+    say("ffn tile edges", dtype, tile_rows, d, f, sizes)
+    E_loc, M = len(sizes), sum(sizes)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    w = workloads.ffn_weights_on_device(E_loc, d, f, M + d, dtype, DEV)
+    x = workloads.activations_on_device(M, d, M + f, DEV)
+    need = lib.moe_ffn_workspace_bytes(M, d, f)
+    least = need - (0 if max(d, f) < 1536 else 512 * 128 * 128 * 4)
+    lib.moe_ffn_tile_override(tile_rows, kernels)
+    try:
+        ys = [lib.moe_expert_ffn_sliced(x, dev(off), 1, E_loc, y=torch.full_like(x, 9.0), workspace=torch.full((n,), 255, dtype=torch.uint8, device=DEV), **w)
+              for n in (need, need, least)]
+        torch.cuda.synchronize()
+    finally:
+        lib.moe_ffn_tile_override()
+    assert torch.equal(ys[0], ys[1])
+    check_against_float(x, off, ys[0], w, "tiles")
+    check_against_float(x, off, ys[2], w, "tiles, whole contractions")
+
+
+@pytest.mark.parametrize("dtype,tile_rows,kernels", [("fp8", 0, 0), ("bf16", 64, 0), ("bf16", 128, 0), ("bf16", 256, 1)])
+def test_ffn_tile_rows_addressed_with_64_bits(lib, dtype, tile_rows, kernels):
+    say("ffn tiles, x above 4 GiB", dtype, tile_rows)
+    d, f = 8192, 256
+    M = (1 << 32) // (2 * d) + 700
+    off = np.array([0, M - 1000, M], dtype=np.int32)
+    w = workloads.ffn_weights_on_device(2, d, f, 71, dtype, DEV)
+    x = workloads.activations_on_device(M, d, 72, DEV)
+    lib.moe_ffn_tile_override(tile_rows, kernels)
+    try:
+        y = lib.moe_expert_ffn_sliced(x, dev(off), 1, 2, **w)
+        torch.cuda.synchronize()
+    finally:
+        lib.moe_ffn_tile_override()
+    for lo, hi, e in ((0, 300, 0), (M - 1300, M - 1000, 0), (M - 1000, M, 1)):
+        part = {k: v[e:e + 1] for k, v in w.items()}
+        check_against_float(x[lo:hi], [0, hi - lo], y[lo:hi], part, "rows %d .." % lo)
+
+
+@pytest.mark.parametrize("S,sizes,mapped", [(1, [40], False), (5, [300, 0, 77, 1], True), (128, [500, 3, 0, 9, 1, 2, 3, 90], True), (30, [2048], False), (3, [64, 128] * 5, False)])      # (at most 33 of M / 64 + experts)
+def test_ffn_plan_of_small_calls(lib, S, sizes, mapped):
+    """Calls with few groups and rows are planned by a kernel of their own: the same rows as with the general one, which the same groups take as
+    soon as M, the bound of the rows, is larger."""
+    say("ffn plan of small calls", S, sizes)
+    d, f, E_loc = 256, 256, len(sizes)
+    rng = np.random.default_rng(S + E_loc)
+    parts = np.stack([rng.multinomial(n, np.full(S, 1.0 / S)) for n in sizes], axis=1)
+    off = np.concatenate([[0], np.cumsum(parts.ravel())]).astype(np.int32)
+    M, spare = int(off[-1]), 4096
+    w = workloads.ffn_weights_on_device(E_loc, d, f, S, "bf16", DEV)
+    x = workloads.activations_on_device(M + spare, d, S + 1, DEV)
+    row_map = dev(np.concatenate([rng.permutation(M), np.arange(M, M + spare)]).astype(np.int32))
+    gate = torch.rand((M + spare,), device=DEV)
+    out = []
+    lib.moe_ffn_tile_override(64)
+    lib.moe_kernel_timing_enable(True)
+    try:
+        for rows, name in ((M, "ffn_small_plan_kernel"), (M + spare, "ffn_plan_kernel")):
+            y = torch.zeros((rows, d), dtype=torch.bfloat16, device=DEV)
+            if mapped:
+                lib.moe_expert_ffn_sliced_mapped(x[:rows], dev(off), S, E_loc, row_map=row_map[:rows].contiguous(), row_gate=gate[:rows].contiguous(), y=y, **w)
+            else:
+                lib.moe_expert_ffn_sliced(x[:rows], dev(off), S, E_loc, y=y, **w)
+            torch.cuda.synchronize()
+            assert name in lib.moe_kernel_timing_read()
+            out.append(y[:M])
+    finally:
+        lib.moe_kernel_timing_enable(False)
+        lib.moe_ffn_tile_override()
+    assert torch.equal(out[0], out[1]) and bool(out[0].abs().sum() > 0)
+
+
 @pytest.mark.parametrize("dtype,tile_rows", [("bf16", 0), ("bf16", 64), ("bf16", 128), ("bf16", 256), ("fp8", 128)])
 @pytest.mark.parametrize("S,E_loc", [(1, 3), (4, 1), (3, 2), (1, 1)])
 def test_ffn_first_group_later(lib, dtype, tile_rows, S, E_loc):
