@@ -464,74 +464,150 @@ __device__ __forceinline__ int wave_min_scalar(int x) {
     }
     return m;
 }
-template <int NPL, int NW, bool PACKED, typename T>
-__device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 16 : 1], int N, int ld, int r, int lane, int (&u)[NPL],
-                                          int (&v)[NPL], int (&p)[NPL], int (&sigma)[NPL], int& D_end) {
+// Up to 64 ranks a lane's column of the residual lies in registers for the duration of a matching: the row that a search step needs is then picked by a
+// scalar index instead of an LDS round trip.  (Of two columns per lane the compiler makes a table in memory.)
+typedef int i32x16 __attribute__((ext_vector_type(16)));
+typedef int i32x32 __attribute__((ext_vector_type(32)));
+template <int NPL, int NW, typename T> struct Columns {
+    typedef typename std::conditional<NW == 1, i32x16, i32x32>::type Piece;
+    static constexpr int ROWS = NW == 1 ? 16 : 32;
+    Piece q0, q1;                                                         // rows 0 .., 32 ..
+    __device__ __forceinline__ static Piece load_piece(const T* column, int first, int N, int ld) {
+        Piece q;
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) q[i] = (int)column[min(first + i, N - 1) * ld];
+        return q;
+    }
+    __device__ __forceinline__ void load(const T* R, int N, int ld, int lane) {
+        q0 = load_piece(R + min(lane, N - 1), 0, N, ld);
+        if constexpr (NW == 4) q1 = load_piece(R + min(lane, N - 1), 32, N, ld);
+    }
+    __device__ __forceinline__ void row(int i, int (&entry)[NPL]) const { // (i is uniform)
+        int x = q0[i & (ROWS - 1)];
+        if constexpr (NW == 4) x = i & 32 ? (int)q1[i & 31] : x;
+        entry[0] = x;
+    }
+};
+template <int NW, typename T> struct Columns<2, NW, T> {
+    const T *c0, *c1;
+    int ld;
+    __device__ __forceinline__ void load(const T* R, int N, int ld_, int lane) { c0 = R + min(lane, N - 1); c1 = R + min(lane + 64, N - 1); ld = ld_; }
+    __device__ __forceinline__ void row(int i, int (&entry)[2]) const { entry[0] = (int)c0[i * ld]; entry[1] = (int)c1[i * ld]; }
+};
+__device__ __forceinline__ int mad_column(int entry, int mul, int add) {         // (packed keys: entries below 2^21)
+    int r;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(entry), "s"(mul), "v"(add));
+    return r;
+}
+// The search with packed keys.  Everything a step needs to know about the row it goes on with lies with the column
+// that led to it: p[j] = the row that holds column j, uo[j] = that row's u, shifted as in a key.  A search changes the u of the rows whose columns it has
+// scanned, so uo is kept up to date in its own lane, without a shuffle.  (64 ranks, one matrix, 16 matchings: 756 -> 685 us;
+// 128 ranks, 1024 matrices, 32 matchings: 7.24 -> 5.86 ms; 16 and 32 ranks 12 and 15 %.)
+template <int NPL, int NW, typename T>
+__device__ __forceinline__ int search_packed(const Columns<NPL, NW, T>& cols, int N, int r, int lane, int u_r, int (&uo)[NPL], int (&v)[NPL], int (&p)[NPL],
+                                             int& D_end) {
     typedef Packed<NPL> P;
+    constexpr int LOW = (1 << P::SHIFT) - 1;
+    const int scale = -(1 << P::SHIFT);
+    int key[NPL], way[NPL], pot[NPL];
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) {
+        const int j = lane + 64 * s;
+        key[s] = INT_MAX;
+        way[s] = -1;
+        pot[s] = j < N ? (int)((unsigned)v[s] << P::SHIFT) + (p[s] >= 0 ? P::OWNED : 0) + j : P::CLOSED;
+    }
+    int i0 = r, j0 = -1, m = 0, steps = 0;
+    int base = (int)((unsigned)u_r << P::SHIFT);                          // the distance at which row i0 entered the tree, plus its u
+    for (;;) {
+        int entry[NPL], c[NPL], low = INT_MAX;
+        cols.row(i0, entry);
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) {
+            c[s] = mad_column(entry[s], scale, pot[s] + base);
+            way[s] = c[s] < key[s] ? j0 : way[s];
+            key[s] = min(key[s], c[s]);
+            low = min(low, key[s]);
+        }
+        m = wave_min_scalar<NW>(low);                                     // (finite: row r is unmatched, so a column is vacant)
+        j0 = m & (P::OWNED - 1);
+        i0 = bcast<NPL>(p, j0);
+        base = (m & ~LOW) + bcast<NPL>(uo, j0);
+        ++steps;
+#pragma unroll
+        for (int s = 0; s < NPL; ++s) {                                   // (a vacant column that ends the search rises by D - D below)
+            const int shut = key[s] == m ? P::CLOSED : 0;
+            key[s] += shut;
+            pot[s] += shut;
+        }
+        int go = ((m << (31 - P::COL_BITS)) >> 31) & (N - steps);         // (one number: the conjunction would be a chain of scalar selects)
+        asm("" : "+s"(go));
+        if (go <= 0) break;
+    }
+    const int D = m >> P::SHIFT;
+    // duals: a scanned column j rises by D - dist_j, its row falls by the same amount, row r falls by D
+    // (tree edges stay tight, everything stays feasible, the new path is tight)
+#pragma unroll
+    for (int s = 0; s < NPL; ++s) {
+        const int rise = key[s] & P::CLOSED && lane + 64 * s < N ? D - ((key[s] & (P::CLOSED - 1)) >> P::SHIFT) : 0;
+        v[s] += rise;
+        uo[s] -= rise << P::SHIFT;
+    }
+    // flip the path back to row r
+    for (int guard = 0; guard <= N; ++guard) {
+        const int j1 = bcast<NPL>(way, j0);
+        int i = r, us = (int)((unsigned)(u_r - D) << P::SHIFT);
+        if (j1 >= 0) { i = bcast<NPL>(p, j1); us = bcast<NPL>(uo, j1); }
+        set_at<NPL>(p, j0, i, lane);
+        set_at<NPL>(uo, j0, us, lane);
+        if (j1 < 0) break;
+        j0 = j1;
+    }
+    D_end = D;
+    return steps;
+}
+// The search in its plain form, for weights that leave no room in a key: the rows of the residual come from LDS
+template <int NPL, int NW, typename T>
+__device__ __forceinline__ int search_row(const T* R, int N, int ld, int r, int lane, int (&u)[NPL], int (&v)[NPL], int (&p)[NPL], int (&sigma)[NPL]) {
     const Mask<NPL> cols = below<NPL>(N);
     int key[NPL], way[NPL], pot[NPL], at[NPL];
-    Mask<NPL> used, vacant;            // plain form: scanned columns (those that do not exist count as scanned); columns without an owner
+    Mask<NPL> used, vacant;            // scanned columns (those that do not exist count as scanned); columns without an owner
 #pragma unroll
     for (int s = 0; s < NPL; ++s) {
         const int j = lane + 64 * s;
         key[s] = INT_MAX;
         way[s] = -1;
         at[s] = j < N ? j : N - 1;
-        if (PACKED) pot[s] = j < N ? (int)((unsigned)v[s] << P::SHIFT) + (p[s] >= 0 ? P::OWNED : 0) + j : P::CLOSED;
-        else        { pot[s] = v[s]; used.w[s] = ~cols.w[s]; vacant.w[s] = ballot64(p[s] < 0) & cols.w[s]; }
+        pot[s] = v[s];
+        used.w[s] = ~cols.w[s];
+        vacant.w[s] = ballot64(p[s] < 0) & cols.w[s];
     }
     int i0 = r, j0 = -1, D = 0, steps = 0;
     while (steps < N) {
-        int entry[NPL], local = INT_MAX;
-#pragma unroll
-        for (int s = 0; s < NPL; ++s) {
-            if constexpr (NW == 1) entry[s] = Rc[i0 & 15]; else entry[s] = (int)R[i0 * ld + at[s]];
-        }
+        int local = INT_MAX;
         const int base = D + bcast<NPL>(u, i0);                          // row i0 entered the tree at distance D
         int keyed[NPL];
 #pragma unroll
         for (int s = 0; s < NPL; ++s) {
-            if constexpr (PACKED) {
-                const int c = pot[s] + (int)((unsigned)base << P::SHIFT) - (int)((unsigned)entry[s] << P::SHIFT);
-                way[s] = c < key[s] ? j0 : way[s];
-                key[s] = min(key[s], c);
-                local = min(local, key[s]);
-            } else {
-                const bool open = !__builtin_amdgcn_inverse_ballot_w64(used.w[s]);
-                const int c = open ? base + pot[s] - entry[s] : INT_MAX;
-                way[s] = c < key[s] ? j0 : way[s];
-                key[s] = min(key[s], c);
-                keyed[s] = open ? key[s] : INT_MAX;
-                local = min(local, keyed[s]);
-            }
+            const bool open = !__builtin_amdgcn_inverse_ballot_w64(used.w[s]);
+            const int c = open ? base + pot[s] - (int)R[i0 * ld + at[s]] : INT_MAX;
+            way[s] = c < key[s] ? j0 : way[s];
+            key[s] = min(key[s], c);
+            keyed[s] = open ? key[s] : INT_MAX;
+            local = min(local, keyed[s]);
         }
-        const int m = wave_min_scalar<NW>(local);                        // (finite: row r is unmatched, so a column is vacant)
+        D = wave_min_scalar<NW>(local);                                  // (finite: row r is unmatched, so a column is vacant)
         ++steps;
-        if constexpr (PACKED) {
-            D = m >> P::SHIFT;
-            j0 = m & (P::OWNED - 1);
-            if (!(m & P::OWNED)) break;
+        Mask<NPL> eq;
 #pragma unroll
-            for (int s = 0; s < NPL; ++s) {
-                const int shut = key[s] == m ? P::CLOSED : 0;
-                key[s] += shut;
-                pot[s] += shut;
-            }
-        } else {
-            D = m;
-            Mask<NPL> eq;
-#pragma unroll
-            for (int s = 0; s < NPL; ++s) eq.w[s] = ballot64(keyed[s] == m);
-            const Mask<NPL> ends = eq & vacant;
-            const bool last = ends.any();
-            j0 = last ? ends.first() : eq.first();
-            used.set(j0);
-            if (last) break;
-        }
+        for (int s = 0; s < NPL; ++s) eq.w[s] = ballot64(keyed[s] == D);
+        const Mask<NPL> ends = eq & vacant;
+        const bool last = ends.any();
+        j0 = last ? ends.first() : eq.first();
+        used.set(j0);
+        if (last) break;
         i0 = bcast<NPL>(p, j0);
     }
-    // duals: a scanned column j rises by D - dist_j, its row falls by the same amount, row r falls by D
-    // (tree edges stay tight, everything stays feasible, the new path is tight)
     int du[NPL];
 #pragma unroll
     for (int s = 0; s < NPL; ++s) {
@@ -539,25 +615,13 @@ __device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 
         const int src = sg < 0 ? 0 : sg;
         int kc = __shfl(key[0], src & 63);
         if (NPL > 1) { const int k1 = __shfl(key[NPL - 1], src & 63); kc = (src >> 6) ? k1 : kc; }
-        bool rin;
-        if constexpr (PACKED) {
-            rin = sg >= 0 && (kc & P::CLOSED);
-            kc = (kc & (P::CLOSED - 1)) >> P::SHIFT;
-        } else {
-            rin = sg >= 0 && used.test(src);
-        }
-        du[s] = lane + 64 * s == r ? D : (rin ? D - kc : 0);
+        du[s] = lane + 64 * s == r ? D : (sg >= 0 && used.test(src) ? D - kc : 0);
     }
 #pragma unroll
     for (int s = 0; s < NPL; ++s) {
-        if constexpr (PACKED) {
-            if (lane + 64 * s < N && (key[s] & P::CLOSED)) v[s] += D - ((key[s] & (P::CLOSED - 1)) >> P::SHIFT);
-        } else {
-            if (__builtin_amdgcn_inverse_ballot_w64(used.w[s] & cols.w[s])) v[s] += D - key[s];
-        }
+        if (__builtin_amdgcn_inverse_ballot_w64(used.w[s] & cols.w[s])) v[s] += D - key[s];
         u[s] -= du[s];
     }
-    // flip the path back to row r
     for (int guard = 0; guard <= N; ++guard) {
         const int j1 = bcast<NPL>(way, j0);
         int i = r;
@@ -567,7 +631,6 @@ __device__ __forceinline__ int search_row(const T* R, const int (&Rc)[NW == 1 ? 
         if (j1 < 0) break;
         j0 = j1;
     }
-    D_end = D;
     return steps;
 }
 
@@ -819,14 +882,6 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
     while (t < kmax && nnz > 0) {
 #pragma unroll
         for (int s = 0; s < NPL; ++s) { p[s] = -1; sigma[s] = -1; }
-        // N <= 16: this lane's column of the residual sits in registers for the whole matching (a row picked at run time
-        // is then a register selected by a scalar index, not an LDS round trip)
-        int Rc[NW == 1 ? 16 : 1];
-        if constexpr (NW == 1) {
-            const T* col = R + (lane < N ? lane : N - 1);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) Rc[i] = i < N ? (int)col[i * ld] : 0;
-        }
         // ---- column reduction: lower v_j until column j has a tight edge.  The matching before took its entries out of the
         //      residual, which leaves room; the searches below get shorter by it (16 / 64 / 128 ranks: 43 / 378 / 1115 -> 30 / 252 /
         //      872 steps per matching), and it costs no reduction across lanes.
@@ -834,11 +889,7 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
             int top[NPL];
 #pragma unroll
             for (int s = 0; s < NPL; ++s) top[s] = INT_MIN;
-            if constexpr (NW == 1) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (i < N) top[0] = max(top[0], Rc[i] - __builtin_amdgcn_readlane(u[0], i));
-            } else {
+            {
 #pragma unroll
                 for (int half = 0; half < NPL; ++half) {
                     const int rows = min(N - 64 * half, 64);
@@ -875,17 +926,48 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
                 return mu < Packed<NPL>::MOST && mv < Packed<NPL>::MOST ? max(mu, 0) + max(mv, 0) : Packed<NPL>::MOST;
             };
             int bound = dual_bound();
+            {
+                if (todo.any() && bound < Packed<NPL>::MOST) {
+                    Columns<NPL, NW, T> columns;
+                    columns.load(R, N, ld, lane);
+                    int uo[NPL];
+#pragma unroll
+                    for (int s = 0; s < NPL; ++s) {
+                        const int owner = max(p[s], 0);
+                        int x = __shfl(u[0], owner & 63);
+                        if (NPL > 1) { const int y = __shfl(u[NPL - 1], owner & 63); x = owner >> 6 ? y : x; }
+                        uo[s] = (int)((unsigned)x << Packed<NPL>::SHIFT);
+                    }
+                    while (todo.any() && bound < Packed<NPL>::MOST) {
+                        const int r = todo.first();
+                        todo.reset(r);
+                        int D;
+                        n_steps += search_packed<NPL, NW, T>(columns, N, r, lane, bcast<NPL>(u, r), uo, v, p, D);
+                        bound += D;
+                        ++n_searches;
+                    }
+                    // back to the rows: row i's column and u
+#pragma unroll
+                    for (int s = 0; s < NPL; ++s) slot[lane + 64 * s] = -1;
+                    lds_fence();
+#pragma unroll
+                    for (int s = 0; s < NPL; ++s)
+                        if (p[s] >= 0) slot[p[s]] = lane + 64 * s;
+                    lds_fence();
+#pragma unroll
+                    for (int s = 0; s < NPL; ++s) {
+                        const int j = slot[lane + 64 * s], from = max(j, 0);
+                        int x = __shfl(uo[0], from & 63);
+                        if (NPL > 1) { const int y = __shfl(uo[NPL - 1], from & 63); x = from >> 6 ? y : x; }
+                        if (j >= 0) { sigma[s] = j; u[s] = x >> Packed<NPL>::SHIFT; }
+                    }
+                    lds_fence();
+                }
+            }
             while (todo.any()) {
                 const int r = todo.first();
                 todo.reset(r);
-                int D;
-                if (bound < Packed<NPL>::MOST) {
-                    n_steps += search_row<NPL, NW, true>(R, Rc, N, ld, r, lane, u, v, p, sigma, D);
-                    bound += D;
-                    if (bound >= Packed<NPL>::MOST) bound = dual_bound();
-                } else {
-                    n_steps += search_row<NPL, NW, false>(R, Rc, N, ld, r, lane, u, v, p, sigma, D);
-                }
+                n_steps += search_row<NPL, NW, T>(R, N, ld, r, lane, u, v, p, sigma);
                 ++n_searches;
             }
         }
