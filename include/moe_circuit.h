@@ -40,6 +40,7 @@ typedef int moe_status;
 
 /* flags of the decomposition calls */
 #define MOE_DECOMP_ZERO_DIAGONAL 1  /* treat the diagonal (tokens whose expert is local) as zero */
+#define MOE_DECOMP_CLEAR_TAIL    8  /* perms and durations behind the last matching become zero (else they are untouched) */
 /* moe_decompose_greedy keeps the residual of a matrix on chip, in 16 bits when that lets more matrices share a
  * compute unit (N > 64 in batches that fill the chip more than twice over); a matrix with an entry >= 65536 is
  * then decomposed again with a 32-bit residual by a second launch.  Results do not depend on the choice.  The two

@@ -19,6 +19,7 @@ _INCLUDE = os.path.join(os.path.dirname(_HERE), "include")
 MOE_DECOMP_ZERO_DIAGONAL = 1
 MOE_DECOMP_RESIDUAL_I32 = 2
 MOE_DECOMP_RESIDUAL_U16 = 4
+MOE_DECOMP_CLEAR_TAIL = 8
 MOE_W_BF16 = 0
 MOE_W_FP8_E4M3_B128 = 1
 MOE_MAX_RANKS = 128
@@ -185,17 +186,21 @@ def _decomp_buffers(mats, kmax, want_perms, want_residual, want_hashes, out):
     B, N, _ = mats.shape
     dev = mats.device
     out = dict(out or {})
+    # what lies behind the last matching is zero in tensors that are made here, and untouched in the caller's: the kernel clears both
+    # or none (three fills were a tenth of a small layer's time)
+    clear = "perms" not in out and "durations" not in out
+    fresh = torch.empty if clear else torch.zeros
     if "perms" not in out:
-        out["perms"] = torch.zeros((B, kmax, N), dtype=torch.uint8, device=dev) if want_perms else None
+        out["perms"] = fresh((B, kmax, N), dtype=torch.uint8, device=dev) if want_perms else None
     if "durations" not in out:
-        out["durations"] = torch.zeros((B, kmax), dtype=torch.int32, device=dev)
+        out["durations"] = fresh((B, kmax), dtype=torch.int32, device=dev)
     if "counts" not in out:
-        out["counts"] = torch.zeros((B,), dtype=torch.int32, device=dev)
+        out["counts"] = torch.empty((B,), dtype=torch.int32, device=dev)
     if "residual" not in out:
         out["residual"] = torch.empty((B, N, N), dtype=torch.int32, device=dev) if want_residual else None
     if "hashes" not in out:
-        out["hashes"] = torch.zeros((B,), dtype=torch.int64, device=dev) if want_hashes else None
-    return out
+        out["hashes"] = torch.empty((B,), dtype=torch.int64, device=dev) if want_hashes else None
+    return out, MOE_DECOMP_CLEAR_TAIL if clear else 0
 
 
 def moe_decompose_profile(counters=None):
@@ -216,9 +221,9 @@ def moe_decompose_greedy(mats, kmax: int, zero_diag: bool = False, want_perms=Tr
     import torch
     _dev_check(mats, torch.int32, "mats")
     B, N, _ = mats.shape
-    o = _decomp_buffers(mats, kmax, want_perms, want_residual, want_hashes, out)
+    o, clear = _decomp_buffers(mats, kmax, want_perms, want_residual, want_hashes, out)
     _check(load().moe_decompose_greedy(_ptr(mats), B, N, kmax,
-                                       (MOE_DECOMP_ZERO_DIAGONAL if zero_diag else 0)
+                                       (MOE_DECOMP_ZERO_DIAGONAL if zero_diag else 0) | clear
                                        | {0: 0, 32: MOE_DECOMP_RESIDUAL_I32, 16: MOE_DECOMP_RESIDUAL_U16}[residual_bits],
                                        _ptr(o["perms"]), _ptr(o["durations"]), _ptr(o["counts"]), _ptr(o["residual"]),
                                        _ptr(o["hashes"]), _stream()), "moe_decompose_greedy")
@@ -231,10 +236,10 @@ def moe_decompose_bvn(mats, kmax: int, zero_diag: bool = False, want_perms=True,
     import torch
     _dev_check(mats, torch.int32, "mats")
     B, N, _ = mats.shape
-    o = _decomp_buffers(mats, kmax, want_perms, want_residual, want_hashes, out)
+    o, clear = _decomp_buffers(mats, kmax, want_perms, want_residual, want_hashes, out)
     if "pad_total" not in o:
-        o["pad_total"] = torch.zeros((B,), dtype=torch.int32, device=mats.device)
-    _check(load().moe_decompose_bvn(_ptr(mats), B, N, kmax, MOE_DECOMP_ZERO_DIAGONAL if zero_diag else 0,
+        o["pad_total"] = torch.empty((B,), dtype=torch.int32, device=mats.device)
+    _check(load().moe_decompose_bvn(_ptr(mats), B, N, kmax, (MOE_DECOMP_ZERO_DIAGONAL if zero_diag else 0) | clear,
                                     _ptr(o["perms"]), _ptr(o["durations"]), _ptr(o["counts"]), _ptr(o["residual"]),
                                     _ptr(o["pad_total"]), _ptr(o["hashes"]), _stream()), "moe_decompose_bvn")
     return o

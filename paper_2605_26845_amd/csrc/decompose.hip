@@ -426,6 +426,22 @@ __device__ __forceinline__ void emit_matching(const int (&sigma)[NPL], int durat
     }
 }
 
+// MOE_DECOMP_CLEAR_TAIL: the matchings behind the last one are zero.  (16 bytes per lane where the address allows it)
+__device__ __forceinline__ void clear_tail(int t, int kmax, int N, int lane, uint8_t* perms_b, int32_t* dur_b) {
+    if (perms_b) {
+        uint8_t* const end = perms_b + (size_t)kmax * N;
+        uint8_t* at = perms_b + (size_t)t * N;
+        uint8_t* const whole = (uint8_t*)(((uintptr_t)at + 15) & ~(uintptr_t)15);
+        uint8_t* const head = whole < end ? whole : end;
+        for (uint8_t* q = at + lane; q < head; q += MOE_WAVE) *q = 0;
+        at = head + (size_t)(end - head) / 16 * 16;
+        for (uint8_t* q = head + 16 * lane; q < at; q += 16 * MOE_WAVE) *reinterpret_cast<int4*>(q) = make_int4(0, 0, 0, 0);
+        for (uint8_t* q = at + lane; q < end; q += MOE_WAVE) *q = 0;
+    }
+    if (dur_b)
+        for (int i = t + lane; i < kmax; i += MOE_WAVE) dur_b[i] = 0;
+}
+
 // ------------------------------------------------------------------------------ greedy search
 // One shortest augmenting path from the unmatched row r, in Dijkstra form: dist_j = length of the shortest alternating path
 // found so far from row r to column j in the reduced costs u_i + v_j - R_ij of the duals at the start of the search (they
@@ -996,6 +1012,7 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
         emit_matching<NPL>(sigma, dmax, N, lane, t, perms_b, dur_b, hashes ? &fnv : nullptr);
         ++t;
     }
+    if (flags & MOE_DECOMP_CLEAR_TAIL) clear_tail(t, kmax, N, lane, perms_b, dur_b);
     if (lane == 0) {
         counts[b] = t;
         if (hashes) hashes[b] = fnv.h;
@@ -1200,6 +1217,7 @@ void bvn_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags, ui
         }
         lds_fence();
     }
+    if (flags & MOE_DECOMP_CLEAR_TAIL) clear_tail(t, kmax, N, lane, perms_b, dur_b);
     if (lane == 0) {
         counts[b] = broken ? -1 : t;
         if (pad_total) pad_total[b] = target;
@@ -1470,7 +1488,7 @@ extern "C" moe_status moe_decompose_greedy(const int32_t* mats, int B, int N, in
     bool narrow = N > 64 && B > 2 * compute_units();
     if (flags & MOE_DECOMP_RESIDUAL_I32) narrow = false;
     if (flags & MOE_DECOMP_RESIDUAL_U16) narrow = true;
-    const int kflags = flags & MOE_DECOMP_ZERO_DIAGONAL;
+    const int kflags = flags & (MOE_DECOMP_ZERO_DIAGONAL | MOE_DECOMP_CLEAR_TAIL);
     unsigned long long* prof = g_prof.load(std::memory_order_relaxed);
     const int prof_cap = g_prof_cap.load(std::memory_order_relaxed);
     const size_t lds32 = greedy_lds_bytes<int32_t>(N);

@@ -136,6 +136,27 @@ def test_bvn_random(lib, N, density, high, zero_diag):
     check_decomposition(lib, "bvn", mats, oracle.bvn_bound(N) if N <= 65 else 600, zero_diag)
 
 
+@pytest.mark.parametrize("N,kmax", [(5, 3), (7, 26), (8, 50), (13, 20), (16, 60), (65, 9)])
+@pytest.mark.parametrize("which", ["greedy", "bvn"])
+def test_decompose_tail_is_zero(lib, which, N, kmax):
+    """Tensors that the binding makes are zero behind the last matching, whatever the memory held (odd sizes: heads and tails of the 16-byte
+    stores), and where only one of them is the caller's, that one is untouched there."""
+    mats = workloads.random_matrices(5, N, seed=N + kmax, density=0.3, high=40)
+    mats[1] = 0
+    fn = getattr(lib, "moe_decompose_" + which)
+    junk = [torch.full((5 * kmax * N + n,), 0xA5, dtype=torch.uint8, device=DEV) for n in (0, 16 * 5 * kmax)]
+    del junk                                                             # (its memory is what the call's tensors are made of)
+    o = fn(dev(mats), kmax)
+    mine = torch.full((5, kmax), -7, dtype=torch.int32, device=DEV)
+    o2 = fn(dev(mats), kmax, out={"durations": mine})
+    torch.cuda.synchronize()
+    assert int(o["counts"][1]) == 0 and torch.equal(o["perms"], o2["perms"]) and torch.equal(o["counts"], o2["counts"])
+    for b in range(5):
+        c = int(o["counts"][b])
+        assert not bool(o["perms"][b, c:].any()) and not bool(o["durations"][b, c:].any())
+        assert bool((mine[b, c:] == -7).all()) and torch.equal(mine[b, :c], o["durations"][b, :c])
+
+
 def test_decompose_special_cases(lib):
     say("decompose special cases")
     n = 16
