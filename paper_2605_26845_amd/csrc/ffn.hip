@@ -2272,23 +2272,41 @@ __global__ void bwd_zero_kernel(unsigned int* __restrict__ p, size_t n) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
 }
 
-// Batched transpose: dst[b][c][coff + r] (pitch ldd, slices of dstride elements) = src[b][r][c] (R x C, contiguous);
-// rows c in C .. Cpad-1 of dst are zero-filled over the same column range.
+// The weights as the backward pass's row products need them (K contiguous), all three of all experts in one launch:
+// w_down [E][d][f] -> wdt [E][f_pad][d] (rows f .. f_pad - 1 zero);  w_gate, w_up [E][f][d] -> wgut [E][d][2 f] = [gate^T | up^T].
+// HBM bound: 64 x 64 blocks through LDS, 16 bytes per lane both ways (with 2 bytes per lane, in three
+// launches: E 4, d 2048, f 1408, 69 MB each way, 76 us, now 27; E 1, d 4096, f 14336, 352 MB, 294 us, now 129: 5.5 TB/s).
+struct TransposeArgs {
+    const __bf16 *wg, *wu, *wd;
+    __bf16 *wdt, *wgut;
+    int d, f, f_pad, gu_blocks, d_blocks;      // blocks per expert of w_gate (and of w_up), of w_down with its padding
+};
 __global__ __launch_bounds__(256)
-void bwd_transpose_kernel(const __bf16* __restrict__ src, int R, int C, int Cpad, __bf16* __restrict__ dst, long long ldd,
-                          long long dstride, int coff) {
-    __shared__ unsigned short tile[64][66];
-    const int b = blockIdx.z;
-    const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const unsigned short* s16 = reinterpret_cast<const unsigned short*>(src) + (size_t)b * R * C;
-    for (int r = ty; r < 64; r += 4)
-        tile[r][tx] = (r0 + r < R && c0 + tx < C) ? s16[(size_t)(r0 + r) * C + c0 + tx] : (unsigned short)0;
+void bwd_transpose_kernel(TransposeArgs a) {
+    __shared__ unsigned short tile[64][72];                              // [column][row], padded
+    typedef unsigned short us8 __attribute__((ext_vector_type(8)));
+    const int e = blockIdx.y, b = blockIdx.x;
+    const bool down = b >= 2 * a.gu_blocks;
+    const int which = down ? 2 : b / a.gu_blocks, i = down ? b - 2 * a.gu_blocks : b % a.gu_blocks;
+    const int R = down ? a.d : a.f, C = down ? a.f : a.d;                 // of the source
+    const int rows = R / 64, r0 = i % rows * 64, c0 = i / rows * 64;      // (d and f are multiples of 64)
+    const unsigned short* const src = (const unsigned short*)(down ? a.wd : (which ? a.wu : a.wg)) + (size_t)e * R * C;
+    unsigned short* const dst = (unsigned short*)(down ? a.wdt : a.wgut) + (size_t)e * (down ? (size_t)a.f_pad * a.d : (size_t)a.d * 2 * a.f) + (which == 1 ? a.f : 0);
+    const size_t ldd = down ? a.d : 2 * a.f;
+    const int part = threadIdx.x & 7, line = threadIdx.x >> 3;           // 8 lanes per 64 values, 32 lines per pass
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int r = line + 32 * p;
+        us8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (c0 < C) v = *reinterpret_cast<const us8*>(src + (size_t)(r0 + r) * C + c0 + part * 8);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) tile[part * 8 + k][r] = v[k];
+    }
     __syncthreads();
-    unsigned short* d16 = reinterpret_cast<unsigned short*>(dst) + (size_t)b * dstride;
-    for (int r = ty; r < 64; r += 4) {
-        const int c = c0 + r;
-        if (c < Cpad && r0 + tx < R) d16[(size_t)c * ldd + coff + r0 + tx] = tile[tx][r];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int c = line + 32 * p;
+        *reinterpret_cast<us8*>(dst + (size_t)(c0 + c) * ldd + r0 + part * 8) = *reinterpret_cast<const us8*>(&tile[c][part * 8]);
     }
 }
 
@@ -2549,15 +2567,8 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     }
     {
         moe::LaunchScope k("bwd_transpose_kernel", s);
-        const dim3 blk(256);
-        // w_down [E][d][f] -> wdt [E][f_pad][d] (rows f .. f_pad-1 zero)
-        hipLaunchKernelGGL(bwd_transpose_kernel, dim3((d + 63) / 64, (L.f_pad + 63) / 64, E_loc), blk, 0, s, (const __bf16*)w_down, d, f,
-                           L.f_pad, wdt, (long long)d, (long long)L.f_pad * d, 0);
-        // w_gate, w_up [E][f][d] -> wgut [E][d][2f] = [gate^T | up^T]
-        hipLaunchKernelGGL(bwd_transpose_kernel, dim3((f + 63) / 64, (d + 63) / 64, E_loc), blk, 0, s, (const __bf16*)w_gate, f, d, d, wgut,
-                           (long long)2 * f, (long long)d * 2 * f, 0);
-        hipLaunchKernelGGL(bwd_transpose_kernel, dim3((f + 63) / 64, (d + 63) / 64, E_loc), blk, 0, s, (const __bf16*)w_up, f, d, d, wgut,
-                           (long long)2 * f, (long long)d * 2 * f, f);
+        const TransposeArgs t = {(const __bf16*)w_gate, (const __bf16*)w_up, (const __bf16*)w_down, wdt, wgut, d, f, L.f_pad, f / 64 * (d / 64), d / 64 * (L.f_pad / 64)};
+        hipLaunchKernelGGL(bwd_transpose_kernel, dim3(2 * t.gu_blocks + t.d_blocks, E_loc), dim3(256), 0, s, t);
         if ((st = k.done()) != MOE_OK) return st;
     }
 
