@@ -306,9 +306,9 @@ moe_status moe_combine_topk_sum(const void* y, const int32_t* row_of, const floa
  * calls choose the height of their row blocks (64, 128 or 256 rows), the kernel family (both
  * phases in one launch over 256 x 256 tiles, tiles of 128 columns in a launch per phase, or streamed
  * weights) and the order in which the output tiles are walked from the shape of the schedule; this
- * call pins any of these choices for
- * all following moe_expert_ffn_sliced(_mapped) calls of the process, so that every kernel can be
- * driven on small inputs and timed on any input.
+ * call pins any of these choices for all following FFN calls of the process (of the backward pass:
+ * rows and kernels of its row products), so that every kernel can be driven on small inputs and
+ * timed on any input.
  *   tile_rows    0 = chosen per call (the default), else 64, 128 or 256
  *   kernels      0 = chosen per call (the default), 1 = tiles of 128 columns also where 256 x 256
  *                tiles would run, 2 = 256 x 256 tiles with one launch per phase instead of both

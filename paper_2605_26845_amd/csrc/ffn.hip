@@ -33,6 +33,7 @@ constexpr int MAX_GROUPS = 65536;
 constexpr int PLAN_EXPERTS_LDS = 2048; // row bases of the experts kept in LDS by the plan kernel (more: in the workspace)
 constexpr int LIST_PAD = 256;          // valid entries behind the last row of the row list (a row block may read past its end)
 constexpr int TILE_COUNTERS = 512;     // counters per phase of the parts of split contractions (see ffn_tile_kernel; a split call has fewer tiles)
+constexpr int TILE_LAUNCHES = 3;       // launches of such a kernel behind one plan, at most
 constexpr int PLAN_HDR = 5;            // plan[0] = (row blocks, 0, 0, 0); plan[1..2] / plan[3..4] = tile queue counters of phase 1 / 2
 
 struct FfnArgs {
@@ -250,7 +251,7 @@ void ffn_plan_kernel(PlanArgs a) {
         }
     }
     // per row block: column units of h complete (fused kernel); per tile of a split contraction: parts that are done (tile kernel)
-    for (int i = tid; i < min(max(run_full, 2 * TILE_COUNTERS), a.cap); i += PLAN_THREADS) a.ready[i] = 0;
+    for (int i = tid; i < min(max(run_full, TILE_LAUNCHES * TILE_COUNTERS), a.cap); i += PLAN_THREADS) a.ready[i] = 0;
     if (tid == 0) a.plan[0] = make_int4(min(run_full, a.cap), 0, 0, 0);
     if (tid >= 1 && tid < PLAN_HDR) a.plan[tid] = make_int4(0, 0, 0, 0);    // tile queue counters
 }
@@ -269,7 +270,7 @@ void ffn_small_plan_kernel(PlanArgs a) {
     int lo = 0, rows = 0;
     if (e < a.e_loc) rows = group_rows(a.offsets, s * a.e_loc + e, M, lo);
     const int start = a.list ? 0 : first_row(a.offsets, M);
-    for (int i = tid; i < 2 * TILE_COUNTERS && i < a.cap; i += PLAN_THREADS) a.ready[i] = 0;
+    for (int i = tid; i < TILE_LAUNCHES * TILE_COUNTERS && i < a.cap; i += PLAN_THREADS) a.ready[i] = 0;
     int incl = rows;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -1297,7 +1298,10 @@ struct TileArgs {
     int* arrived;                      // [TILE_COUNTERS] parts of the tile that are done
     int slots, cap;
 };
-template <int PHASE, bool FP8, int ROWS, bool WIDE>
+// What a launch computes.  FORWARD: phase 1 or 2 of the forward pass.  The backward pass's row products: BWD_DH = phase 2's arithmetic with listed rows in and
+// plain rows out (dh = dy Wd), BWD_ACT = phase 1 with the gradient read-out (EPI 1 of the adaptive kernel), BWD_DX = phase 2's without router weights.
+enum { FORWARD = 0, BWD_DH = 1, BWD_ACT = 2, BWD_DX = 3 };
+template <int PHASE, bool FP8, int ROWS, bool WIDE, int KIND>
 __global__ __launch_bounds__((TileShape<ROWS, FP8>::THREADS), 2)
 void ffn_tile_kernel(TileArgs t) {
     typedef TileShape<ROWS, FP8> S;
@@ -1308,7 +1312,8 @@ void ffn_tile_kernel(TileArgs t) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1, l31 = lane & 31, lhi = lane >> 5;
-    const int K = PHASE == 1 ? a.d : a.f, NT = PHASE == 1 ? a.f / 64 : a.d / TILE;
+    constexpr bool LISTED_IN = PHASE == 1 || KIND == BWD_DH, LISTED_OUT = PHASE == 2 && KIND != BWD_DH;
+    const int K = PHASE == 1 ? a.d : a.g2.K, NT = PHASE == 1 ? a.f / 64 : a.g2.NU * 2;
     const int nblocks = a.plan[0].x;
     const int P = tile_parts((long long)nblocks * NT, t.slots, K, t.cap);
     // workgroup -> unit: every die (workgroup number modulo 8) takes a stretch of the units; row blocks are innermost, so that those which share
@@ -1328,11 +1333,11 @@ void ffn_tile_kernel(TileArgs t) {
     // Rows past the end lie behind the buffer descriptor: zeros are deposited, from no memory.  WIDE: x or h does not fit 32-bit offsets.
     const unsigned char* a_ptr[WIDE ? 4 : 1];
     unsigned int a_voff[4];
-    const __bf16* const A = PHASE == 1 ? a.x : (const __bf16*)a.h;
+    const __bf16* const A = PHASE == 1 ? a.x : a.g2.A;                      // (row pitch K)
 #pragma unroll
     for (int i = 0; i < CA; ++i) {
         const int r = row0 + RPC * i, m = m0 + min(r, rows - 1);
-        const unsigned int row = (unsigned int)(PHASE == 1 ? mapped_row(a, m) : m);
+        const unsigned int row = (unsigned int)(LISTED_IN ? mapped_row(a, m) : m);
         if (WIDE) a_ptr[WIDE ? i : 0] = (const unsigned char*)(A + (size_t)row * K) + (size_t)kb0 * 256 + kcg * 16;     // (repeats the last row)
         else      a_voff[i] = r < rows ? row * (unsigned int)K * 2u + (unsigned int)kb0 * 256u + (unsigned int)kcg * 16u : 0xFFFFFF00u;
     }
@@ -1344,7 +1349,7 @@ void ffn_tile_kernel(TileArgs t) {
         const size_t at = ((size_t)e * a.f + (size_t)nt * 64) * pitch;
         b_lo = (const unsigned char*)a.wg + at; b_hi = (const unsigned char*)a.wu + at;
     } else {
-        b_lo = (const unsigned char*)a.wd + ((size_t)e * a.d + (size_t)nt * TILE) * pitch; b_hi = b_lo + 64 * pitch;
+        b_lo = (const unsigned char*)a.g2.B + ((size_t)e * a.g2.strideB + (size_t)nt * TILE * K) * ESZ; b_hi = b_lo + 64 * pitch;
     }
     b_lo += (size_t)kb0 * 128 * ESZ; b_hi += (size_t)kb0 * 128 * ESZ;
     const unsigned int b_voff = (unsigned int)row0 * (unsigned int)pitch + (unsigned int)kcg * 16u;
@@ -1577,28 +1582,58 @@ void ffn_tile_kernel(TileArgs t) {
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
         const int wrow = m0 + wm * 32 * MB + mb * 32;
-        float gate = 1.0f;
-        if (PHASE == 2 && a.gate) gate = a.gate[min(wrow + l31, m_end - 1)];
+        auto stage4 = [&](int q, int g, float v0, float v1, float v2, float v3) __attribute__((always_inline)) {
+            *reinterpret_cast<u32x2*>(stage + l31 * SROW + (((q * 4 + g) ^ swz_out(l31)) << 4) + lhi * 8) = pack4(v0, v1, v2, v3);
+        };
+        auto store = [&](__bf16* base, int ld, int col, bool listed) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < (PHASE == 1 ? 1 : 2); ++q)
+            for (int i = 0; i < 32 / RPI; ++i) {
+                const int r = i * RPI + sr, m = wrow + r;
+                const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * SROW + ((sc ^ swz_out(r)) << 4));
+                if (m < m_end) *reinterpret_cast<u32x4*>(base + (size_t)(unsigned int)(listed ? mapped_row(a, m) : m) * ld + col + sc * 8) = v;
+            }
+        };
+        if constexpr (PHASE == 1) {
+            const int col = nt * 64 + wn * 32;
+            if constexpr (KIND == BWD_ACT) {
+                // h, then dg = dh * u * silu'(g) and du = dh * silu(g), left in the accumulators of g and u
+                const __bf16* const src = a.dh + (size_t)(unsigned int)min(wrow + l31, m_end - 1) * a.lddh + col + lhi * 4;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float o[4];
+                for (int g = 0; g < 4; ++g) {
+                    const bf16x4 d4 = __builtin_bit_cast(bf16x4, *reinterpret_cast<const u32x2*>(src + g * 8));
+                    float hv[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const float v = acc[mb][q][g * 4 + j];
-                    o[j] = PHASE == 1 ? silu(v) * acc[mb][1][g * 4 + j] : gate * v;
+                    for (int j = 0; j < 4; ++j) {
+                        const float gv = acc[mb][0][g * 4 + j], uv = acc[mb][1][g * 4 + j], dv = (float)d4[j];
+                        const float sig = __builtin_amdgcn_rcpf(1.0f + __expf(-gv));
+                        hv[j] = (gv * sig) * uv;
+                        acc[mb][0][g * 4 + j] = dv * uv * (sig * (1.0f + gv * (1.0f - sig)));
+                        acc[mb][1][g * 4 + j] = dv * (gv * sig);
+                    }
+                    stage4(0, g, hv[0], hv[1], hv[2], hv[3]);
                 }
-                *reinterpret_cast<u32x2*>(stage + l31 * SROW + (((q * 4 + g) ^ swz_out(l31)) << 4) + lhi * 8) = pack4(o[0], o[1], o[2], o[3]);
-            }
+                store(a.h, a.f, col, false);
 #pragma unroll
-        for (int i = 0; i < 32 / RPI; ++i) {
-            const int r = i * RPI + sr, m = wrow + r;
-            const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * SROW + ((sc ^ swz_out(r)) << 4));
-            if (m < m_end) {
-                if (PHASE == 1) *reinterpret_cast<u32x4*>(a.h + (size_t)(unsigned int)m * a.f + nt * 64 + wn * 32 + sc * 8) = v;
-                else            *reinterpret_cast<u32x4*>(a.y + (size_t)(unsigned int)mapped_row(a, m) * a.d + nt * TILE + wn * 64 + sc * 8) = v;
+                for (int q = 0; q < 2; ++q) {
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) stage4(0, g, acc[mb][q][g * 4], acc[mb][q][g * 4 + 1], acc[mb][q][g * 4 + 2], acc[mb][q][g * 4 + 3]);
+                    store(a.dgu + (q ? a.f : 0), 2 * a.f, col, false);
+                }
+            } else {
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    stage4(0, g, silu(acc[mb][0][g * 4]) * acc[mb][1][g * 4], silu(acc[mb][0][g * 4 + 1]) * acc[mb][1][g * 4 + 1],
+                           silu(acc[mb][0][g * 4 + 2]) * acc[mb][1][g * 4 + 2], silu(acc[mb][0][g * 4 + 3]) * acc[mb][1][g * 4 + 3]);
+                store(a.h, a.f, col, false);
             }
+        } else {
+            float gate = 1.0f;
+            if (KIND == FORWARD && a.gate) gate = a.gate[min(wrow + l31, m_end - 1)];
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) stage4(q, g, gate * acc[mb][q][g * 4], gate * acc[mb][q][g * 4 + 1], gate * acc[mb][q][g * 4 + 2], gate * acc[mb][q][g * 4 + 3]);
+            store(a.g2.O, a.g2.ldo, nt * TILE + wn * 64, LISTED_OUT);
         }
     }
 }
@@ -1709,35 +1744,41 @@ moe_status launch_both_adaptive(const FfnArgs& a, long long max_blocks, int E_lo
     return launch_adaptive<2, ROWS_PLAIN, ROWS>(a, max_blocks * (a.d / 256), s);
 }
 
-template <int PHASE, bool FP8, int ROWS, bool WIDE>
+template <int PHASE, bool FP8, int ROWS, bool WIDE, int KIND>
 moe_status launch_tile(const TileArgs& a, long long max_blocks, hipStream_t s) {
     typedef TileShape<ROWS, FP8> S;
     static moe::DeviceOnce attr;
-    auto kern = ffn_tile_kernel<PHASE, FP8, ROWS, WIDE>;
+    auto kern = ffn_tile_kernel<PHASE, FP8, ROWS, WIDE, KIND>;
     int dev;
     if (attr.needed(dev)) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::LDS);
         if (e != hipSuccess) { moe::note_hip_error(e, "hipFuncSetAttribute(MaxDynamicSharedMemorySize)"); return MOE_ERR_HIP; }
         attr.mark(dev);
     }
-    const long long units = std::max<long long>(max_blocks * (PHASE == 1 ? a.a.f / 64 : a.a.d / TILE), a.cap > 0 ? a.slots : 0);
-    moe::LaunchScope k(PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
+    const long long units = std::max<long long>(max_blocks * (PHASE == 1 ? a.a.f / 64 : a.a.g2.NU * 2), a.cap > 0 ? a.slots : 0);
+    moe::LaunchScope k(KIND == BWD_DH ? "ffn_bwd_dh_kernel" : KIND == BWD_ACT ? "ffn_bwd_act_kernel" : KIND == BWD_DX ? "ffn_bwd_dx_kernel"
+                       : PHASE == 1 ? "ffn_gemm1_kernel" : "ffn_gemm2_kernel", s);
     hipLaunchKernelGGL(kern, dim3((unsigned int)((units + 7) / 8 * 8)), dim3(S::THREADS), S::LDS, s, a);
     return k.done();
 }
-template <bool FP8, int ROWS>
-moe_status launch_both_tile(const FfnArgs& a, long long max_blocks, f32x4* part, size_t part_bytes, hipStream_t s) {
+// One launch; `counters`: which TILE_COUNTERS of the plan's it uses
+template <int PHASE, bool FP8, int ROWS, int KIND>
+moe_status launch_tiles(const FfnArgs& a, int counters, long long max_blocks, f32x4* part, size_t part_bytes, hipStream_t s) {
+    typedef TileShape<ROWS, FP8> S;
     TileArgs t;
     t.a = a;
     t.part = part;
-    t.slots = TileShape<ROWS, FP8>::SPLIT_PER_CU * num_cus();
-    t.cap = (int)std::min<size_t>(part_bytes / TileShape<ROWS, FP8>::UNIT_BYTES, (size_t)t.slots);
-    t.arrived = a.ready;
-    const bool wide = (unsigned long long)a.M * std::max(a.d, a.f) * 2 >= 0xFFFFFF00ull;
-    moe_status st = wide ? launch_tile<1, FP8, ROWS, true>(t, max_blocks, s) : launch_tile<1, FP8, ROWS, false>(t, max_blocks, s);
+    t.slots = S::SPLIT_PER_CU * num_cus();
+    t.cap = (int)std::min<size_t>(part_bytes / S::UNIT_BYTES, (size_t)t.slots);
+    t.arrived = a.ready + counters * TILE_COUNTERS;
+    const bool wide = (unsigned long long)a.M * (PHASE == 1 ? a.d : a.g2.K) * 2 >= 0xFFFFFF00ull;
+    return wide ? launch_tile<PHASE, FP8, ROWS, true, KIND>(t, max_blocks, s) : launch_tile<PHASE, FP8, ROWS, false, KIND>(t, max_blocks, s);
+}
+template <bool FP8, int ROWS>
+moe_status launch_both_tile(const FfnArgs& a, long long max_blocks, f32x4* part, size_t part_bytes, hipStream_t s) {
+    const moe_status st = launch_tiles<1, FP8, ROWS, FORWARD>(a, 0, max_blocks, part, part_bytes, s);
     if (st != MOE_OK) return st;
-    t.arrived = a.ready + TILE_COUNTERS;
-    return wide ? launch_tile<2, FP8, ROWS, true>(t, max_blocks, s) : launch_tile<2, FP8, ROWS, false>(t, max_blocks, s);
+    return launch_tiles<2, FP8, ROWS, FORWARD>(a, 1, max_blocks, part, part_bytes, s);
 }
 
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
@@ -1856,6 +1897,13 @@ Route route(int M, int S, int E_loc, int d, int f, bool fp8) {
     if (!fp8 && f >= 256 && M >= 256LL * E_loc) consider(FUSED, fused_us(M, E_loc, d, f));
     if (E_loc <= 8 && can_stream) consider(STREAM, stream_us(M, E_loc, d, f, fp8));
     return best;
+}
+
+// the choice that moe_ffn_tile_override has pinned, if any
+Route pinned(Route way, int f, bool fp8) {
+    const int rows = g_force_rows.load(std::memory_order_relaxed);
+    if (rows != 0) way = rows == 64 ? TILE_64 : (rows == 128 ? TILE_128 : (fp8 || f < 256 ? TILE_256 : FUSED));
+    return way == FUSED && g_force_kernels.load(std::memory_order_relaxed) == 1 ? TILE_256 : way;
 }
 
 moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
@@ -2440,10 +2488,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
                                             row_map, row_gate, y, workspace, base_bytes, hip_stream);
     }
 
-    const int forced_rows = g_force_rows.load(std::memory_order_relaxed), forced_kernels = g_force_kernels.load(std::memory_order_relaxed);
-    Route way = route(M, S, E_loc, d, f, fp8);
-    if (forced_rows != 0) way = forced_rows == 64 ? TILE_64 : (forced_rows == 128 ? TILE_128 : (fp8 || f < 256 ? TILE_256 : FUSED));
-    if (way == FUSED && forced_kernels == 1) way = TILE_256;
+    const Route way = pinned(route(M, S, E_loc, d, f, fp8), f, fp8);
     if (way == STREAM) {
         // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
         // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
@@ -2555,7 +2600,12 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     const bool listed = S > 1 && E_loc > 1;      // else the rows already lie expert by expert
     int32_t* list = listed ? (int32_t*)(ws + L.list) : nullptr;
     int* bases = (int*)(ws + L.bases);
-    const PlanArgs rows_plan = {offsets, S, E_loc, M, 256, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr,
+    // The row products run in tiles of 128 columns where the forward pass would (see route: the shapes are alike), with few rows of 64 where it would stream.
+    // us, whole call with 256 x 256 tiles / now: E 4, d 2048, f 1408, 200 / 1000 / 4000 rows 260 / 122, 300 / 159, 540 / 299; E 1, d 4096, f 14336, 200 / 1000 / 4000 rows 1190 / 510, 1630 /
+    // 1067, 3450 / 3171; E 8, d 1024, f 640, 1000 / 4000 rows 190 / 95, 270 / 153.
+    const Route way = pinned(route(M, S, E_loc, d, f, false), f, false);
+    const int bm = way == TILE_64 || way == STREAM ? 64 : (way == TILE_128 ? 128 : 256);
+    const PlanArgs rows_plan = {offsets, S, E_loc, M, bm, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr,
                                 (int*)(ws + L.ebase), bases};
     if ((st = launch_plan(rows_plan, s)) != MOE_OK) return st;
     const int tiles = dw_tiles(d, f), units = (int)std::min<size_t>(DW_MAX_UNITS, (workspace_bytes - L.part) / DW_UNIT_BYTES);
@@ -2590,6 +2640,9 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     auto workgroups = [&](int units, int K) -> long long { return K >= 4096 ? num_cus() : 2LL * (M / 256 + E_loc) * units; };
     const bool off32 = (unsigned long long)M * d * 2 < 0xFFFFFF00ull;
 
+    f32x4* const part = (f32x4*)(ws + L.part);
+    const size_t part_bytes = workspace_bytes - L.part;
+    const long long max_blocks = M / bm + E_loc;
     // ---- dh = dy Wd: rows x f_pad, K = d
     a.g2.A = (const __bf16*)dy; a.g2.lda = d;
     a.g2.B = wdt; a.g2.ldb = d; a.g2.strideB = (long long)L.f_pad * d;
@@ -2597,12 +2650,18 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.g2.K = d; a.g2.NU = L.f_pad / 256;
     a.g2.queues = counters + 0;
     a.g2.o_bytes = 0;
-    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dh_kernel")
+    st = way != FUSED ? (bm == 64    ? launch_tiles<2, false, 64, BWD_DH>(a, 0, max_blocks, part, part_bytes, s)
+                         : bm == 128 ? launch_tiles<2, false, 128, BWD_DH>(a, 0, max_blocks, part, part_bytes, s)
+                                     : launch_tiles<2, false, 256, BWD_DH>(a, 0, max_blocks, part, part_bytes, s))
+       : !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dh_kernel")
        : off32   ? launch_adaptive<2, ROWS_LIST32, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dh_kernel")
                  : launch_adaptive<2, ROWS_LIST64, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dh_kernel");
     if (st != MOE_OK) return st;
     // ---- g, u recomputed; dg, du, h
-    st = !listed ? launch_adaptive<1, ROWS_PLAIN, ROWS_PLAIN, 1>(a, workgroups(f / 128, d), s, "ffn_bwd_act_kernel")
+    st = way != FUSED ? (bm == 64    ? launch_tiles<1, false, 64, BWD_ACT>(a, 1, max_blocks, part, part_bytes, s)
+                         : bm == 128 ? launch_tiles<1, false, 128, BWD_ACT>(a, 1, max_blocks, part, part_bytes, s)
+                                     : launch_tiles<1, false, 256, BWD_ACT>(a, 1, max_blocks, part, part_bytes, s))
+       : !listed ? launch_adaptive<1, ROWS_PLAIN, ROWS_PLAIN, 1>(a, workgroups(f / 128, d), s, "ffn_bwd_act_kernel")
        : off32   ? launch_adaptive<1, ROWS_LIST32, ROWS_PLAIN, 1>(a, workgroups(f / 128, d), s, "ffn_bwd_act_kernel")
                  : launch_adaptive<1, ROWS_LIST64, ROWS_PLAIN, 1>(a, workgroups(f / 128, d), s, "ffn_bwd_act_kernel");
     if (st != MOE_OK) return st;
@@ -2613,7 +2672,10 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.g2.K = 2 * f; a.g2.NU = d / 256;
     a.g2.queues = counters + 16;
     a.g2.o_bytes = off32 ? (unsigned int)M * (unsigned int)d * 2u : 0u;
-    st = !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel")
+    st = way != FUSED ? (bm == 64    ? launch_tiles<2, false, 64, BWD_DX>(a, 2, max_blocks, part, part_bytes, s)
+                         : bm == 128 ? launch_tiles<2, false, 128, BWD_DX>(a, 2, max_blocks, part, part_bytes, s)
+                                     : launch_tiles<2, false, 256, BWD_DX>(a, 2, max_blocks, part, part_bytes, s))
+       : !listed ? launch_adaptive<2, ROWS_PLAIN, ROWS_PLAIN>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel")
        : off32   ? launch_adaptive<2, ROWS_PLAIN, ROWS_LIST32>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel")
                  : launch_adaptive<2, ROWS_PLAIN, ROWS_LIST64>(a, workgroups(a.g2.NU, a.g2.K), s, "ffn_bwd_dx_kernel");
     if (st != MOE_OK) return st;
@@ -2625,7 +2687,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     w.entries = (const int4*)(ws + L.entries);
     w.queues = counters + DW_QUEUES;
     w.arrived = (int*)(ws + L.arrived);
-    w.part = (f32x4*)(ws + L.part);
+    w.part = part;
     w.zeros = (const unsigned char*)(ws + L.zeros);
     w.dwg = (__bf16*)dw_gate; w.dwu = (__bf16*)dw_up; w.dwd = (__bf16*)dw_down;
     w.M = M; w.d = d; w.f = f;

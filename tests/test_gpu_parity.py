@@ -1175,6 +1175,35 @@ def test_ffn_backward_weight_gradient_slabs(lib, f, S, sizes):
                 check_ffn_error(float(np.abs(got[e] - want[e]).max() / np.abs(want[e]).max()), "bf16", "%s[%d] of %s" % (name, e, sizes))
 
 
+@pytest.mark.parametrize("tile_rows,kernels", [(64, 0), (128, 0), (256, 1), (256, 0)])
+@pytest.mark.parametrize("d,f,S,sizes", [(256, 384, 3, [300, 0, 1, 64]), (512, 1664, 1, [65, 130]), (1536, 256, 2, [129, 7])])
+def test_ffn_backward_row_products(lib, tile_rows, kernels, d, f, S, sizes):
+    """dh, the gradient read-out and dx in tiles of every height (listed rows and rows in order, contractions split over workgroups where d or 2 f
+    are long), twice with the same bits, against the float64 chain rule."""
+    say("ffn backward row products", tile_rows, kernels, d, f, S, sizes)
+    E_loc, M = len(sizes), sum(sizes)
+    rng = np.random.default_rng(d + f)
+    parts = np.stack([rng.multinomial(n, np.full(S, 1.0 / S)) for n in sizes], axis=1)
+    off = np.concatenate([[0], np.cumsum(parts.ravel())]).astype(np.int32)
+    W = workloads.ffn_weights(E_loc, d, f, seed=d + f)
+    w = upload_weights(W)
+    x, dy = workloads.activations(M, d, seed=f + 1), workloads.activations(M, d, seed=f + 2)
+    lib.moe_ffn_tile_override(tile_rows, kernels)
+    try:
+        out, again = [lib.moe_expert_ffn_backward_sliced(dev_bf16(x), dev_bf16(dy), dev(off), S, E_loc, w["w_gate"], w["w_up"], w["w_down"]) for _ in range(2)]
+        torch.cuda.synchronize()
+    finally:
+        lib.moe_ffn_tile_override()
+    ref = oracle.expert_ffn_backward_sliced(x, dy, off, E_loc, W)
+    check_ffn_error(ffn_error(host_bf16_bits(out["dx"]), ref[0], off), "bf16", "dx")
+    for name, want in zip(("dw_gate", "dw_up", "dw_down"), ref[1:]):
+        got = oracle.decode_bf16(host_bf16_bits(out[name]))
+        for e in range(E_loc):
+            if sizes[e]:
+                check_ffn_error(float(np.abs(got[e] - want[e]).max() / np.abs(want[e]).max()), "bf16", "%s[%d]" % (name, e))
+    assert all(torch.equal(out[k], again[k]) for k in out)
+
+
 def test_ffn_backward_edge_cases(lib):
     say("ffn backward edge cases")
     # an expert without rows (zero weight gradients), a single row, no rows at all
