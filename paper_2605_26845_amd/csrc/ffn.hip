@@ -18,6 +18,7 @@
 #include "rows.hpp"
 #include <type_traits>
 #include <algorithm>
+#include <cmath>
 
 namespace {
 
@@ -1816,7 +1817,15 @@ moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
 // Weight rows per workgroup: 64 (the 64 rows of activations are then fetched as often as the weights), but 16 in phase 2 when
 // the strips of 64 would leave half the compute units idle: d = 4096, f = 14336, one expert, phase 2 at 37 rows: 64 rows 75 us,
 // 16 rows 39 us; d = 7168, f = 2048, four fp8 experts, 203 rows: 28 us, 59 us.
-int skinny_strips2(int E_loc, int d) { return (long long)(d / 64) * E_loc >= num_cus() / 2 ? d / 64 : d / 16; }     // strips per expert in phase 2
+// Up to 32 rows it is the experts that can hold rows which count, not all of them, and a strip's chain over f costs more than the activations (at most
+// two 16-row tiles): 16 rows below three strips per four compute units, as long as the workgroups of the other experts are few (they leave at once, some 5 ns each).
+// 64 / 16 rows, us: E 2, d 4096, f 14336, 1 / 8 rows 104 / 68, 156 / 136, in fp8 68 / 46, 96 / 83; E 8, d 1280, f 5248, 1 / 8 rows 34 / 21, 55 / 51; E 2, d 6912,
+// f 3968, 1 / 8 rows (108 and 216 strips) 51 / 46, 66 / 67; E 8, d 7168, f 2048, one row (3584 workgroups) 42 / 43, in fp8 27 / 29.
+int skinny_strips2(int M, int E_loc, int d) {                              // strips per expert in phase 2
+    const int cus = num_cus(), wide = d / 64, narrow = d / 16;
+    if ((long long)wide * E_loc < cus / 2) return narrow;
+    return M <= 32 && 4LL * wide * std::min(E_loc, M) < 3LL * cus && (long long)narrow * E_loc <= 8LL * cus ? narrow : wide;
+}
 template <bool FP8>
 moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
     moe_status st;
@@ -1827,14 +1836,14 @@ moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
         if ((st = k.done()) != MOE_OK) return st;
     }
     if ((st = launch_skinny<1, 4, 4, 2, FP8>(a, s)) != MOE_OK) return st;
-    if (skinny_strips2(a.E, a.d) == a.d / 64) return launch_skinny<2, 4, 4, 2, FP8>(a, s);
+    if (skinny_strips2(a.M, a.E, a.d) == a.d / 64) return launch_skinny<2, 4, 4, 2, FP8>(a, s);
     return launch_skinny<2, 4, 1, 4, FP8>(a, s);
 }
 
 // ---- which kernels a call takes.  Only M, an upper bound of the rows, is known here, and not how unequal the experts are.  Up to 8 experts the times
 // of the ways are estimated (us) and the least is taken.  The constants were fitted to 2050 calls timed in every way (E 1 .. 128, d 256 .. 7168, f 256 .. 14336,
 // 1 .. 6144 rows per expert, bf16 and fp8; equal experts, Zipf popularity and all rows at one expert): with up to 8 experts the chosen way takes 1.4 % longer
-// than the best one on average, 1.37 times at most (one row for each of eight fp8 experts).
+// than the best one on average.  (Up to 32 rows: streams_few.)
 // us, streaming / tiles of 64 / 128 / 256 rows / fused, at 8, 64, 256, 1024, 4096 rows per expert:
 //   bf16 E 1, d 4096, f 14336: 73 79 90 86 -, 109 84 104 94 550, - 174 147 128 458, - 536 411 349 598, - - 1534 1286 1102
 //   bf16 E 4, d 2048, f 1408: 26 31 45 38 -, 44 37 48 46 113, - 50 58 60 120, - 126 118 111 141, - - 374 372 266
@@ -1846,7 +1855,7 @@ size_t tile_part_bytes(int d, int f) { return std::max(d, f) / 64 < 2 * TILE_MIN
 double tile_us(int M, int E_loc, int d, int f, bool fp8, int rows) {
     const double blocks = E_loc == 1 ? (M + rows - 1) / rows : std::max<double>(std::min(E_loc, M), (double)M / rows + 0.5 * E_loc);
     const double slab_us = rows == 64 ? (fp8 ? 0.68 : 0.77) : (rows == 128 ? (fp8 ? 1.05 : 1.39) : (fp8 ? 1.05 : 0.98));
-    const int slots = (rows == 256 ? 1 : 2) * num_cus(), split_slots = (rows == 128 ? 2 : 1) * num_cus();
+    const int cus = num_cus(), slots = (rows == 256 ? 1 : 2) * cus, split_slots = (rows == 128 ? 2 : 1) * cus;
     double us = 0.0;
     for (int phase = 1; phase <= 2; ++phase) {
         const int K = phase == 1 ? d : f;
@@ -1880,14 +1889,47 @@ bool streams_many(int M, int E_loc, int d, int f, bool fp8) {
     const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
     const long long most = fp8 ? std::min(640LL, std::max(64LL, 60000 / col_tiles)) : std::min(384LL, std::max(64LL, 36000 / col_tiles));
     if (M > most * E_loc && !(M <= 2048 && (long long)M * d * f <= (1LL << 30))) return false;
-    const long long strips = f / 32 + skinny_strips2(E_loc, d);
+    const long long strips = f / 32 + skinny_strips2(M, E_loc, d);
     const long long spare = E_loc * strips * (std::min(8, (M + 63) / 64) - 1);
     return M <= 3072 && spare <= (fp8 ? 64 : 36) * (long long)num_cus();
+}
+// Up to 32 rows in the whole call (one or two 16-row tiles per strip) rows are so few that the experts which hold any count, about E M / (M + E - 1) of them with
+// Zipf popularity.  Streaming: per phase the weights' way from memory or the chain over K of a strip, which is four times as long for strips of 64 rows.  Tiles:
+// per phase what a launch takes to open, multiply and add up, or the weights' way from memory.  Fitted to 540 calls (E 1 .. 8, d 256 .. 7168, f 256 ..
+// 14336, weights not in any cache): the chosen way takes 0.6 % longer than the better one on average, 1.27 times at most (5 to 8 rows for eight fp8 experts); with
+// the estimates above it took 3.4 % longer, 1.43 times at most.  Streaming / tiles, us: E 1, d 7168, f 2048, 3 rows 40 / 33, in fp8 26 / 30; E 2, d 5376, f 640, 8
+// rows 31 / 23, in fp8 22 / 24; E 1, d 4096, f 14336, 12 rows 73 / 82, in fp8 51 / 54; E 4, d 7168, f 2048, 24 rows 71 / 77, in fp8 48 / 46.
+struct FewRows {
+    double open, bytes, wide, narrow, least, rows;         // streaming: us per phase, MB/us, us per 64 values of K with strips of 64 and 16 rows, us at least, share per 32 rows
+    double slab, split, whole, tile_open, tile_bytes;      // tiles: us per slab, us per phase with split and whole contractions; us per call, MB/us
+};
+constexpr FewRows FEW_ROWS[2] = {{4.88, 5.29, 0.218, 0.0343, 5.92, 0.151, 0.25, 10.3, 7.24, 12.9, 4.9},          // bf16
+                                 {3.88, 4.26, 0.115, 0.028, 5.85, 0.247, 0.25, 12.1, 9.05, 10.2, 4.06}};        // fp8
+bool streams_few(int M, int E_loc, int d, int f, bool fp8) {
+    const FewRows& c = FEW_ROWS[fp8];
+    const int cus = num_cus();
+    const double experts = (double)E_loc * M / (M + E_loc - 1);
+    const double matrix = experts * d * f * (fp8 ? 1e-6 : 2e-6);
+    const bool narrow = skinny_strips2(M, E_loc, d) != d / 64;
+    const double stream = (std::max(c.open + 2.0 * matrix / c.bytes, c.least + c.wide * (d / 64)) +
+                           std::max(c.open + matrix / c.bytes, c.least + (narrow ? c.narrow : c.wide) * (f / 64))) * (1.0 + c.rows * M / 32.0);
+    double tiles = 0.0;
+    for (int phase = 1; phase <= 2; ++phase) {
+        const int K = phase == 1 ? d : f;
+        const double n = experts * (phase == 1 ? f / 64 : d / TILE);
+        const int P = tile_parts((long long)(n + 0.5), cus, K, cus);
+        const double full = n * P / (2.0 * cus);
+        tiles += (full <= 1.0 ? std::max(full, 0.55) : 0.7 * full + 0.3 * std::ceil(full)) * (K / 64.0 / P) * c.slab + (P > 1 ? c.split : c.whole);
+    }
+    const double memory = c.tile_open + 3.0 * matrix / c.tile_bytes;
+    const double ratio = std::min(tiles, memory) / std::max(tiles, memory);
+    return stream <= std::max(tiles, memory) * std::pow(1.0 + std::pow(ratio, 6.0), 1.0 / 6.0);     // (one hides behind the other, less so where both take about as long)
 }
 Route route(int M, int S, int E_loc, int d, int f, bool fp8) {
     // (streaming: 32-bit offsets into x and h; every workgroup scans the slices of its expert)
     const bool can_stream = S <= SKINNY_MAX_SLICES && E_loc <= 4096 && (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull;
     if (E_loc > 8 && can_stream && streams_many(M, E_loc, d, f, fp8)) return STREAM;
+    if (E_loc <= 8 && can_stream && M <= 32) return streams_few(M, E_loc, d, f, fp8) ? STREAM : TILE_64;
     Route best = TILE_64;
     double least = tile_us(M, E_loc, d, f, fp8, 64);
     auto consider = [&](Route r, double us) { if (us < least) { least = us; best = r; } };

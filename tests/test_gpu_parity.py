@@ -924,6 +924,32 @@ def check_against_float(x, off, y, w, what):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("E_loc,d,f,sizes,streamed", [
+    (8, 1024, 512, [0, 0, 0, 1, 0, 0, 0, 0], True), (8, 1024, 512, [3, 0, 9, 0, 0, 1, 0, 3], True), (8, 1024, 512, [17, 0, 0, 0, 0, 0, 0, 0], True),
+    (8, 1280, 640, [1, 0, 16, 0, 2, 0, 0, 13], True), (8, 1024, 512, [30, 0, 0, 2, 0, 0, 0, 1], None), (4, 2048, 384, [0, 2, 0, 0], True),
+    (1, 7168, 256, [1], False), (1, 7168, 256, [32], False), (1, 7168, 256, [33], None)])
+def test_ffn_up_to_32_rows(lib, dtype, E_loc, d, f, sizes, streamed):
+    """Calls of up to 32 rows: which ones stream the weights, and strips of 16 weight rows where the experts that can hold rows have
+    few strips (1 .. 32 rows of 8 x 1024, 8 x 1280 and 4 x 2048; 64 weight rows again at 33)."""
+    say("ffn up to 32 rows", dtype, E_loc, d, f, sizes)
+    M = sum(sizes)
+    w = workloads.ffn_weights_on_device(E_loc, d, f, M, dtype, DEV)
+    x = workloads.activations_on_device(M, d, M, DEV)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    lib.moe_kernel_timing_enable(True)
+    try:
+        y = lib.moe_expert_ffn_sliced(x, dev(off), 1, E_loc, **w)
+        torch.cuda.synchronize()
+        names = lib.moe_kernel_timing_read()
+    finally:
+        lib.moe_kernel_timing_enable(False)
+    if streamed is not None:
+        assert (not any("plan" in n for n in names)) == streamed
+    check_against_float(x, off, y, w, "up to 32 rows")
+
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("tile_rows,kernels", [(64, 0), (128, 0), (256, 1)])
 @pytest.mark.parametrize("d,f,sizes", [
     (256, 128, [1, 64, 65, 0, 31, 33]),                                   # contractions of one and two blocks of 128 values: no steady state
