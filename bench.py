@@ -71,9 +71,9 @@ def code_digest(path):
 
 def kernel_key(name):
     """Library kernel behind a profiler kernel name."""
-    if "ffn_adaptive_kernel<1" in name or "ffn_gemm_kernel<1," in name:
+    if "ffn_adaptive_kernel<1" in name or "ffn_tile_kernel<1," in name:
         return "ffn_gemm1_kernel"
-    if "ffn_adaptive_kernel<2" in name or "ffn_gemm_kernel<2," in name:
+    if "ffn_adaptive_kernel<2" in name or "ffn_tile_kernel<2," in name:
         return "ffn_gemm2_kernel"
     if "ffn_fused_kernel" in name:
         return "ffn_fused_kernel"

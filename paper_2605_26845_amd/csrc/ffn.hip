@@ -421,7 +421,7 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // ---------------------------------------------------------------------------------- adaptive-shape GEMM kernel (bf16)
-// Same dataflow as ffn_gemm_kernel with 8 wavefronts of 64 x 128 each, but the arrangement of the wavefronts is chosen
+// Eight wavefronts of 64 x 128 each, K slabs copied global -> LDS as they lie.  The arrangement of the wavefronts is chosen
 // per row block so that ragged slices do not pay for 256 rows they do not have:
 //   class 0: 4 x 2 wavefronts = 256 rows x 256 columns;  64-wide K slabs (128-byte rows) of 64 KiB, two in LDS
 //   class 1: 2 x 4            = 128 rows x 512 columns;  32-wide K slabs (64-byte rows) of 40 KiB, three in LDS
@@ -1729,7 +1729,7 @@ moe_status launch_fused(const FfnArgs& a, long long max_tiles, hipStream_t s) {
 }
 
 // One workgroup per tile of the larger phase, half as many more with one expert: its row blocks make few chunks, so that more of the
-// workgroups find their own queue empty and come late to the others (see launch_gemm).  us, 1 / 1.5 / 2 per tile: E 1, d 2048, f 1408, 384 / 2048
+// workgroups find their own queue empty and come late to the others.  us, 1 / 1.5 / 2 per tile: E 1, d 2048, f 1408, 384 / 2048
 // rows 119 / 84 / 85, 132 / 96 / 103; E 1, d 1024, f 512, 2048 rows 73 / 51 / 53; E 1, d = f = 4096, 512 / 640 rows 260 / 207 / 212, 212 / 246 / 213; E 4, d = f =
 // 512, 2048 rows per expert 57 / 66 / 74.  Mean over the best of the three: one expert 1.09 / 1.02 / 1.02, two 1.02 / 1.02 / 1.03, more 1.01 / 1.02 / 1.04.
 // Not below d = 1024: where a tile takes a few microseconds and M may be a bound above the rows, the idle ones show (8 ranks, d 256, f 512, M
@@ -2675,7 +2675,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     a.panel1 = a.panel2 = 1 << 20;
     a.dh = dh; a.lddh = L.f_pad; a.dgu = dgu;
     a.queues1 = counters + 8;
-    // Workgroups of the kernels over rows: two per tile (see launch_gemm), but one on every compute unit where a tile is long
+    // Workgroups of the kernels over rows: two per tile (one per tile draws its next ticket before others have found their first), but one on every compute unit where a tile is long
     // (K >= 4096), since what the idle ones cost the queues, some 8 us, does not count there.  Whole call, us, one per tile / two per
     // tile / every unit: E 1, d 4096, f 14336, 3000 rows 3970 / 3365 / 3365, 700 rows 2190 / 2050 / 1695; E 1, d 2048, f 1408, 700 rows 395 /
     // 310 / 390; E 1, d = f = 256, 1500 rows 256 / 222 / 312.
