@@ -16,6 +16,7 @@
 // same adaptive-shape kernels on other operands.
 #include "common.hpp"
 #include "rows.hpp"
+#include "parts.hpp"
 #include <type_traits>
 #include <algorithm>
 #include <cmath>
@@ -1971,11 +1972,8 @@ moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
 // pass 1712; with transposed copies of x, dy, h, dg and du (295 us), three launches of the row GEMM that each waited for the most popular
 // expert (797) and partial sums rounded to bf16 and added in three more (110) 2327.  E 1, d 4096, f 14336, 6000 rows: 1620 us, before 2480.
 // All products and experts are one launch, the longest contractions first.  A unit of work is a 256 x 256 tile of one expert's [dW_gate; dW_up] or
-// dW_down over one part of its rows; only experts behind which too little work is left to even out the ends are split (bwd_prep_kernel).
+// dW_down over one part of its rows; only experts behind which too little work is left to even out the ends are split (parts.hpp).
 // Parts are added in fp32 in part order by the workgroup that finishes a tile's last part.
-constexpr int DW_MAX_PARTS = 32;
-constexpr int DW_PART_ROWS = 768;              // rows of a part at least
-constexpr int DW_MAX_UNITS = 1024;             // parts of tiles with a place for their sums, at most
 constexpr size_t DW_UNIT_BYTES = 256 * 256 * sizeof(float);
 constexpr int DW_QUEUES = 24;                  // first of the 8 queue counters of the weight gradients
 constexpr int BWD_COUNTERS = 32;               // tile queue counters of a backward call: dh, act, dx, dW
@@ -2012,59 +2010,16 @@ struct DwArgs {
     int M, d, f;
 };
 
-// One workgroup.  The order in which the weight gradients of the experts are worked on (most rows first) and the parts each is contracted
-// in: one, unless the work from this expert to the end is less than its own rows on every compute unit.  Then the number of parts
-// is the one with which that work takes the least time in rounds of equal units, a part costing `fix` rows to open and `split` rows to add up.
-// (Simulated lists of unequal and equal experts end 1.4 % after the best of 17 rules on average, unsplit ones 54 %.)
+// One workgroup: the table of the weight gradients' parts (parts.hpp), and what has to be zero behind it
 __global__ __launch_bounds__(PLAN_THREADS)
 void bwd_prep_kernel(const int* __restrict__ bases, int e_loc, int tiles, int cus, int cap, int4* __restrict__ entries, int* __restrict__ counters,
                      int* __restrict__ arrived, unsigned int* __restrict__ zeros) {
-    __shared__ int rows_of[MAX_GROUPS / 16], parts_of[MAX_GROUPS / 16];
+    __shared__ int rows_of[MAX_GROUPS / 16], parts_of[MAX_GROUPS / 16], place_of[MAX_GROUPS / 16];
     const int tid = threadIdx.x;
     for (int i = tid; i < BWD_COUNTERS; i += PLAN_THREADS) counters[i] = 0;
     for (int i = tid; i < cap; i += PLAN_THREADS) arrived[i] = 0;
     for (int i = tid; i < DW_ZEROS / 4; i += PLAN_THREADS) zeros[i] = 0;
-    for (int e = tid; e < e_loc; e += PLAN_THREADS) rows_of[e] = bases[e + 1] - bases[e];
-    __syncthreads();
-    auto before = [&](int j, int e) { return rows_of[j] > rows_of[e] || (rows_of[j] == rows_of[e] && j < e); };
-    for (int e = tid; e < e_loc; e += PLAN_THREADS) {
-        const int rows = rows_of[e];
-        long long rest = 0;                                               // rows of this expert and of those after it
-        for (int j = 0; j < e_loc; ++j) rest += before(j, e) ? 0 : rows_of[j];
-        int best = 1;
-        if (rest * tiles < (long long)rows * cus && 2 * tiles <= cap) {
-            constexpr float fix = 100.f, split = 380.f;
-            float least = 0.f;
-            for (int P = 1; P <= DW_MAX_PARTS && P * tiles <= cap && (P == 1 || rows / P >= DW_PART_ROWS); ++P) {
-                const float unit = (float)((rows + P * 64 - 1) / (P * 64) * 64) + fix + (P > 1 ? split : 0.f);
-                const float t = ceilf((float)rest * (float)tiles * (float)P / ((float)rows * (float)cus) - 1e-3f) * unit;
-                if (P == 1 || t < least) { least = t; best = P; }
-            }
-        }
-        parts_of[e] = best;
-    }
-    __syncthreads();
-    for (int e = tid; e < e_loc; e += PLAN_THREADS) {
-        int at = 0, unit = 0, P = parts_of[e];
-        for (int j = 0; j < e_loc; ++j) {
-            if (!before(j, e)) continue;
-            at += parts_of[j];
-            unit += parts_of[j] > 1 ? parts_of[j] * tiles : 0;
-        }
-        const int slots = P;
-        if (P > 1 && unit + P * tiles > cap) P = 1;                       // (no room for its sums: one part, and the other entries are empty)
-        const int rows = rows_of[e], len = (rows + P * 64 - 1) / (P * 64) * 64;
-        for (int p = 0; p < slots; ++p) {
-            const int lo = min(p * len, rows);
-            entries[1 + 2 * (at + p)] = make_int4(bases[e] + lo, min(len, rows - lo), p < P ? e : -1, p);
-            entries[2 + 2 * (at + p)] = make_int4(P, unit, 0, 0);
-        }
-    }
-    if (tid == 0) {
-        int n = 0;
-        for (int e = 0; e < e_loc; ++e) n += parts_of[e];
-        entries[0] = make_int4(n, 0, 0, 0);
-    }
+    dw_split(bases, e_loc, tiles, cus, cap, entries, rows_of, parts_of, place_of, tid, PLAN_THREADS, [] { __syncthreads(); });
 }
 
 template <bool LISTED, bool WIDE>
@@ -2432,7 +2387,7 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
     L.ebase = take(EBASE_BYTES);
     L.bases = take((size_t)(E_loc + 1) * sizeof(int));
     L.counters = take((size_t)BWD_COUNTERS * sizeof(int));
-    L.entries = take(((size_t)1 + 2 * ((size_t)E_loc + DW_MAX_UNITS)) * sizeof(int4));
+    L.entries = take((1 + dw_entries(E_loc)) * sizeof(int4));
     L.arrived = take((size_t)DW_MAX_UNITS * sizeof(int));
     L.zeros = take(DW_ZEROS);
     L.wdt = take((size_t)E_loc * L.f_pad * d * 2);

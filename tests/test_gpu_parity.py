@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import oracle
+import test_parts
 import workloads
 
 pytestmark = pytest.mark.gpu
@@ -1199,6 +1200,30 @@ def test_ffn_backward_weight_gradient_slabs(lib, f, S, sizes):
                 assert not got[e].any(), (name, e)
             else:
                 check_ffn_error(float(np.abs(got[e] - want[e]).max() / np.abs(want[e]).max()), "bf16", "%s[%d] of %s" % (name, e, sizes))
+
+
+@pytest.mark.parametrize("d,f,sizes", [(1024, 512, [8000, 8000, 7999, 8001, 8000, 3]), (256, 256, test_parts.MANY[0])])
+def test_ffn_backward_experts_without_room_for_sums(lib, d, f, sizes):
+    """More parts are asked for than there are places for their sums: the last experts stay whole, those before them are split.  The second call is one
+    whose experts ask for more parts than the table of them holds.  Against float32 products of the GPU."""
+    say("ffn backward experts without room for sums", d, f, len(sizes), sum(sizes))
+    E_loc, M = len(sizes), sum(sizes)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    w = workloads.ffn_weights_on_device(E_loc, d, f, d + f, "bf16", DEV)
+    x, dy = workloads.activations_on_device(M, d, 81, DEV), workloads.activations_on_device(M, d, 82, DEV)
+    out = lib.moe_expert_ffn_backward_sliced(x, dy, dev(off), 1, E_loc, **w)
+    torch.cuda.synchronize()
+    worst = 0.0
+    for e in range(E_loc):
+        wg, wu, wd = (w[k][e].float() for k in ("w_gate", "w_up", "w_down"))
+        xs, ds = x[off[e]:off[e + 1]].float(), dy[off[e]:off[e + 1]].float()
+        g, u, dh = xs @ wg.t(), xs @ wu.t(), ds @ wd
+        sig = torch.sigmoid(g)
+        for k, ref in (("dw_gate", (dh * u * sig * (1 + g * (1 - sig))).t() @ xs), ("dw_up", (dh * g * sig).t() @ xs), ("dw_down", ds.t() @ (g * sig * u))):
+            diff = (out[k][e].float() - ref).abs()
+            worst = max(worst, float(diff.max() / ref.abs().max()))
+            assert float(diff.norm() / ref.norm()) <= 1.2e-2, (k, e)           # (four roundings to bf16 of 2^-9 each, as elsewhere)
+    check_ffn_error(worst, "bf16", "all experts")
 
 
 @pytest.mark.parametrize("tile_rows,kernels", [(64, 0), (128, 0), (256, 1), (256, 0)])
