@@ -954,13 +954,26 @@ void greedy_kernel(const int32_t* __restrict__ mats, int N, int kmax, int flags,
                         if (NPL > 1) { const int y = __shfl(u[NPL - 1], owner & 63); x = owner >> 6 ? y : x; }
                         uo[s] = (int)((unsigned)x << Packed<NPL>::SHIFT);
                     }
-                    while (todo.any() && bound < Packed<NPL>::MOST) {
+                    for (;;) {
                         const int r = todo.first();
                         todo.reset(r);
                         int D;
                         n_steps += search_packed<NPL, NW, T>(columns, N, r, lane, bcast<NPL>(u, r), uo, v, p, D);
                         bound += D;
                         ++n_searches;
+                        if (!todo.any()) break;
+                        if (bound >= Packed<NPL>::MOST) {                 // (the sum of the lengths is the looser bound: see what it is now)
+                            int mu = 0, mv = 0;
+#pragma unroll
+                            for (int s = 0; s < NPL; ++s) {
+                                if (lane + 64 * s < N) mv = max(mv, v[s]);
+                                if (p[s] >= 0) mu = max(mu, uo[s] >> Packed<NPL>::SHIFT);
+                                if (__builtin_amdgcn_inverse_ballot_w64(todo.w[s])) mu = max(mu, u[s]);
+                            }
+                            mu = wave_max(mu); mv = wave_max(mv);
+                            bound = min(mu, Packed<NPL>::MOST) + min(mv, Packed<NPL>::MOST);
+                            if (bound >= Packed<NPL>::MOST) break;
+                        }
                     }
                     // back to the rows: row i's column and u
 #pragma unroll

@@ -192,6 +192,16 @@ def test_greedy_keys_of_32_bits(lib, N, limit):
         check_decomposition(lib, "greedy", mats, kmax, False)
 
 
+@pytest.mark.parametrize("N,high", [(16, 2000000), (33, 2000000), (64, 2000000), (96, 1000000), (128, 1000000)])
+def test_greedy_keys_whose_bound_is_taken_again(lib, N, high):
+    """Entries just below the largest that keys have room for: the duals stay below it, the sum of the lengths of a matching's searches, by which they
+    are bounded between two looks at them, does not (128 ranks, uniform up to 10^6: 1.25 and 1.04 million)."""
+    say("greedy keys whose bound is taken again", N, high)
+    mats = np.random.default_rng(N).integers(0, high, (6, N, N)).astype(np.int32)
+    for kmax in (4, N):
+        check_decomposition(lib, "greedy", mats, kmax, False)
+
+
 def test_greedy_16_bit_residual(lib):
     """How the residual is held on chip (32 bits, or 16 bits with a second launch for the matrices that do not fit)
     does not change a byte of the result."""
