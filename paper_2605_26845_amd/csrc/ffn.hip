@@ -2095,10 +2095,12 @@ void ffn_bwd_dw_kernel(DwArgs a) {
         }
     };
     // Copies are written out: the compiler would hold every transposed read of LDS until all copies in flight have landed.  (No register
-    // is written; the waits that cover the copies are wait_vmcnt's.)
+    // but m0 is written; the waits that cover the copies are wait_vmcnt's.  The five wait states between a scalar register that a vector
+    // instruction has written, as one that was kept in a vector lane, and a memory instruction that reads it are not counted into assembly by the
+    // compiler: they stand in the text.)
     auto copy = [&](unsigned long long base, unsigned int bytes, unsigned int voff, int to) __attribute__((always_inline)) {
         const u32x4 rs = {(unsigned int)base, (unsigned int)(base >> 32), bytes, 0x00020000u};
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(voff), "s"(rs) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(voff), "s"(rs) : "memory", "m0");
     };
     auto slab_bytes = [&](int s, unsigned int pitch) __attribute__((always_inline)) -> unsigned int {       // rows past the end: zeros are deposited
         const int left = min(rows - s * 64, 64);
@@ -2119,7 +2121,7 @@ void ffn_bwd_dw_kernel(DwArgs a) {
             const bool live = s * 64 + 8 * wave + 2 * i + lhi < rows;
             if constexpr (WIDE) {
                 const unsigned char* const from = live ? (const unsigned char*)lbase + (unsigned long long)row * pitch + lvoff[i & 1] : a.zeros + l31 * 16;
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory");
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory", "m0");
             } else {
                 copy(lbase, lbytes, live ? row * pitch + lvoff[i & 1] : 0xFFFFFF00u, to);
             }
