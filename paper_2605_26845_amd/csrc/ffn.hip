@@ -1267,6 +1267,7 @@ void ffn_skinny_kernel(SkinnyArgs a) {
 // v_cvt_scalef32_pk_bf16_fp8, and the scale of a 128 x 128 block multiplies the fp32 sum over that block's 128 values of K.
 constexpr int TILE = 128;                                    // columns
 constexpr int TILE_MAX_PARTS = 16, TILE_MIN_SLABS = 12;       // parts of a contraction, slabs of 64 values of K per part at least
+constexpr int TILE_SQUARE = 8;                               // column tiles that many row blocks are walked for at a time
 // ROWS = rows per tile:
 //    64: 4 wavefronts (2 x 2) of 32 x 64, three slabs of 24 KiB (fp8: four of activations, three of codes), 2 workgroups per compute unit
 //   128: 4 wavefronts (2 x 2) of 64 x 64, two slabs of 32 KiB, 2 workgroups per compute unit
@@ -1277,6 +1278,11 @@ template <int ROWS, bool FP8> struct TileShape {
     // Workgroups per compute unit up to which contractions are split.  (64 rows, one / two: E 1, d 4096, f 14336, 37 rows 85 / 100 us; fp8 E 4, d 7168, f 2048, 64
     // rows 48 / 58, 203 rows 69 / 65.  128 rows, 203 rows of the former 139 / 134; E 2, d 3584, f 4864, 512 rows 130 / 103.)
     static constexpr int SPLIT_PER_CU = ROWS == 128 ? 2 : 1;
+    // Row blocks up to which they are innermost in the order of the units.  Innermost against walked for 8 column tiles at a time, mean of 36 shapes, bf16 / fp8:
+    // 64 rows, 17 .. 20 / 25 .. 32 / 33 .. 48 blocks 0.97 / 1.01 / 1.04, 0.99 / 1.03 / 1.06; 128 rows, 13 .. 16 / 17 .. 20 / 33 .. 48 0.99 / 1.01 / 1.09, 1.03 / 1.04 /
+    // 1.15; 256 rows, 9 .. 12 / 13 .. 16 / 33 .. 48 1.01 / 1.03 / 1.21, 1.01 / 1.03 / 1.14.  E 8, d 7168, f 2048, 1250 rows per expert, 128 / 256 rows: bf16 1199 -> 1022 us,
+    // 1209 -> 975; fp8 1080 -> 911, 1103 -> 937.
+    static constexpr int FEW_BLOCKS = ROWS == 64 ? 24 : (ROWS == 128 ? 16 : 12);
     static constexpr int NST = ROWS == 64 ? (FP8 ? 4 : 3) : (ROWS == 128 ? 2 : 3);      // places for slabs of 64 values of K of the activations
     static constexpr int NB = !FP8 ? NST : (ROWS == 64 ? 3 : 2);                        // places for slabs of 128 bytes per weight row
     static constexpr int A_BYTES = ROWS * 128, B_BYTES = TILE * 128;                    // of a place
@@ -1318,12 +1324,20 @@ void ffn_tile_kernel(TileArgs t) {
     const int K = PHASE == 1 ? a.d : a.g2.K, NT = PHASE == 1 ? a.f / 64 : a.g2.NU * 2;
     const int nblocks = a.plan[0].x;
     const int P = tile_parts((long long)nblocks * NT, t.slots, K, t.cap);
-    // workgroup -> unit: every die (workgroup number modulo 8) takes a stretch of the units; row blocks are innermost, so that those which share
-    // weights share an L2
+    // workgroup -> unit: every die (workgroup number modulo 8) takes a stretch of the units.  With few row blocks these are innermost, so that those which share
+    // weights share an L2; more of them are walked for TILE_SQUARE column tiles at a time, so that the tiles which run together on a die are about as many
+    // columns wide as rows high, and a row is read once per TILE_SQUARE column tiles instead of for each
     const int units = nblocks * NT * P, xcd = blockIdx.x & 7;              // (< 2^28: a condition of this route)
     const int last = units * (xcd + 1) / 8, unit = units * xcd / 8 + (int)(blockIdx.x >> 3);
     if (unit >= last) return;
-    const int blk = unit % nblocks, rest = unit / nblocks, p = rest % P, nt = rest / P;
+    int blk, p = 0, nt;
+    if (P > 1 || nblocks <= S::FEW_BLOCKS) {
+        const int rest = unit / nblocks;
+        blk = unit - rest * nblocks; nt = rest / P; p = rest - nt * P;
+    } else {
+        const int first = unit / (nblocks * TILE_SQUARE) * TILE_SQUARE, rest = unit - first * nblocks, width = min(TILE_SQUARE, NT - first);
+        blk = rest / width; nt = first + rest - blk * width;
+    }
     const int4 info = a.plan[PLAN_HDR + blk];
     const int m0 = __builtin_amdgcn_readfirstlane(info.x), m_end = __builtin_amdgcn_readfirstlane(info.y), e = __builtin_amdgcn_readfirstlane(info.z);
     const int rows = min(ROWS, m_end - m0);

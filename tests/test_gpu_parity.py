@@ -966,7 +966,8 @@ def test_ffn_up_to_32_rows(lib, dtype, E_loc, d, f, sizes, streamed):
     (256, 128, [1, 64, 65, 0, 31, 33]),                                   # contractions of one and two blocks of 128 values: no steady state
     (512, 384, [128, 129, 257, 63]),                                      # of three and four; row blocks and their remainders
     (2048, 1664, [70, 3]), (1536, 2048, [300]),                           # contractions split over workgroups: with a block more for some, in one phase only
-    (3328, 256, [5, 40, 0, 1])])
+    (3328, 256, [5, 40, 0, 1]),
+    (1280, 640, [3500, 0, 70]), (256, 1152, [3137, 65])])                # many row blocks, walked for 8 column tiles at a time: 8 and 2, 8 and 8 and 2, or the only 2
 def test_ffn_tile_edges(lib, dtype, tile_rows, kernels, d, f, sizes):
     """Tiles of 64, 128 and 256 rows: short contractions, remainders of rows, split contractions (the same bits on every call, which
     needs every counter of finished parts to start at zero and the parts to be added in order), and the same calls in a workspace without room for
