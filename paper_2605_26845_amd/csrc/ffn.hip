@@ -1856,53 +1856,81 @@ moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
 }
 
 // ---- which kernels a call takes.  Only M, an upper bound of the rows, is known here, and not how unequal the experts are.  Up to 8 experts the times
-// of the ways are estimated (us) and the least is taken.  The constants were fitted to 2050 calls timed in every way (E 1 .. 128, d 256 .. 7168, f 256 .. 14336,
-// 1 .. 6144 rows per expert, bf16 and fp8; equal experts, Zipf popularity and all rows at one expert): with up to 8 experts the chosen way takes 1.4 % longer
-// than the best one on average.  (Up to 32 rows: streams_few.)
-// us, streaming / tiles of 64 / 128 / 256 rows / fused, at 8, 64, 256, 1024, 4096 rows per expert:
-//   bf16 E 1, d 4096, f 14336: 73 79 90 86 -, 109 84 104 94 550, - 174 147 128 458, - 536 411 349 598, - - 1534 1286 1102
-//   bf16 E 4, d 2048, f 1408: 26 31 45 38 -, 44 37 48 46 113, - 50 58 60 120, - 126 118 111 141, - - 374 372 266
-//   fp8  E 4, d 7168, f 2048: 51 46 60 64 -, 120 69 77 81 -, - 155 157 151 -, - 485 478 431 -, - - 1647 1657 -
-enum Route { STREAM, TILE_64, TILE_128, TILE_256, FUSED };
-// Tiles: rounds of the units the chip holds at once, times the slabs of a unit, times a slab's time on a full chip.  An expert's last block is half full; a
-// round that is not full counts less (the compute units hold one workgroup instead of two, or wait less for memory).
+// of the ways are estimated (us) and the least is taken.  The constants were fitted to 2999 calls timed in every way (75 shapes of E 1 .. 8, d 256 .. 7168, f 256 .. 14336;
+// 33 rows .. 5000 rows per expert, Zipf popularity, bf16 and fp8): the chosen way takes 1.6 % (bf16) and 0.6 % (fp8) longer than the best one on average.
+// (Up to 32 rows: streams_few.)
+// us, streaming / tiles of 64 / 128 / 256 rows / fused, rows in all:
+//   bf16 E 1, d 4096, f 14336: 36 rows 94 87 107 94 -, 69 rows 124 97 116 97 -, 274 rows 349 218 182 160 453, 1063 rows 1089 582 453 425 578, 4497 rows - 2006 1635 1513 1456
+//   bf16 E 4, d 2048, f 1408: 42 rows 23 26 35 30 -, 293 rows 51 28 38 40 -, 1449 rows 124 56 53 51 116, 5042 rows - 137 114 112 148, 16073 rows - 374 299 313 273
+//   fp8  E 4, d 7168, f 2048: 40 rows 49 45 59, 310 rows 118 72 79, 1028 rows 287 155 159, 3851 rows 919 435 371, 15617 rows - 1597 1376
+enum Route { STREAM, TILE_64, TILE_128, TILE_256, FUSED, EXPAND };         // (EXPAND: fp8 weights to bf16, then fused)
+struct Estimate {
+    // Tiles of 64, 128 and (bf16) 256 rows: us per slab of 64 values of K, per tile besides, share of a full round that an empty one takes, us per phase with split contractions;
+    // us per phase with whole ones, share of a round that does not end with the others; us per call and MB/us of the weights' way from memory
+    double slab[3], tile[3], least[3], split[3], whole, spread, open, bytes;
+    // Streaming: us per phase and MB/us of the weights' way from memory; us per phase at least, per 64 values of K with strips of 64 and of 16 rows, share per 16-row
+    // tile; us per row and 10^8 weights of a matrix
+    double stream_open, stream_bytes, chain, wide, narrow, row_tile, rows;
+};
+constexpr Estimate ESTIMATE[2] = {{{0.749, 1.18, 0.792}, {0.383, 1.31, 6.67}, {0.259, 0.332, 0.457}, {6.67, 15.4, 9.98}, 6.91, 0.716, 12.9, 3.79, 1.74, 3.92, 6.61, 0.179, 0.00535, 0.22, 3.13},        // bf16
+                                  {{0.635, 0.968}, {0.87, 2.37}, {0.306, 0.266}, {12.9, 17.8}, 6.95, 0.843, 11.7, 4.31, 3.73, 3.65, 7.08, 0.101, 0.00953, 0.323, 2.49}};       // fp8
 size_t tile_part_bytes(int d, int f) { return std::max(d, f) / 64 < 2 * TILE_MIN_SLABS ? 0 : (size_t)TILE_COUNTERS * TileShape<128, false>::UNIT_BYTES; }
-double tile_us(int M, int E_loc, int d, int f, bool fp8, int rows) {
+double experts_with_rows(int M, int E_loc) { return (double)E_loc * M / (M + E_loc - 1); }       // (about, with Zipf popularity)
+// of two times of which one hides behind the other, less so where both are about as long
+double overlapped(double a, double b) {
+    const double ratio = std::min(a, b) / std::max(a, b);
+    return std::max(a, b) * std::pow(1.0 + std::pow(ratio, 6.0), 1.0 / 6.0);
+}
+// Tiles: rounds of the units the chip holds at once, times what a unit takes on a full chip.  An expert's last block is half full; the parts of a round that is not full count
+// less (the compute units hold one workgroup instead of two, or wait less for memory).
+double tile_us(int M, int E_loc, int d, int f, bool fp8, int rows, int cus) {
+    const Estimate& c = ESTIMATE[fp8];
+    const int k = rows == 64 ? 0 : (rows == 128 ? 1 : 2);
     const double blocks = E_loc == 1 ? (M + rows - 1) / rows : std::max<double>(std::min(E_loc, M), (double)M / rows + 0.5 * E_loc);
-    const double slab_us = rows == 64 ? (fp8 ? 0.68 : 0.77) : (rows == 128 ? (fp8 ? 1.05 : 1.39) : (fp8 ? 1.05 : 0.98));
-    const int cus = num_cus(), slots = (rows == 256 ? 1 : 2) * cus, split_slots = (rows == 128 ? 2 : 1) * cus;
+    const int slots = (rows == 256 ? 1 : 2) * cus, split_slots = (rows == 128 ? 2 : 1) * cus;
     double us = 0.0;
     for (int phase = 1; phase <= 2; ++phase) {
         const int K = phase == 1 ? d : f;
         const double tiles = blocks * (phase == 1 ? f / 64 : d / TILE);
         const int P = tile_parts((long long)(tiles + 0.5), split_slots, K, split_slots);
         const double full = tiles * P / slots;
-        us += (full <= 1.0 ? std::max(full, 0.55) : 0.7 * full + 0.3 * std::ceil(full)) * (K / 64.0 / P) * slab_us + (P > 1 ? 16.5 : 7.4);
+        us += (full <= 1.0 ? c.least[k] + (1.0 - c.least[k]) * full : c.spread * full + (1.0 - c.spread) * std::ceil(full)) * (K / 64.0 / P * c.slab[k] + c.tile[k]) +
+              (P > 1 ? c.split[k] : c.whole);
     }
-    const double weights = 3.0 * std::min(E_loc, M) * d * f * (fp8 ? 1 : 2);
-    return std::max(us, 11.5 + weights / (fp8 ? 2.4e6 : 3.84e6));
+    const double weights = 3.0 * experts_with_rows(M, E_loc) * d * f * (fp8 ? 1e-6 : 2e-6);
+    return overlapped(us, c.open + weights / c.bytes);
 }
-// fused: the same with tiles of 256 x 256 and one round at least per phase (what the phases' overlap returns is in the slab's time)
-double fused_us(int M, int E_loc, int d, int f) {
+// fused: the same with tiles of 256 x 256 and one round at least per phase
+double fused_us(int M, int E_loc, int d, int f, int cus) {
     const double blocks = E_loc == 1 ? (M + 255) / 256 : (double)M / 256 + 0.5 * E_loc;
-    double us = 22.0;
+    double us = 50.3;
     for (int phase = 1; phase <= 2; ++phase) {
-        const double full = blocks * (phase == 1 ? f / 128 : d / 256) / num_cus();
-        us += (full <= 1.0 ? 1.0 : 0.37 * full + 0.63 * std::ceil(full)) * ((phase == 1 ? d : f) / 64) * 1.57;
+        const double full = blocks * (phase == 1 ? f / 128 : d / 256) / cus;
+        us += (full <= 1.0 ? 1.0 : 0.86 * full + 0.14 * std::ceil(full)) * ((phase == 1 ? d : f) / 64 * 1.59 + 1.28);
     }
     return us;
 }
-// streaming: the weights' way from memory, or a strip's steps, and every strip of 32 (64) weight rows reads all activations
+// expansion of fp8 weights: 3 bytes of traffic per weight
+double expand_us(int E_loc, int d, int f) { return 6.0 + 1.59e-6 * E_loc * d * f; }
+// streaming: per phase the weights' way from memory or the chain over K of a strip, which gets longer with the rows of the most popular expert (Zipf, up to four
+// 16-row tiles at once), and every strip reads all activations
 double stream_us(int M, int E_loc, int d, int f, bool fp8) {
-    const double df = (double)d * f;
-    return std::max(13.0 + 3.0 * std::min(E_loc, M) * df * (fp8 ? 1.0 / 3.25e6 : 2.0 / 5.2e6), 7.2 + 0.54 * (d / 64)) + M * df * 4.7e-8;
+    const Estimate& c = ESTIMATE[fp8];
+    double popular = 0.0;
+    for (int e = 1; e <= E_loc; ++e) popular += std::pow(e, -1.2);
+    const double chain = 1.0 + c.row_tile * std::min(4.0, std::ceil(M / popular / 16.0));
+    const double matrix = experts_with_rows(M, E_loc) * d * f * (fp8 ? 1e-6 : 2e-6);
+    const bool narrow = skinny_strips2(M, E_loc, d) != d / 64;
+    return std::max(c.stream_open + 2.0 * matrix / c.stream_bytes, c.chain + c.wide * (d / 64) * chain) +
+           std::max(c.stream_open + matrix / c.stream_bytes, c.chain + (narrow ? c.narrow : c.wide) * (f / 64) * chain) + 1e-8 * c.rows * M * d * f;
 }
 // More than 8 experts: a popular expert's rows are chunks behind each other that each read its weights, so at most 3072 rows are streamed (E 16, d = f = 256,
-// Zipf, 4096 rows 59 / 40, 8192 rows 98 / 42), up to a constant over the column tiles and at least 64 rows per expert; and as every expert gets
+// Zipf, 4096 rows 59 / 40, 8192 rows 98 / 42), in bf16 up to a constant over the column tiles and at least 64 rows per expert, in fp8 up to 32 (E 16, d 2048, f 1408, 553 /
+// 1365 / 2227 rows streamed 85 / 134 / 180 us, in tiles 48 / 62 / 82; E 32, d 2048, f 768, 2192 rows 182, 66); and as every expert gets
 // workgroups for up to 8 chunks, most of which find no rows (some 5 ns each on the whole chip), a limit to those beyond the first.
 bool streams_many(int M, int E_loc, int d, int f, bool fp8) {
     const long long col_tiles = (long long)E_loc * (d / 256 + f / 128);
-    const long long most = fp8 ? std::min(640LL, std::max(64LL, 60000 / col_tiles)) : std::min(384LL, std::max(64LL, 36000 / col_tiles));
+    const long long most = fp8 ? 32LL : std::min(384LL, std::max(64LL, 36000 / col_tiles));
     if (M > most * E_loc && !(M <= 2048 && (long long)M * d * f <= (1LL << 30))) return false;
     const long long strips = f / 32 + skinny_strips2(M, E_loc, d);
     const long long spare = E_loc * strips * (std::min(8, (M + 63) / 64) - 1);
@@ -1923,7 +1951,7 @@ constexpr FewRows FEW_ROWS[2] = {{4.88, 5.29, 0.218, 0.0343, 5.92, 0.151, 0.25, 
 bool streams_few(int M, int E_loc, int d, int f, bool fp8) {
     const FewRows& c = FEW_ROWS[fp8];
     const int cus = num_cus();
-    const double experts = (double)E_loc * M / (M + E_loc - 1);
+    const double experts = experts_with_rows(M, E_loc);
     const double matrix = experts * d * f * (fp8 ? 1e-6 : 2e-6);
     const bool narrow = skinny_strips2(M, E_loc, d) != d / 64;
     const double stream = (std::max(c.open + 2.0 * matrix / c.bytes, c.least + c.wide * (d / 64)) +
@@ -1936,22 +1964,23 @@ bool streams_few(int M, int E_loc, int d, int f, bool fp8) {
         const double full = n * P / (2.0 * cus);
         tiles += (full <= 1.0 ? std::max(full, 0.55) : 0.7 * full + 0.3 * std::ceil(full)) * (K / 64.0 / P) * c.slab + (P > 1 ? c.split : c.whole);
     }
-    const double memory = c.tile_open + 3.0 * matrix / c.tile_bytes;
-    const double ratio = std::min(tiles, memory) / std::max(tiles, memory);
-    return stream <= std::max(tiles, memory) * std::pow(1.0 + std::pow(ratio, 6.0), 1.0 / 6.0);     // (one hides behind the other, less so where both take about as long)
+    return stream <= overlapped(tiles, c.tile_open + 3.0 * matrix / c.tile_bytes);
 }
-Route route(int M, int S, int E_loc, int d, int f, bool fp8) {
+// `room`: for the expanded weights, which are not made below 2048 rows per expert
+Route route(int M, int S, int E_loc, int d, int f, bool fp8, bool room) {
     // (streaming: 32-bit offsets into x and h; every workgroup scans the slices of its expert)
     const bool can_stream = S <= SKINNY_MAX_SLICES && E_loc <= 4096 && (unsigned long long)M * std::max(d, f) * 2 < 0xFFFFFF00ull;
     if (E_loc > 8 && can_stream && streams_many(M, E_loc, d, f, fp8)) return STREAM;
     if (E_loc <= 8 && can_stream && M <= 32) return streams_few(M, E_loc, d, f, fp8) ? STREAM : TILE_64;
+    const int cus = num_cus();
     Route best = TILE_64;
-    double least = tile_us(M, E_loc, d, f, fp8, 64);
+    double least = tile_us(M, E_loc, d, f, fp8, 64, cus);
     auto consider = [&](Route r, double us) { if (us < least) { least = us; best = r; } };
-    consider(TILE_128, tile_us(M, E_loc, d, f, fp8, 128));
-    consider(TILE_256, tile_us(M, E_loc, d, f, fp8, 256));
+    consider(TILE_128, tile_us(M, E_loc, d, f, fp8, 128, cus));
+    if (!fp8) consider(TILE_256, tile_us(M, E_loc, d, f, fp8, 256, cus));
     // (below 256 rows per expert the fused kernel was never the best one; f >= 256: it chains tiles over their last two slabs and needs four)
-    if (!fp8 && f >= 256 && M >= 256LL * E_loc) consider(FUSED, fused_us(M, E_loc, d, f));
+    if (!fp8 && f >= 256 && M >= 256LL * E_loc) consider(FUSED, fused_us(M, E_loc, d, f, cus));
+    if (fp8 && f >= 256 && M >= 2048LL * E_loc && room) consider(EXPAND, expand_us(E_loc, d, f) + fused_us(M, E_loc, d, f, cus));
     if (E_loc <= 8 && can_stream) consider(STREAM, stream_us(M, E_loc, d, f, fp8));
     return best;
 }
@@ -1959,7 +1988,7 @@ Route route(int M, int S, int E_loc, int d, int f, bool fp8) {
 // the choice that moe_ffn_tile_override has pinned, if any
 Route pinned(Route way, int f, bool fp8) {
     const int rows = g_force_rows.load(std::memory_order_relaxed);
-    if (rows != 0) way = rows == 64 ? TILE_64 : (rows == 128 ? TILE_128 : (fp8 || f < 256 ? TILE_256 : FUSED));
+    if (rows != 0) way = rows == 64 ? TILE_64 : (rows == 128 || fp8 ? TILE_128 : (f < 256 ? TILE_256 : FUSED));
     return way == FUSED && g_force_kernels.load(std::memory_order_relaxed) == 1 ? TILE_256 : way;
 }
 
@@ -2479,12 +2508,12 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     if (!workspace || workspace_bytes < base_bytes) return MOE_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
 
-    // fp8 weights and many rows per expert: when the caller has added room for it the weights are expanded to bf16 once per call and the fused
-    // kernel runs, which takes bf16 only.  Worth it from about 2048 rows per expert on, where bf16 weights would take that kernel (3 bytes of traffic per
-    // weight).  us, tiles on the codes / expansion and fused kernel: E 4, d 7168, f 2048, 1536 / 2048 / 4096 rows per expert 659 / 667, 875 / 807, 1663 /
-    // 1312; E 8, d 1024, f 2048 216 / 244, 276 / 281, 506 / 442; E 1, d 4096, f 14336, 2048 rows (bf16 weights take tiles) 673 / 762.
-    if (fp8 && (long long)M >= 2048LL * E_loc && workspace_bytes - base_bytes >= moe_ffn_expanded_weights_bytes(E_loc, d, f) &&
-        route(M, S, E_loc, d, f, false) == FUSED) {
+    // fp8 weights and many rows per expert: when the caller has added room for it the weights may be expanded to bf16 once per call, for the fused
+    // kernel, which takes bf16 only.  Where that is estimated to be the faster way, us, tiles on the codes / expansion and fused kernel: E 4, d 7168, f 2048, 2100 /
+    // 3300 / 5000 rows per expert 746 / 788, 1105 / 1064, 1675 / 1514; E 8, d 1024, f 3456, 3100 / 5000 578 / 551, 901 / 813; E 1, d 4096, f 14336, 2560 / 3600
+    // 870 / 929, 1166 / 1132.
+    const Route chosen = route(M, S, E_loc, d, f, fp8, workspace_bytes - base_bytes >= moe_ffn_expanded_weights_bytes(E_loc, d, f));
+    if (chosen == EXPAND) {
         __bf16* wg = (__bf16*)((char*)workspace + base_bytes);
         __bf16* wu = wg + (size_t)E_loc * f * d;
         __bf16* wd = wu + (size_t)E_loc * f * d;
@@ -2501,7 +2530,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
                                             row_map, row_gate, y, workspace, base_bytes, hip_stream);
     }
 
-    const Route way = pinned(route(M, S, E_loc, d, f, fp8), f, fp8);
+    const Route way = pinned(chosen, f, fp8);
     if (way == STREAM) {
         // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
         // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
@@ -2558,7 +2587,7 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
                : off32 ? launch_both_adaptive<ROWS_LIST32>(a, max_blocks, E_loc, s) : launch_both_adaptive<ROWS_LIST64>(a, max_blocks, E_loc, s);
     f32x4* part = (f32x4*)((char*)workspace + base_bytes);
     const size_t part_bytes = workspace_bytes - base_bytes;
-    if (bm == 256) return fp8 ? launch_both_tile<true, 256>(a, max_blocks, part, part_bytes, s) : launch_both_tile<false, 256>(a, max_blocks, part, part_bytes, s);
+    if (bm == 256) return launch_both_tile<false, 256>(a, max_blocks, part, part_bytes, s);
     if (bm == 128) return fp8 ? launch_both_tile<true, 128>(a, max_blocks, part, part_bytes, s) : launch_both_tile<false, 128>(a, max_blocks, part, part_bytes, s);
     return fp8 ? launch_both_tile<true, 64>(a, max_blocks, part, part_bytes, s) : launch_both_tile<false, 64>(a, max_blocks, part, part_bytes, s);
 }
@@ -2616,7 +2645,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     // The row products run in tiles of 128 columns where the forward pass would (see route: the shapes are alike), with few rows of 64 where it would stream.
     // us, whole call with 256 x 256 tiles / now: E 4, d 2048, f 1408, 200 / 1000 / 4000 rows 260 / 122, 300 / 159, 540 / 299; E 1, d 4096, f 14336, 200 / 1000 / 4000 rows 1190 / 510, 1630 /
     // 1067, 3450 / 3171; E 8, d 1024, f 640, 1000 / 4000 rows 190 / 95, 270 / 153.
-    const Route way = pinned(route(M, S, E_loc, d, f, false), f, false);
+    const Route way = pinned(route(M, S, E_loc, d, f, false, false), f, false);
     const int bm = way == TILE_64 || way == STREAM ? 64 : (way == TILE_128 ? 128 : 256);
     const PlanArgs rows_plan = {offsets, S, E_loc, M, bm, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr,
                                 (int*)(ws + L.ebase), bases};

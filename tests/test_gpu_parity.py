@@ -558,8 +558,8 @@ def test_ffn_buffers_at_addresses_with_bit_31_set(lib):
 
 
 def test_ffn_fp8_weights_expanded_once(lib):
-    """With room in the workspace and >= 2048 rows per expert the fp8 weights are expanded to bf16 before the GEMMs:
-    same values, so the same result up to the order of the fp32 sums."""
+    """Room in the workspace lets a call expand the fp8 weights to bf16, which rounds the scaled weights: the same result as without it, up to that
+    rounding and the order of the fp32 sums."""
     say("ffn fp8: weights expanded to bf16 once per call")
     E_loc, d, f, M, S = 2, 256, 384, 4500, 3
     W = workloads.ffn_weights(E_loc, d, f, seed=77, dtype="fp8")
@@ -580,6 +580,33 @@ def test_ffn_fp8_weights_expanded_once(lib):
         outs.append(oracle.decode_bf16(yb))
     scale = np.abs(outs[0]).max()
     assert np.abs(outs[0] - outs[1]).max() <= 0.02 * scale
+
+
+@pytest.mark.parametrize("E_loc,d,f,M,expanded", [(8, 512, 1408, 72000, True), (8, 512, 1408, 16383, False), (1, 2048, 1408, 4096, False), (2, 256, 384, 4500, False)])
+def test_ffn_fp8_calls_that_expand(lib, E_loc, d, f, M, expanded):
+    """fp8 weights are expanded where there is room, 2048 rows per expert and the fused kernel is the faster way all the same; a few thousand rows are
+    worked on in tiles."""
+    say("ffn fp8: calls that expand", E_loc, d, f, M)
+    w = workloads.ffn_weights_on_device(E_loc, d, f, M, "fp8", DEV)
+    x = workloads.activations_on_device(M, d, 83, DEV)
+    off = (np.arange(E_loc + 1) * M // E_loc).astype(np.int32)
+    base = lib.moe_ffn_workspace_bytes(M, d, f)
+    for nbytes, want in ((base + lib.moe_ffn_expanded_weights_bytes(E_loc, d, f), expanded), (base, False)):
+        if not want and nbytes > base and M < 2048 * E_loc:
+            nbytes *= 2                                                   # (however much room there is)
+        lib.moe_kernel_timing_enable(True)
+        try:
+            y = lib.moe_expert_ffn_sliced(x, dev(off), 1, E_loc, workspace=torch.empty((nbytes,), dtype=torch.uint8, device=DEV), **w)
+            torch.cuda.synchronize()
+            names = lib.moe_kernel_timing_read()
+        finally:
+            lib.moe_kernel_timing_enable(False)
+        assert ("ffn_expand_fp8_kernel" in names) == want, names
+        for e in range(E_loc):
+            wg, wu, wd = float_weights(w, e)
+            xs = x[off[e]:off[e] + 300].float()
+            ref = (torch.nn.functional.silu(xs @ wg.t()) * (xs @ wu.t())) @ wd.t()
+            check_ffn_error(float((y[off[e]:off[e] + 300].float() - ref).abs().max() / ref.abs().max()), "fp8", "expert %d" % e)
 
 
 @pytest.mark.parametrize("mapped", [False, True])
