@@ -1057,8 +1057,10 @@ void ffn_kmajor_kernel(const __bf16* __restrict__ x, const int32_t* __restrict__
 }
 
 // W wavefronts, NC 16-row column tiles of weights, at most MT 16-row tiles of activations, D register buffers
+// (fp8, two row tiles: two workgroups per compute unit.  Its registers would let in three, which leaves other units with one: 448 workgroups of E 16, d 7168, f 2048,
+// 24 rows, phase 1 65 us, with two 50; E 32, d 2048, f 768, 17 rows 18, 14.)
 template <int PHASE, int W, int NC, int MT, int D, bool FP8>
-__global__ __launch_bounds__(W * 64)
+__global__ __attribute__((amdgpu_waves_per_eu(1, FP8 && MT == 2 ? 2 : 8))) __launch_bounds__(W * 64)
 void ffn_skinny_kernel(SkinnyArgs a) {
     static_assert(PHASE == 2 || NC % 2 == 0, "gate and up tiles in pairs");
     constexpr int ESZ = FP8 ? 1 : 2, WL = FP8 ? 1 : 2;                     // 16-byte weight loads per lane, column tile and 64 values of K
@@ -1814,18 +1816,19 @@ moe_status launch_skinny(const SkinnyArgs& a, hipStream_t s) {
     // (fewer rows in the whole call than a workgroup takes: the variants with fewer row tiles need fewer registers)
     if (a.M <= 16) return launch_skinny_tiles<PHASE, W, NC, 1, D, FP8>(a, s);
     if (a.M <= 32) return launch_skinny_tiles<PHASE, W, NC, 2, D, FP8>(a, s);
-    // 128 rows per workgroup (one wavefront per SIMD) halve the readings of the weights, as long as enough workgroups are left for the
+    // bf16: 128 rows per workgroup (one wavefront per SIMD) halve the readings of the weights, as long as enough workgroups are left for the
     // chip: for more than every other compute unit with one expert, for three units in eight with several, whose rows are unequal.
     // From more than 64 rows per expert on average; from 32 with 5 to 16 experts, the popular ones of which have several chunks of 64, and
-    // in bf16 where a second reading of the weights is long (a matrix of 16 MiB).  64 / 128 rows, us: E 1, d 4096, f 14336, 128 rows
-    // 191 / 154; E 1, d 2048, f 1408, 128 / 384 rows 29 / 38, 53 / 42; E 1, d 256, f 512, 1024 / 1536 rows 18 / 25, 29 / 26; Zipf popularity: E 4, d = f =
-    // 512, 256 rows per expert 35 / 25; E 4, d 2048, f 1408, 48 / 64 / 96 rows 35 / 42, 44 / 47, 52 / 50; E 4, d 7168, f 2048, 48 rows 126 / 112, in fp8 89 / 93;
-    // E 8, d 768, f 384, 96 rows 39 / 30; E 16, d 2048, f 1408, 32 rows 113 / 99, in fp8 89 / 79; fp8 E 32, d 2048, f 768, 32 rows 109 / 127.
-    const long long groups = (long long)a.E * (a.f / 32) * ((a.M / a.E + 127) / 128);
-    const bool fills = a.E == 1 ? 2 * groups > num_cus() : 8 * groups >= 3 * num_cus();
-    const bool early = a.E > 4 ? a.E <= 16 && a.M >= 32LL * a.E : !FP8 && a.E > 1 && a.M > 32LL * a.E && (long long)a.d * a.f >= (8LL << 20);
-    if (fills && (a.M > 64LL * a.E || early))
-        return launch_skinny_tiles<PHASE, W, NC, 8, 2, FP8>(a, s);
+    // where a second reading of the weights is long (a matrix of 16 MiB).  64 / 128 rows, us: E 1, d 256, f 512, 300 / 1000 rows 17 / 21, 18 / 25; E 4, d 256, f 512,
+    // 75 rows per expert 16 / 19; E 8, d 256, f 512, 75 / 100 23.3 / 20.6, 25.4 / 23.8; E 8, d 512, f 1024, 35 / 50 26 / 23, 27 / 25; E 16, d 2048, f 1408, 32 / 75 / 93
+    // 114 / 97, 158 / 138, 190 / 156.  In fp8 the scales of 128 rows' sums cost more than a second reading: E 16, d 2048, f 1408, 18 / 32 rows 63 / 64, 76 / 80; E 32,
+    // d 2048, f 768, 18 rows 81 / 95; E 8, d 256, f 512, 37 / 100 rows 16.7 / 19.0, 21.4 / 24.3.
+    if constexpr (!FP8) {
+        const long long groups = (long long)a.E * (a.f / 32) * ((a.M / a.E + 127) / 128);
+        const bool fills = a.E == 1 ? 2 * groups > num_cus() : 8 * groups >= 3 * num_cus();
+        const bool early = a.E > 4 ? a.E <= 16 && a.M >= 32LL * a.E : a.E > 1 && a.M > 32LL * a.E && (long long)a.d * a.f >= (8LL << 20);
+        if (fills && (a.M > 64LL * a.E || early)) return launch_skinny_tiles<PHASE, W, NC, 8, 2, FP8>(a, s);
+    }
     return launch_skinny_tiles<PHASE, W, NC, 4, D, FP8>(a, s);
 }
 
@@ -2533,8 +2536,8 @@ extern "C" moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t*
     const Route way = pinned(chosen, f, fp8);
     if (way == STREAM) {
         // x K-major: where rows of x lie a multiple of 4 KiB apart (all 16 rows of a fragment in one memory channel) and there are
-        // enough of them to pay for the launch.  Without / with, us: E 1, d 4096, f 14336, 16 / 64 / 128 / 256 rows: 77 / 119 / 171 /
-        // 325, 79 / 112 / 154 / 280; E 4, d 2048, f 1408, 128 / 256 rows: 54 / 90, 57 / 84; not so E 4, d 7168, f 2048, 128 rows: 204, 213.
+        // enough of them to pay for the launch (more than 8 experts: fewer work in tiles from there on).  Without / with, us: E 16, d 2048, f 1408, 800 / 1200 / 1500 rows
+        // 122 / 140 / 162, 123 / 138 / 156.
         __bf16* xk = nullptr;
         const bool pays = d % 2048 == 0 && M >= ((long long)E_loc * f >= 8192 ? 48LL : 160LL) * E_loc;
         if (pays && M <= KMAJOR_ROWS && workspace_bytes - base_bytes >= kmajor_bytes(M, d)) xk = (__bf16*)((char*)workspace + base_bytes);
