@@ -2303,13 +2303,21 @@ void ffn_bwd_dw_kernel(DwArgs a) {
                         f32x16 sum;
 #pragma unroll
                         for (int v = 0; v < 16; ++v) sum[v] = 0.f;
-                        for (int p = 0; p < eparts; ++p) {
+                        for (int p = 0; p < eparts; p += 4) {             // (four parts' loads in flight: each is a round trip to where every die sees them)
+                            f32x4 v[4][4];
 #pragma unroll
-                            for (int g = 0; g < 4; ++g) {
-                                const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16,
-                                                    first + (unsigned int)p * (unsigned int)DW_UNIT_BYTES + (unsigned int)((mb * 4 + q) * 4 + g) * 1024u, DEVICE_SCOPE));
+                            for (int i = 0; i < 4; ++i)
 #pragma unroll
-                                for (int k = 0; k < 4; ++k) sum[g * 4 + k] += v[k];
+                                for (int g = 0; g < 4; ++g)
+                                    v[i][g] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16,
+                                                  first + (unsigned int)min(p + i, eparts - 1) * (unsigned int)DW_UNIT_BYTES + (unsigned int)((mb * 4 + q) * 4 + g) * 1024u, DEVICE_SCOPE));
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {                 // (every load is used: one left behind would be waited for among the next unit's copies)
+                                const bool live = p + i < eparts;
+#pragma unroll
+                                for (int g = 0; g < 4; ++g)
+#pragma unroll
+                                    for (int k = 0; k < 4; ++k) sum[g * 4 + k] += live ? v[i][g][k] : 0.f;
                             }
                         }
                         acc[mb][q] = sum;
