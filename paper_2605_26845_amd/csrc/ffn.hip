@@ -1861,7 +1861,7 @@ moe_status launch_both_skinny(const SkinnyArgs& a, hipStream_t s) {
 // ---- which kernels a call takes.  Only M, an upper bound of the rows, is known here, and not how unequal the experts are.  Up to 8 experts the times
 // of the ways are estimated (us) and the least is taken.  The constants were fitted to 2999 calls timed in every way (75 shapes of E 1 .. 8, d 256 .. 7168, f 256 .. 14336;
 // 33 rows .. 5000 rows per expert, Zipf popularity, bf16 and fp8): the chosen way takes 1.6 % (bf16) and 0.6 % (fp8) longer than the best one on average.
-// (Up to 32 rows: streams_few.)
+// (Up to 32 rows: streams_few.)  Where M is twice the rows, bf16 calls take 4.0 % longer than in the best way.
 // us, streaming / tiles of 64 / 128 / 256 rows / fused, rows in all:
 //   bf16 E 1, d 4096, f 14336: 36 rows 94 87 107 94 -, 69 rows 124 97 116 97 -, 274 rows 349 218 182 160 453, 1063 rows 1089 582 453 425 578, 4497 rows - 2006 1635 1513 1456
 //   bf16 E 4, d 2048, f 1408: 42 rows 23 26 35 30 -, 293 rows 51 28 38 40 -, 1449 rows 124 56 53 51 116, 5042 rows - 137 114 112 148, 16073 rows - 374 299 313 273
@@ -1875,7 +1875,7 @@ struct Estimate {
     // tile; us per row and 10^8 weights of a matrix
     double stream_open, stream_bytes, chain, wide, narrow, row_tile, rows;
 };
-constexpr Estimate ESTIMATE[2] = {{{0.749, 1.18, 0.792}, {0.383, 1.31, 6.67}, {0.259, 0.332, 0.457}, {6.67, 15.4, 9.98}, 6.91, 0.716, 12.9, 3.79, 1.74, 3.92, 6.61, 0.179, 0.00535, 0.22, 3.13},        // bf16
+constexpr Estimate ESTIMATE[2] = {{{0.749, 1.19, 0.809}, {0.332, 1.57, 6.04}, {0.268, 0.325, 0.471}, {6.22, 15, 11}, 7.17, 0.713, 12.7, 3.7, 1.79, 3.84, 6.7, 0.179, 0.0144, 0.212, 3.27},        // bf16
                                   {{0.635, 0.968}, {0.87, 2.37}, {0.306, 0.266}, {12.9, 17.8}, 6.95, 0.843, 11.7, 4.31, 3.73, 3.65, 7.08, 0.101, 0.00953, 0.323, 2.49}};       // fp8
 size_t tile_part_bytes(int d, int f) { return std::max(d, f) / 64 < 2 * TILE_MIN_SLABS ? 0 : (size_t)TILE_COUNTERS * TileShape<128, false>::UNIT_BYTES; }
 double experts_with_rows(int M, int E_loc) { return (double)E_loc * M / (M + E_loc - 1); }       // (about, with Zipf popularity)
@@ -1906,10 +1906,10 @@ double tile_us(int M, int E_loc, int d, int f, bool fp8, int rows, int cus) {
 // fused: the same with tiles of 256 x 256 and one round at least per phase
 double fused_us(int M, int E_loc, int d, int f, int cus) {
     const double blocks = E_loc == 1 ? (M + 255) / 256 : (double)M / 256 + 0.5 * E_loc;
-    double us = 50.3;
+    double us = 44.6;
     for (int phase = 1; phase <= 2; ++phase) {
         const double full = blocks * (phase == 1 ? f / 128 : d / 256) / cus;
-        us += (full <= 1.0 ? 1.0 : 0.86 * full + 0.14 * std::ceil(full)) * ((phase == 1 ? d : f) / 64 * 1.59 + 1.28);
+        us += (full <= 1.0 ? 1.0 : 0.884 * full + 0.116 * std::ceil(full)) * ((phase == 1 ? d : f) / 64 * 1.65 + 2.3);
     }
     return us;
 }
