@@ -2451,24 +2451,19 @@ BwdLayout bwd_layout(int M, int E_loc, int d, int f) {
     L.dh = take((size_t)M * L.f_pad * 2);
     L.dgu = take((size_t)M * 2 * f * 2);
     L.h = take((size_t)M * f * 2);
-    L.part = o;                                  // (last: places for partial sums, as many as the workspace has room for)
+    L.part = o;                                  // (last: bwd_part_bytes)
     return L;
 }
-// What a caller is told to bring.  The size is that of the tables, of dh, dg, du, h and the transposed weights, and of copies and 16-bit partial sums that a call
-// no longer makes: programs size their buffers by it, and the places for partial sums (at most DW_MAX_UNITS are used) lie there.
-size_t bwd_workspace_bytes(int M, int E_loc, int d, int f) {
-    const long long tiles = (long long)E_loc * ((f + 255) / 256) * (d / 256);
-    int P = 1;
-    while (P < 16 && tiles * P < 8 * 256 && (long long)M / E_loc / (2 * P) >= 1024) P *= 2;
-    const int f_pad = (f + 255) / 256 * 256, cols = (M + 127) / 128 * 128 + 256 * P * E_loc, wrows = E_loc * P * f;
-    size_t o = 0;
-    for (int rows : {M, wrows}) o += al256((size_t)(plan_capacity(rows) + PLAN_HDR) * sizeof(int4)) + al256((size_t)plan_capacity(rows) * sizeof(int));
-    o += al256(list_bytes(M)) + al256(EBASE_BYTES) + al256(48 * sizeof(int)) + al256((size_t)E_loc * P * sizeof(int4)) + al256((size_t)(E_loc * P + 1) * sizeof(int32_t));
-    o += 2 * al256((size_t)cols * sizeof(int)) + al256((size_t)E_loc * f_pad * d * 2) + al256((size_t)E_loc * d * 2 * f * 2);
-    o += al256((size_t)M * f_pad * 2) + al256((size_t)M * 2 * f * 2) + al256((size_t)M * f * 2);
-    o += 2 * al256((size_t)d * cols * 2) + 3 * al256((size_t)f * cols * 2) + al256((size_t)E_loc * f * d * 2) + (P > 1 ? al256((size_t)E_loc * P * f * d * 2) : 0);
-    return o;
+// Places for the sums of the weight gradients' parts: an expert of r rows has at most r / DW_PART_ROWS parts with a place per tile, and fewer than two of
+// them serve nobody
+int dw_places(int M, int d, int f) {
+    const long long tiles = dw_tiles(d, f), places = std::min<long long>(DW_MAX_UNITS, (long long)(M / DW_PART_ROWS) * tiles);
+    return places < 2 * tiles ? 0 : (int)places;
 }
+// The tables, dh, dg, du, h, the transposed weights (all that a call must have), and places for the sums of the weight gradients' parts or of the row products' split
+// contractions, without which these are in fewer parts.  More room than that changes nothing.
+size_t bwd_part_bytes(int M, int d, int f) { return std::max(dw_places(M, d, f) * DW_UNIT_BYTES, tile_part_bytes(d, 2 * f)); }
+size_t bwd_workspace_bytes(int M, int E_loc, int d, int f) { return bwd_layout(M, E_loc, d, f).part + bwd_part_bytes(M, d, f); }
 
 }  // namespace
 
@@ -2631,8 +2626,9 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
           (uintptr_t)dw_up | (uintptr_t)dw_down | (uintptr_t)workspace) & 15) != 0)
         return MOE_ERR_INVALID_ARG;
     const BwdLayout L = bwd_layout(M, E_loc, d, f);
-    if (M + 256LL * E_loc >= (1LL << 22)) return MOE_ERR_UNSUPPORTED_SHAPE;       // (a limit of the interface)
-    if (!workspace || workspace_bytes < bwd_workspace_bytes(M, E_loc, d, f)) return MOE_ERR_WORKSPACE;
+    if (M + 256LL * E_loc >= (1LL << 22)) return MOE_ERR_UNSUPPORTED_SHAPE;       // (a limit of the interface, which no kernel here needs any more)
+    if (!workspace || workspace_bytes < L.part) return MOE_ERR_WORKSPACE;
+    const size_t part_bytes = std::min(workspace_bytes - L.part, bwd_part_bytes(M, d, f));
     hipStream_t s = (hipStream_t)hip_stream;
     char* ws = (char*)workspace;
     int4* plan_rows = (int4*)(ws + L.plan_rows);
@@ -2661,7 +2657,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     const PlanArgs rows_plan = {offsets, S, E_loc, M, bm, plan_capacity(M), plan_rows, (int*)(ws + L.ready_rows), nullptr, nullptr, list, nullptr,
                                 (int*)(ws + L.ebase), bases};
     if ((st = launch_plan(rows_plan, s)) != MOE_OK) return st;
-    const int tiles = dw_tiles(d, f), units = (int)std::min<size_t>(DW_MAX_UNITS, (workspace_bytes - L.part) / DW_UNIT_BYTES);
+    const int tiles = dw_tiles(d, f), units = (int)std::min<size_t>(dw_places(M, d, f), part_bytes / DW_UNIT_BYTES);
     {
         moe::LaunchScope k("bwd_prep_kernel", s);
         hipLaunchKernelGGL(bwd_prep_kernel, dim3(1), dim3(PLAN_THREADS), 0, s, bases, E_loc, tiles, num_cus(), units, (int4*)(ws + L.entries), counters,
@@ -2694,7 +2690,6 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     const bool off32 = (unsigned long long)M * d * 2 < 0xFFFFFF00ull;
 
     f32x4* const part = (f32x4*)(ws + L.part);
-    const size_t part_bytes = workspace_bytes - L.part;
     const long long max_blocks = M / bm + E_loc;
     // ---- dh = dy Wd: rows x f_pad, K = d
     a.g2.A = (const __bf16*)dy; a.g2.lda = d;

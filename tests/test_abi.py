@@ -71,17 +71,21 @@ def test_ffn_workspace_grows_with_the_rows(d, f):
     assert sizes == sorted(sizes)
 
 
-@pytest.mark.parametrize("E_loc,d,f,first", [(1, 1024, 1024, [2048, 4096, 8192, 16384]), (64, 1024, 512, [2048, 4096]), (1, 4096, 14336, [2048, 4096])])
-def test_parts_of_the_weight_gradients(E_loc, d, f, first):
-    """The contraction of a weight gradient is cut into parts of at least 1024 rows per expert (a part's sum is rounded to bf16), up to
-    16 of them and 2048 output tiles: the rows per expert from which on the workspace holds twice the partial sums."""
+@pytest.mark.parametrize("E_loc,d,f", [(1, 256, 256), (64, 1024, 512), (1, 1024, 1024), (4, 2048, 1408), (1, 4096, 14336), (300, 256, 384)])
+def test_backward_workspace_holds_what_a_call_uses(E_loc, d, f):
+    """dh, dg, du and h of every row, the transposed weights, places for partial sums (256 KiB per tile and part of 768 rows, 1024 of them at most; 32 MiB
+    where contractions of 1536 values or more are split), and tables of a few bytes per row; no copies of x or dy, and never less for more rows."""
     L = moe.load()
-    need = lambda rows: L.moe_ffn_backward_workspace_bytes(rows * E_loc, E_loc, d, f)
-    # (a row adds to the transposed operands, dh, dg, du and h, and in steps of 128 rows to their padding)
-    part = 2 * E_loc * d * f * 2
-    jumps = [r for r in range(32, 20001, 32) if need(r) - need(r - 32) > part]
-    assert jumps == first
-    assert need(first[0]) - need(first[0] - 1) > part > need(first[0] - 1) - need(first[0] - 32)
+    f_pad, tiles = -(-f // 256) * 256, f // 128 * (d // 256) + d // 256 * -(-f // 256)
+    before = 0
+    for M in (0, 1, 100, 767, 1535, 1536, 4000, 36833, 72408, 1 << 20):
+        need = L.moe_ffn_backward_workspace_bytes(M, E_loc, d, f)
+        operands = 2 * M * (f_pad + 3 * f) + 2 * E_loc * (f_pad * d + 2 * d * f)
+        places = min(1024, M // 768 * tiles)
+        sums = max((places << 18) if places >= 2 * tiles else 0, (32 << 20) if max(d, 2 * f) >= 1536 else 0)
+        assert 0 < need - operands - sums <= (3 << 20) + 8 * M, M
+        assert need >= before
+        before = need
 
 
 def test_probe_argument_checks_need_no_gpu():

@@ -1150,13 +1150,13 @@ def test_ffn_backward_without_groups(lib, S, M, E_loc):
 
 @pytest.mark.parametrize("E_loc,M", [(1, 1023), (1, 1024), (1, 2100), (2, 4500), (1, 4200), (1, 9000), (1, 16500)])
 def test_ffn_backward_parts(lib, E_loc, M):
-    """1, 1, 2, 2, 4, 8 and 16 parts of the contraction of the weight gradients (at least 1024 rows each)."""
+    """Contractions of the weight gradients over a few hundred rows up to many parts of at least 768 rows: three slices' rows listed, remainders."""
     check_backward(lib, E_loc, 256, 256, M, 3, M, "parts")
 
 
 @pytest.mark.parametrize("M", [1024, 1500, 2047])
 def test_ffn_backward_sums_below_2048_rows_are_exact(lib, M):
-    """An expert with fewer than 2048 rows is one fp32 accumulation: with the same x in every row and dy of +1 for the first half
+    """The sums of an expert's rows, in one part or in two (from 1536 rows), are fp32: with the same x in every row and dy of +1 for the first half
     (and three more rows), -1 for the rest, dw_down is a small multiple of h, which a partial sum rounded to bf16 would lose
     (half the rows times h keeps 8 bits).  Every fp32 sum here is a multiple of h below 2^11 h: exact."""
     say("ffn backward exact sums", M)
@@ -1291,6 +1291,42 @@ def test_ffn_backward_row_products(lib, tile_rows, kernels, d, f, S, sizes):
             if sizes[e]:
                 check_ffn_error(float(np.abs(got[e] - want[e]).max() / np.abs(want[e]).max()), "bf16", "%s[%d]" % (name, e))
     assert all(torch.equal(out[k], again[k]) for k in out)
+
+
+@pytest.mark.parametrize("tile_rows,kernels", [(0, 0), (64, 0), (128, 0), (256, 1)])
+@pytest.mark.parametrize("d,f,S,sizes", [(256, 256, 1, [1536, 1]), (512, 1664, 2, [700, 90]), (256, 384, 3, [40000, 200]), (1024, 512, 1, [9000, 8000])])
+def test_ffn_backward_stays_inside_its_workspace(lib, tile_rows, kernels, d, f, S, sizes):
+    """A workspace of just the stated size, in front of bytes that are looked at afterwards: more of it changes no bit.  One without places for partial sums serves
+    as well, with whole contractions; one without room for the tables and operands is refused."""
+    say("ffn backward stays inside its workspace", tile_rows, d, f, S, sizes)
+    E_loc, M = len(sizes), sum(sizes)
+    rng = np.random.default_rng(d + f)
+    parts = np.stack([rng.multinomial(n, np.full(S, 1.0 / S)) for n in sizes], axis=1)
+    off = dev(np.concatenate([[0], np.cumsum(parts.ravel())]).astype(np.int32))
+    w = workloads.ffn_weights_on_device(E_loc, d, f, d + f, "bf16", DEV)
+    x, dy = workloads.activations_on_device(M, d, 91, DEV), workloads.activations_on_device(M, d, 92, DEV)
+    need = int(lib.load().moe_ffn_backward_workspace_bytes(M, E_loc, d, f))
+    room = torch.full((need + (64 << 20),), 0xA5, dtype=torch.uint8, device=DEV)
+    lib.moe_ffn_tile_override(tile_rows, kernels)
+    try:
+        just = lib.moe_expert_ffn_backward_sliced(x, dy, off, S, E_loc, **w, workspace=room[:need])
+        torch.cuda.synchronize()
+        assert bool((room[need:] == 0xA5).all())
+        more = lib.moe_expert_ffn_backward_sliced(x, dy, off, S, E_loc, **w, workspace=room)
+        torch.cuda.synchronize()
+        tiles = f // 128 * (d // 256) + d // 256 * -(-f // 256)
+        places = min(1024, M // 768 * tiles)
+        least = need - max((places << 18) if places >= 2 * tiles else 0, (32 << 20) if max(d, 2 * f) >= 1536 else 0)
+        room.fill_(0xA5)
+        whole = lib.moe_expert_ffn_backward_sliced(x, dy, off, S, E_loc, **w, workspace=room[:least])
+        torch.cuda.synchronize()
+        assert bool((room[least:] == 0xA5).all())
+        with pytest.raises(lib.MoeError):
+            lib.moe_expert_ffn_backward_sliced(x, dy, off, S, E_loc, **w, workspace=room[:least - 1])
+    finally:
+        lib.moe_ffn_tile_override()
+    assert all(float((just[k].float() - whole[k].float()).norm() / whole[k].float().norm()) <= 2.0 ** -7 for k in just)      # (dh, dg and du round to bf16 in between)
+    assert all(torch.equal(just[k], more[k]) for k in just)
 
 
 def test_ffn_backward_edge_cases(lib):
