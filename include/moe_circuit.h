@@ -40,7 +40,8 @@ typedef int moe_status;
 
 /* flags of the decomposition calls */
 #define MOE_DECOMP_ZERO_DIAGONAL 1  /* treat the diagonal (tokens whose expert is local) as zero */
-#define MOE_DECOMP_CLEAR_TAIL    8  /* perms and durations behind the last matching become zero (else they are untouched) */
+#define MOE_DECOMP_CLEAR_TAIL    8  /* perms and durations behind the last matching become zero (else they are untouched);
+                                       moe_decompose_greedy and moe_decompose_bvn, no effect on moe_decompose_sinkhorn_bvn */
 /* moe_decompose_greedy keeps the residual of a matrix on chip, in 16 bits when that lets more matrices share a
  * compute unit (N > 64 in batches that fill the chip more than twice over); a matrix with an entry >= 65536 is
  * then decomposed again with a 32-bit residual by a second launch.  Results do not depend on the choice.  The two
@@ -81,7 +82,7 @@ moe_status moe_route_histogram(const int32_t* ids, int L, int N, int T, int topk
  *   residual   out  int32 [B][N][N]  R at exit (all zero unless the cap stopped it); may be NULL
  *   hashes     out  uint64 [B]; may be NULL.  FNV-1a (64 bit) over the byte stream
  *                   sigma_t(0..N-1), duration_t (4 bytes little endian), t = 0..count-1
- * Entries of perms / durations at t >= counts[b] are left untouched.
+ * Entries of perms / durations at t >= counts[b] are left untouched, with MOE_DECOMP_CLEAR_TAIL set to zero.
  * Limits: 1 <= N <= MOE_MAX_RANKS, kmax >= 0, B >= 0.
  * ------------------------------------------------------------------------------------------- */
 moe_status moe_decompose_greedy(const int32_t* mats, int B, int N, int kmax, int flags,
@@ -213,13 +214,19 @@ moe_status moe_slice_table_rows(const int32_t* ids, int N, int T, int topk, int 
  *   s_gate,s_up in  float [E_loc][f/128][d/128], s_down float [E_loc][d/128][f/128]
  *                   (MOE_W_FP8_E4M3_B128 only, else NULL): weight = decode(code) * scale
  *   y          out  bf16 [M][d]; rows >= offsets[last] are left untouched
- *   workspace       moe_ffn_workspace_bytes(M, d, f) bytes (holds the hidden activations and, for up to
- *                   4096 rows, a copy of x; a call whose workspace lacks room for the copy reads x itself;
- *                   never less for a larger M, so one sized for the largest M serves every call).  With
- *                   MOE_W_FP8_E4M3_B128 the caller may add moe_ffn_expanded_weights_bytes(E_loc, d, f)
- *                   bytes: when there are at least 2048 rows per local expert on average the weights
- *                   are then expanded to bf16 once per call (the same values the kernels would form
- *                   tile by tile) and the faster bf16 kernels run
+ *   workspace       moe_ffn_workspace_bytes(M, d, f) bytes: the hidden activations and tables of the rows,
+ *                   and behind them a copy of x for up to 4096 rows or the fp32 sums of contractions that
+ *                   are split over workgroups (32 MiB where d or f is 1536 or more).  Never less for a
+ *                   larger M, so one sized for the largest M serves every call.  A call whose workspace
+ *                   lacks room for the copy reads x itself, and one that lacks room for the sums splits
+ *                   contractions less: the fp32 sums are then added in another order and the last bits
+ *                   of y may differ.  With MOE_W_FP8_E4M3_B128 the caller may add
+ *                   moe_ffn_expanded_weights_bytes(E_loc, d, f) bytes: from 2048 rows per local expert on
+ *                   average the weights are then expanded to bf16 once per call where the bf16 kernels
+ *                   are expected to be the faster way all the same.  An expanded weight is decode(code) *
+ *                   scale rounded to bf16; the kernels that read the codes themselves round no weight
+ *                   (the scale multiplies the fp32 sums), so results of the two ways differ by that
+ *                   rounding
  * Limits: d % 256 == 0, f % 128 == 0, S*E_loc <= 65536, M < 2^31, d and f <= 2^22, d*f < 2^31
  * (MOE_ERR_UNSUPPORTED_SHAPE otherwise; M*d may exceed 2^31: rows are addressed with 64 bits); x, y,
  * the weights and the workspace 16-byte aligned (MOE_ERR_INVALID_ARG otherwise).  The sigmoid inside
@@ -265,17 +272,21 @@ moe_status moe_expert_ffn_sliced_mapped(const void* x, const int32_t* offsets, i
  *     dw_down[e] = dy^T h  [d][f] ;  dw_gate[e] = dg^T x  [f][d] ;  dw_up[e] = du^T x  [f][d]
  * bf16 inputs, fp32 accumulation; dh, dg, du and h are rounded to bf16 once (g and u are recomputed
  * from x, nothing is kept from the forward call), the outputs are bf16.
- * The weight gradients of few output tiles are summed in 2 to 16 parts of at least 1024 rows per expert on
- * average; a part is accumulated in fp32 and rounded to bf16, the parts are added in fp32.
+ * An expert's weight gradients are summed over its rows in one part or, where that shortens the call, in up
+ * to 32 parts of at least 768 rows; a part is accumulated in fp32 and kept in fp32, the parts are added in
+ * fp32 in their order.
  *   x, dy      in   bf16 [M][d]   grouped rows as in moe_expert_ffn_sliced
  *   offsets    in   int32 [S*E_loc + 1]
  *   w_gate, w_up in bf16 [E_loc][f][d], w_down in bf16 [E_loc][d][f]   (bf16 weights only)
  *   dx         out  bf16 [M][d]; rows >= offsets[last] are left untouched
  *   dw_gate, dw_up out bf16 [E_loc][f][d], dw_down out bf16 [E_loc][d][f], overwritten (an expert
  *                   without rows gets zeros)
- *   workspace       moe_ffn_backward_workspace_bytes(M, E_loc, d, f) bytes
+ *   workspace       moe_ffn_backward_workspace_bytes(M, E_loc, d, f) bytes: tables, dh, dg, du, h and the
+ *                   transposed weights, which a call must have, and behind them the fp32 partial sums; a
+ *                   call that lacks room for these takes fewer parts (other last bits), more room than
+ *                   stated changes nothing.  Never less for a larger M
  * Limits: d % 256 == 0, f % 128 == 0, f >= 256, S*E_loc <= 65536, E_loc <= 4096, d*f < 2^30,
- * M < about 4 million rows (MOE_ERR_UNSUPPORTED_SHAPE otherwise); every pointer 16-byte aligned.
+ * M + 256*E_loc < 2^22 (MOE_ERR_UNSUPPORTED_SHAPE otherwise); every pointer 16-byte aligned.
  * ------------------------------------------------------------------------------------------- */
 size_t     moe_ffn_backward_workspace_bytes(int M, int E_loc, int d, int f);
 moe_status moe_expert_ffn_backward_sliced(const void* x, const void* dy, const int32_t* offsets, int M, int S, int E_loc,
