@@ -37,7 +37,7 @@ def parse():
     ap.add_argument("--workload", default="c3", choices=["tiny", "c2", "c3", "c4"])
     ap.add_argument("--ffn-kernels", type=int, default=0, choices=[0, 1, 2],
                     help="moe_ffn_tile_override's kernel choice: 0 = the library's own (both phases in one launch where it applies), "
-                         "1 = fixed-shape kernels, 2 = adaptive-shape kernels with one launch per phase")
+                         "1 = tiles of 128 columns instead of 256, 2 = adaptive-shape kernels with one launch per phase")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-extras", action="store_true")
     ap.add_argument("--vendor-gemm", action="store_true",

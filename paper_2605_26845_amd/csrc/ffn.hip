@@ -13,7 +13,7 @@
 // rows by 128 columns and splits contractions that would leave the chip idle; ffn_fused_kernel (bf16) runs both phases in one persistent
 // launch over tiles of 256 x 256, phase-2 tiles waiting for the rows of H they read (ffn_adaptive_kernel: one launch per phase).
 // moe_expert_ffn_backward_sliced (the backward pass: the exchange of Section 2.1 repeated for the gradients) runs the
-// same adaptive-shape kernels on other operands.
+// adaptive-shape and the tile kernels on other operands, and ffn_bwd_dw_kernel for the weight gradients.
 #include "common.hpp"
 #include "rows.hpp"
 #include "parts.hpp"
@@ -259,8 +259,8 @@ void ffn_plan_kernel(PlanArgs a) {
 }
 
 // The same plan for a call with few groups and rows: a group per thread, one scan and two barriers instead of loops around ten.  4 experts, 1024
-// rows in 6 slices: 6.6 -> 4.6 us (with the events around the launch); a call of that size takes 42.  (At most 33 blocks of 64 rows, so that
-// two passes fill the list and a thread per expert the table.)
+// rows in 6 slices: 6.6 -> 4.6 us (with the events around the launch); a call of that size takes 42.  (At most 33 experts and blocks of 64
+// rows, i.e. 2111 rows: the list is filled in three passes at most, and one wavefront's first threads write the table.)
 constexpr int SMALL_PLAN_BLOCKS = 33;
 bool small_plan(int M, int S, int e_loc) { return (long long)S * e_loc <= PLAN_THREADS && M / 64 + e_loc <= SMALL_PLAN_BLOCKS; }
 __global__ __launch_bounds__(PLAN_THREADS)
@@ -1276,7 +1276,6 @@ constexpr int TILE_SQUARE = 8;                               // column tiles tha
 //   256: 8 wavefronts (4 x 2) of 64 x 64, three slabs of 48 KiB, 1 workgroup per compute unit
 template <int ROWS, bool FP8> struct TileShape {
     static constexpr int WM = ROWS == 256 ? 4 : 2, MB = ROWS / (32 * WM), THREADS = 128 * WM;
-    static constexpr int PER_CU = WM == 4 ? 1 : 2;
     // Workgroups per compute unit up to which contractions are split.  (64 rows, one / two: E 1, d 4096, f 14336, 37 rows 85 / 100 us; fp8 E 4, d 7168, f 2048, 64
     // rows 48 / 58, 203 rows 69 / 65.  128 rows, 203 rows of the former 139 / 134; E 2, d 3584, f 4864, 512 rows 130 / 103.)
     static constexpr int SPLIT_PER_CU = ROWS == 128 ? 2 : 1;

@@ -664,7 +664,7 @@ def test_ffn_many_tiles_per_workgroup_all_rows(lib, dtype, tile_rows, fixed):
     """Every row against the oracle on a schedule large enough that the tile loop, the hand-over from one tile to the
     next (chained or not), ticket stealing, the counted-store wait and (both phases in one launch, the default for bf16
     weights and 256-row tiles) the wait of a phase-2 tile for its rows of h all run, for every kernel family
-    (`fixed`: 0 = the call's own choice, 1 = fixed-shape kernels, 2 = adaptive-shape kernels, one launch per phase)."""
+    (`fixed`: 0 = the call's own choice, 1 = tiles of 128 columns, 2 = adaptive-shape kernels, one launch per phase)."""
     say("ffn many tiles per workgroup", dtype, tile_rows, fixed)
     c = multi_tile_case(dtype)
     w = upload_weights(c["W"])
