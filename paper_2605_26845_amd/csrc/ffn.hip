@@ -352,12 +352,15 @@ __device__ __forceinline__ u32x4 dequant8(u32x2 codes, float scale) {
     return __builtin_bit_cast(u32x4, o);
 }
 
-// half of 16 consecutive codes -> 8 bf16, without a scale: every E4M3 value is a bf16 value
+// half of 16 consecutive codes -> 8 bf16, without their block's scale but times CODE_UNIT: every E4M3 value is a bf16 value, and 128 products of the
+// largest ones with any finite x stay finite in fp32 (with the codes as they are sums overflowed from |x| = 6e33 on, whatever the scale).  The scale that multiplies
+// a sum is divided by it, a power of two: no bit of a result changes.
+constexpr float CODE_UNIT = 0x1p-16f;
 __device__ __forceinline__ bf16x8 widen8(u32x4 codes, int half) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     const unsigned int lo = half ? codes.z : codes.x, hi = half ? codes.w : codes.y;
-    const bf16x2 v0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, false), v1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, true);
-    const bf16x2 v2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, false), v3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, true);
+    const bf16x2 v0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, CODE_UNIT, false), v1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, CODE_UNIT, true);
+    const bf16x2 v2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, CODE_UNIT, false), v3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, CODE_UNIT, true);
     return bf16x8{v0.x, v0.y, v1.x, v1.y, v2.x, v2.y, v3.x, v3.y};
 }
 
@@ -1193,7 +1196,7 @@ void ffn_skinny_kernel(SkinnyArgs a) {
                         }
                     }
                     if (FP8) {
-                        const float sc = b.sc[PHASE == 1 && c >= NH ? 1 : 0];
+                        const float sc = b.sc[PHASE == 1 && c >= NH ? 1 : 0] * (1.0f / CODE_UNIT);
 #pragma unroll
                         for (int t = 0; t < T; ++t)
 #pragma unroll
@@ -1490,7 +1493,7 @@ void ffn_tile_kernel(TileArgs t) {
             __builtin_amdgcn_sched_barrier(0);
         }
         if (FP8 && ODD) {
-            const float sc[2] = {scale[0][s >> 1], scale[1][s >> 1]};
+            const float sc[2] = {scale[0][s >> 1] * (1.0f / CODE_UNIT), scale[1][s >> 1] * (1.0f / CODE_UNIT)};
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll

@@ -987,6 +987,30 @@ def test_ffn_up_to_32_rows(lib, dtype, E_loc, d, f, sizes, streamed):
 
 
 
+@pytest.mark.parametrize("tile_rows,E_loc,d,f,sizes", [(0, 8, 1024, 512, [17, 0, 3, 0, 0, 1, 0, 0]), (0, 8, 1024, 512, [3, 0, 9, 0, 0, 1, 0, 3]),
+                                                       (64, 2, 1024, 512, [70, 130]), (128, 2, 512, 1664, [140, 0])])
+def test_ffn_fp8_large_activations(lib, tile_rows, E_loc, d, f, sizes):
+    """Sums of 128 products with codes stay finite where y does, though the scale multiplies them only afterwards: x times 2^118 with the scales of the gate
+    divided by it gives y times 2^118, bit by bit (scales are powers of two; no value leaves the normal range but the gate's scales, which stay exact)."""
+    say("ffn fp8 large activations", tile_rows, E_loc, d, f, sizes)
+    M, big = sum(sizes), 2.0 ** 118
+    w = workloads.ffn_weights_on_device(E_loc, d, f, M, "fp8", DEV)
+    for k in ("gate", "up", "down"):
+        w["s_" + k] = torch.full_like(w["s_" + k], 2.0 ** -12)
+    x = workloads.activations_on_device(M, d, M, DEV)
+    off = dev(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32))
+    lib.moe_ffn_tile_override(tile_rows)
+    try:
+        y = lib.moe_expert_ffn_sliced(x, off, 1, E_loc, **w)
+        w["s_gate"] = torch.full_like(w["s_gate"], 2.0 ** -130)
+        large = lib.moe_expert_ffn_sliced((x.float() * big).bfloat16(), off, 1, E_loc, **w)
+        torch.cuda.synchronize()
+    finally:
+        lib.moe_ffn_tile_override()
+    assert bool(torch.isfinite(large).all()) and float(y.abs().max()) * big * 2 ** 12 > torch.finfo(torch.float32).max
+    assert torch.equal(large, (y.float() * big).bfloat16())
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("tile_rows,kernels", [(64, 0), (128, 0), (256, 1)])
 @pytest.mark.parametrize("d,f,sizes", [
