@@ -1267,7 +1267,9 @@ void ffn_skinny_kernel(SkinnyArgs a) {
 // 64 x 64, two workgroups per compute unit, and where the tiles do not fill the slots (both workgroups of every compute unit) the contraction of
 // a tile is split over up to TILE_MAX_PARTS workgroups, which add their sums in fp32 in part order (the last one to finish does).
 // The plan says how many row blocks there are, so every workgroup works out the tiles, the split and its unit by itself; workgroups beyond the last unit
-// leave at once.  Bound by the operands' way from the L2 into LDS: 32 KiB per slab of 64 values of K for 4.2 Mflop.
+// leave at once.  With few rows bound by the weights' way from memory (37 rows of E 1, d 4096, f 14336: 5.0 and 4.2 TB/s in the two phases; 203 fp8 rows of E 4, d 7168, f 2048: 3.2 and
+// 3.0, where 160 tiles of phase 1 are too many to be split over 256 compute units and leave 96 of them idle), above that by the operands' way through LDS, 32 KiB per slab of 64 values
+// of K for 4.2 Mflop: 4000 rows of the latter 281 and 133 us, matrix cores busy 51 % of the cycles in which a compute unit has work, wavefronts waiting 27 %.
 // Both operands are copied global -> LDS as they lie; fp8 codes are widened to bf16 (exactly) on the way from LDS to the matrix cores, two values per
 // v_cvt_scalef32_pk_bf16_fp8, and the scale of a 128 x 128 block multiplies the fp32 sum over that block's 128 values of K.
 constexpr int TILE = 128;                                    // columns
@@ -2016,8 +2018,8 @@ moe_status launch_plan(const PlanArgs& p, hipStream_t s) {
 // global -> LDS as they lie, and the MFMA fragments are read with ds_read_b64_tr_b16, which hands lane c of 16 the values of four rows
 // in column c.  x and dy are gathered through the row list by the copies themselves (a row number is a scalar load, one slab
 // ahead); rows past an expert's end lie behind the buffer descriptor, for which the copy deposits zeros.
-// Bound by the matrix cores (67 % busy, at 1.02 PFLOP/s) and, beside them, by unequal experts.  E 4, d 2048, f 1408, 36833 rows: 623 us, whole backward
-// pass 1712; with transposed copies of x, dy, h, dg and du (295 us), three launches of the row GEMM that each waited for the most popular
+// Bound by the matrix cores (busy 69 % of the cycles in which a compute unit has work, 57 % of the launch's; 1.03 PFLOP/s) and, beside them, by unequal experts.  E 4, d 2048,
+// f 1408, 36833 rows: 620 us, whole backward pass 1654; with transposed copies of x, dy, h, dg and du (295 us), three launches of the row GEMM that each waited for the most popular
 // expert (797) and partial sums rounded to bf16 and added in three more (110) 2327.  E 1, d 4096, f 14336, 6000 rows: 1620 us, before 2480.
 // All products and experts are one launch, the longest contractions first.  A unit of work is a 256 x 256 tile of one expert's [dW_gate; dW_up] or
 // dW_down over one part of its rows; only experts behind which too little work is left to even out the ends are split (parts.hpp).
