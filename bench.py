@@ -101,7 +101,7 @@ def ffn_kernel_work(cfg, M):
 
 
 def profile_suffix(args):
-    return "_per_phase" if args.ffn_kernels == 2 else ("_fixed_shape" if args.ffn_kernels == 1 else "")
+    return "_per_phase" if args.ffn_kernels == 2 else ("_tiles_128" if args.ffn_kernels == 1 else "")
 
 
 def bench_flags(args):
