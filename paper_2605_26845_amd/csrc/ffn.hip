@@ -2064,12 +2064,12 @@ struct DwArgs {
 __global__ __launch_bounds__(PLAN_THREADS)
 void bwd_prep_kernel(const int* __restrict__ bases, int e_loc, int tiles, int cus, int cap, int4* __restrict__ entries, int* __restrict__ counters,
                      int* __restrict__ arrived, unsigned int* __restrict__ zeros) {
-    __shared__ int rows_of[MAX_GROUPS / 16], parts_of[MAX_GROUPS / 16], place_of[MAX_GROUPS / 16];
+    __shared__ int rows[DW_MAX_EXPERTS], order[DW_MAX_EXPERTS], parts[DW_MAX_EXPERTS], sums[PLAN_THREADS];
     const int tid = threadIdx.x;
     for (int i = tid; i < BWD_COUNTERS; i += PLAN_THREADS) counters[i] = 0;
     for (int i = tid; i < cap; i += PLAN_THREADS) arrived[i] = 0;
     for (int i = tid; i < DW_ZEROS / 4; i += PLAN_THREADS) zeros[i] = 0;
-    dw_split(bases, e_loc, tiles, cus, cap, entries, rows_of, parts_of, place_of, tid, PLAN_THREADS, [] { __syncthreads(); });
+    dw_split(bases, e_loc, tiles, cus, cap, entries, rows, order, parts, sums, tid, PLAN_THREADS, [] { __syncthreads(); });
 }
 
 template <bool LISTED, bool WIDE>
@@ -2623,7 +2623,7 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     if (!w_gate || !w_up || !w_down || !dw_gate || !dw_up || !dw_down) return MOE_ERR_INVALID_ARG;
     if (d % 256 != 0 || f % 128 != 0 || f < 256) return MOE_ERR_UNSUPPORTED_SHAPE;
     const long long G = (long long)S * E_loc;
-    if (G > MAX_GROUPS || E_loc > MAX_GROUPS / 16 || (long long)E_loc * 16 * f >= (1LL << 31)) return MOE_ERR_UNSUPPORTED_SHAPE;
+    if (G > MAX_GROUPS || E_loc > DW_MAX_EXPERTS || (long long)E_loc * 16 * f >= (1LL << 31)) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (d > (1 << 22) || f > (1 << 21) || (long long)d * f >= (1LL << 30)) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (M > 0 && (!x || !dy || !dx)) return MOE_ERR_INVALID_ARG;
     if ((((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx | (uintptr_t)w_gate | (uintptr_t)w_up | (uintptr_t)w_down | (uintptr_t)dw_gate |

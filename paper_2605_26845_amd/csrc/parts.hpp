@@ -14,6 +14,7 @@
 constexpr int DW_MAX_PARTS = 32;               // of one expert
 constexpr int DW_PART_ROWS = 768;              // rows of a part at least
 constexpr int DW_MAX_UNITS = 1024;             // parts of tiles with a place for their sums, at most
+constexpr int DW_MAX_EXPERTS = 4096;           // of a call (a power of two)
 
 // entries behind the first one, in pairs.  Only experts that have a place for the sums of all their parts are split, a part of an expert takes
 // a place per tile, and an expert has a tile at least: there are no more parts than one per expert and one per place.
@@ -25,50 +26,89 @@ MOE_PARTS_FN size_t dw_entries(int e_loc) { return 2 * ((size_t)e_loc + DW_MAX_U
 // Experts are granted their parts in that order while the `cap` places for sums last; from the first one that finds no room they stay in one part.
 //   bases     first position of every expert, and the end          tiles  of an expert's gradients
 //   entries   [0].x = number of parts; then per part (position, rows, expert, part), (parts of the expert, first place, 0, 0)
-//   rows_of, parts_of, place_of   [e_loc] each, shared by the threads
+//   rows, order   [least power of two >= e_loc] each, parts [e_loc], sums [threads]: shared by the threads
+// The experts are sorted by exchanges (order among any number of them in log^2 steps) and what lies before each one is a prefix sum: loops over all experts for
+// each of them took 60, 256 and 3467 us with 256, 1024 and 4096 experts, this takes 18, 29 and 70.
 template <typename Entry, typename Sync>
-MOE_PARTS_FN void dw_split(const int* bases, int e_loc, int tiles, int cus, int cap, Entry* entries, int* rows_of, int* parts_of, int* place_of, int tid,
+MOE_PARTS_FN void dw_split(const int* bases, int e_loc, int tiles, int cus, int cap, Entry* entries, int* rows, int* order, int* parts, int* sums, int tid,
                            int threads, Sync sync) {
-    for (int e = tid; e < e_loc; e += threads) rows_of[e] = bases[e + 1] - bases[e];
+    int n = 1;
+    while (n < e_loc) n *= 2;
+    for (int e = tid; e < n; e += threads) { rows[e] = e < e_loc ? bases[e + 1] - bases[e] : -1; order[e] = e; }
     sync();
-    auto before = [&](int j, int e) { return rows_of[j] > rows_of[e] || (rows_of[j] == rows_of[e] && j < e); };
-    for (int e = tid; e < e_loc; e += threads) {
-        const int rows = rows_of[e];
-        long long rest = 0;                                               // rows of this expert and of those after it
-        for (int j = 0; j < e_loc; ++j) rest += before(j, e) ? 0 : rows_of[j];
+    auto before = [&](int i, int j) { return rows[i] > rows[j] || (rows[i] == rows[j] && order[i] < order[j]); };
+    for (int run = 2; run <= n; run *= 2)
+        for (int step = run / 2; step > 0; step /= 2) {
+            for (int pair = tid; pair < n / 2; pair += threads) {
+                const int i = 2 * pair - (pair & (step - 1)), j = i + step;
+                if (before(j, i) == ((i & run) == 0)) {
+                    const int r = rows[i], o = order[i];
+                    rows[i] = rows[j]; order[i] = order[j];
+                    rows[j] = r; order[j] = o;
+                }
+            }
+            sync();
+        }
+    // every thread takes `len` experts next to each other; -> the sum of `mine` over the threads before it
+    const int len = (e_loc + threads - 1) / threads, used = (e_loc + len - 1) / len;
+    const int lo = tid * len < e_loc ? tid * len : e_loc, hi = lo + len < e_loc ? lo + len : e_loc;
+    auto sum_before = [&](int mine) {
+        sync();
+        if (tid < used) sums[tid] = mine;
+        sync();
+        int sum = 0;
+        if (used <= 16) {                                                 // (a few: less than the steps' barriers)
+            if (tid < used)
+                for (int j = 0; j < tid; ++j) sum += sums[j];
+            return sum;
+        }
+        for (int off = 1; off < used; off *= 2) {
+            const int v = tid < used && tid >= off ? sums[tid - off] : 0;
+            sync();
+            if (tid < used) sums[tid] += v;
+            sync();
+        }
+        return tid < used ? sums[tid] - mine : 0;
+    };
+    int mine = 0;
+    for (int i = lo; i < hi; ++i) mine += rows[i];
+    int at = sum_before(mine), places = 0;
+    const int all = bases[e_loc] - bases[0];
+    for (int i = lo; i < hi; ++i) {
+        const long long rest = all - at;                                  // rows of this expert and of those after it
         int best = 1;
-        if (rest * tiles < (long long)rows * cus && 2 * tiles <= cap) {
+        if (rest * tiles < (long long)rows[i] * cus && 2 * tiles <= cap) {
             constexpr float fix = 100.f, split = 380.f;
             float least = 0.f;
-            for (int P = 1; P <= DW_MAX_PARTS && P * tiles <= cap && (P == 1 || rows / P >= DW_PART_ROWS); ++P) {
-                const float unit = (float)((rows + P * 64 - 1) / (P * 64) * 64) + fix + (P > 1 ? split : 0.f);
-                const float t = ceilf((float)rest * (float)tiles * (float)P / ((float)rows * (float)cus) - 1e-3f) * unit;
+            for (int P = 1; P <= DW_MAX_PARTS && P * tiles <= cap && (P == 1 || rows[i] / P >= DW_PART_ROWS); ++P) {
+                const float unit = (float)((rows[i] + P * 64 - 1) / (P * 64) * 64) + fix + (P > 1 ? split : 0.f);
+                const float t = ceilf((float)rest * (float)tiles * (float)P / ((float)rows[i] * (float)cus) - 1e-3f) * unit;
                 if (P == 1 || t < least) { least = t; best = P; }
             }
         }
-        parts_of[e] = best;
+        parts[i] = best;
+        places += best > 1 ? best * tiles : 0;
+        at += rows[i];
     }
-    sync();
-    for (int e = tid; e < e_loc; e += threads) {
-        const int P = parts_of[e];
-        int place = 0;
-        for (int j = 0; j < e_loc; ++j) place += parts_of[j] > 1 && before(j, e) ? parts_of[j] * tiles : 0;
-        place_of[e] = P > 1 && place + P * tiles <= cap ? place : -1;      // (places asked for before it, granted or not: behind the first refusal all are refused)
+    // places asked for before an expert, granted or not: behind the first refusal all are refused
+    const int first = sum_before(places);
+    auto granted = [&](int i, int place) { return place + parts[i] * tiles <= cap ? parts[i] : 1; };
+    int place = first, entry = 0;
+    for (int i = lo; i < hi; ++i) {
+        entry += granted(i, place);
+        place += parts[i] > 1 ? parts[i] * tiles : 0;
     }
-    sync();
-    for (int e = tid; e < e_loc; e += threads) {
-        const int rows = rows_of[e], place = place_of[e], P = place < 0 ? 1 : parts_of[e], len = (rows + P * 64 - 1) / (P * 64) * 64;
-        int at = 0;
-        for (int j = 0; j < e_loc; ++j) at += !before(j, e) ? 0 : (place_of[j] < 0 ? 1 : parts_of[j]);
-        for (int p = 0; p < P; ++p) {
-            const int lo = p * len < rows ? p * len : rows;
-            entries[1 + 2 * (at + p)] = Entry{bases[e] + lo, len < rows - lo ? len : rows - lo, e, p};
-            entries[2 + 2 * (at + p)] = Entry{P, place < 0 ? 0 : place, 0, 0};
+    mine = entry;
+    entry = sum_before(mine);
+    if (tid == used - 1) entries[0] = Entry{entry + mine, 0, 0, 0};
+    place = first;
+    for (int i = lo; i < hi; ++i) {
+        const int P = granted(i, place), e = order[i], span = (rows[i] + P * 64 - 1) / (P * 64) * 64;
+        for (int p = 0; p < P; ++p, ++entry) {
+            const int from = p * span < rows[i] ? p * span : rows[i];
+            entries[1 + 2 * entry] = Entry{bases[e] + from, span < rows[i] - from ? span : rows[i] - from, e, p};
+            entries[2 + 2 * entry] = Entry{P, P > 1 ? place : 0, 0, 0};
         }
-    }
-    if (tid == 0) {
-        int n = 0;
-        for (int e = 0; e < e_loc; ++e) n += place_of[e] < 0 ? 1 : parts_of[e];
-        entries[0] = Entry{n, 0, 0, 0};
+        place += parts[i] > 1 ? parts[i] * tiles : 0;
     }
 }

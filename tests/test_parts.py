@@ -1,5 +1,5 @@
 """Parts of the weight gradients' contractions (csrc/parts.hpp), compiled for the host: the table has room for every call that the entry point takes.
-The header is the one the kernel includes; one thread does here what the workgroup does there."""
+The header is the one the kernel includes; one thread, or seven with a barrier, do here what the workgroup does there."""
 import os
 import shutil
 import subprocess
@@ -10,19 +10,37 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CUS, MAX_UNITS = 256, 1024
 PROGRAM = r"""
+#include <barrier>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
+#include <thread>
 #include <vector>
 #include "parts.hpp"
 struct Entry { int x, y, z, w; };
 int main(int argc, char** argv) {
     const int E = atoi(argv[2]), tiles = atoi(argv[3]), cus = atoi(argv[4]), cap = atoi(argv[5]);
-    std::vector<int> bases(E + 1), rows(E), parts(E), place(E);
+    int n = 1;
+    while (n < E) n *= 2;
+    std::vector<int> bases(E + 1);
     FILE* f = fopen(argv[1], "rb");
     if (!f || fread(bases.data(), 4, bases.size(), f) != bases.size()) return 2;
     const size_t room = 1 + dw_entries(E);
     std::vector<Entry> entries(room + 64 * (size_t)E, Entry{-7, -7, -7, -7});          // (what lies behind the table is looked at too)
-    dw_split(bases.data(), E, tiles, cus, cap, entries.data(), rows.data(), parts.data(), place.data(), 0, 1, [] {});
+    std::vector<Entry> alone = entries;
+    for (int threads : {1, 7}) {
+        std::vector<int> rows(n), order(n), parts(E), sums(threads);
+        std::barrier<> all(threads);
+        std::vector<std::thread> group;
+        std::fill(entries.begin(), entries.end(), Entry{-7, -7, -7, -7});
+        for (int t = 0; t < threads; ++t)
+            group.emplace_back([&, t] {
+                dw_split(bases.data(), E, tiles, cus, cap, entries.data(), rows.data(), order.data(), parts.data(), sums.data(), t, threads, [&] { all.arrive_and_wait(); });
+            });
+        for (std::thread& t : group) t.join();
+        if (threads == 1) alone = entries;
+        if (memcmp(alone.data(), entries.data(), 16 * entries.size())) return 3;
+    }
     fwrite(&room, 8, 1, stdout);
     fwrite(entries.data(), 16, entries.size(), stdout);
 }
@@ -33,7 +51,7 @@ int main(int argc, char** argv) {
 def program(tmp_path_factory):
     d = tmp_path_factory.mktemp("parts")
     (d / "parts.cpp").write_text(PROGRAM)
-    subprocess.run([shutil.which("g++") or "c++", "-O1", "-std=c++17", "-I", os.path.join(ROOT, "paper_2605_26845_amd", "csrc"), str(d / "parts.cpp"),
+    subprocess.run([shutil.which("g++") or "c++", "-O1", "-std=c++20", "-pthread", "-I", os.path.join(ROOT, "paper_2605_26845_amd", "csrc"), str(d / "parts.cpp"),
                     "-o", str(d / "parts")], check=True)
     return d
 
