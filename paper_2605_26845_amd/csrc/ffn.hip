@@ -2029,6 +2029,7 @@ constexpr int DW_QUEUES = 24;                  // first of the 8 queue counters 
 constexpr int BWD_COUNTERS = 32;               // tile queue counters of a backward call: dh, act, dx, dW
 constexpr int DW_ZEROS = 1024;                 // bytes of zeros that rows past an expert's end read where the operands need 64-bit addresses
 
+constexpr int DW_CHUNK = 5;                    // log2 of the largest chunk of tiles
 struct DwGrid {                                // tiles of one product of one expert, walked in chunks of at most 32 for the workgroups of one L2
     int C, CN, RB, R, ncg, chunks;
     __host__ __device__ __forceinline__ void init(int rows, int cols) {
@@ -2045,6 +2046,17 @@ struct DwGrid {                                // tiles of one product of one ex
         return j < RB * CN && r < R && c < C;
     }
 };
+// log2 of the tickets of a chunk, which hold either product's tiles: with 32 for few tiles per expert most tickets are empty, an atomic operation each.  E 64 / 1024 / 4096,
+// d = f = 256, 20000 rows: 83 -> 40, 778 -> 111, 3011 -> 371 us; E 1, d 256, f 512, 26206 rows in 32 parts 139 -> 125.
+int dw_tickets(int d, int f) {
+    DwGrid g[2];
+    g[0].init(f / 128, d / 256);
+    g[1].init(d / 256, (f + 255) / 256);
+    int shift = 0;
+    for (const DwGrid& p : g)
+        while ((1 << shift) < std::min(p.R, p.RB) * p.CN) ++shift;
+    return shift;
+}
 __host__ __device__ inline int dw_tiles(int d, int f) { return f / 128 * (d / 256) + d / 256 * ((f + 255) / 256); }       // per expert
 
 struct DwArgs {
@@ -2057,7 +2069,7 @@ struct DwArgs {
     f32x4* part;                       // [units][256 * 256 / 4]
     const unsigned char* zeros;
     __bf16 *dwg, *dwu, *dwd;
-    int M, d, f;
+    int M, d, f, tickets;              // (dw_tickets)
 };
 
 // One workgroup: the table of the weight gradients' parts (parts.hpp), and what has to be zero behind it
@@ -2072,7 +2084,8 @@ void bwd_prep_kernel(const int* __restrict__ bases, int e_loc, int tiles, int cu
     dw_split(bases, e_loc, tiles, cus, cap, entries, rows, order, parts, sums, tid, PLAN_THREADS, [] { __syncthreads(); });
 }
 
-template <bool LISTED, bool WIDE>
+// FEW: chunks of fewer than 32 tickets (a number read at run time moves enough scalar registers in the slab loop to cost the other calls 2 %)
+template <bool LISTED, bool WIDE, bool FEW>
 __global__ __launch_bounds__(512, 1)
 void ffn_bwd_dw_kernel(DwArgs a) {
     constexpr int ROWB = 512, OPERAND = 64 * ROWB, SLAB = 2 * OPERAND;    // bytes of a slab row, of an operand's slab, of both
@@ -2094,11 +2107,11 @@ void ffn_bwd_dw_kernel(DwArgs a) {
         dn.init(a.d / 256, (a.f + 255) / 256);
         const int per = gu.chunks + dn.chunks, n_chunks = ((scalar_ints)a.entries)[0] * per;
         for (int tries = 0; tries < 8;) {
-            const int k = atomicAdd(&a.queues[q], 1), chunk = (k >> 5) * 8 + q;
+            const int shift = FEW ? a.tickets : DW_CHUNK, k = atomicAdd(&a.queues[q], 1), chunk = (k >> shift) * 8 + q, j = k & ((1 << shift) - 1);
             if (chunk >= n_chunks) { ++tries; q = (q + 1) & 7; continue; }
             const int en = chunk / per, rem = chunk - en * per;
             product = rem >= gu.chunks;
-            const bool tile = product ? dn.at(rem - gu.chunks, k & 31, r, c) : gu.at(rem, k & 31, r, c);
+            const bool tile = product ? dn.at(rem - gu.chunks, j, r, c) : gu.at(rem, j, r, c);
             if (tile && ((scalar_ints)a.entries)[4 * (1 + 2 * __builtin_amdgcn_readfirstlane(en)) + 2] >= 0) { entry = en; break; }
         }
         s_ticket[0] = entry; s_ticket[1] = product; s_ticket[2] = r; s_ticket[3] = c;
@@ -2415,10 +2428,10 @@ void bwd_transpose_kernel(TransposeArgs a) {
     }
 }
 
-template <bool LISTED, bool WIDE>
+template <bool LISTED, bool WIDE, bool FEW>
 moe_status launch_dw(const DwArgs& a, long long most_units, hipStream_t s) {
     static moe::DeviceOnce attr;
-    auto kern = ffn_bwd_dw_kernel<LISTED, WIDE>;
+    auto kern = ffn_bwd_dw_kernel<LISTED, WIDE, FEW>;
     int dev;
     if (attr.needed(dev)) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, ADAPTIVE_LDS);
@@ -2742,7 +2755,9 @@ extern "C" moe_status moe_expert_ffn_backward_sliced(const void* x, const void* 
     w.part = part;
     w.zeros = (const unsigned char*)(ws + L.zeros);
     w.dwg = (__bf16*)dw_gate; w.dwu = (__bf16*)dw_up; w.dwd = (__bf16*)dw_down;
-    w.M = M; w.d = d; w.f = f;
+    w.M = M; w.d = d; w.f = f; w.tickets = dw_tickets(d, f);
     const long long most = (long long)E_loc * tiles + units;
-    return !listed ? launch_dw<false, false>(w, most, s) : off32 ? launch_dw<true, false>(w, most, s) : launch_dw<true, true>(w, most, s);
+    if (w.tickets < DW_CHUNK)
+        return !listed ? launch_dw<false, false, true>(w, most, s) : off32 ? launch_dw<true, false, true>(w, most, s) : launch_dw<true, true, true>(w, most, s);
+    return !listed ? launch_dw<false, false, false>(w, most, s) : off32 ? launch_dw<true, false, false>(w, most, s) : launch_dw<true, true, false>(w, most, s);
 }

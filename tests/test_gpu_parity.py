@@ -1152,6 +1152,14 @@ def test_ffn_backward_small(lib, E_loc, d, f, M, S):
     check_backward(lib, E_loc, d, f, M, S, seed=d + f + M, what="small", spare=5)
 
 
+@pytest.mark.parametrize("E_loc,d,f", [(40, 256, 256), (20, 256, 640), (12, 768, 384), (6, 1280, 256), (3, 2304, 1152), (2, 256, 4352)])
+def test_ffn_backward_tickets(lib, E_loc, d, f):
+    """Chunks of 2, 8 (5 used), 16 (9 used), 16 (10 used), 32 (30 used) and 32 places in the queues of the weight gradients, one and several chunks per
+    product: every tile of every expert is computed."""
+    say("ffn backward tickets", E_loc, d, f)
+    check_backward(lib, E_loc, d, f, 700, 2, seed=d + f, what="tickets", empty_frac=0.3)
+
+
 @pytest.mark.parametrize("S,M,E_loc", [(0, 0, 3), (0, 40, 3), (0, 40, 1100), (0, 40, 2100), (5, 0, 3)])
 def test_ffn_backward_without_groups(lib, S, M, E_loc):
     """No slices (also with more experts than the planning workgroup has threads, or keeps in LDS) or no rows: zero weight gradients and
